@@ -74,9 +74,9 @@ def _log_int(rng, lo, hi):
 def _cost(c):
     """Flops weighted by how far below the matrix-core rate the case's type and shape run."""
     gemm, attn = _stage_flops(c)
-    if c["dtype"] == "bf16" and c["seq"] % 128 == 0:
-        return gemm + attn
-    return 60 * gemm + 600 * attn
+    matrix = c["dtype"] == "bf16" and c["seq"] % 128 == 0
+    return (1 if matrix and all(w % 128 == 0 for w in (c["hidden"], c["ffn"], _qkv_width(c))) else 60) * gemm + \
+        (1 if matrix else 600) * attn
 
 
 def draw(rng):
@@ -87,7 +87,7 @@ def draw(rng):
     head_size = rng.choice([64, 128])
     if kind == "attention":
         heads = _log_int(rng, 2, 40)
-        seq = _log_int(rng, 100, 4000)
+        seq = _log_int(rng, 100, min(4000, int(math.sqrt(2e10 / (heads * head_size)))))
         if rng.random() < 0.5:
             seq = 128 * max(1, seq // 128)
         group = rng.choice([g for g in (1, 1, 2, 4, 8) if heads % g == 0])
