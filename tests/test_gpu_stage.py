@@ -112,6 +112,24 @@ def test_offload_is_bit_identical_in_every_mode(gpu_device, shape):
             _assert_bit_identical(base, snap)
 
 
+@pytest.mark.parametrize("seq", [64, 512, 1600])
+def test_offload_copies_below_and_above_a_row_of_the_dma_copy(gpu_device, seq):
+    """A slab leaves for the host in rows of 1 MiB and one remainder: slabs of only a remainder, of one row and a
+    remainder, of several rows and a remainder all come back bit for bit."""
+    shape = syn.StageShape(2, 1, 64, 1, 256, seq, dtype="f32", pipeline_degree=3, n_microbatches=4)
+    rows, rest = divmod(po.po_saved_bytes_per_layer(po.po_config_default(
+        n_layers=2, hidden=64, n_heads=1, ffn=256, seq=seq)), 1 << 20)
+    assert rest and rows == {64: 0, 512: 1, 1600: 3}[seq]
+    with StageRunner(shape) as r:
+        r.make_inputs()
+        r.run(po.PO_SCHED_1F1B, 0.0)
+        want = _snapshot(r)
+        for ratio in (1.0, 0.5, 1.0):
+            r.zero_grads()
+            r.run(po.PO_SCHED_1F1B, ratio)
+            _assert_bit_identical(want, _snapshot(r))
+
+
 def test_interleaved_schedule_chunks_and_residency(gpu_device):
     shape = syn.StageShape(4, 2, 128, 2, 512, 64, dtype="bf16", pipeline_degree=2, n_microbatches=4)
     results = {}
