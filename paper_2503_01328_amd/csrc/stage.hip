@@ -186,6 +186,7 @@ struct PoolBuf {
   char* ptr = nullptr;
   hipEvent_t free_event = nullptr;  // work after which the buffer may be overwritten
   hipStream_t guard_stream = nullptr;  // stream that event was recorded on
+  uint64_t guard_seq = 0;  // position of that record among the pool's releases
   bool guarded = false;
 };
 
@@ -196,24 +197,42 @@ struct Pool {
   std::vector<PoolBuf> bufs;
   std::deque<int> free_list;
   int in_use = 0;
+  uint64_t releases = 0;
 
   uint64_t allocated() const { return (uint64_t)bufs.size() * buf_bytes; }
 
-  // Takes a buffer; `stream` (the first stream that will write it) waits for the guard event.
-  int acquire(hipStream_t stream, int* out) {
+  // Takes a buffer; `stream` (the first stream that will write it) waits for the guard event.  With `later` that wait
+  // is left to the caller: *later is the event to wait for before the first write, or null.
+  // after_stream / after_seq: `stream` already waits for everything the pool's releases up to number after_seq on
+  // after_stream stand for.
+  int acquire(hipStream_t stream, int* out, hipEvent_t* later = nullptr, hipStream_t after_stream = nullptr,
+              uint64_t after_seq = 0) {
     int idx;
+    if (later) *later = nullptr;
     if (!free_list.empty()) {
-      // Oldest buffer that needs no wait (never used, or handed back on the taker's own stream, where stream
-      // order already protects it); else the oldest of all, whose guard event the taker's stream waits for.
-      auto pick = free_list.begin();
-      for (auto it = free_list.begin(); it != free_list.end(); ++it)
-        if (!bufs[*it].guarded || bufs[*it].guard_stream == stream) {
-          pick = it;
-          break;
-        }
+      // In this order: a buffer whose guard the taker waits for anyway (of no use to anyone else yet: a reload that
+      // took a free buffer instead left the next forward the buffer of an offload still under way, and 8 of the 46 ms
+      // of a step at C3's widths with every other microbatch offloaded were that forward's wait); the oldest one that
+      // needs no wait (not guarded, or handed back on the taker's own stream, where stream order already protects
+      // it); the oldest of all, whose guard event the taker's stream waits for.
+      auto pick = free_list.end();
+      if (after_stream && after_stream != stream)
+        pick = std::find_if(free_list.begin(), free_list.end(), [&](int i) {
+          return bufs[i].guarded && bufs[i].guard_stream == after_stream && bufs[i].guard_seq <= after_seq;
+        });
+      bool wait = false;
+      if (pick == free_list.end())
+        pick = std::find_if(free_list.begin(), free_list.end(),
+                            [&](int i) { return !bufs[i].guarded || bufs[i].guard_stream == stream; });
+      if (pick == free_list.end()) {
+        pick = free_list.begin();
+        wait = true;
+      }
       idx = *pick;
       free_list.erase(pick);
-      if (bufs[idx].guarded && bufs[idx].guard_stream != stream)
+      if (wait && later)
+        *later = bufs[idx].free_event;
+      else if (wait)
         PO_HIP(hipStreamWaitEvent(stream, bufs[idx].free_event, 0));
     } else {
       if (cap && allocated() + buf_bytes > cap) {
@@ -247,10 +266,16 @@ struct Pool {
   int release(int idx, hipStream_t stream) {
     PO_HIP(hipEventRecord(bufs[idx].free_event, stream));
     bufs[idx].guard_stream = stream;
+    bufs[idx].guard_seq = ++releases;
     bufs[idx].guarded = true;
     free_list.push_back(idx);
     --in_use;
     return PO_OK;
+  }
+
+  // All streams have been drained: nothing guards the free buffers any more.
+  void drained() {
+    for (int i : free_list) bufs[i].guarded = false;
   }
 
   void destroy() {
@@ -293,6 +318,7 @@ struct UnitLayer {
   int dev = -1;              // device slab index
   int hostbuf = -1;          // host slab index
   hipEvent_t d2h_done = nullptr;
+  uint64_t d2h_seq = 0;  // the device pool's release number at that point of the offload stream
   hipEvent_t h2d_done = nullptr;  // non-null: backward must wait for it
 };
 
@@ -465,6 +491,16 @@ static int st_attention(po_stage* st, bool backward, const void* qkv, void* o, f
     if (rc__) return rc__;   \
   } while (0)
 
+// The compute stream waits for an event in the middle of a pass.  The pass's timed span is closed before the wait and
+// a new one opened behind it, so that time spent waiting is not booked as compute (span == nullptr: none is open).
+static int await_event(po_stage* st, hipEvent_t ev, size_t* span) {
+  if (!ev) return PO_OK;
+  if (span) PO_RC(span_end(st, st->compute, *span));
+  PO_HIP(hipStreamWaitEvent(st->compute, ev, 0));
+  if (span) PO_RC(span_begin(st, st->compute, 0, span));
+  return PO_OK;
+}
+
 // Dropout site `site` of `layer` for microbatch `mb` (scale 0 = off) with the stage's probability and seed.
 static DropoutSite site_of(const po_stage* st, int layer, int site, int mb) {
   if (st->cfg.dropout_p > 0.f) return make_dropout_site(st->cfg.dropout_p, st->cfg.dropout_seed, layer, site, mb);
@@ -473,7 +509,9 @@ static DropoutSite site_of(const po_stage* st, int layer, int site, int mb) {
   return d;
 }
 
-static int layer_forward(po_stage* st, int layer, int mb, char* slab, void* y_out) {
+// before_out: null, or the event to wait for before y_out is written (it lies in a slab whose last user has to end
+// first); `span` is the pass's timed span.
+static int layer_forward(po_stage* st, int layer, int mb, char* slab, void* y_out, hipEvent_t before_out, size_t* span) {
   const po_config& c = st->cfg;
   const ParamLayout& pl = st->pl;
   const SlabLayout& sl = st->sl;
@@ -512,6 +550,7 @@ static int layer_forward(po_stage* st, int layer, int mb, char* slab, void* y_ou
   e.bias = st->P(layer, pl.b_fc2);
   e.residual = drop ? nullptr : x1;
   e.out = drop ? (void*)st->w_dz[0] : y_out;
+  PO_RC(await_event(st, before_out, span));
   PO_RC(st_gemm(st, 0, 0, s, h, f, st->w_g, f, st->P(layer, pl.w_fc2), h, e));
   if (drop) PO_K(dropout_apply(dt, st->w_dz[0], x1, y_out, s, h, site_of(st, layer, 1, mb), q));
   return PO_OK;
@@ -670,10 +709,16 @@ int stage_forward(po_stage* st, int mb, int chunk, const void* x_in, void* y_out
     return PO_E_STATE;
   }
   u.layers.assign(st->Lu, UnitLayer());
+  // A slab still on its way to the host is waited for right before the first kernel that writes it, not before the
+  // whole pass: the slabs of an offloaded unit come free one by one, and layer 0 starts with the first of them.
+  std::vector<hipEvent_t> slab_free(st->Lu);
   for (int l = 0; l < st->Lu; ++l) {
-    int rc = st->dev_pool.acquire(st->compute, &u.layers[l].dev);
+    int rc = st->dev_pool.acquire(st->compute, &u.layers[l].dev, &slab_free[l]);
     if (rc) {
-      for (int k = 0; k < l; ++k) st->dev_pool.release(u.layers[k].dev, st->compute);
+      for (int k = 0; k < l; ++k) {  // handed back as guarded as they came: behind the wait that was put off
+        (void)await_event(st, slab_free[k], nullptr);
+        st->dev_pool.release(u.layers[k].dev, st->compute);
+      }
       st->units.erase(unit_key(mb, chunk));
       return rc;
     }
@@ -685,8 +730,10 @@ int stage_forward(po_stage* st, int mb, int chunk, const void* x_in, void* y_out
   ++st->resident_units;
   st->note_usage();
 
+  int rc = await_event(st, slab_free[0], nullptr);
+  if (rc) return rc;
   size_t span;
-  int rc = span_begin(st, st->compute, 0, &span);
+  rc = span_begin(st, st->compute, 0, &span);
   if (rc) return rc;
   bool embed = c.vocab > 0 && chunk == 0;
   char* slab0 = st->dev_pool.bufs[u.layers[0].dev].ptr;
@@ -700,7 +747,7 @@ int stage_forward(po_stage* st, int mb, int chunk, const void* x_in, void* y_out
   for (int l = 0; l < st->Lu; ++l) {
     char* slab = st->dev_pool.bufs[u.layers[l].dev].ptr;
     void* out = (l + 1 < st->Lu) ? (void*)(st->dev_pool.bufs[u.layers[l + 1].dev].ptr + st->sl.off_x) : y_out;
-    rc = layer_forward(st, chunk * st->Lu + l, mb, slab, out);
+    rc = layer_forward(st, chunk * st->Lu + l, mb, slab, out, l + 1 < st->Lu ? slab_free[l + 1] : nullptr, &span);
     if (rc) return rc;
   }
   rc = span_end(st, st->compute, span);
@@ -823,6 +870,7 @@ int stage_offload(po_stage* st, int mb, int chunk, float ratio) {
     rc = st->sync_events.get(&L.d2h_done);
     if (rc) return rc;
     PO_HIP(hipEventRecord(L.d2h_done, q));
+    L.d2h_seq = st->dev_pool.releases;
     L.dev = -1;
     L.state = L_HOST;
     ++st->stats.n_offloads;
@@ -851,7 +899,7 @@ int stage_reload(po_stage* st, int mb, int chunk) {
     UnitLayer& L = u->layers[l];
     if (L.state != L_HOST) continue;
     if (q != st->offload) PO_HIP(hipStreamWaitEvent(q, L.d2h_done, 0));
-    rc = st->dev_pool.acquire(q, &L.dev);
+    rc = st->dev_pool.acquire(q, &L.dev, nullptr, st->offload, L.d2h_seq);
     if (rc) return rc;
     st->note_usage();
     char* dev = st->dev_pool.bufs[L.dev].ptr;
@@ -935,14 +983,9 @@ static int backward_prologue(po_stage* st, int mb, int chunk, const void* dy, vo
 }
 
 // The compute stream waits for a layer's outstanding reload right before the first kernel that reads its slab.
-// A wait in the middle of a pass closes the pass's timed span and opens a new one behind it, so that time spent
-// waiting for a copy is not booked as compute (span == nullptr: no span is open yet).
 static int await_layer(po_stage* st, UnitLayer& L, size_t* span) {
-  if (!L.h2d_done) return PO_OK;
-  if (span) PO_RC(span_end(st, st->compute, *span));
-  PO_HIP(hipStreamWaitEvent(st->compute, L.h2d_done, 0));
+  PO_RC(await_event(st, L.h2d_done, span));
   L.h2d_done = nullptr;
-  if (span) PO_RC(span_begin(st, st->compute, 0, span));
   return PO_OK;
 }
 
@@ -1155,6 +1198,9 @@ int stage_synchronize(po_stage* st) {
   if (st->wstream) PO_HIP(hipStreamSynchronize(st->wstream));
   PO_HIP(hipStreamSynchronize(st->offload));
   if (st->reload != st->offload) PO_HIP(hipStreamSynchronize(st->reload));
+  st->dev_pool.drained();
+  st->host_pool.drained();
+  st->grad_pool.drained();
   return PO_OK;
 }
 
