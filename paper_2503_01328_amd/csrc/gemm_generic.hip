@@ -1,5 +1,5 @@
-// Shape-agnostic GEMM on the vector ALU: the fp32 debug path and the home of
-// every shape the MFMA kernel does not take (ragged tiles).  64x64 block tile,
+// Shape-agnostic GEMM on the vector ALU: the home of what the matrix-core kernels do not take (rows that are no whole
+// 16-byte vectors, unaligned operands) and what force_generic asks for.  64x64 block tile,
 // 16-deep k slices staged through LDS as fp32, each thread owns a 4x4 micro-tile.
 // All bounds are checked, so any M, N, K >= 1 and any leading dimension works.
 #include "kernels.h"
@@ -117,6 +117,8 @@ bool gemm(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* 
           const Epilogue& ep, bool force_generic, hipStream_t stream) {
   if (dtype == kBF16 && !force_generic && gemm_mfma_supported(trans_a, trans_b, M, N, K, lda, ldb, ep.ldc))
     return gemm_mfma_bf16(trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
+  if (!force_generic && gemm_small_supported(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb))
+    return gemm_small(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
   return gemm_generic(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
 }
 

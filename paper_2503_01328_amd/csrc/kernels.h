@@ -80,7 +80,16 @@ struct GemmProblem {
 };
 bool gemm_mfma_grouped_supported(int n, const GemmProblem* p);
 bool gemm_mfma_grouped_accumulate(int n, const GemmProblem* p, hipStream_t stream);
-// Picks the MFMA kernel for bf16 when the shape allows it, else the generic one.
+// Matrix-core kernel for fp32 and for bf16 shapes of any size (gemm_small.hip): rows of both operands whole 16-byte
+// vectors, operands 16-byte aligned.
+bool gemm_small_supported(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda,
+                          const void* B, int ldb);
+bool gemm_small(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda, const void* B,
+                int ldb, const Epilogue& ep, hipStream_t stream);
+// The counterpart of gemm_mfma_grouped_accumulate for its shapes and types.
+bool gemm_small_grouped_supported(int dtype, int n, const GemmProblem* p);
+bool gemm_small_grouped_accumulate(int dtype, int n, const GemmProblem* p, hipStream_t stream);
+// Picks the kernel by type and shape; force_generic: the vector kernel.
 bool gemm(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
           const Epilogue& ep, bool force_generic, hipStream_t stream);
 

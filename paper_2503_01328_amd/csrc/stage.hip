@@ -462,7 +462,8 @@ static int st_gemm_grouped(po_stage* st, int n, const GemmProblem* prob, hipStre
     if (rc) return rc;
     for (int i = 0; i < n; ++i) st->spans[span].flops += 2.0 * prob[i].M * prob[i].N * prob[i].K;
   }
-  PO_K(gemm_mfma_grouped_accumulate(n, prob, q));
+  if (st->cfg.dtype == PO_BF16 && gemm_mfma_grouped_supported(n, prob)) PO_K(gemm_mfma_grouped_accumulate(n, prob, q));
+  else PO_K(gemm_small_grouped_accumulate(st->cfg.dtype, n, prob, q));
   return span_end(st, q, span);
 }
 
@@ -660,9 +661,9 @@ static int layer_backward_weight(po_stage* st, int layer, const char* slab, cons
     jobs[5] = ReduceJob{b.dn1, x, b.lnws1, st->G(layer, pl.ln1_g), st->G(layer, pl.ln1_b), b.lnws1 + (size_t)s * 2, h};
     PO_K(column_reductions(dt, jobs, 6, s, q));
   }
-  // The four products dW = operand^T gradient.  They do not depend on each other, so where the matrix-core
-  // kernel can take them as one grouped launch (both LayerNorm outputs recomputed first, into two buffers) the
-  // chip works through the tiles of all four without a launch boundary in between; else one launch each.
+  // The four products dW = operand^T gradient.  They do not depend on each other, so they go out as one grouped launch
+  // (both LayerNorm outputs recomputed first, into two buffers) and the chip works through the tiles of all four
+  // without a launch boundary in between; one launch each where a tensor is not aligned as those kernels need it.
   char* n2 = n_out;
   char* n1 = n_out + st->gl_sh;
   GemmProblem prob[4] = {
@@ -671,7 +672,7 @@ static int layer_backward_weight(po_stage* st, int layer, const char* slab, cons
       {h, h, s, o, h, dz1, h, st->G(layer, pl.w_o), h},
       {h, wq, s, n1, h, b.dqkv, wq, st->G(layer, pl.w_qkv), wq},
   };
-  if (dt == PO_BF16 && gemm_mfma_grouped_supported(4, prob)) {
+  if ((dt == PO_BF16 && gemm_mfma_grouped_supported(4, prob)) || gemm_small_grouped_supported(dt, 4, prob)) {
     if (!n_ready) {
       PO_K(layernorm_forward(dt, x1, st->P(layer, pl.ln2_g), st->P(layer, pl.ln2_b), n2, s, h, c.ln_eps, q));
       PO_K(layernorm_forward(dt, x, st->P(layer, pl.ln1_g), st->P(layer, pl.ln1_b), n1, s, h, c.ln_eps, q));

@@ -144,6 +144,51 @@ def test_gemm_mfma_epilogues(gpu_device, epilogue, shape):
     _gemm_case(gpu_device, "bf16", *form, *shape, epilogue, 0)
 
 
+# the kernel for fp32 and for bf16 results of any size: one row, tiles that end inside, K with a remainder, and result
+# sizes on both sides of the lines between its forms (32 x 32 and 64 x 64 tiles, 8, 4, 2 and 1 waves); a multiple of 8
+# in N, and in whichever of M and K is contiguous, is what its 16-byte loads need
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (40, 24, 520), (1, 64, 72), (33, 200, 1096), (1000, 520, 264),
+                                   (1000, 520, 1160), (1032, 2008, 72), (2056, 2008, 328)])
+def test_gemm_small_edges(gpu_device, dtype, ta, tb, M, N, K):
+    """Against the product in fp64.  K sums of fp32 products each round by at most 2^-24 of a partial sum, independent of
+    each other: 2^-24 sqrt(K) relative (2-norm) is generous; a bf16 result (8 significant bits) adds its own rounding,
+    at most 2^-8 of every element and so of the norm."""
+    code, tdt, _ = DT[dtype]
+    if ta:
+        M = 8 * -(-M // 8)
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(M + N + K + ta)
+    # operands followed by NaNs: what lies past an operand's end must not reach the result
+    def rand(rows, cols):
+        t = torch.full((rows * cols + 70000,), float("nan"), dtype=tdt, device=gpu_device)
+        t[:rows * cols] = torch.randn(rows * cols, generator=g, device=gpu_device).to(tdt)
+        return t[:rows * cols].view(rows, cols)
+    A, B = rand(*((K, M) if ta else (M, K))), rand(*((N, K) if tb else (K, N)))
+    bias, res, u = rand(1, N)[0], rand(M, N), rand(M, N)
+    a64, b64 = (A.t() if ta else A).double(), (B.t() if tb else B).double()
+    ref = a64 @ b64
+    rel = lambda got, want: float((got.double() - want).norm() / want.norm())
+    sums = 2.0 ** -24 * K ** 0.5
+    tol = sums + 2.0 ** -23 + (2.0 ** -8 if dtype == "bf16" else 0.0)
+    call = lambda **kw: po.po_op_gemm(code, ta, tb, M, N, K, A, A.shape[1], B, B.shape[1], **kw)
+    out, gel = torch.empty(M, N, dtype=tdt, device=gpu_device), torch.empty(M, N, dtype=tdt, device=gpu_device)
+    call(out=out, bias=bias, residual=res)
+    assert rel(out, ref + bias.double() + res.double()) < tol
+    call(out=out, bias=bias, gelu_out=gel)
+    assert rel(out, ref + bias.double()) < tol
+    gelu = lambda x: torch.nn.functional.gelu(x, approximate="tanh")
+    assert rel(gel, gelu(out.double())) < tol + 2e-6  # the gate's exp2 and reciprocal: 1 ulp each of values near one
+    ud = u.double().requires_grad_()
+    gelu(ud).sum().backward()
+    call(out=out, gelu_u=u, gelu_out=gel)
+    assert rel(out, ref * ud.grad) < tol + 2e-6 and rel(gel, gelu(u.double())) < tol + 2e-6
+    acc = torch.ones(M, N, device=gpu_device)
+    call(acc_f32=acc)
+    assert rel(acc, ref + 1.0) < sums + 2.0 ** -23
+
+
 def test_gemm_grouped_equals_single_launches_and_the_oracle(gpu_device):
     """Four weight-gradient products of different shapes in one launch: each accumulator equals, bit for bit, what
     the single launch of that product leaves, and the fp64 product within the bf16 tolerance.  Tile counts

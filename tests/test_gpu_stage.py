@@ -81,6 +81,19 @@ def test_bf16_stage_against_oracle(gpu_device, shape):
         _compare(shape, r.results(), _oracle(shape, r, shape.n_microbatches), 2e-2)
 
 
+@pytest.mark.parametrize("shape", [
+    syn.StageShape(1, 1, 448, 7, 1024, 200, dtype="bf16", pipeline_degree=2, n_microbatches=2),
+    syn.StageShape(1, 1, 512, 8, 1536, 37, dtype="f32", pipeline_degree=2, n_microbatches=2),
+    syn.StageShape(1, 1, 1024, 8, 2048, 300, dtype="f32", pipeline_degree=2, n_microbatches=2)],
+    ids=["bf16-64-tiles", "f32-64-tiles-short", "f32-64-tiles-long"])
+def test_grouped_weight_gradients_of_any_shape(gpu_device, shape):
+    """The one launch of a layer's four weight-gradient products where the 256 x 256 tiles do not fit."""
+    with StageRunner(shape) as r:
+        r.make_inputs()
+        r.run(po.PO_SCHED_1F1B, 0.0)
+        _compare(shape, r.results(), _oracle(shape, r, 2), 1e-4 if shape.dtype == "f32" else 2e-2)
+
+
 @pytest.mark.parametrize("shape", [SMALL_BF16, syn.StageShape(2, 1, 128, 2, 512, 96, vocab=50, dtype="f32",
                                                              pipeline_degree=4, n_microbatches=6)],
                          ids=["bf16", "f32-embed"])
