@@ -1,6 +1,6 @@
 // Causal attention on the vector ALU for any dtype, sequence length and head
-// size up to 256: the fp32 debug path and the home of shapes the MFMA kernels
-// do not take.  One wave owns one (head, row): lanes split the keys of a
+// size up to 256: what force_generic asks for and the home of shapes the
+// matrix-core kernels do not take.  One wave owns one (head, row): lanes split the keys of a
 // 64-wide chunk for the scores (online softmax, running max and sum), then
 // split the head dimension for the weighted sums, the per-key weights being
 // broadcast with shuffles.  Backward is split into a dQ kernel (wave per query
@@ -271,6 +271,8 @@ bool attention_forward(int dtype, const void* qkv, void* o, float* lse, int s, i
                        bool force_generic, hipStream_t stream) {
   if (dtype == kBF16 && !force_generic && attention_mfma_supported(s, h, n_heads, n_kv_heads))
     return attention_forward_mfma(qkv, o, lse, s, h, n_heads, n_kv_heads, stream);
+  if (dtype == kF32 && !force_generic && attention_f32_supported(qkv, o, s, h, n_heads, n_kv_heads))
+    return attention_forward_f32((const float*)qkv, (float*)o, lse, s, h, n_heads, n_kv_heads, stream);
   return attention_forward_generic(dtype, qkv, o, lse, s, h, n_heads, n_kv_heads, stream);
 }
 
@@ -279,6 +281,13 @@ bool attention_backward(int dtype, const void* qkv, const void* o, const float* 
                         hipStream_t stream) {
   if (dtype == kBF16 && !force_generic && attention_mfma_supported(s, h, n_heads, n_kv_heads))
     return attention_backward_mfma(qkv, o, lse, d_o, dqkv, delta, partials, s, h, n_heads, n_kv_heads, stream);
+  if (dtype == kF32 && !force_generic && attention_f32_supported(qkv, d_o, s, h, n_heads, n_kv_heads) &&
+      (uintptr_t)dqkv % 16 == 0) {
+    attn_delta_kernel<float><<<dim3(ceil_div(s, 4), n_heads), 256, 0, stream>>>((const float*)o, (const float*)d_o, delta,
+                                                                               s, h, h / n_heads);
+    return attention_backward_f32((const float*)qkv, lse, delta, (const float*)d_o, (float*)dqkv, s, h, n_heads,
+                                  n_kv_heads, stream);
+  }
   return attention_backward_generic(dtype, qkv, o, lse, d_o, dqkv, delta, s, h, n_heads, n_kv_heads, stream);
 }
 

@@ -246,6 +246,14 @@ def test_attention_forward_and_backward(gpu_device, dtype, s, h, a, force_generi
     _attention_case(gpu_device, dtype, s, h, a, force_generic)
 
 
+# the fp32 matrix-core kernels: every head size, tiles of 32 rows that end inside, fewer tiles than waves, one row,
+# key/value heads shared by groups
+@pytest.mark.parametrize("s,h,a,akv", [(1, 32, 1, 1), (31, 64, 1, 1), (33, 192, 2, 1), (97, 256, 2, 2), (160, 128, 4, 2),
+                                       (161, 512, 4, 1), (300, 192, 3, 3)])
+def test_attention_f32(gpu_device, s, h, a, akv):
+    _attention_case(gpu_device, "f32", s, h, a, 0, akv)
+
+
 # shapes the matrix-core kernels take: head size 64 / 128, s a multiple of 128; the last two
 # are large enough in (s / 256) * heads to select the forward kernel's 256-row blocks (both head sizes)
 @pytest.mark.parametrize("s,h,a", [(128, 128, 2), (256, 256, 2), (384, 128, 1), (640, 192, 3), (512, 16384, 256),
