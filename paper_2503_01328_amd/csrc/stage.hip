@@ -13,7 +13,8 @@
 // event (Appendix C, deterministic device memory management: buffers are
 // handed out in host order and guarded by events, not by deferred frees).
 //
-// Streams.  Compute runs on the caller's stream.  D2H copies run on the offload
+// Streams.  Copy streams belong to the device, not to a stage: a stage leases them for as long as it has work in flight
+// (StreamPool below).  Compute runs on the caller's stream.  D2H copies run on the offload
 // stream after the unit's forward-done event; H2D copies run on the reload
 // stream (the same stream when copy_streams == 1, Section 4.2) after an event
 // recorded on the compute stream when po_reload is called, so a reload never
@@ -25,6 +26,7 @@
 #include <chrono>
 #include <deque>
 #include <map>
+#include <mutex>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -289,6 +291,56 @@ struct Pool {
   }
 };
 
+// The non-blocking streams of one device that its stages share.  HIP maps the streams of a process onto four hardware
+// queues, and a stream that waits for a copy holds up every other stream of its queue: with two streams per stage, the
+// second stage of a process had its compute and its copies on one queue (C2 with full offload 99 instead of 65 ms per
+// step).  So a stage takes its streams when it first copies and hands them back once it has drained them: stages that
+// run one after the other use the same two, stages that run at the same time have streams of their own.  The streams
+// go with the device's last stage.
+struct StreamPool {
+  std::vector<hipStream_t> idle;
+  int stages = 0;
+
+  static std::mutex& lock() {
+    static std::mutex m;
+    return m;
+  }
+  static StreamPool& of(int device) {  // the lock is held
+    static std::map<int, StreamPool>* pools = new std::map<int, StreamPool>();  // outlives static destruction
+    return (*pools)[device];
+  }
+  static void join(int device) {
+    std::lock_guard<std::mutex> g(lock());
+    ++of(device).stages;
+  }
+  static void leave(int device) {
+    std::lock_guard<std::mutex> g(lock());
+    StreamPool& p = of(device);
+    if (--p.stages > 0) return;
+    for (hipStream_t s : p.idle) (void)hipStreamDestroy(s);
+    p.idle.clear();
+  }
+  static bool lease(int device, hipStream_t* out) {
+    std::lock_guard<std::mutex> g(lock());
+    StreamPool& p = of(device);
+    if (p.idle.empty()) {
+      if (hipStreamCreateWithFlags(out, hipStreamNonBlocking) == hipSuccess) return true;  // at the default priority
+      (void)hipGetLastError();
+      *out = nullptr;
+      return false;
+    }
+    *out = p.idle.back();
+    p.idle.pop_back();
+    return true;
+  }
+  static void give_back(int device, hipStream_t* s) {  // drained
+    if (!*s) return;
+    std::lock_guard<std::mutex> g(lock());
+    of(device).idle.push_back(*s);
+    *s = nullptr;
+  }
+};
+
 // Reusable events (timing enabled where asked).
 struct EventBank {
   std::vector<hipEvent_t> ev;
@@ -350,9 +402,11 @@ struct po_stage {
   SlabLayout sl;
   int Lu = 0;
   size_t E = 2;
-  hipStream_t compute = nullptr, offload = nullptr, reload = nullptr;
+  hipStream_t compute = nullptr;
+  // leased (lease_streams) from the first use until the stage has been drained, null in between
+  hipStream_t offload = nullptr, reload = nullptr;
   hipStream_t wstream = nullptr;  // weight-gradient passes run here when cfg.weight_stream is set
-  bool own_reload_stream = false;
+  int device = -1;
   const char* params = nullptr;
   float* grads = nullptr;
   Pool dev_pool, host_pool;
@@ -373,6 +427,7 @@ struct po_stage {
   int resident_units = 0, in_flight_units = 0;
   po_stats stats;
   bool collect_timing = false;
+  bool link_bound = false;  // the schedule being run: see copy_slab
   uint64_t gemm_launch_counter = 0, attn_launch_counter = 0;  // for profile_kernels sampling
 
   void note_usage() {
@@ -390,6 +445,26 @@ struct po_stage {
 namespace po {
 
 static int64_t unit_key(int mb, int chunk) { return ((int64_t)chunk << 32) | (uint32_t)mb; }
+
+static int lease_streams(po_stage* st) {
+  auto lease = [&](hipStream_t* s, const char* what) -> int {
+    if (*s || StreamPool::lease(st->device, s)) return PO_OK;
+    set_error("creating the %s stream failed", what);
+    return PO_E_HIP;
+  };
+  int rc = lease(&st->offload, "offload");
+  if (rc) return rc;
+  if (st->cfg.copy_streams != 2) st->reload = st->offload;
+  else if ((rc = lease(&st->reload, "reload"))) return rc;
+  return st->cfg.weight_stream ? lease(&st->wstream, "weight-gradient") : PO_OK;
+}
+// All of them have been drained.
+static void return_streams(po_stage* st) {
+  StreamPool::give_back(st->device, &st->wstream);
+  if (st->reload == st->offload) st->reload = nullptr;
+  StreamPool::give_back(st->device, &st->reload);
+  StreamPool::give_back(st->device, &st->offload);
+}
 
 static int span_begin(po_stage* st, hipStream_t stream, int kind, size_t* idx) {
   if (!st->collect_timing) {
@@ -778,20 +853,40 @@ static void slab_segments(const SlabLayout& sl, char* slab, void** ptrs, uint64_
   }
 }
 
-// A slab to pinned host memory on the DMA engine.  hipMemcpyAsync in this direction runs as a copy kernel of the
-// runtime on all CUs when the process uses the HIP runtime PyTorch ships (H2D does not): the memory-bound kernels
-// beside it took up to ten times as long (LayerNorm at [4096, 4096] 114 instead of 13 us) and a copy in the other
-// direction slowed it (57 GB/s for both directions together in a bare loop).  The two-dimensional form of the same
-// contiguous copy goes to the DMA engine: 56.8 GB/s alone as before, 96.9 with both directions busy, no kernel in the
-// trace.  C4's widths, 8 microbatches, split backward, half the chunks offloaded: 110.4 -> 90.9 ms per step.
+// A slab between device and pinned host memory.  hipMemcpyAsync to the host runs as a copy kernel of the runtime on all
+// CUs when the process uses the HIP runtime PyTorch ships: the memory-bound kernels beside it take up to ten times as long
+// (LayerNorm at [4096, 4096] 114 instead of 13 us).  The two-dimensional form of the same contiguous copy goes to the
+// direction's DMA engine at the same 56.8 GB/s (96.8 with both directions busy): C4's widths, 8 microbatches, split
+// backward, half the chunks offloaded, 110.4 -> 90.9 ms per step.  But the driver clears freed device memory on the
+// engine of the copies to the host, about a second per 10 GB, and halves them meanwhile (56.6 -> 42 GB/s).  So a
+// run whose copies take longer than its compute (link_bound), which has CUs to spare, stays with the copy kernel: C2
+// with full offload 65.3 ms per step by kernel, 65.0 by DMA, 83 by DMA for the first second after 10 GB were freed.
 // Rows of 1 MiB; 4 KiB to one single row of 84 MiB measured the same.
-static int copy_to_host(char* host, const char* dev, size_t bytes, hipStream_t q) {
+static int copy_slab(const po_stage* st, char* dst, const char* src, size_t bytes, hipMemcpyKind kind, hipStream_t q) {
+  if (st->link_bound) {
+    PO_HIP(hipMemcpyAsync(dst, src, bytes, kind, q));
+    return PO_OK;
+  }
   constexpr size_t kRow = (size_t)1 << 20;
-  size_t rows = bytes / kRow, rest = bytes % kRow;
-  if (rows) PO_HIP(hipMemcpy2DAsync(host, kRow, dev, kRow, kRow, rows, hipMemcpyDeviceToHost, q));
-  if (rest)
-    PO_HIP(hipMemcpy2DAsync(host + rows * kRow, rest, dev + rows * kRow, rest, rest, 1, hipMemcpyDeviceToHost, q));
+  size_t rows = bytes / kRow, rest = bytes % kRow, done = rows * kRow;
+  if (rows) PO_HIP(hipMemcpy2DAsync(dst, kRow, src, kRow, kRow, rows, kind, q));
+  if (rest) PO_HIP(hipMemcpy2DAsync(dst + done, rest, src + done, rest, rest, 1, kind, q));
   return PO_OK;
+}
+
+// Whether a schedule's copies (both directions share about 97 GB/s) take longer than its compute at the rates that whole
+// steps reach.  C2 with every unit offloaded: 55 against 27 ms; C3's widths with half of them 24 against 30, C4's 55
+// against 80 (there the copy kernel costs 45.5 instead of 37.7 and 111 instead of 90 ms per step).
+static bool copies_bound(const po_stage* st, const std::vector<po_op>& ops) {
+  const po_config& c = st->cfg;
+  double moved = 0., passes = 0.;
+  for (const po_op& op : ops) {
+    if (op.kind == 0) passes += st->Lu;
+    if (op.kind == 2) moved += 2. * ceil((double)op.ratio * st->Lu - 1e-9) * st->sl.bytes;
+  }
+  const double s = c.seq, h = c.hidden;
+  const double flops = passes * 6. * s * h * (qkv_width_of(c) + h + 2. * c.ffn + s);
+  return moved / 97e9 > flops / (c.dtype == PO_BF16 ? 0.8e15 : 0.08e15);
 }
 
 int stage_offload(po_stage* st, int mb, int chunk, float ratio) {
@@ -812,6 +907,7 @@ int stage_offload(po_stage* st, int mb, int chunk, float ratio) {
       return PO_E_STATE;
     }
   bool was_resident = unit_has_resident_layer(*u);
+  PO_RC(lease_streams(st));
   hipStream_t q = st->offload;
   if (n > 0) PO_HIP(hipStreamWaitEvent(q, u->fwd_done, 0));
   // The n lowest layers go, the top one of them first: the reload brings the layers back in that order too (the
@@ -851,7 +947,7 @@ int stage_offload(po_stage* st, int mb, int chunk, float ratio) {
       if (rc) return rc;
       rc = span_begin(st, q, 1, &span);
       if (rc) return rc;
-      PO_RC(copy_to_host(host, staging, st->sl.packed_bytes, q));
+      PO_RC(copy_slab(st, host, staging, st->sl.packed_bytes, hipMemcpyDeviceToHost, q));
       rc = span_end(st, q, span);
       if (rc) return rc;
       rc = st->dev_pool.release(stg, q);
@@ -860,7 +956,7 @@ int stage_offload(po_stage* st, int mb, int chunk, float ratio) {
     } else {
       rc = span_begin(st, q, 1, &span);
       if (rc) return rc;
-      PO_RC(copy_to_host(host, dev, st->sl.bytes, q));
+      PO_RC(copy_slab(st, host, dev, st->sl.bytes, hipMemcpyDeviceToHost, q));
       rc = span_end(st, q, span);
       if (rc) return rc;
       if (st->cfg.debug_poison) PO_K(fill_u32(dev, 0x7fc07fc0u, st->sl.bytes, q));
@@ -887,6 +983,7 @@ int stage_reload(po_stage* st, int mb, int chunk) {
   for (const UnitLayer& L : u->layers) any |= L.state == L_HOST;
   if (!any) return PO_OK;
   bool was_resident = unit_has_resident_layer(*u);
+  PO_RC(lease_streams(st));
   hipStream_t q = st->reload;
   // The reload may start once the compute work enqueued so far has been reached.
   hipEvent_t gate;
@@ -914,7 +1011,7 @@ int stage_reload(po_stage* st, int mb, int chunk) {
       char* staging = st->dev_pool.bufs[stg].ptr;
       rc = span_begin(st, q, 2, &span);
       if (rc) return rc;
-      PO_HIP(hipMemcpyAsync(staging, host, st->sl.packed_bytes, hipMemcpyHostToDevice, q));
+      PO_RC(copy_slab(st, staging, host, st->sl.packed_bytes, hipMemcpyHostToDevice, q));
       rc = span_end(st, q, span);
       if (rc) return rc;
       void* ptrs[6];
@@ -931,7 +1028,7 @@ int stage_reload(po_stage* st, int mb, int chunk) {
     } else {
       rc = span_begin(st, q, 2, &span);
       if (rc) return rc;
-      PO_HIP(hipMemcpyAsync(dev, host, st->sl.bytes, hipMemcpyHostToDevice, q));
+      PO_RC(copy_slab(st, dev, host, st->sl.bytes, hipMemcpyHostToDevice, q));
       rc = span_end(st, q, span);
       if (rc) return rc;
       st->stats.bytes_h2d += st->sl.bytes;
@@ -1046,7 +1143,7 @@ static int backward_weight_impl(po_stage* st, int mb, int chunk, bool count_pass
 // (same kernels, same inputs, same results), so that the next passes overlap the weight gradients.
 int stage_backward(po_stage* st, int mb, int chunk, const void* dy, void* dx) {
   const po_config& c = st->cfg;
-  if (st->wstream) {
+  if (c.weight_stream) {
     int rc = stage_backward_input(st, mb, chunk, dy, dx);
     if (rc) return rc;
     return backward_weight_impl(st, mb, chunk, false);
@@ -1130,7 +1227,7 @@ int stage_backward_input(po_stage* st, int mb, int chunk, const void* dy, void* 
   }
   rc = span_end(st, st->compute, span);
   if (rc) return rc;
-  if (st->wstream) {
+  if (c.weight_stream) {
     rc = st->sync_events.get(&u->b_done);
     if (rc) return rc;
     PO_HIP(hipEventRecord(u->b_done, st->compute));
@@ -1157,8 +1254,9 @@ static int backward_weight_impl(po_stage* st, int mb, int chunk, bool count_pass
     return PO_E_STATE;
   }
   bool embed = c.vocab > 0 && chunk == 0;
-  hipStream_t q = st->wstream ? st->wstream : st->compute;
-  if (st->wstream) PO_HIP(hipStreamWaitEvent(q, u->b_done, 0));
+  if (c.weight_stream) PO_RC(lease_streams(st));
+  hipStream_t q = c.weight_stream ? st->wstream : st->compute;
+  if (c.weight_stream) PO_HIP(hipStreamWaitEvent(q, u->b_done, 0));
   char* buf = st->grad_pool.bufs[u->grad_buf].ptr;
   size_t span;
   int rc = span_begin(st, q, 0, &span);
@@ -1197,8 +1295,9 @@ int stage_reset(po_stage* st);
 int stage_synchronize(po_stage* st) {
   PO_HIP(hipStreamSynchronize(st->compute));
   if (st->wstream) PO_HIP(hipStreamSynchronize(st->wstream));
-  PO_HIP(hipStreamSynchronize(st->offload));
-  if (st->reload != st->offload) PO_HIP(hipStreamSynchronize(st->reload));
+  if (st->offload) PO_HIP(hipStreamSynchronize(st->offload));
+  if (st->reload && st->reload != st->offload) PO_HIP(hipStreamSynchronize(st->reload));
+  return_streams(st);
   st->dev_pool.drained();
   st->host_pool.drained();
   st->grad_pool.drained();
@@ -1341,6 +1440,7 @@ int stage_run_schedule(po_stage* st, int schedule, int m, float ratio, const voi
   st->sync_events.reset();
   reset_run_stats(st);
   st->collect_timing = true;
+  st->link_bound = copies_bound(st, ops);
   auto t0 = std::chrono::steady_clock::now();
   for (const po_op& op : ops) {
     size_t i = (size_t)op.chunk * m + op.mb;
@@ -1362,7 +1462,7 @@ int stage_run_schedule(po_stage* st, int schedule, int m, float ratio, const voi
   }
   int rc2 = stage_synchronize(st);
   auto t1 = std::chrono::steady_clock::now();
-  st->collect_timing = false;
+  st->collect_timing = st->link_bound = false;
   if (rc) return rc;
   if (rc2) return rc2;
   st->stats.wall_s = std::chrono::duration<double>(t1 - t0).count();
@@ -1409,29 +1509,15 @@ int stage_create(const po_config* cfg, void* compute_stream, po_stage** out) {
     po_stage_destroy(st);
     return code;
   };
-  // Copy streams at the default priority.
-  if (hipStreamCreateWithFlags(&st->offload, hipStreamNonBlocking) != hipSuccess) {
-    set_error("creating the offload stream failed");
-    st->offload = nullptr;
+  if (hipGetDevice(&st->device) != hipSuccess) {
+    (void)hipGetLastError();
+    set_error("no current device");
     return fail(PO_E_HIP);
   }
-  if (cfg->copy_streams == 2) {
-    if (hipStreamCreateWithFlags(&st->reload, hipStreamNonBlocking) != hipSuccess) {
-      set_error("creating the reload stream failed");
-      st->reload = nullptr;
-      return fail(PO_E_HIP);
-    }
-    st->own_reload_stream = true;
-  } else {
-    st->reload = st->offload;
-  }
-  if (cfg->weight_stream) {
-    if (hipStreamCreateWithFlags(&st->wstream, hipStreamNonBlocking) != hipSuccess) {
-      set_error("creating the weight-gradient stream failed");
-      st->wstream = nullptr;
-      return fail(PO_E_HIP);
-    }
-  }
+  StreamPool::join(st->device);
+  rc = lease_streams(st);  // they exist before the first pass
+  if (rc) return fail(rc);
+  return_streams(st);
   // Workspaces: one allocation, carved up.
   size_t s = cfg->seq, h = cfg->hidden, f = cfg->ffn, E = st->E;
   size_t sh = align_up(s * h * E, 256), sf = align_up(s * f * E, 256), s3h = align_up(s * (size_t)qkv_width_of(*cfg) * E, 256);
@@ -1604,16 +1690,17 @@ int po_stage_create(const po_config* cfg, void* compute_stream, po_stage** out) 
 
 void po_stage_destroy(po_stage* st) {
   if (!st) return;
-  if (st->compute || st->offload) (void)stage_synchronize(st);
+  if (st->device >= 0) (void)stage_synchronize(st);
   st->dev_pool.destroy();
   st->host_pool.destroy();
   st->grad_pool.destroy();
   st->sync_events.destroy();
   st->time_events.destroy();
   if (st->ws) (void)hipFree(st->ws);
-  if (st->own_reload_stream && st->reload) (void)hipStreamDestroy(st->reload);
-  if (st->offload) (void)hipStreamDestroy(st->offload);
-  if (st->wstream) (void)hipStreamDestroy(st->wstream);
+  if (st->device >= 0) {
+    return_streams(st);
+    StreamPool::leave(st->device);
+  }
   delete st;
 }
 

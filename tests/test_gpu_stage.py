@@ -3,6 +3,8 @@
 Gradients, outputs and input gradients of the HIP path are compared per tensor
 with max |got - ref| / max |ref| and with the relative L2 norm (both printed): 1e-4 in fp32, 2e-2 in bf16.  With offload the
 HIP path must reproduce its own no-offload results bit for bit (offload is a copy)."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -139,8 +141,60 @@ def test_offload_copies_below_and_above_a_row_of_the_dma_copy(gpu_device, seq):
         want = _snapshot(r)
         for ratio in (1.0, 0.5, 1.0):
             r.zero_grads()
-            r.run(po.PO_SCHED_1F1B, ratio)
+            r.run(po.PO_SCHED_1F1B, ratio)  # so small a stage is bound by its copies
             _assert_bit_identical(want, _snapshot(r))
+            r.zero_grads()
+            _manual_steps([r], ratio)  # calls outside a schedule always use the DMA engines
+            _assert_bit_identical(want, _snapshot(r))
+
+
+def _manual_steps(runners, ratio):
+    """One step of every runner through single calls, the runners' calls interleaved and nothing waited for in between:
+    all units forwarded and offloaded, then reloaded and differentiated in the same order."""
+    units = runners[0].shape.n_microbatches
+    for j in range(units):
+        for r in runners:
+            po.po_stage_forward(r.stage, j, 0, r.x[j], r.y[j])
+            po.po_offload(r.stage, j, 0, ratio)
+    for j in range(units):
+        for r in runners:
+            po.po_reload(r.stage, j, 0)
+            po.po_stage_backward(r.stage, j, 0, r.dy[j], r.dx[j])
+    for r in runners:
+        po.po_synchronize(r.stage)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(copy_streams=1), dict(weight_stream=1)], ids=["two", "one", "weight"])
+def test_stages_share_the_copy_streams_of_their_device(gpu_device, kw):
+    """Copy streams are leased while a stage has work in flight: stages in flight at the same time, one that outlives
+    another, and stages driven by threads of their own give what each gives alone."""
+    shape = syn.StageShape(2, 1, 128, 2, 512, 96, dtype="f32", pipeline_degree=3, n_microbatches=4)
+    with StageRunner(shape, seed=1, **kw) as a, StageRunner(shape, seed=2, **kw) as b:
+        for r in (a, b):
+            r.make_inputs()
+        want = []
+        for r in (a, b):
+            r.run(po.PO_SCHED_1F1B, 0.0)
+            want.append(_snapshot(r))
+            r.zero_grads()
+        for _ in range(2):
+            _manual_steps([a, b], 1.0)
+            for r, w in zip((a, b), want):
+                _assert_bit_identical(w, _snapshot(r))
+                r.zero_grads()
+        with StageRunner(shape, seed=1, **kw) as c:
+            c.make_inputs()
+            _manual_steps([c, a], 1.0)
+            _assert_bit_identical(want[0], _snapshot(c))
+            _assert_bit_identical(want[0], _snapshot(a))
+        a.zero_grads()
+        threads = [threading.Thread(target=lambda r=r: r.run(po.PO_SCHED_1F1B, 1.0)) for r in (a, b)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for r, w in zip((a, b), want):
+            _assert_bit_identical(w, _snapshot(r))
 
 
 def test_interleaved_schedule_chunks_and_residency(gpu_device):
