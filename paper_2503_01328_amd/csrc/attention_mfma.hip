@@ -23,20 +23,19 @@
 // dK and dV over the query tiles at or below the diagonal; one kernel per query
 // block accumulates dQ over the key tiles up to the diagonal.  Both recompute
 // S = Q K^T and dP = dO V^T.
-#include <math.h>
-
-#include <type_traits>
-
-#include "kernels.h"
+//
+// Every kernel has a second form, EDGE, for sequences that are no multiple of 128: tiles are loaded through buffer
+// descriptors that end with the sequence (rows past it read as zero: such a key is masked like any key above the
+// diagonal, such a query row adds zero to every gradient), results past it are not stored.  It also multiplies P and
+// dS as the sum of two bf16 terms, the rounded value and the rounded remainder (16 bits together), because these
+// sequences ran on the vector kernels, which hold P and dS in fp32.  Relative error against 64 bits at s 1733, 16 heads
+// of 128: o 1.608e-3, dq 1.768e-3 -> 1.770e-3, dk 1.765e-3, dv 1.659e-3, all of it the rounding of the results to bf16
+// (2.8e-3 with one term).  The second term costs a third of the MFMAs.  Vector kernels -> this form,
+// us: s 1733, 16 heads of 128: forward 2235 -> 75, backward 20450 -> 132; s 3000, 32 heads of 64 over 8: 5406 -> 116 and
+// 72760 -> 446; s 100, 16 heads of 128: 35 -> 19 and 147 -> 20.
+#include "mfma_common.h"
 
 namespace po {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 #define LDS_AS3(p) ((s16x4 __attribute__((address_space(3)))*)(p))
 
@@ -79,8 +78,13 @@ __device__ __forceinline__ unsigned tile_lane_offset(int ld, int wave, int lane)
   int c = ((byte % ROW_BYTES) >> 4) ^ swz<DH>(row);
   return (unsigned)((row * ld + c * 8) * 2);
 }
-template <int DH, int WAVES = 4>
-__device__ __forceinline__ void load_tile_async(const bf16* __restrict__ base, int ld, int row0, char* tile,
+// EDGE: rows from s on become zeros.
+template <int DH>
+__device__ __forceinline__ i32x4 rows_buffer(const bf16* src, int ld, int rows_left) {  // at most 64 rows from src on
+  return buffer_of(src, rows_left > 0 ? (unsigned)((min(rows_left, kKeysPerTile) - 1) * ld + DH) * 2u : 0u);
+}
+template <int DH, bool EDGE, int WAVES = 4>
+__device__ __forceinline__ void load_tile_async(const bf16* __restrict__ base, int ld, int row0, int s, char* tile,
                                                 int wave, unsigned lane_offset) {
   constexpr int PER_WAVE = tile_bytes<DH>() / (1024 * WAVES);
   constexpr int ROWS_PER_LOAD = 1024 * WAVES / (DH * 2);  // rows the WAVES waves cover with one load each
@@ -90,9 +94,12 @@ __device__ __forceinline__ void load_tile_async(const bf16* __restrict__ base, i
     const bf16* src = base + (size_t)(row0 + u * ROWS_PER_LOAD) * ld;
     unsigned lds_addr =
         (unsigned)(size_t)((void __attribute__((address_space(3)))*)(tile + (u * WAVES + wave) * 1024));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr),
-                 "v"(lane_offset), "s"(src)
-                 : "memory");
+    if constexpr (EDGE)
+      buffer_to_lds(lds_addr, lane_offset, rows_buffer<DH>(src, ld, s - row0 - u * ROWS_PER_LOAD));
+    else
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr),
+                   "v"(lane_offset), "s"(src)
+                   : "memory");
   }
 }
 // Through the builtin, not inline assembly: the compiler keeps its own count of outstanding loads and cannot see
@@ -145,6 +152,14 @@ __device__ __forceinline__ bf16x8 pack_bf16x8(const f32x16& a, int first) {
   bf16x8 r;
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = (bf16)a[first + e];
+  return r;
+}
+
+// What that rounding left over, as a second fragment.
+__device__ __forceinline__ bf16x8 pack_remainder(const f32x16& a, int first, const bf16x8& rounded) {
+  bf16x8 r;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = (bf16)(a[first + e] - (float)rounded[e]);
   return r;
 }
 
@@ -221,9 +236,10 @@ __device__ __forceinline__ bf16x8 read_k_fragment(unsigned kb, int j, int kk) {
 
 // Softmax of one tile for the 32 rows of a wave: raw scores in, probabilities out as the P fragments of P V;
 // running reference maximum and row sum updated, output accumulators rescaled when the reference moved.
-template <int DH, bool MASK>
+template <int DH, bool EDGE, bool MASK>
 __device__ __forceinline__ void fwd_softmax(f32x16 (&sacc)[2], f32x16 (&oacc)[DH / 32], float& m_run, float& l_run,
-                                            bf16x8 (&pf)[2][2], int key0, int q, int lane, float c) {
+                                            bf16x8 (&pf)[2][2], bf16x8 (&pr)[2][2], int key0, int q, int lane,
+                                            float c) {
   constexpr int DT = DH / 32;
   const int half = lane >> 5;
   if (MASK) {
@@ -275,6 +291,10 @@ __device__ __forceinline__ void fwd_softmax(f32x16 (&sacc)[2], f32x16 (&oacc)[DH
   for (int j = 0; j < 2; ++j) {
     pf[j][0] = pack_bf16x8(sacc[j], 0);
     pf[j][1] = pack_bf16x8(sacc[j], 8);
+    if constexpr (EDGE) {
+      pr[j][0] = pack_remainder(sacc[j], 0, pf[j][0]);
+      pr[j][1] = pack_remainder(sacc[j], 8, pf[j][1]);
+    }
   }
 }
 
@@ -289,11 +309,11 @@ constexpr int q_in_regs() {
   return 4;
 }
 
-template <int DH, bool PV, bool SC>
+template <int DH, bool EDGE, bool PV, bool SC>
 __device__ __forceinline__ void fwd_matrix_slot(const char* vtile, const char* ktile, unsigned q_addr,
                                                 const bf16x8 (&qreg)[q_in_regs<DH>() > 0 ? q_in_regs<DH>() : 1],
                                                 const FragmentOffsets<DH>& fo, const bf16x8 (&pf)[2][2],
-                                                f32x16 (&oacc)[DH / 32], f32x16 (&sacc)[2]) {
+                                                const bf16x8 (&pr)[2][2], f32x16 (&oacc)[DH / 32], f32x16 (&sacc)[2]) {
   constexpr int KS = DH / 16, DT = DH / 32, QR = q_in_regs<DH>();
   constexpr int NPV = PV ? 4 * DT : 0;  // P V MFMAs, one V fragment each
   constexpr int NSC = SC ? 2 * KS : 0;  // score MFMAs; step kk reads K(0, kk), K(1, kk) and, from QR on, Q(kk) first
@@ -342,6 +362,8 @@ __device__ __forceinline__ void fwd_matrix_slot(const char* vtile, const char* k
     if constexpr (m + AV >= NPV && m + AV < NPV + PRE_S) fetch_s(std::integral_constant<int, m + AV - NPV>());
     constexpr int js = m / DT, d = m % DT;
     oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring_v[m % RV], pf[js >> 1][js & 1], oacc[d], 0, 0, 0);
+    if constexpr (EDGE)
+      oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring_v[m % RV], pr[js >> 1][js & 1], oacc[d], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   });
   static_for<0, NSC>([&](auto mc) {
@@ -365,7 +387,7 @@ __device__ __forceinline__ void fwd_matrix_slot(const char* vtile, const char* k
   });
 }
 
-template <int DH, int G>
+template <int DH, int G, bool EDGE>
 __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16* __restrict__ qkv,
                                                                     bf16* __restrict__ o, float* __restrict__ lse,
                                                                     int s, int h, int hkv, int group, float scale) {
@@ -406,9 +428,12 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
       for (int q = 0; q < PIECES; ++q) {
         const bf16* src = base + (size_t)(row0 + (q >> 2) * ROWS_PER_4K) * ld;
         unsigned lds_addr = lds_address_of(tile + q * 1024);
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr),
-                     "v"(lane_off[q & 3]), "s"(src)
-                     : "memory");
+        if constexpr (EDGE)
+          buffer_to_lds(lds_addr, lane_off[q & 3], rows_buffer<DH>(src, ld, s - row0 - (q >> 2) * ROWS_PER_4K));
+        else
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr),
+                       "v"(lane_off[q & 3]), "s"(src)
+                       : "memory");
       }
     };
     const int tile_last = nkv - 1;
@@ -468,7 +493,7 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
   // this wave's Q rows: tile wrow / 2 of the Q area, rows 32 (wrow % 2) ..
   const unsigned q_addr = lds_address_of(smem + (wrow >> 1) * TBYTES) + fo.k + (wrow & 1) * 32 * DH * 2;
   f32x16 oacc[DT], sacc[2];
-  bf16x8 pf[2][2];
+  bf16x8 pf[2][2], pr[2][2];  // P and (EDGE) the remainders of its rounding
   float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
   for (int d = 0; d < DT; ++d)
@@ -491,13 +516,13 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
     const char* st = my_stages + (j % NST) * STAGE;
     __builtin_amdgcn_s_setprio(1);
     if constexpr (decltype(pv)::value || decltype(sc)::value)
-      fwd_matrix_slot<DH, decltype(pv)::value, decltype(sc)::value>(st, st + TBYTES, q_addr, qreg, fo, pf, oacc,
-                                                                      sacc);
+      fwd_matrix_slot<DH, EDGE, decltype(pv)::value, decltype(sc)::value>(st, st + TBYTES, q_addr, qreg, fo, pf, pr,
+                                                                          oacc, sacc);
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
     if constexpr (decltype(sc)::value)
-      fwd_softmax<DH, decltype(mask)::value>(sacc, oacc, m_run, l_run, pf, (G * j + tg) * kKeysPerTile, qw0 + col,
-                                             lane, c);
+      fwd_softmax<DH, EDGE, decltype(mask)::value>(sacc, oacc, m_run, l_run, pf, pr, (G * j + tg) * kKeysPerTile,
+                                                   qw0 + col, lane, c);
     if (last_barrier) __syncthreads();
   };
   const std::true_type yes;
@@ -544,6 +569,7 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
   }
   const int q = qw0 + col;
   float l = l_run + __shfl_xor(l_run, 32, 64);
+  if (EDGE && q >= s) return;
   float inv = 1.0f / l;
 #pragma unroll
   for (int d = 0; d < DT; ++d)
@@ -570,7 +596,7 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
 // The backward kernels are written as block functions: bx, by and gy stand for blockIdx.x, blockIdx.y and gridDim.y,
 // so that a kernel of its own (the thin wrapper after each function) and the one-launch kernel further down, which
 // numbers its blocks itself, run the same code.
-template <int DH>
+template <int DH, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
     const float* __restrict__ lse, const float* __restrict__ delta, bf16* __restrict__ out, int ld_out, int out_k0,
     int out_v_delta, int hpb, int s, int h, int hkv, int group, float scale, int bx, int by, int gy) {
@@ -603,7 +629,8 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
   bf16x8 kf[KS], vf[V_IN_REG > 0 ? V_IN_REG : 1];
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) {
-    const bf16* row = qkv + (size_t)(kw0 + col) * ld + h + kv_head * DH + 16 * kk + 8 * half;
+    const int key = EDGE ? min(kw0 + col, s - 1) : kw0 + col;  // (keys past the end: computed, not stored)
+    const bf16* row = qkv + (size_t)key * ld + h + kv_head * DH + 16 * kk + 8 * half;
     kf[kk] = *reinterpret_cast<const bf16x8*>(row);
     bf16x8 v = *reinterpret_cast<const bf16x8*>(row + hkv);
     if (kk < V_IN_REG)
@@ -619,7 +646,7 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
 
   // Query tiles [q_first, q_last) of every query head of this block, one head after the other:
   // iteration `it` works on head head_first + it / n_qt, tile q_first + it % n_qt.
-  int q_first = kb0 / kKeysPerTile, q_last = s / kKeysPerTile;
+  int q_first = kb0 / kKeysPerTile, q_last = 2 * gy;
   int n_qt = q_last - q_first, n_it = hpb * n_qt;
   // Row statistics enter as the initial value of the accumulators: S starts at -lse / scale, so that
   // exp2((S - lse / scale) * scale * log2 e) = P, and dP starts at -delta, so that dS = P * acc.
@@ -630,23 +657,28 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
   const float stat_mul = (tid & 64) ? -1.0f : __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(
                                                    __builtin_bit_cast(int, -1.0f / scale)));
   float stat = 0.f;
-  auto load_stats = [&](int head, int q0) { stat = stat_src[(size_t)head * s + q0]; };
+  auto load_stats = [&](int head, int q0) {
+    if constexpr (EDGE) stat = stat_src[(size_t)head * s + min(q0, s - 1 - (tid & 63))];
+    else stat = stat_src[(size_t)head * s + q0];
+  };
   auto tile_of = [&](int it, int& head, int& qt) {
     int g = it / n_qt;
     head = head_first + g;
     qt = q_first + it - g * n_qt;
   };
-  auto store_stats = [&](char* stage) {
-    if (tid < 128) reinterpret_cast<float*>(stage + 2 * TBYTES)[tid] = stat * stat_mul;
+  auto store_stats = [&](char* stage, int q0) {  // a row past the end: P = exp(0), times its dO of zeros
+    float v = stat * stat_mul;
+    if (EDGE && q0 + (tid & 63) >= s) v = 0.f;
+    if (tid < 128) reinterpret_cast<float*>(stage + 2 * TBYTES)[tid] = v;
   };
   const unsigned q_lane_off = tile_lane_offset<DH>(ld, wave, lane), do_lane_off = tile_lane_offset<DH>(h, wave, lane);
   {
     int head0 = head_first;
-    load_tile_async<DH>(qkv + head0 * DH, ld, q_first * kKeysPerTile, smem, wave, q_lane_off);
-    load_tile_async<DH>(d_o + head0 * DH, h, q_first * kKeysPerTile, smem + TBYTES, wave, do_lane_off);
+    load_tile_async<DH, EDGE>(qkv + head0 * DH, ld, q_first * kKeysPerTile, s, smem, wave, q_lane_off);
+    load_tile_async<DH, EDGE>(d_o + head0 * DH, h, q_first * kKeysPerTile, s, smem + TBYTES, wave, do_lane_off);
     load_stats(head0, q_first * kKeysPerTile);
   }
-  store_stats(smem);
+  store_stats(smem, q_first * kKeysPerTile);
   wait_tile_loads_opaque();
   __syncthreads();
 
@@ -670,8 +702,8 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
     if (more) {  // the other stage was last read before the barrier that ended the previous iteration
       int nhead, nqt;
       tile_of(it + 1, nhead, nqt);
-      load_tile_async<DH>(qkv + nhead * DH, ld, nqt * kKeysPerTile, nxt, wave, q_lane_off);
-      load_tile_async<DH>(d_o + nhead * DH, h, nqt * kKeysPerTile, nxt + TBYTES, wave, do_lane_off);
+      load_tile_async<DH, EDGE>(qkv + nhead * DH, ld, nqt * kKeysPerTile, s, nxt, wave, q_lane_off);
+      load_tile_async<DH, EDGE>(d_o + nhead * DH, h, nqt * kKeysPerTile, s, nxt + TBYTES, wave, do_lane_off);
       load_stats(nhead, nqt * kKeysPerTile);
     }
     int q0 = qt * kKeysPerTile;
@@ -688,8 +720,55 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           sacc[4 * b + r] = l4[r];
-          pacc[4 * b + r] = d4[r];
+          if (!EDGE) pacc[4 * b + r] = d4[r];
         }
+      }
+      if constexpr (EDGE) {
+        // One product after the other, so that the two-term operands need no more registers than the other form:
+        // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              read_row_fragment<DH>(qtile, 32 * j + col_l, 2 * kk + half_l), kf[kk], sacc, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          sacc[e] = fast_exp2(sacc[e] * c);
+          if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) sacc[e] = 0.f;
+        }
+        auto accumulate = [&](f32x16 (&to)[DT], const f32x16& w, const char* tile) __attribute__((always_inline)) {
+#pragma unroll
+          for (int st = 0; st < 2; ++st) {
+            const bf16x8 hi = pack_bf16x8(w, 8 * st), lo = pack_remainder(w, 8 * st, hi);
+#pragma unroll
+            for (int d = 0; d < DT; ++d) {
+              bf16x8 tr = read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane_l);
+              to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, lo, to[d], 0, 0, 0);
+              to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, hi, to[d], 0, 0, 0);
+            }
+          }
+        };
+        accumulate(dv, sacc, dotile);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          f32x4 d4 = *reinterpret_cast<const f32x4*>(st_delta + 32 * j + 8 * b + 4 * half_l);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) pacc[4 * b + r] = d4[r];
+        }
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+          bf16x8 vb;
+          if (kk < V_IN_REG)
+            vb = vf[kk];
+          else
+            vb = *reinterpret_cast<const bf16x8*>(vslot_l + (kk - V_IN_REG) * 1024);
+          pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              read_row_fragment<DH>(dotile, 32 * j + col_l, 2 * kk + half_l), vb, pacc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) pacc[e] *= sacc[e];
+        accumulate(dk, pacc, qtile);
+        continue;
       }
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
@@ -725,12 +804,17 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
           dk[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qtr, dsf[st], dk[d], 0, 0, 0);
         }
     }
-    if (more) store_stats(nxt);
+    if (more) {
+      int nhead, nqt;
+      tile_of(it + 1, nhead, nqt);
+      store_stats(nxt, nqt * kKeysPerTile);
+    }
     wait_tile_loads_opaque();
     __syncthreads();
   }
 
   int key = kw0 + col;
+  if (EDGE && key >= s) return;
 #pragma unroll
   for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -747,17 +831,17 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
     }
 }
 
-template <int DH>
+template <int DH, bool EDGE>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ out, int ld_out, int out_k0, int out_v_delta, int hpb, int s, int h, int hkv, int group,
     float scale) {
-  attn_bwd_dkv_mfma_block<DH>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group, scale,
+  attn_bwd_dkv_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group, scale,
       (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y);
 }
 
 // dK, dV for launches too small to give every CU two blocks: the kernel above with eight waves per block.
-template <int DH>
+template <int DH, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ out, int ld_out, int out_k0, int out_v_delta, int hpb, int s, int h, int hkv, int group,
@@ -796,7 +880,8 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
   bf16x8 kf[KS], vf[V_IN_REG > 0 ? V_IN_REG : 1];
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) {
-    const bf16* row = qkv + (size_t)(kw0 + col) * ld + h + kv_head * DH + 16 * kk + 8 * half;
+    const int key = EDGE ? min(kw0 + col, s - 1) : kw0 + col;  // (keys past the end: computed, not stored)
+    const bf16* row = qkv + (size_t)key * ld + h + kv_head * DH + 16 * kk + 8 * half;
     kf[kk] = *reinterpret_cast<const bf16x8*>(row);
     bf16x8 v = *reinterpret_cast<const bf16x8*>(row + hkv);
     if (kk < V_IN_REG)
@@ -812,7 +897,7 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
 
   // Query tiles [q_first, q_last) of every query head of this block, one head after the other:
   // iteration `it` works on head head_first + it / n_qt, tile q_first + it % n_qt.
-  int q_first = kb0 / kKeysPerTile, q_last = s / kKeysPerTile;
+  int q_first = kb0 / kKeysPerTile, q_last = 2 * gy;
   int n_qt = q_last - q_first, n_it = hpb * n_qt;
   // Row statistics enter as the initial value of the accumulators: S starts at -lse / scale, so that
   // exp2((S - lse / scale) * scale * log2 e) = P, and dP starts at -delta, so that dS = P * acc.
@@ -823,24 +908,33 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
   const float stat_mul = (tid & 64) ? -1.0f : __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(
                                                    __builtin_bit_cast(int, -1.0f / scale)));
   float stat = 0.f;
-  auto load_stats = [&](int head, int q0) { stat = stat_src[(size_t)head * s + q0]; };
+  auto load_stats = [&](int head, int q0) {
+    if constexpr (EDGE) stat = stat_src[(size_t)head * s + min(q0, s - 1 - (tid & 63))];
+    else stat = stat_src[(size_t)head * s + q0];
+  };
   auto tile_of = [&](int it, int& head, int& qt) {
     int g = it / n_qt;
     head = head_first + g;
     qt = q_first + it - g * n_qt;
   };
-  auto store_stats = [&](char* stage) {
-    if (tid < 128) reinterpret_cast<float*>(stage + 2 * TBYTES)[tid] = stat * stat_mul;
+  auto store_stats = [&](char* stage, int q0) {  // a row past the end: P = exp(0), times its dO of zeros
+    float v = stat * stat_mul;
+    if (EDGE && q0 + (tid & 63) >= s) v = 0.f;
+    if (tid < 128) reinterpret_cast<float*>(stage + 2 * TBYTES)[tid] = v;
   };
   const unsigned q_lane_off = tile_lane_offset<DH>(ld, wave, lane), do_lane_off = tile_lane_offset<DH>(h, wave, lane);
   {  // n_it >= 2 (a key block has at least two query tiles at or below it): both groups have a first tile
     int head0, qt0;
     tile_of(grp, head0, qt0);
-    load_tile_async<DH>(qkv + head0 * DH, ld, qt0 * kKeysPerTile, smem, wave, q_lane_off);
-    load_tile_async<DH>(d_o + head0 * DH, h, qt0 * kKeysPerTile, smem + TBYTES, wave, do_lane_off);
+    load_tile_async<DH, EDGE>(qkv + head0 * DH, ld, qt0 * kKeysPerTile, s, smem, wave, q_lane_off);
+    load_tile_async<DH, EDGE>(d_o + head0 * DH, h, qt0 * kKeysPerTile, s, smem + TBYTES, wave, do_lane_off);
     load_stats(head0, qt0 * kKeysPerTile);
   }
-  store_stats(smem);
+  {
+    int head0, qt0;
+    tile_of(grp, head0, qt0);
+    store_stats(smem, qt0 * kKeysPerTile);
+  }
   wait_tile_loads_opaque();
   __syncthreads();
 
@@ -867,8 +961,8 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
     if (more) {  // the other stage was last read before the barrier that ended the previous iteration
       int nhead, nqt;
       tile_of(it + 2, nhead, nqt);
-      load_tile_async<DH>(qkv + nhead * DH, ld, nqt * kKeysPerTile, nxt, wave, q_lane_off);
-      load_tile_async<DH>(d_o + nhead * DH, h, nqt * kKeysPerTile, nxt + TBYTES, wave, do_lane_off);
+      load_tile_async<DH, EDGE>(qkv + nhead * DH, ld, nqt * kKeysPerTile, s, nxt, wave, q_lane_off);
+      load_tile_async<DH, EDGE>(d_o + nhead * DH, h, nqt * kKeysPerTile, s, nxt + TBYTES, wave, do_lane_off);
       load_stats(nhead, nqt * kKeysPerTile);
     }
     int q0 = qt * kKeysPerTile;
@@ -885,8 +979,55 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           sacc[4 * b + r] = l4[r];
-          pacc[4 * b + r] = d4[r];
+          if (!EDGE) pacc[4 * b + r] = d4[r];
         }
+      }
+      if constexpr (EDGE) {
+        // One product after the other, so that the two-term operands need no more registers than the other form:
+        // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              read_row_fragment<DH>(qtile, 32 * j + col_l, 2 * kk + half_l), kf[kk], sacc, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          sacc[e] = fast_exp2(sacc[e] * c);
+          if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) sacc[e] = 0.f;
+        }
+        auto accumulate = [&](f32x16 (&to)[DT], const f32x16& w, const char* tile) __attribute__((always_inline)) {
+#pragma unroll
+          for (int st = 0; st < 2; ++st) {
+            const bf16x8 hi = pack_bf16x8(w, 8 * st), lo = pack_remainder(w, 8 * st, hi);
+#pragma unroll
+            for (int d = 0; d < DT; ++d) {
+              bf16x8 tr = read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane_l);
+              to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, lo, to[d], 0, 0, 0);
+              to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, hi, to[d], 0, 0, 0);
+            }
+          }
+        };
+        accumulate(dv, sacc, dotile);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          f32x4 d4 = *reinterpret_cast<const f32x4*>(st_delta + 32 * j + 8 * b + 4 * half_l);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) pacc[4 * b + r] = d4[r];
+        }
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+          bf16x8 vb;
+          if (kk < V_IN_REG)
+            vb = vf[kk];
+          else
+            vb = *reinterpret_cast<const bf16x8*>(vslot_l + (kk - V_IN_REG) * 1024);
+          pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              read_row_fragment<DH>(dotile, 32 * j + col_l, 2 * kk + half_l), vb, pacc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) pacc[e] *= sacc[e];
+        accumulate(dk, pacc, qtile);
+        continue;
       }
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
@@ -922,7 +1063,11 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
           dk[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qtr, dsf[st], dk[d], 0, 0, 0);
         }
     }
-    if (more) store_stats(nxt);
+    if (more) {
+      int nhead, nqt;
+      tile_of(it + 2, nhead, nqt);
+      store_stats(nxt, nqt * kKeysPerTile);
+    }
     wait_tile_loads_opaque();
     __syncthreads();
   }
@@ -945,6 +1090,7 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
   if (grp == 0) {
     int half = lane_e >> 5;
     int key = kw0 + (lane_e & 31);
+    if (EDGE && key >= s) return;
 #pragma unroll
     for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -963,12 +1109,12 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
   }
 }
 
-template <int DH>
+template <int DH, bool EDGE>
 __global__ __launch_bounds__(512, 1) void attn_bwd_dkv_split_mfma_kernel(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ out, int ld_out, int out_k0, int out_v_delta, int hpb, int s, int h, int hkv, int group,
     float scale) {
-  attn_bwd_dkv_split_mfma_block<DH>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group,
+  attn_bwd_dkv_split_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group,
       scale, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y);
 }
 
@@ -977,7 +1123,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkv_split_mfma_kernel(const b
 // key tiles up to the diagonal.  The K tile is read both ways (row fragments for
 // S^T = K Q^T, transposing fragments for dQ^T = K^T dS^T), the V tile as row fragments.
 // ==================================================================================
-template <int DH, int QT>
+template <int DH, int QT, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ qkv, const bf16* __restrict__ d_o,
     const float* __restrict__ lse, const float* __restrict__ delta, bf16* __restrict__ dqkv, int s, int h, int hkv,
     int group, float scale, int bx, int by, int gy) {
@@ -1004,6 +1150,7 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
     int q = qw0 + 32 * t + col;
+    if (EDGE) q = min(q, s - 1);  // (rows past the end: computed, not stored)
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
       qf[t][kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)q * ld + head * DH + 16 * kk + 8 * half);
@@ -1022,8 +1169,8 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
 
   int nkv = (q0 + BQ) / kKeysPerTile;
   const unsigned lane_off = tile_lane_offset<DH>(ld, wave, lane);
-  load_tile_async<DH>(kbase, ld, 0, smem, wave, lane_off);
-  load_tile_async<DH>(vbase, ld, 0, smem + KBYTES, wave, lane_off);
+  load_tile_async<DH, EDGE>(kbase, ld, 0, s, smem, wave, lane_off);
+  load_tile_async<DH, EDGE>(vbase, ld, 0, s, smem + KBYTES, wave, lane_off);
   wait_tile_loads();
   __syncthreads();
 
@@ -1033,8 +1180,8 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
     char* nxt = smem + ((kt + 1) & 1) * STAGE;
     bool more = kt + 1 < nkv;
     if (more) {  // the other stage was last read before the barrier that ended the previous iteration
-      load_tile_async<DH>(kbase, ld, (kt + 1) * kKeysPerTile, nxt, wave, lane_off);
-      load_tile_async<DH>(vbase, ld, (kt + 1) * kKeysPerTile, nxt + KBYTES, wave, lane_off);
+      load_tile_async<DH, EDGE>(kbase, ld, (kt + 1) * kKeysPerTile, s, nxt, wave, lane_off);
+      load_tile_async<DH, EDGE>(vbase, ld, (kt + 1) * kKeysPerTile, s, nxt + KBYTES, wave, lane_off);
     }
     int key0 = kt * kKeysPerTile;
 #pragma unroll
@@ -1056,7 +1203,7 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
           pacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, dof[t][kk], pacc[t], 0, 0, 0);
         }
       }
-      bf16x8 dsf[QT][2];
+      bf16x8 dsf[QT][2], dsr[QT][2];
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
         int q = qw0 + 32 * t + col;
@@ -1072,6 +1219,10 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
         for (int e = 0; e < 16; ++e) pacc[t][e] = sacc[t][e] * (pacc[t][e] - delta_q[t]);
         dsf[t][0] = pack_bf16x8(pacc[t], 0);
         dsf[t][1] = pack_bf16x8(pacc[t], 8);
+        if constexpr (EDGE) {
+          dsr[t][0] = pack_remainder(pacc[t], 0, dsf[t][0]);
+          dsr[t][1] = pack_remainder(pacc[t], 8, dsf[t][1]);
+        }
       }
 #pragma unroll
       for (int d = 0; d < DT; ++d)
@@ -1079,8 +1230,11 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
         for (int st = 0; st < 2; ++st) {
           bf16x8 ktr = read_tr_fragment<DH>(ktile, 32 * j + 16 * st, 32 * d, lane);
 #pragma unroll
-          for (int t = 0; t < QT; ++t)
+          for (int t = 0; t < QT; ++t) {
+            if constexpr (EDGE)
+              dq[t][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr, dsr[t][st], dq[t][d], 0, 0, 0);
             dq[t][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr, dsf[t][st], dq[t][d], 0, 0, 0);
+          }
         }
     }
     wait_tile_loads();
@@ -1090,6 +1244,7 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
     int q = qw0 + 32 * t + col;
+    if (EDGE && q >= s) continue;
 #pragma unroll
     for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -1102,18 +1257,18 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
   }
 }
 
-template <int DH, int QT>
+template <int DH, int QT, bool EDGE>
 __global__ __launch_bounds__(256, QT == 1 ? 2 : 1) void attn_bwd_dq_mfma_kernel(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ dqkv, int s, int h, int hkv, int group, float scale) {
-  attn_bwd_dq_mfma_block<DH, QT>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, (int)blockIdx.x,
+  attn_bwd_dq_mfma_block<DH, QT, EDGE>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, (int)blockIdx.x,
       (int)blockIdx.y, (int)gridDim.y);
 }
 
 // dQ for launches too small to give every CU two blocks: eight waves, waves w and w + 4 own the same 32
 // query rows and alternate key tiles, as the two groups of the forward kernel's 128-row form do; group 1's
 // partial dQ goes to group 0 through LDS at the end (one addition per element, always in the same order).
-template <int DH>
+template <int DH, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ dqkv, int s, int h, int hkv, int group, float scale, int bx, int by, int gy) {
@@ -1140,13 +1295,14 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
 
   bf16x8 qf[KS], dof[KS];
   int q = qw0 + col;
+  const int q_in = EDGE ? min(q, s - 1) : q;  // (rows past the end: computed, not stored)
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) {
-    qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)q * ld + head * DH + 16 * kk + 8 * half);
-    dof[kk] = *reinterpret_cast<const bf16x8*>(d_o + (size_t)q * h + head * DH + 16 * kk + 8 * half);
+    qf[kk] = *reinterpret_cast<const bf16x8*>(qkv + (size_t)q_in * ld + head * DH + 16 * kk + 8 * half);
+    dof[kk] = *reinterpret_cast<const bf16x8*>(d_o + (size_t)q_in * h + head * DH + 16 * kk + 8 * half);
   }
-  float lse_q = lse[(size_t)head * s + q] * LOG2E;
-  float delta_q = delta[(size_t)head * s + q];
+  float lse_q = lse[(size_t)head * s + q_in] * LOG2E;
+  float delta_q = delta[(size_t)head * s + q_in];
   f32x16 dq[DT];
 #pragma unroll
   for (int d = 0; d < DT; ++d)
@@ -1155,8 +1311,8 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
 
   int n_it = (q0 + BQ) / kKeysPerTile / 2;  // tiles per group
   const unsigned lane_off = tile_lane_offset<DH>(ld, wave, lane);
-  load_tile_async<DH>(kbase, ld, grp * kKeysPerTile, smem, wave, lane_off);
-  load_tile_async<DH>(vbase, ld, grp * kKeysPerTile, smem + KBYTES, wave, lane_off);
+  load_tile_async<DH, EDGE>(kbase, ld, grp * kKeysPerTile, s, smem, wave, lane_off);
+  load_tile_async<DH, EDGE>(vbase, ld, grp * kKeysPerTile, s, smem + KBYTES, wave, lane_off);
   wait_tile_loads();
   __syncthreads();
 
@@ -1166,8 +1322,8 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
     const char* vtile = ktile + KBYTES;
     char* nxt = smem + ((it + 1) & 1) * STAGE;
     if (it + 1 < n_it) {
-      load_tile_async<DH>(kbase, ld, (kt + 2) * kKeysPerTile, nxt, wave, lane_off);
-      load_tile_async<DH>(vbase, ld, (kt + 2) * kKeysPerTile, nxt + KBYTES, wave, lane_off);
+      load_tile_async<DH, EDGE>(kbase, ld, (kt + 2) * kKeysPerTile, s, nxt, wave, lane_off);
+      load_tile_async<DH, EDGE>(vbase, ld, (kt + 2) * kKeysPerTile, s, nxt + KBYTES, wave, lane_off);
     }
     int key0 = kt * kKeysPerTile;
 #pragma unroll
@@ -1193,12 +1349,17 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) pacc[e] = sacc[e] * (pacc[e] - delta_q);
-      bf16x8 dsf[2] = {pack_bf16x8(pacc, 0), pack_bf16x8(pacc, 8)};
+      bf16x8 dsf[2] = {pack_bf16x8(pacc, 0), pack_bf16x8(pacc, 8)}, dsr[2];
+      if constexpr (EDGE) {
+        dsr[0] = pack_remainder(pacc, 0, dsf[0]);
+        dsr[1] = pack_remainder(pacc, 8, dsf[1]);
+      }
 #pragma unroll
       for (int d = 0; d < DT; ++d)
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
           bf16x8 ktr = read_tr_fragment<DH>(ktile, 32 * j + 16 * st, 32 * d, lane);
+          if constexpr (EDGE) dq[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr, dsr[st], dq[d], 0, 0, 0);
           dq[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr, dsf[st], dq[d], 0, 0, 0);
         }
     }
@@ -1214,7 +1375,7 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
       for (int e = 0; e < 16; ++e) xch[(d * 16 + e) * 64 + lane] = dq[d][e];
   }
   __syncthreads();
-  if (grp == 0) {
+  if (grp == 0 && !(EDGE && q >= s)) {
 #pragma unroll
     for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -1230,11 +1391,11 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
   }
 }
 
-template <int DH>
+template <int DH, bool EDGE>
 __global__ __launch_bounds__(512, 1) void attn_bwd_dq_split_mfma_kernel(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ dqkv, int s, int h, int hkv, int group, float scale) {
-  attn_bwd_dq_split_mfma_block<DH>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, (int)blockIdx.x,
+  attn_bwd_dq_split_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, (int)blockIdx.x,
       (int)blockIdx.y, (int)gridDim.y);
 }
 
@@ -1244,29 +1405,29 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_split_mfma_kernel(const bf
 // are the dQ blocks, the dQ blocks start on the CUs that the light dK/dV blocks leave early.  The two parts
 // share nothing but their inputs (dQ, and dK/dV or their partials, are disjoint outputs), so a block runs
 // exactly what it would run in its own kernel and the results are the same bit for bit.
-template <int DH, bool EIGHT>
+template <int DH, bool EIGHT, bool EDGE>
 __global__ __launch_bounds__(EIGHT ? 512 : 256, EIGHT ? 1 : 2) void attn_bwd_fused_mfma_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ d_o, const float* __restrict__ lse,
     const float* __restrict__ delta, bf16* __restrict__ out, int ld_out, int out_k0, int out_v_delta, int hpb,
     bf16* __restrict__ dqkv, int s, int h, int hkv, int group, float scale, int x_kv, int x_q) {
-  int gy = s / 128;
+  int gy = (s + 127) / 128;
   int b = (int)blockIdx.x, n_kv = x_kv * gy;
   if (b < n_kv) {
     int by = b / x_kv, bx = b - by * x_kv;
     if constexpr (EIGHT)
-      attn_bwd_dkv_split_mfma_block<DH>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group,
+      attn_bwd_dkv_split_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group,
                                         scale, bx, by, gy);
     else
-      attn_bwd_dkv_mfma_block<DH>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group,
+      attn_bwd_dkv_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group,
           scale,
                                   bx, by, gy);
   } else {
     b -= n_kv;
     int by = b / x_q, bx = b - by * x_q;
     if constexpr (EIGHT)
-      attn_bwd_dq_split_mfma_block<DH>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, bx, by, gy);
+      attn_bwd_dq_split_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, bx, by, gy);
     else
-      attn_bwd_dq_mfma_block<DH, 1>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, bx, by, gy);
+      attn_bwd_dq_mfma_block<DH, 1, EDGE>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, bx, by, gy);
   }
 }
 
@@ -1326,17 +1487,17 @@ __global__ __launch_bounds__(256) void attn_delta_mfma_path_kernel(const bf16* _
 bool attention_mfma_supported(int s, int h, int n_heads, int n_kv_heads) {
   if (n_heads <= 0 || h % n_heads != 0 || n_kv_heads <= 0 || n_heads % n_kv_heads != 0) return false;
   int dh = h / n_heads;
-  return (dh == 64 || dh == 128) && s >= 128 && s % 128 == 0;
+  return (dh == 64 || dh == 128) && s >= 1;
 }
 
-template <int DH>
+template <int DH, bool EDGE>
 static bool launch_fwd(const bf16* qkv, bf16* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                        hipStream_t stream) {
   constexpr int smem = 10 * tile_bytes<DH>();  // Q tiles and stage rings: 160 KiB for DH = 128 in either form
   // 256-row blocks where they still give every CU one; else 128-row blocks whose two groups split the key tiles.
-  const bool big = s % 256 == 0 && (int64_t)n_heads * (s / 256) >= 256;
-  auto k1 = attn_fwd_roles_mfma_kernel<DH, 1>;
-  auto k2 = attn_fwd_roles_mfma_kernel<DH, 2>;
+  const bool big = (EDGE || s % 256 == 0) && (int64_t)n_heads * ceil_div(s, 256) >= 256;
+  auto k1 = attn_fwd_roles_mfma_kernel<DH, 1, EDGE>;
+  auto k2 = attn_fwd_roles_mfma_kernel<DH, 2, EDGE>;
   static bool configured = false;
   if (!configured) {
     PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(k1), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1347,9 +1508,11 @@ static bool launch_fwd(const bf16* qkv, bf16* o, float* lse, int s, int h, int n
   }
   const float scale = 1.0f / sqrtf((float)DH);
   if (big)
-    k1<<<dim3(n_heads, s / 256), 576, smem, stream>>>(qkv, o, lse, s, h, n_kv_heads * DH, n_heads / n_kv_heads, scale);
+    k1<<<dim3(n_heads, ceil_div(s, 256)), 576, smem, stream>>>(qkv, o, lse, s, h, n_kv_heads * DH,
+                                                               n_heads / n_kv_heads, scale);
   else
-    k2<<<dim3(n_heads, s / 128), 576, smem, stream>>>(qkv, o, lse, s, h, n_kv_heads * DH, n_heads / n_kv_heads, scale);
+    k2<<<dim3(n_heads, ceil_div(s, 128)), 576, smem, stream>>>(qkv, o, lse, s, h, n_kv_heads * DH,
+                                                               n_heads / n_kv_heads, scale);
   return launch_ok("attn_fwd_roles_mfma_kernel");
 }
 
@@ -1363,17 +1526,21 @@ bool attention_forward_mfma(const void* qkv, void* o, float* lse, int s, int h, 
   }
   const bf16* q = (const bf16*)qkv;
   bf16* out = (bf16*)o;
-  if (h / n_heads == 128) return launch_fwd<128>(q, out, lse, s, h, n_heads, n_kv_heads, stream);
-  return launch_fwd<64>(q, out, lse, s, h, n_heads, n_kv_heads, stream);
+  if (s % 128 == 0) {
+    if (h / n_heads == 128) return launch_fwd<128, false>(q, out, lse, s, h, n_heads, n_kv_heads, stream);
+    return launch_fwd<64, false>(q, out, lse, s, h, n_heads, n_kv_heads, stream);
+  }
+  if (h / n_heads == 128) return launch_fwd<128, true>(q, out, lse, s, h, n_heads, n_kv_heads, stream);
+  return launch_fwd<64, true>(q, out, lse, s, h, n_heads, n_kv_heads, stream);
 }
 
-template <int DH>
+template <int DH, bool EDGE>
 static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const bf16* d_o, bf16* dqkv, float* delta,
                        bf16* partials, int s, int h, int n_heads, int n_kv_heads, hipStream_t stream) {
   constexpr int smem_kv = 2 * (2 * tile_bytes<DH>() + 512) + (DH == 128 ? 8192 : 0);  // + V fragments kept in LDS
   constexpr int smem_q = 4 * tile_bytes<DH>();
-  auto kkv = attn_bwd_dkv_mfma_kernel<DH>;
-  auto kq1 = attn_bwd_dq_mfma_kernel<DH, 1>;
+  auto kkv = attn_bwd_dkv_mfma_kernel<DH, EDGE>;
+  auto kq1 = attn_bwd_dq_mfma_kernel<DH, 1, EDGE>;
   static bool configured = false;
   if (!configured) {
     PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kkv), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1386,29 +1553,31 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
   int hkv = n_kv_heads * DH, group = n_heads / n_kv_heads;
   attn_delta_mfma_path_kernel<DH><<<(unsigned)(((size_t)s * h / 8 + 255) / 256), 256, 0, stream>>>(o, d_o, delta, s, h);
   // Few key/value heads: one block per query head and a per-group sum afterwards (needs the [s, 2h] workspace),
-  // once the direct launch would not fill the chip's 512 block slots.
-  bool split = group > 1 && partials && (int64_t)n_kv_heads * (s / 128) < 512;
+  // once the direct launch would not fill the chip's 512 block slots.  The partials are rounded to bf16, which the
+  // EDGE form, whose sums over a group have always been fp32, does not do.
+  const int blocks = ceil_div(s, 128);
+  bool split = !EDGE && group > 1 && partials && (int64_t)n_kv_heads * blocks < 512;
   // At most one block per CU: the eight-wave kernel, which halves a wave's chain of tiles.
   constexpr int smem_kv8 = 4 * (2 * tile_bytes<DH>() + 512) + (DH == 128 ? 24576 : 0);
-  auto kkv8 = attn_bwd_dkv_split_mfma_kernel<DH>;
-  bool eight = (int64_t)(split ? n_heads : n_kv_heads) * (s / 128) <= 256;
+  auto kkv8 = attn_bwd_dkv_split_mfma_kernel<DH, EDGE>;
+  bool eight = (int64_t)(split ? n_heads : n_kv_heads) * blocks <= 256;
   static bool eight_configured = false;
   if (eight && !eight_configured) {
     PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kkv8), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   smem_kv8));
     eight_configured = true;
   }
-  const bool dq_eight = (int64_t)n_heads * (s / 128) <= 256;  // one block per CU at most: the eight-wave kernel
+  const bool dq_eight = (int64_t)n_heads * blocks <= 256;  // one block per CU at most: the eight-wave kernel
   constexpr int smem_split = 8 * tile_bytes<DH>();
   // where dK/dV go: per-head partials [s, 2h] or dqkv itself
   bf16* kv_out = split ? partials : dqkv;
   const int kv_ld = split ? 2 * h : h + 2 * hkv, kv_k0 = split ? 0 : h, kv_vd = split ? h : hkv;
   const int kv_hpb = split ? 1 : group, x_kv = split ? n_heads : n_kv_heads;
   if (eight == dq_eight) {  // same block shape: one launch, the dQ blocks queued behind the dK/dV blocks
-    unsigned n_blocks = (unsigned)((x_kv + n_heads) * (s / 128));
+    unsigned n_blocks = (unsigned)((x_kv + n_heads) * blocks);
     if (eight) {
       constexpr int smem_f = smem_kv8 > smem_split ? smem_kv8 : smem_split;
-      auto kf = attn_bwd_fused_mfma_kernel<DH, true>;
+      auto kf = attn_bwd_fused_mfma_kernel<DH, true, EDGE>;
       static bool fused8_configured = false;
       if (!fused8_configured) {
         PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1420,7 +1589,7 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
                                             group, scale, x_kv, n_heads);
     } else {
       constexpr int smem_f = smem_kv > smem_q ? smem_kv : smem_q;
-      auto kf = attn_bwd_fused_mfma_kernel<DH, false>;
+      auto kf = attn_bwd_fused_mfma_kernel<DH, false, EDGE>;
       static bool fused4_configured = false;
       if (!fused4_configured) {
         PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1433,24 +1602,24 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
     }
   } else {
     if (eight)
-      kkv8<<<dim3(x_kv, s / 128), 512, smem_kv8, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb,
+      kkv8<<<dim3(x_kv, blocks), 512, smem_kv8, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb,
           s,
                                                            h, hkv, group, scale);
     else
-      kkv<<<dim3(x_kv, s / 128), 256, smem_kv, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, s,
+      kkv<<<dim3(x_kv, blocks), 256, smem_kv, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, s,
           h,
                                                          hkv, group, scale);
     if (dq_eight) {
-      auto kqs = attn_bwd_dq_split_mfma_kernel<DH>;
+      auto kqs = attn_bwd_dq_split_mfma_kernel<DH, EDGE>;
       static bool split_configured = false;
       if (!split_configured) {
         PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kqs), hipFuncAttributeMaxDynamicSharedMemorySize,
                                       smem_split));
         split_configured = true;
       }
-      kqs<<<dim3(n_heads, s / 128), 512, smem_split, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
+      kqs<<<dim3(n_heads, blocks), 512, smem_split, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
     } else {
-      kq1<<<dim3(n_heads, s / 128), 256, smem_q, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
+      kq1<<<dim3(n_heads, blocks), 256, smem_q, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
     }
   }
   if (split) {
@@ -1469,11 +1638,10 @@ bool attention_backward_mfma(const void* qkv, const void* o, const float* lse, c
               n_kv_heads);
     return false;
   }
-  if (h / n_heads == 128)
-    return launch_bwd<128>((const bf16*)qkv, (const bf16*)o, lse, (const bf16*)d_o, (bf16*)dqkv, delta,
-                           (bf16*)partials, s, h, n_heads, n_kv_heads, stream);
-  return launch_bwd<64>((const bf16*)qkv, (const bf16*)o, lse, (const bf16*)d_o, (bf16*)dqkv, delta, (bf16*)partials,
-                        s, h, n_heads, n_kv_heads, stream);
+  auto launch = s % 128 == 0 ? (h / n_heads == 128 ? launch_bwd<128, false> : launch_bwd<64, false>)
+                             : (h / n_heads == 128 ? launch_bwd<128, true> : launch_bwd<64, true>);
+  return launch((const bf16*)qkv, (const bf16*)o, lse, (const bf16*)d_o, (bf16*)dqkv, delta, (bf16*)partials, s, h,
+                n_heads, n_kv_heads, stream);
 }
 
 }  // namespace po

@@ -262,6 +262,46 @@ def test_attention_mfma(gpu_device, s, h, a):
     _attention_case(gpu_device, "bf16", s, h, a, 0)
 
 
+# bf16 sequences that end inside a tile, both head sizes: one row, ends around 64 and 128 rows, a last key block with one
+# query tile, 256-row forward blocks with four-wave backward blocks, key/value heads shared by groups with one and with
+# two launches.  What lies behind the tensors is NaN and must not be read, what lies behind the results must stay.
+# 2^-8 for o: half of it is the rounding of o, P enters with 16 bits.
+@pytest.mark.parametrize("s,h,a,akv", [(1, 128, 1, 1), (1, 64, 1, 1), (63, 128, 2, 1), (65, 256, 2, 2), (127, 256, 4, 2),
+                                       (129, 128, 1, 1), (191, 64, 1, 1), (193, 512, 4, 1), (255, 256, 4, 4),
+                                       (300, 16384, 128, 128), (300, 8192, 128, 2), (700, 1024, 8, 2)])
+def test_attention_ragged_bf16(gpu_device, s, h, a, akv):
+    rng = np.random.default_rng(s + h + a)
+    dh, hkv, group = h // a, h // a * akv, a // akv
+    pad = lambda *size, t=torch.bfloat16: torch.full(size, float("nan"), dtype=t, device=gpu_device)
+    qkv, d_o = _rand(rng, (s, h + 2 * hkv), "bf16"), _rand(rng, (s, h), "bf16")
+    qd, dod, o, dqkv = pad(s + 130, h + 2 * hkv), pad(s + 130, h), pad(s + 130, h), pad(s + 130, h + 2 * hkv)
+    lse, delta = pad(a * s + 200, t=torch.float32), pad(a * s + 200, t=torch.float32)
+    qd[:s], dod[:s] = torch.from_numpy(qkv).to(gpu_device), torch.from_numpy(d_o).to(gpu_device)
+    po.po_op_attention_forward(po.PO_BF16, qd, o, lse, s, h, a, n_kv_heads=akv)
+    po.po_op_attention_backward(po.PO_BF16, qd, o, lse, dod, dqkv, delta, s, h, a, n_kv_heads=akv)
+    for t, n in ((o, s), (dqkv, s), (lse, a * s), (delta, a * s)):
+        assert not torch.isnan(t[:n]).any() and torch.isnan(t[n:]).all()
+    # the same in 64 bits, head by head
+    q, k, v = (torch.from_numpy(x).to(gpu_device).double() for x in (qkv[:, :h], qkv[:, h:h + hkv], qkv[:, h + hkv:]))
+    g = dod[:s].double()
+    future = torch.ones(s, s, dtype=torch.bool, device=gpu_device).triu(1)
+    ro, rq, rk, rv = torch.zeros_like(g), torch.zeros_like(g), torch.zeros_like(k), torch.zeros_like(k)
+    for t in range(a):
+        c, ck = slice(t * dh, (t + 1) * dh), slice(t // group * dh, (t // group + 1) * dh)
+        sc = (q[:, c] @ k[:, ck].T.contiguous() / np.sqrt(dh)).masked_fill(future, -np.inf)
+        p = torch.softmax(sc, 1)
+        ro[:, c] = p @ v[:, ck]
+        ds = p * (g[:, c] @ v[:, ck].T.contiguous() - (g[:, c] * ro[:, c]).sum(1, keepdim=True)) / np.sqrt(dh)
+        rq[:, c] = ds @ k[:, ck]
+        rk[:, ck] += ds.T.contiguous() @ q[:, c]
+        rv[:, ck] += p.T.contiguous() @ g[:, c]
+        assert (lse[t * s:(t + 1) * s] - torch.logsumexp(sc, 1)).abs().max() < 1e-5 * max(1.0, lse[:a * s].abs().max())
+    assert max_rel_err(_np(o[:s]), ro.cpu().numpy()) < 2.0 ** -8
+    got = _np(dqkv[:s])
+    for name, mine, ref in (("dQ", got[:, :h], rq), ("dK", got[:, h:h + hkv], rk), ("dV", got[:, h + hkv:], rv)):
+        check_parity(mine, ref.cpu().numpy(), 2e-2, name)
+
+
 def _attention_case(gpu_device, dtype, s, h, a, force_generic, akv=0, with_partials=False):
     code, tdt, tol = DT[dtype]
     rng = np.random.default_rng(s * 31 + h + a + 7 * akv)
