@@ -283,9 +283,10 @@ int po_op_gemm_grouped(int32_t n, const int32_t* M, const int32_t* N, const int3
                        const int32_t* lda, const void* const* B, const int32_t* ldb, float* const* acc_f32,
                        const int32_t* ldc, void* stream);
 
-/* Pure host code: the output tile (rows, columns) of the bf16 matrix-core kernel that po_op_gemm and the stage
- * use for an M x N result whose K is a multiple of 64: 256 x 256, 256 x 192 or 128 x 128, chosen so that a round of
- * tiles fills the 256 compute units; 0, 0 when M, N fit none of them (the shape-generic kernel runs instead). */
+/* Pure host code: the output tile (rows, columns) of the bf16 matrix-core kernel for whole tiles, for an M x N result
+ * whose K is a multiple of 64: 256 x 256, 256 x 192 or 128 x 128, chosen so that a round of tiles fills the 256 compute
+ * units; 0, 0 when M, N fit none of them (kernels for results of any size run instead, as they do where so few of these
+ * tiles would leave most of the chip idle). */
 int po_op_gemm_tile(int32_t M, int32_t N, int32_t* tile_rows, int32_t* tile_cols);
 
 /* Causal attention forward: qkv [s, h + 2 hkv] (q | k | v blocks, hkv = n_kv_heads * h / n_heads;

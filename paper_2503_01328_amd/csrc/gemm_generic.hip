@@ -115,11 +115,35 @@ bool gemm_generic(int dtype, int trans_a, int trans_b, int M, int N, int K, cons
 
 bool gemm(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
           const Epilogue& ep, bool force_generic, hipStream_t stream) {
-  if (dtype == kBF16 && !force_generic && gemm_mfma_supported(trans_a, trans_b, M, N, K, lda, ldb, ep.ldc))
-    return gemm_mfma_bf16(trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
-  if (!force_generic && gemm_small_supported(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb))
-    return gemm_small(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
+  if (force_generic) return gemm_generic(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
+  const bool small = gemm_small_supported(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb);
+  if (dtype == kBF16) {
+    // bf16 by size.  Whole tiles: the large tiles, or the small ones where those leave most of the chip idle, for the
+    // forward and the input gradients (512 x 512, K 512: 11.8 -> 5 us); a weight gradient on its own stays with the large
+    // ones, bit for bit what a group of them gives.
+    const bool few = small && (trans_a || gemm_mfma_edge_supported(trans_a, trans_b, M, N, K, A, lda, B, ldb, ep)) &&
+                     gemm_small_is_faster(M, N, K);
+    if (gemm_mfma_supported(trans_a, trans_b, M, N, K, lda, ldb, ep.ldc) && (trans_a || !few))
+      return gemm_mfma_bf16(trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
+    if (!few && gemm_mfma_edge_supported(trans_a, trans_b, M, N, K, A, lda, B, ldb, ep))
+      return gemm_mfma_edge(trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
+  }
+  if (small) return gemm_small(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
   return gemm_generic(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
+}
+
+bool gemm_grouped_supported(int dtype, int n, const GemmProblem* p) {
+  return gemm_small_grouped_supported(dtype, n, p) ||
+         (dtype == kBF16 && (gemm_mfma_grouped_supported(n, p) || gemm_mfma_grouped_edge_supported(n, p)));
+}
+
+bool gemm_grouped_accumulate(int dtype, int n, const GemmProblem* p, hipStream_t stream) {
+  const bool small = gemm_small_grouped_supported(dtype, n, p);
+  if (dtype == kBF16 && !(small && gemm_small_group_is_faster(n, p))) {
+    if (gemm_mfma_grouped_supported(n, p)) return gemm_mfma_grouped_accumulate(n, p, stream);
+    if (gemm_mfma_grouped_edge_supported(n, p)) return gemm_mfma_grouped_edge_accumulate(n, p, stream);
+  }
+  return gemm_small_grouped_accumulate(dtype, n, p, stream);
 }
 
 }  // namespace po

@@ -36,6 +36,10 @@
 // bytes per lane, whole 128-byte lines per row: bias, residual, GeLU, GeLU-backward
 // and the fp32 accumulate all happen on that coalesced side.
 //
+// Results that are no whole tiles use a second form of the same kernel, EDGE: loads through buffer descriptors, guarded
+// stores.  A stage of C2's widths at 1733 rows: forward products 101, 133 and 73 us with the 64 x 64 tiles of
+// gemm_small.hip -> 54, 68 and 52 us, the four weight gradients 345 -> 261 us, the step 5.18 -> 3.96 ms.
+//
 // Workgroup ids are remapped so that the blocks that land on one XCD (ids equal
 // modulo 8) work on neighbouring tiles and share operand slices in that XCD's L2.
 #include <type_traits>
@@ -44,15 +48,9 @@
 #include <stdlib.h>
 #include <string.h>
 
-#include "kernels.h"
+#include "mfma_common.h"
 
 namespace po {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 #define PO_LDS3(p) ((void __attribute__((address_space(3)))*)(p))
 #define PO_GLB1(p) ((const void __attribute__((address_space(1)))*)(p))
@@ -83,7 +81,10 @@ __device__ __forceinline__ unsigned lds_address(const void* p) { return (unsigne
 // What a lane fetches for piece u never changes from slice to slice except for a step that is the same for every
 // lane, so the lane keeps one 32-bit byte offset per piece and the wave one 64-bit slice pointer in scalar
 // registers: a load costs its own instruction and the M0 set-up, no address arithmetic.
-template <int R, bool KMAJOR>
+// EDGE: the loads go through a buffer descriptor that starts at the slice pointer and ends with the operand, so rows of
+// a k-contiguous operand past its last one and k of the other kind past K read as zero; what a k-major slice reads past
+// its rows is the next k's (or zero) and ends up in results that are not stored.
+template <int R, bool KMAJOR, bool EDGE>
 struct SliceLoader {
   static constexpr int N_INST = R * 128 / 1024;
   static constexpr int PER_WAVE = N_INST / 4;
@@ -91,9 +92,10 @@ struct SliceLoader {
   unsigned voff[PER_WAVE];  // this lane's byte offset from the slice pointer, per piece
   const char* slice;        // first byte of the next slice to request (same in every lane)
   unsigned step;            // bytes from one slice to the next
+  int left;                 // EDGE: bytes from the slice pointer to the end of the operand (may fall below zero)
 
-  // `base` points at (first row of the tile, k = 0).
-  __device__ __forceinline__ void init(const bf16* base, int ld, int wave, int lane) {
+  // `base` points at (first row of the tile, k = 0); rows: how many the operand has from there on.
+  __device__ __forceinline__ void init(const bf16* base, int ld, int rows, int K, int wave, int lane) {
 #pragma unroll
     for (int u = 0; u < PER_WAVE; ++u) {
       int g = u * 4 + wave;  // which 1 KiB piece of the tile
@@ -114,6 +116,7 @@ struct SliceLoader {
     }
     slice = reinterpret_cast<const char*>(base);
     step = KMAJOR ? 128u * (unsigned)ld : 128u;
+    if (EDGE) left = KMAJOR ? ((K - 1) * ld + rows) * 2 : ((min(rows, R) - 1) * ld + K) * 2;
   }
   // Piece u of the slice at `slice` -> LDS at lds_wave + 4096 u (lds_wave: the LDS address of this wave's piece 0
   // in the target stage).  Issued as inline assembly on purpose: through the builtin the compiler treats every
@@ -121,10 +124,14 @@ struct SliceLoader {
   // The caller waits (wait_slice_loads) before the barrier that publishes the slice.
   __device__ __forceinline__ void issue(int u, unsigned lds_wave) const {
     unsigned dst = lds_wave + 4096u * u;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff[u]), "s"(slice)
+    if constexpr (EDGE) buffer_to_lds(dst, voff[u], buffer_of(slice, (unsigned)max(left, 0)));
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff[u]), "s"(slice)
                  : "memory");
   }
-  __device__ __forceinline__ void advance() { slice += step; }
+  __device__ __forceinline__ void advance() {
+    slice += step;
+    if (EDGE) left -= (int)step;
+  }
 };
 
 // Waits until at most N of this wave's loads are outstanding (they complete in issue order).
@@ -245,9 +252,11 @@ __device__ __forceinline__ const bf16* uniform(const bf16* p) {
 // ---- one output tile -----------------------------------------------------------
 // TA: A is [K, M] (m-contiguous).  TB: B is [K, N] (n-contiguous).  All 256 threads of the block call it with
 // the same arguments; `smem` is the block's dynamic LDS (stages, then reused by the epilogue strips).
-template <int WTM, int WTN, bool TA, bool TB, int EPI>
-__device__ __forceinline__ void gemm_tile(int K, const bf16* __restrict__ A, int lda, const bf16* __restrict__ B,
-                                          int ldb, const Epilogue& ep, int tile_m, int tile_n, char* smem) {
+// EDGE: M x N need not be whole tiles (N a multiple of 8), nor K whole slices where TA and TB.
+template <int WTM, int WTN, bool TA, bool TB, int EPI, bool EDGE>
+__device__ __forceinline__ void gemm_tile(int M, int N, int K, const bf16* __restrict__ A, int lda,
+                                          const bf16* __restrict__ B, int ldb, const Epilogue& ep, int tile_m,
+                                          int tile_n, char* smem) {
   constexpr int BM = 64 * WTM, BN = 64 * WTN;
   constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128;
   constexpr int STAGE = A_BYTES + B_BYTES;
@@ -277,14 +286,14 @@ __device__ __forceinline__ void gemm_tile(int K, const bf16* __restrict__ A, int
   //                from k-step 1 on) and releases stage kt % NSTAGE (whose last fragments were read in k-step 0).
   // The big tiles have room for two stages, the small tile (a slice is four times shorter) gets four.
   constexpr int NSTAGE = stages_of(WTM, WTN);
-  using LoaderA = SliceLoader<BM, TA>;
-  using LoaderB = SliceLoader<BN, TB>;
+  using LoaderA = SliceLoader<BM, TA, EDGE>;
+  using LoaderB = SliceLoader<BN, TB, EDGE>;
   constexpr int PER_SLICE = LoaderA::PER_WAVE + LoaderB::PER_WAVE;  // load instructions of one wave per slice
-  int nk = K / kBK;
+  int nk = EDGE ? (K + kBK - 1) / kBK : K / kBK;
   LoaderA la;
   LoaderB lb;
-  la.init(a_base, lda, wave, lane);
-  lb.init(b_base, ldb, wave, lane);
+  la.init(a_base, lda, M - m0, K, wave, lane);
+  lb.init(b_base, ldb, N - n0, K, wave, lane);
   const unsigned lds0 = uniform((int)lds_address(smem)) + 1024u * wave;  // this wave's piece 0 of stage 0, operand A
   // Load q (0 .. PER_SLICE - 1, A's pieces first) of the slice the loaders point at, into stage `st`.
   auto issue_load = [&](int q, unsigned st) {
@@ -440,6 +449,7 @@ __device__ __forceinline__ void gemm_tile(int K, const bf16* __restrict__ A, int
   constexpr int STRIP_LD = STRIP_N + 4;  // floats; the 16-byte pad staggers rows over the banks
   float* strip = reinterpret_cast<float*>(smem) + wave * (32 * STRIP_LD);
   int col = lane & 31, half = lane >> 5;
+  auto inside = [&](int m, int n) { return m < M && n < N; };
 #pragma unroll
   for (int i = 0; i < WTM; ++i) {
 #pragma unroll
@@ -463,6 +473,7 @@ __device__ __forceinline__ void gemm_tile(int K, const bf16* __restrict__ A, int
 #pragma unroll
       for (int it = 0; it < NIT; ++it) {
         int piece = it * 64 + lane;
+        if (EDGE && !inside(mrow0 + piece / LPR, ncol0 + (piece % LPR) * 4)) continue;
         old[it] = *reinterpret_cast<const f32x4*>(cbase + (size_t)(piece / LPR) * ep.ldc + (piece % LPR) * 4);
       }
 #pragma unroll
@@ -470,6 +481,7 @@ __device__ __forceinline__ void gemm_tile(int K, const bf16* __restrict__ A, int
         int piece = it * 64 + lane;
         int r = piece / LPR;
         int c = (piece % LPR) * 4;
+        if (EDGE && !inside(mrow0 + r, ncol0 + c)) continue;
         f32x4 v = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c);
         *reinterpret_cast<f32x4*>(cbase + (size_t)r * ep.ldc + c) = old[it] + v;
       }
@@ -486,6 +498,7 @@ __device__ __forceinline__ void gemm_tile(int K, const bf16* __restrict__ A, int
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
           int piece = it * 64 + lane;
+          if (EDGE && !inside(mrow0 + piece / LPR, ncol0 + (piece % LPR) * 8)) continue;
           aux[it] = *reinterpret_cast<const bf16x8_t*>(abase + (size_t)(piece / LPR) * ep.ldc + (piece % LPR) * 8);
         }
       }
@@ -494,6 +507,7 @@ __device__ __forceinline__ void gemm_tile(int K, const bf16* __restrict__ A, int
         int piece = it * 64 + lane;
         int r = piece / LPR;
         int c = (piece % LPR) * 8;
+        if (EDGE && !inside(mrow0 + r, ncol0 + c)) continue;
         f32x4 v0 = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c);
         f32x4 v1 = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c + 4);
         float vv[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
@@ -514,8 +528,8 @@ __device__ __forceinline__ void gemm_tile(int K, const bf16* __restrict__ A, int
 
 // ---- the kernels -----------------------------------------------------------------
 // One tile per block.  XCD-aware remap: ids equal modulo 8 share an XCD; each XCD gets a contiguous run of tiles.
-template <int WTM, int WTN, bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void gemm_mfma_kernel(int K, const bf16* __restrict__ A, int lda,
+template <int WTM, int WTN, bool TA, bool TB, int EPI, bool EDGE>
+__global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, const bf16* __restrict__ A, int lda,
                                                         const bf16* __restrict__ B, int ldb, Epilogue ep,
                                                         int tiles_m, int tiles_n) {
   extern __shared__ __align__(16) char smem[];
@@ -524,7 +538,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int K, const bf16* __res
   int lin = (n_tiles % 8 == 0) ? (pid % 8) * (n_tiles / 8) + pid / 8 : pid;
   int tile_m, tile_n;
   tile_of(lin, tiles_m, tiles_n, tile_m, tile_n);
-  gemm_tile<WTM, WTN, TA, TB, EPI>(K, A, lda, B, ldb, ep, tile_m, tile_n, smem);
+  gemm_tile<WTM, WTN, TA, TB, EPI, EDGE>(M, N, K, A, lda, B, ldb, ep, tile_m, tile_n, smem);
 }
 
 // Several independent GEMMs of one form in one launch: the 256 x 256 tiles of all problems are numbered one
@@ -536,14 +550,14 @@ struct GroupedProblem {
   const bf16* A;
   const bf16* B;
   Epilogue ep;
-  int K, lda, ldb, tiles_m, tiles_n, first_tile;
+  int M, N, K, lda, ldb, tiles_m, tiles_n, first_tile;
 };
 struct GroupedArgs {
   GroupedProblem p[kMaxGroupedGemms];
   int n, total_tiles;
 };
 
-template <bool TA, bool TB, int EPI>
+template <bool TA, bool TB, int EPI, bool EDGE>
 __global__ __launch_bounds__(256) void gemm_mfma_grouped_kernel(GroupedArgs g) {
   extern __shared__ __align__(16) char smem[];
   int pid = blockIdx.x, nb = gridDim.x;
@@ -560,7 +574,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_grouped_kernel(GroupedArgs g) {
         if (i < g.n && lin >= g.p[i].first_tile) P = g.p[i];
       int tile_m, tile_n;
       tile_of(lin - P.first_tile, P.tiles_m, P.tiles_n, tile_m, tile_n);
-      gemm_tile<4, 4, TA, TB, EPI>(uniform(P.K), uniform(P.A), uniform(P.lda), uniform(P.B), uniform(P.ldb), P.ep,
+      gemm_tile<4, 4, TA, TB, EPI, EDGE>(uniform(P.M), uniform(P.N), uniform(P.K), uniform(P.A), uniform(P.lda), uniform(P.B), uniform(P.ldb), P.ep,
                                    uniform(tile_m), uniform(tile_n), smem);
     }
     __syncthreads();  // the next tile's operand loads overwrite the epilogue strips of every wave
@@ -609,22 +623,22 @@ bool gemm_mfma_supported(int trans_a, int trans_b, int M, int N, int K, int lda,
   return wtm != 0 && K > 0 && K % kBK == 0 && lda % 8 == 0 && ldb % 8 == 0 && ldc % 8 == 0;
 }
 
-template <int WTM, int WTN, bool TA, bool TB, int EPI>
+template <int WTM, int WTN, bool TA, bool TB, int EPI, bool EDGE = false>
 static bool launch_mfma_epi(int M, int N, int K, const bf16* A, int lda, const bf16* B, int ldb, const Epilogue& ep,
                             hipStream_t stream) {
   constexpr int BM = 64 * WTM, BN = 64 * WTN;
   constexpr int smem_ops = stages_of(WTM, WTN) * (BM + BN) * 128;
   constexpr int smem_epi = 4 * 32 * (WTN * 32 + 4) * 4;
   constexpr int smem = smem_ops > smem_epi ? smem_ops : smem_epi;
-  auto kern = gemm_mfma_kernel<WTM, WTN, TA, TB, EPI>;
+  auto kern = gemm_mfma_kernel<WTM, WTN, TA, TB, EPI, EDGE>;
   static bool configured = false;  // per instantiation
   if (!configured) {
     PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   smem));
     configured = true;
   }
-  int tiles_m = M / BM, tiles_n = N / BN;
-  kern<<<tiles_m * tiles_n, 256, smem, stream>>>(K, A, lda, B, ldb, ep, tiles_m, tiles_n);
+  int tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
+  kern<<<tiles_m * tiles_n, 256, smem, stream>>>(M, N, K, A, lda, B, ldb, ep, tiles_m, tiles_n);
   return launch_ok("gemm_mfma_kernel");
 }
 
@@ -674,6 +688,92 @@ bool gemm_mfma_bf16(int trans_a, int trans_b, int M, int N, int K, const void* A
   return dispatch_trans<2, 2>(trans_a, trans_b, M, N, K, a, lda, b, ldb, ep, stream);
 }
 
+// ---- results of any size ----
+// Time of a launch in us, from timings over M 100 .. 4000, N 1024 .. 16384, K 1024 .. 16384 (k-contiguous and k-major B
+// alike): rounds of `slots` blocks, each a fixed cost and one per K slice that grows from `low` for a lone block to
+// `full` where every CU has one (the clock falls).  Within 10 % of what was measured, e.g. 1733 x 6144, K 2048: 256 x 256
+// 47.5, 256 x 192 42.4, 128 x 128 54.9 us, 64 x 64 73.5; 300 x 1024, K 4096: 73, 57, 25.5 us, 64 x 64 with four waves 13.6.
+static double launch_us(int M, int N, int K, int bm, int bn, int slots, double fixed, double low, double full) {
+  const int64_t tiles = (int64_t)ceil_div(M, bm) * ceil_div(N, bn), rest = tiles % slots;
+  const double slices = ceil_div(K, kBK);
+  double us = (double)(tiles / slots) * (fixed + slices * full);
+  if (rest) us += fixed + slices * (low + (full - low) * (double)rest / slots);
+  return us;
+}
+static double tile_us(int M, int N, int K, int wtm, int wtn) {
+  if (wtn == 4) return launch_us(M, N, K, 256, 256, 256, 8.0, 1.04, 1.44);
+  if (wtm == 4) return launch_us(M, N, K, 256, 192, 256, 6.5, 0.79, 1.12);
+  return launch_us(M, N, K, 128, 128, 256, 4.3, 0.34, 0.44);
+}
+static double pick_edge_tile(int M, int N, int K, int& wtm, int& wtn) {
+  static constexpr int forms[3][2] = {{4, 4}, {4, 3}, {2, 2}};
+  double best = 0.;
+  for (const auto& f : forms) {
+    const double us = tile_us(M, N, K, f[0], f[1]);
+    if (wtm && us >= best) continue;
+    best = us;
+    wtm = f[0];
+    wtn = f[1];
+  }
+  return best;
+}
+
+bool gemm_small_is_faster(int M, int N, int K) {
+  int wtm, wtn;
+  pick_tile(M, N, wtm, wtn);
+  const double big = wtm && K % kBK == 0 ? tile_us(M, N, K, wtm, wtn) : pick_edge_tile(M, N, K, wtm = 0, wtn);
+  const double small4 = launch_us(M, N, K, 64, 64, 256, 4.0, 0.17, 0.17);  // a tile's K over four waves
+  const double small1 = launch_us(M, N, K, 64, 64, 1024, 3.5, 0.6, 0.75);
+  return (small4 < small1 ? small4 : small1) < big;
+}
+
+bool gemm_mfma_edge_supported(int ta, int tb, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
+                              const Epilogue& ep) {
+  if (M <= 0 || N <= 0 || K <= 0 || !A || !B || (!ep.out && !ep.acc_f32) || (ep.gelu_u && !ep.out) || ep.ldc < N ||
+      lda < (ta ? M : K) || ldb < (tb ? K : N))
+    return false;
+  if (ta ? (tb || !ep.acc_f32 || M % 8 != 0) : (ep.acc_f32 != nullptr || K % kBK != 0)) return false;  // the forms below
+  if (!ta && !tb && ep.gelu_u) return false;
+  if (tb && ep.gelu_out && !ep.gelu_u) return false;
+  const uintptr_t al = (uintptr_t)A | (uintptr_t)B | (uintptr_t)ep.out | (uintptr_t)ep.gelu_out | (uintptr_t)ep.gelu_u |
+                       (uintptr_t)ep.residual | (uintptr_t)ep.acc_f32 | (uintptr_t)ep.bias;
+  // offsets and sizes of the buffer descriptors fit 31 bits: 256 rows of a k-contiguous operand, all of a k-major one
+  const int64_t a_bytes = 2 * (ta ? (int64_t)K * lda : (int64_t)256 * lda + K);
+  const int64_t b_bytes = 2 * (tb ? (int64_t)256 * ldb + K : (int64_t)K * ldb);
+  const int64_t limit = (int64_t)1 << 31;
+  return N % 8 == 0 && lda % 8 == 0 && ldb % 8 == 0 && ep.ldc % 8 == 0 && al % 16 == 0 && a_bytes < limit &&
+         b_bytes < limit;
+}
+
+// The forms a layer uses: forward (A k-contiguous, B not), input gradients (both k-contiguous), weight gradients (neither,
+// accumulated; there K need not be whole slices either).
+template <int WTM, int WTN>
+static bool launch_edge(int ta, int tb, int M, int N, int K, const bf16* A, int lda, const bf16* B, int ldb,
+                        const Epilogue& ep, hipStream_t stream) {
+  if (ta) return launch_mfma_epi<WTM, WTN, true, true, kEpiAccumulate, true>(M, N, K, A, lda, B, ldb, ep, stream);
+  if (!tb) {
+    if (ep.gelu_out) return launch_mfma_epi<WTM, WTN, false, true, kEpiStoreGelu, true>(M, N, K, A, lda, B, ldb, ep, stream);
+    return launch_mfma_epi<WTM, WTN, false, true, kEpiStore, true>(M, N, K, A, lda, B, ldb, ep, stream);
+  }
+  if (ep.gelu_u) return launch_mfma_epi<WTM, WTN, false, false, kEpiGeluBackward, true>(M, N, K, A, lda, B, ldb, ep, stream);
+  return launch_mfma_epi<WTM, WTN, false, false, kEpiStore, true>(M, N, K, A, lda, B, ldb, ep, stream);
+}
+
+bool gemm_mfma_edge(int ta, int tb, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
+                    const Epilogue& ep, hipStream_t stream) {
+  if (!gemm_mfma_edge_supported(ta, tb, M, N, K, A, lda, B, ldb, ep)) {
+    set_error("gemm_mfma_edge: unsupported M=%d N=%d K=%d lda=%d ldb=%d ldc=%d", M, N, K, lda, ldb, ep.ldc);
+    return false;
+  }
+  int wtm = 0, wtn = 0;
+  pick_edge_tile(M, N, K, wtm, wtn);
+  const bf16* a = (const bf16*)A;
+  const bf16* b = (const bf16*)B;
+  if (wtn == 4) return launch_edge<4, 4>(ta, tb, M, N, K, a, lda, b, ldb, ep, stream);
+  if (wtn == 3) return launch_edge<4, 3>(ta, tb, M, N, K, a, lda, b, ldb, ep, stream);
+  return launch_edge<2, 2>(ta, tb, M, N, K, a, lda, b, ldb, ep, stream);
+}
+
 // ---- grouped launch ---------------------------------------------------------------
 bool gemm_mfma_grouped_supported(int n, const GemmProblem* p) {
   if (n < 1 || n > kMaxGroupedGemms || !p) return false;
@@ -687,12 +787,22 @@ bool gemm_mfma_grouped_supported(int n, const GemmProblem* p) {
   return true;
 }
 
-bool gemm_mfma_grouped_accumulate(int n, const GemmProblem* p, hipStream_t stream) {
-  if (!gemm_mfma_grouped_supported(n, p)) {
-    set_error("gemm_mfma_grouped: %d problems, or a shape, stride or pointer the grouped kernel does not take", n);
-    return false;
+template <bool EDGE>
+static bool launch_grouped(GroupedArgs& g, hipStream_t stream) {
+  constexpr int smem = stages_of(4, 4) * (256 + 256) * 128;
+  auto kern = gemm_mfma_grouped_kernel<true, true, kEpiAccumulate, EDGE>;
+  static bool configured = false;
+  if (!configured) {
+    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  smem));
+    configured = true;
   }
-  GroupedArgs g;
+  int blocks = g.total_tiles < 256 ? g.total_tiles : 256;  // one block per CU; more tiles mean more rounds per block
+  kern<<<blocks, 256, smem, stream>>>(g);
+  return launch_ok("gemm_mfma_grouped_kernel");
+}
+
+static void grouped_args(int n, const GemmProblem* p, GroupedArgs& g) {
   memset(&g, 0, sizeof(g));
   g.n = n;
   int total = 0;
@@ -702,26 +812,65 @@ bool gemm_mfma_grouped_accumulate(int n, const GemmProblem* p, hipStream_t strea
     q.B = static_cast<const bf16*>(p[i].B);
     q.ep.acc_f32 = p[i].acc_f32;
     q.ep.ldc = p[i].ldc;
+    q.M = p[i].M;
+    q.N = p[i].N;
     q.K = p[i].K;
     q.lda = p[i].lda;
     q.ldb = p[i].ldb;
-    q.tiles_m = p[i].M / 256;
-    q.tiles_n = p[i].N / 256;
+    q.tiles_m = ceil_div(p[i].M, 256);
+    q.tiles_n = ceil_div(p[i].N, 256);
     q.first_tile = total;
     total += q.tiles_m * q.tiles_n;
   }
   g.total_tiles = total;
-  constexpr int smem = stages_of(4, 4) * (256 + 256) * 128;
-  auto kern = gemm_mfma_grouped_kernel<true, true, kEpiAccumulate>;
-  static bool configured = false;
-  if (!configured) {
-    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  smem));
-    configured = true;
+}
+
+bool gemm_mfma_grouped_accumulate(int n, const GemmProblem* p, hipStream_t stream) {
+  if (!gemm_mfma_grouped_supported(n, p)) {
+    set_error("gemm_mfma_grouped: %d problems, or a shape, stride or pointer the grouped kernel does not take", n);
+    return false;
   }
-  int blocks = total < 256 ? total : 256;  // one block per CU; more tiles mean more rounds per block
-  kern<<<blocks, 256, smem, stream>>>(g);
-  return launch_ok("gemm_mfma_grouped_kernel");
+  GroupedArgs g;
+  grouped_args(n, p, g);
+  return launch_grouped<false>(g, stream);
+}
+
+// The same for M, N that are multiples of 8 and any K.
+bool gemm_mfma_grouped_edge_supported(int n, const GemmProblem* p) {
+  if (n < 1 || n > kMaxGroupedGemms || !p) return false;
+  for (int i = 0; i < n; ++i) {
+    Epilogue ep;
+    memset(&ep, 0, sizeof(ep));
+    ep.acc_f32 = p[i].acc_f32;
+    ep.ldc = p[i].ldc;
+    if (!gemm_mfma_edge_supported(1, 0, p[i].M, p[i].N, p[i].K, p[i].A, p[i].lda, p[i].B, p[i].ldb, ep)) return false;
+  }
+  return true;
+}
+
+bool gemm_mfma_grouped_edge_accumulate(int n, const GemmProblem* p, hipStream_t stream) {
+  if (!gemm_mfma_grouped_edge_supported(n, p)) {
+    set_error("gemm_mfma_grouped_edge: %d problems, or a shape, stride or pointer the grouped kernel does not take", n);
+    return false;
+  }
+  GroupedArgs g;
+  grouped_args(n, p, g);
+  return launch_grouped<true>(g, stream);
+}
+
+// The four weight-gradient products of a layer of width h over s rows, us with 256 x 256 tiles / 64 x 64 tiles:
+//   h  512 ( 48 tiles of 256): s 100  23.8 /  9.0, s 1733   59 /  25, s 4000   94 /  45
+//   h 1024 (192):              s 100  35.9 / 26.3, s  700 46.7 / 44.0, s 1024 52.3 / 54.0, s 4000 110 / 144
+//   h 2048 (768):              s 100   100 /   90, s  300  115 /  111, s  512  127 /  133, s 4000 408 / 621
+//   h 4096 (3072):             s 100   581 /  519, s  300  619 /  604, s  512  664 /  690, s 1733 985 / 1275
+bool gemm_small_group_is_faster(int n, const GemmProblem* p) {
+  int64_t tiles = 0;
+  int K = 0;
+  for (int i = 0; i < n; ++i) {
+    tiles += (int64_t)ceil_div(p[i].M, 256) * ceil_div(p[i].N, 256);
+    K = p[i].K > K ? p[i].K : K;
+  }
+  return tiles <= 128 || K < (tiles <= 256 ? 896 : 384);
 }
 
 }  // namespace po

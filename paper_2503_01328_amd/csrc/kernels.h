@@ -80,6 +80,17 @@ struct GemmProblem {
 };
 bool gemm_mfma_grouped_supported(int n, const GemmProblem* p);
 bool gemm_mfma_grouped_accumulate(int n, const GemmProblem* p, hipStream_t stream);
+// The same kernels for results that are no whole tiles (gemm_mfma.hip, `edge`): the three forms a layer uses, M any and N a
+// multiple of 8, K of 64 (weight gradients: M of 8, K any), 16-byte alignment of everything.
+bool gemm_mfma_edge_supported(int trans_a, int trans_b, int M, int N, int K, const void* A, int lda, const void* B,
+                              int ldb, const Epilogue& ep);
+bool gemm_mfma_edge(int trans_a, int trans_b, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
+                    const Epilogue& ep, hipStream_t stream);
+bool gemm_mfma_grouped_edge_supported(int n, const GemmProblem* p);
+bool gemm_mfma_grouped_edge_accumulate(int n, const GemmProblem* p, hipStream_t stream);
+// Whether the 64 x 64 and 32 x 32 tiles of gemm_small.hip beat the large ones for a bf16 product (a group of them).
+bool gemm_small_is_faster(int M, int N, int K);
+bool gemm_small_group_is_faster(int n, const GemmProblem* p);
 // Matrix-core kernel for fp32 and for bf16 shapes of any size (gemm_small.hip): rows of both operands whole 16-byte
 // vectors, operands 16-byte aligned.
 bool gemm_small_supported(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda,
@@ -89,6 +100,9 @@ bool gemm_small(int dtype, int trans_a, int trans_b, int M, int N, int K, const 
 // The counterpart of gemm_mfma_grouped_accumulate for its shapes and types.
 bool gemm_small_grouped_supported(int dtype, int n, const GemmProblem* p);
 bool gemm_small_grouped_accumulate(int dtype, int n, const GemmProblem* p, hipStream_t stream);
+// Several weight-gradient products in one launch of whichever of those kernels takes them and is the fastest.
+bool gemm_grouped_supported(int dtype, int n, const GemmProblem* p);
+bool gemm_grouped_accumulate(int dtype, int n, const GemmProblem* p, hipStream_t stream);
 // Picks the kernel by type and shape; force_generic: the vector kernel.
 bool gemm(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
           const Epilogue& ep, bool force_generic, hipStream_t stream);

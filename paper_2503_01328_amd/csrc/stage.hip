@@ -537,8 +537,7 @@ static int st_gemm_grouped(po_stage* st, int n, const GemmProblem* prob, hipStre
     if (rc) return rc;
     for (int i = 0; i < n; ++i) st->spans[span].flops += 2.0 * prob[i].M * prob[i].N * prob[i].K;
   }
-  if (st->cfg.dtype == PO_BF16 && gemm_mfma_grouped_supported(n, prob)) PO_K(gemm_mfma_grouped_accumulate(n, prob, q));
-  else PO_K(gemm_small_grouped_accumulate(st->cfg.dtype, n, prob, q));
+  PO_K(gemm_grouped_accumulate(st->cfg.dtype, n, prob, q));
   return span_end(st, q, span);
 }
 
@@ -747,7 +746,7 @@ static int layer_backward_weight(po_stage* st, int layer, const char* slab, cons
       {h, h, s, o, h, dz1, h, st->G(layer, pl.w_o), h},
       {h, wq, s, n1, h, b.dqkv, wq, st->G(layer, pl.w_qkv), wq},
   };
-  if ((dt == PO_BF16 && gemm_mfma_grouped_supported(4, prob)) || gemm_small_grouped_supported(dt, 4, prob)) {
+  if (gemm_grouped_supported(dt, 4, prob)) {
     if (!n_ready) {
       PO_K(layernorm_forward(dt, x1, st->P(layer, pl.ln2_g), st->P(layer, pl.ln2_b), n2, s, h, c.ln_eps, q));
       PO_K(layernorm_forward(dt, x, st->P(layer, pl.ln1_g), st->P(layer, pl.ln1_b), n1, s, h, c.ln_eps, q));

@@ -86,10 +86,11 @@ def test_bf16_stage_against_oracle(gpu_device, shape):
 @pytest.mark.parametrize("shape", [
     syn.StageShape(1, 1, 448, 7, 1024, 200, dtype="bf16", pipeline_degree=2, n_microbatches=2),
     syn.StageShape(1, 1, 512, 8, 1536, 37, dtype="f32", pipeline_degree=2, n_microbatches=2),
-    syn.StageShape(1, 1, 1024, 8, 2048, 300, dtype="f32", pipeline_degree=2, n_microbatches=2)],
-    ids=["bf16-64-tiles", "f32-64-tiles-short", "f32-64-tiles-long"])
+    syn.StageShape(1, 1, 1024, 8, 2048, 300, dtype="f32", pipeline_degree=2, n_microbatches=2),
+    syn.StageShape(1, 1, 1088, 17, 4096, 905, dtype="bf16", pipeline_degree=2, n_microbatches=2)],
+    ids=["bf16-64-tiles", "f32-64-tiles-short", "f32-64-tiles-long", "bf16-256-tiles-that-end-inside"])
 def test_grouped_weight_gradients_of_any_shape(gpu_device, shape):
-    """The one launch of a layer's four weight-gradient products where the 256 x 256 tiles do not fit."""
+    """The one launch of a layer's four weight-gradient products where the shapes are no whole 256 x 256 tiles."""
     with StageRunner(shape) as r:
         r.make_inputs()
         r.run(po.PO_SCHED_1F1B, 0.0)
