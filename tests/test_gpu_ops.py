@@ -392,8 +392,12 @@ def test_pack_unpack_roundtrip_is_bit_exact(gpu_device):
 
 
 # ---- dropout with regenerated masks ------------------------------------------------------------------------------
+# the last five: one vector per row, widths between the block widths of the kernel that takes whole vectors, one row
 @pytest.mark.parametrize("rows,cols,p,seed,layer,site,mb", [(37, 130, 0.1, 1234, 0, 0, 0), (64, 256, 0.25, 2 ** 40 + 7, 3, 1, 5),
-                                                            (5, 7, 0.5, 1, 11, 0, 2), (300, 1024, 0.9, 99, 1, 1, 31)])
+                                                            (5, 7, 0.5, 1, 11, 0, 2), (300, 1024, 0.9, 99, 1, 1, 31),
+                                                            (9, 8, 0.3, 5, 2, 0, 1), (129, 264, 0.2, 6, 0, 1, 3),
+                                                            (33, 1288, 0.4, 7, 1, 0, 0), (3, 2056, 0.6, 8, 5, 1, 9),
+                                                            (1, 5120, 0.1, 9, 0, 0, 4)])
 def test_dropout_mask_is_the_oracle_mask_bit_for_bit(gpu_device, rows, cols, p, seed, layer, site, mb):
     p = float(np.float32(p))  # the probability the library sees is the fp32 value
     x = torch.ones(rows, cols, dtype=torch.float32, device=gpu_device)
@@ -410,3 +414,9 @@ def test_dropout_mask_is_the_oracle_mask_bit_for_bit(gpu_device, rows, cols, p, 
     ob = torch.empty_like(xb)
     po.po_op_dropout(po.PO_BF16, xb, ob, rows, cols, p, seed, layer, site, mb)
     assert max_rel_err(_np(ob), v.astype(np.float64) * keep / (1.0 - p)) < 1e-2
+    # the same from and to addresses that are no multiple of 16 bytes
+    buf = torch.zeros(2, rows * cols + 1, dtype=torch.bfloat16, device=gpu_device)
+    buf[0, 1:] = xb.view(-1)
+    if buf[0, 1:].data_ptr() % 16:
+        po.po_op_dropout(po.PO_BF16, buf[0, 1:], buf[1, 1:], rows, cols, p, seed, layer, site, mb)
+        assert torch.equal(buf[1, 1:].view(rows, cols), ob)
