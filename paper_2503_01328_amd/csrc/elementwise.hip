@@ -220,18 +220,18 @@ __global__ __launch_bounds__(256) void ln_backward_rows_kernel(const T* __restri
 // there and are widened again in every pass: left alone, the compiler widens them once and keeps 16 floats per vector,
 // which at 10 vectors per lane takes all registers (one wave per SIMD, 3.1 TB/s).  [5001, 5120]: 66.5 -> 46.1 us (52.5 with four
 // waves and 32 bytes of scratch).
-template <typename T>
+// Waves per SIMD asked of the compiler: what the packed vectors and about 40 more registers leave room for; 1: widened once.
+template <typename T, int VPL>
+constexpr int ln_backward_waves() {
+  return sizeof(T) == 4 || VPL < 6 ? 1 : VPL <= 8 ? 4 : VPL <= 12 ? 3 : 2;
+}
+template <typename T, int VPL>
 __device__ __forceinline__ void stay_packed(Vec16<T>& v) {
-  if (sizeof(T) == 2) {
+  if (ln_backward_waves<T, VPL>() > 1) {
     uint4 w = *reinterpret_cast<uint4*>(&v);
     asm volatile("" : "+v"(w.x), "+v"(w.y), "+v"(w.z), "+v"(w.w));
     *reinterpret_cast<uint4*>(&v) = w;
   }
-}
-// Waves per SIMD asked of the compiler: what the packed vectors and about 40 more registers leave room for.
-template <typename T, int VPL>
-constexpr int ln_backward_waves() {
-  return sizeof(T) == 4 ? 1 : VPL <= 4 ? 6 : VPL <= 5 ? 5 : VPL <= 8 ? 4 : VPL <= 12 ? 3 : 2;
 }
 template <typename T, int VPL>
 __global__ __launch_bounds__(256, (ln_backward_waves<T, VPL>())) void ln_backward_rows_cached_kernel(const T* __restrict__ dn, const T* __restrict__ x,
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256, (ln_backward_waves<T, VPL>())) void ln_backwar
     for (int i = 0; i < V; ++i) sum += to_f32(xv[j].v[i]);
   float mean = wave_sum(sum) / (float)h;
 #pragma unroll
-  for (int j = 0; j < VPL; ++j) stay_packed(xv[j]);
+  for (int j = 0; j < VPL; ++j) stay_packed<T, VPL>(xv[j]);
   float sq = 0.f;
 #pragma unroll
   for (int j = 0; j < VPL; ++j)
@@ -272,8 +272,8 @@ __global__ __launch_bounds__(256, (ln_backward_waves<T, VPL>())) void ln_backwar
   float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)h + eps);
 #pragma unroll
   for (int j = 0; j < VPL; ++j) {
-    stay_packed(xv[j]);
-    stay_packed(dv[j]);
+    stay_packed<T, VPL>(xv[j]);
+    stay_packed<T, VPL>(dv[j]);
   }
   float s1 = 0.f, s2 = 0.f;
 #pragma unroll
@@ -289,8 +289,8 @@ __global__ __launch_bounds__(256, (ln_backward_waves<T, VPL>())) void ln_backwar
   float c1 = wave_sum(s1) / (float)h, c2 = wave_sum(s2) / (float)h;
 #pragma unroll
   for (int j = 0; j < VPL; ++j) {
-    stay_packed(xv[j]);
-    stay_packed(dv[j]);
+    stay_packed<T, VPL>(xv[j]);
+    stay_packed<T, VPL>(dv[j]);
   }
 #pragma unroll
   for (int j = 0; j < VPL; ++j) {
