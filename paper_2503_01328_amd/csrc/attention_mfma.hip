@@ -31,8 +31,8 @@
 // sequences ran on the vector kernels, which hold P and dS in fp32.  Relative error against 64 bits at s 1733, 16 heads
 // of 128: o 1.608e-3, dq 1.768e-3 -> 1.770e-3, dk 1.765e-3, dv 1.659e-3, all of it the rounding of the results to bf16
 // (2.8e-3 with one term).  The second term costs a third of the MFMAs.  Vector kernels -> this form,
-// us: s 1733, 16 heads of 128: forward 2235 -> 75, backward 20450 -> 132; s 3000, 32 heads of 64 over 8: 5406 -> 116 and
-// 72760 -> 446; s 100, 16 heads of 128: 35 -> 19 and 147 -> 20.
+// us: s 1733, 16 heads of 128: forward 2235 -> 75, backward 20450 -> 106; s 3000, 32 heads of 64 over 8: 5406 -> 116 and
+// 72760 -> 267; s 100, 16 heads of 128: 35 -> 19 and 147 -> 20.
 #include "mfma_common.h"
 
 namespace po {
@@ -593,6 +593,13 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
 //                                                            initial value of the two accumulators)
 //   dV[key]   += P^T dO         dK[key] += dS^T Q   (times scale at the end)
 // ==================================================================================
+// EDGE with several partial results per key/value head (out_k0 == kFp32Partials): `out` is fp32 and a block's dK and dV go
+// to columns bx * DH of its two halves, out_v_delta columns apart.
+constexpr int kFp32Partials = -1;
+__device__ __forceinline__ void store_partial(bf16* out, size_t row, int ld_out, int column, const float (&v)[4]) {
+  f32x4 w = {v[0], v[1], v[2], v[3]};
+  *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out) + row * ld_out + column) = w;
+}
 // The backward kernels are written as block functions: bx, by and gy stand for blockIdx.x, blockIdx.y and gridDim.y,
 // so that a kernel of its own (the thin wrapper after each function) and the one-launch kernel further down, which
 // numbers its blocks itself, run the same code.
@@ -725,11 +732,20 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
       }
       if constexpr (EDGE) {
         // One product after the other, so that the two-term operands need no more registers than the other form:
-        // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.
+        // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.  The lane id is hidden again before each, so that no LDS address is
+        // carried from one to the next; with them in registers the fragments of K and V were spilled, and every reload
+        // waited for the tile loads under way.
+        auto hide = [&]() __attribute__((always_inline)) {
+          asm volatile("" : "+v"(lane_l));
+          col_l = lane_l & 31, half_l = lane_l >> 5;
+        };
+        hide();
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk)
+        for (int kk = 0; kk < KS; ++kk) {
           sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               read_row_fragment<DH>(qtile, 32 * j + col_l, 2 * kk + half_l), kf[kk], sacc, 0, 0, 0);
+          if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           sacc[e] = fast_exp2(sacc[e] * c);
@@ -745,10 +761,13 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
               to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, lo, to[d], 0, 0, 0);
               to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, hi, to[d], 0, 0, 0);
             }
+            __builtin_amdgcn_sched_barrier(0);
           }
         };
-        accumulate(dv, sacc, dotile);
         __builtin_amdgcn_sched_barrier(0);
+        hide();
+        accumulate(dv, sacc, dotile);
+        hide();
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           f32x4 d4 = *reinterpret_cast<const f32x4*>(st_delta + 32 * j + 8 * b + 4 * half_l);
@@ -764,9 +783,11 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
             vb = *reinterpret_cast<const bf16x8*>(vslot_l + (kk - V_IN_REG) * 1024);
           pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               read_row_fragment<DH>(dotile, 32 * j + col_l, 2 * kk + half_l), vb, pacc, 0, 0, 0);
+          if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) pacc[e] *= sacc[e];
+        hide();
         accumulate(dk, pacc, qtile);
         continue;
       }
@@ -820,6 +841,17 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       bf16x4 vk, vv;
+      if (EDGE && out_k0 == kFp32Partials) {
+        float pk[4], pv[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          pk[r] = dk[d][4 * b + r] * scale;
+          pv[r] = dv[d][4 * b + r];
+        }
+        store_partial(out, key, ld_out, bx * DH + 32 * d + 8 * b + 4 * half, pk);
+        store_partial(out, key, ld_out, out_v_delta + bx * DH + 32 * d + 8 * b + 4 * half, pv);
+        continue;
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         vk[r] = (bf16)(dk[d][4 * b + r] * scale);
@@ -984,11 +1016,20 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
       }
       if constexpr (EDGE) {
         // One product after the other, so that the two-term operands need no more registers than the other form:
-        // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.
+        // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.  The lane id is hidden again before each, so that no LDS address is
+        // carried from one to the next; with them in registers the fragments of K and V were spilled, and every reload
+        // waited for the tile loads under way.
+        auto hide = [&]() __attribute__((always_inline)) {
+          asm volatile("" : "+v"(lane_l));
+          col_l = lane_l & 31, half_l = lane_l >> 5;
+        };
+        hide();
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk)
+        for (int kk = 0; kk < KS; ++kk) {
           sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               read_row_fragment<DH>(qtile, 32 * j + col_l, 2 * kk + half_l), kf[kk], sacc, 0, 0, 0);
+          if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           sacc[e] = fast_exp2(sacc[e] * c);
@@ -1004,10 +1045,13 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
               to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, lo, to[d], 0, 0, 0);
               to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, hi, to[d], 0, 0, 0);
             }
+            __builtin_amdgcn_sched_barrier(0);
           }
         };
-        accumulate(dv, sacc, dotile);
         __builtin_amdgcn_sched_barrier(0);
+        hide();
+        accumulate(dv, sacc, dotile);
+        hide();
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           f32x4 d4 = *reinterpret_cast<const f32x4*>(st_delta + 32 * j + 8 * b + 4 * half_l);
@@ -1023,9 +1067,11 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
             vb = *reinterpret_cast<const bf16x8*>(vslot_l + (kk - V_IN_REG) * 1024);
           pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               read_row_fragment<DH>(dotile, 32 * j + col_l, 2 * kk + half_l), vb, pacc, 0, 0, 0);
+          if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) pacc[e] *= sacc[e];
+        hide();
         accumulate(dk, pacc, qtile);
         continue;
       }
@@ -1096,6 +1142,18 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
         bf16x4 vk, vv;
+        if (EDGE && out_k0 == kFp32Partials) {
+          float pk[4], pv[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            int e = 4 * b + r;
+            pk[r] = (dk[d][e] + xch[(d * 16 + e) * 64]) * scale;
+            pv[r] = dv[d][e] + xch[((DT + d) * 16 + e) * 64];
+          }
+          store_partial(out, key, ld_out, bx * DH + 32 * d + 8 * b + 4 * half, pk);
+          store_partial(out, key, ld_out, out_v_delta + bx * DH + 32 * d + 8 * b + 4 * half, pv);
+          continue;
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           int e = 4 * b + r;
@@ -1431,11 +1489,11 @@ __global__ __launch_bounds__(EIGHT ? 512 : 256, EIGHT ? 1 : 2) void attn_bwd_fus
   }
 }
 
-// Adds the per-query-head dK / dV partials [s, 2h] (dK of head t at columns t * DH, dV at h + t * DH) of every
-// group in head order, in fp32, into the key and value blocks of dqkv [s, h + 2 hkv].  One thread per 8 columns.
-template <int DH>
-__global__ __launch_bounds__(256) void attn_group_sum_kernel(const bf16* __restrict__ part, bf16* __restrict__ dqkv,
-                                                             int s, int h, int hkv, int group) {
+// Adds the dK / dV partials [s, 2 parts hkv] (dK of partial t at columns t * DH, dV parts * hkv further) of every
+// key/value head in order, in fp32, into the key and value blocks of dqkv [s, ld].  One thread per 8 columns.
+template <int DH, typename T>
+__global__ __launch_bounds__(256) void attn_group_sum_kernel(const T* __restrict__ part, bf16* __restrict__ dqkv,
+                                                             int s, int ld, int h, int hkv, int parts) {
   int per_row = 2 * hkv / 8;
   size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (size_t)s * per_row) return;
@@ -1444,15 +1502,20 @@ __global__ __launch_bounds__(256) void attn_group_sum_kernel(const bf16* __restr
   int c = c8 - is_v * hkv;           // column inside the key (or value) block
   int kv_head = c / DH, e = c % DH;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int g = 0; g < group; ++g) {
-    bf16x8 v = *reinterpret_cast<const bf16x8*>(part + (size_t)row * (2 * h) + is_v * h + (kv_head * group + g) * DH + e);
+  for (int g = 0; g < parts; ++g) {
+    const T* p = part + ((size_t)row * 2 + is_v) * ((size_t)parts * hkv) + (kv_head * parts + g) * DH + e;
+    constexpr int V = Vec16<T>::N;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] += (float)v[i];
+    for (int k = 0; k < 8; k += V) {
+      Vec16<T> v = load16(p + k);
+#pragma unroll
+      for (int i = 0; i < V; ++i) acc[k + i] += to_f32(v.v[i]);
+    }
   }
   bf16x8 o;
 #pragma unroll
   for (int i = 0; i < 8; ++i) o[i] = (bf16)acc[i];
-  *reinterpret_cast<bf16x8*>(dqkv + (size_t)row * (h + 2 * hkv) + h + c8) = o;
+  *reinterpret_cast<bf16x8*>(dqkv + (size_t)row * ld + h + c8) = o;
 }
 
 // delta[head][i] = sum_e dO[i, head, e] * O[i, head, e].  Thread t takes the t-th group of eight consecutive
@@ -1539,40 +1602,35 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
                        bf16* partials, int s, int h, int n_heads, int n_kv_heads, hipStream_t stream) {
   constexpr int smem_kv = 2 * (2 * tile_bytes<DH>() + 512) + (DH == 128 ? 8192 : 0);  // + V fragments kept in LDS
   constexpr int smem_q = 4 * tile_bytes<DH>();
-  auto kkv = attn_bwd_dkv_mfma_kernel<DH, EDGE>;
-  auto kq1 = attn_bwd_dq_mfma_kernel<DH, 1, EDGE>;
-  static bool configured = false;
-  if (!configured) {
-    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kkv), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  smem_kv));
-    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kq1), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  smem_q));
-    configured = true;
-  }
   float scale = 1.0f / sqrtf((float)DH);
   int hkv = n_kv_heads * DH, group = n_heads / n_kv_heads;
   attn_delta_mfma_path_kernel<DH><<<(unsigned)(((size_t)s * h / 8 + 255) / 256), 256, 0, stream>>>(o, d_o, delta, s, h);
   // Few key/value heads: one block per query head and a per-group sum afterwards (needs the [s, 2h] workspace),
-  // once the direct launch would not fill the chip's 512 block slots.  The partials are rounded to bf16, which the
-  // EDGE form, whose sums over a group have always been fp32, does not do.
+  // once the direct launch would not fill the chip's 512 block slots.  Those partials are rounded to bf16; the EDGE
+  // form, whose sums over a group have always been fp32, keeps fp32 partials of two (or the group's next divisor) query
+  // heads each, which fit the same workspace (s 3000, 32 heads of 64 over 8: 481 -> 305 us, then 267 with the eight-wave
+  // blocks; s 1000, 8 heads of 128 over 1: 377 -> 108).
   const int blocks = ceil_div(s, 128);
-  bool split = !EDGE && group > 1 && partials && (int64_t)n_kv_heads * blocks < 512;
-  // At most one block per CU: the eight-wave kernel, which halves a wave's chain of tiles.
-  constexpr int smem_kv8 = 4 * (2 * tile_bytes<DH>() + 512) + (DH == 128 ? 24576 : 0);
-  auto kkv8 = attn_bwd_dkv_split_mfma_kernel<DH, EDGE>;
-  bool eight = (int64_t)(split ? n_heads : n_kv_heads) * blocks <= 256;
-  static bool eight_configured = false;
-  if (eight && !eight_configured) {
-    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kkv8), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  smem_kv8));
-    eight_configured = true;
+  bool split = group > 1 && partials && (int64_t)n_kv_heads * blocks < 512;
+  int hpb_split = 1;
+  if (EDGE) {
+    for (hpb_split = 2; hpb_split < group && group % hpb_split != 0;) ++hpb_split;
+    split = split && hpb_split < group && (uintptr_t)partials % 16 == 0;
   }
-  const bool dq_eight = (int64_t)n_heads * blocks <= 256;  // one block per CU at most: the eight-wave kernel
+  const int n_parts = split ? group / hpb_split : 1;
+  // At most one block per CU: the eight-wave kernel, which halves a wave's chain of tiles.  EDGE takes it up to three: the chain
+  // is the longer part there, and one launch with the dQ blocks, of the same form, fills the chip beside it
+  // (256 / 512 / 768 / 1024 blocks of dK/dV at most, us: s 1300, 32 heads of 128 over 4 207 / 152 / 150 / 149; s 3000, 32
+  // heads of 128 over 8 495 / 425 / 424 / 423; s 2500, 40 heads of 64 226 / 214 / 214 / 243).
+  constexpr int smem_kv8 = 4 * (2 * tile_bytes<DH>() + 512) + (DH == 128 ? 24576 : 0);
+  bool eight = (int64_t)n_kv_heads * n_parts * blocks <= (EDGE ? 768 : 256);
+  const bool dq_eight = EDGE ? eight : (int64_t)n_heads * blocks <= 256;  // one block per CU at most: the eight-wave kernel
   constexpr int smem_split = 8 * tile_bytes<DH>();
   // where dK/dV go: per-head partials [s, 2h] or dqkv itself
   bf16* kv_out = split ? partials : dqkv;
-  const int kv_ld = split ? 2 * h : h + 2 * hkv, kv_k0 = split ? 0 : h, kv_vd = split ? h : hkv;
-  const int kv_hpb = split ? 1 : group, x_kv = split ? n_heads : n_kv_heads;
+  const int kv_ld = split ? 2 * n_parts * hkv : h + 2 * hkv, kv_k0 = split ? (EDGE ? kFp32Partials : 0) : h;
+  const int kv_vd = split ? n_parts * hkv : hkv;
+  const int kv_hpb = split ? hpb_split : group, x_kv = n_kv_heads * n_parts;
   if (eight == dq_eight) {  // same block shape: one launch, the dQ blocks queued behind the dK/dV blocks
     unsigned n_blocks = (unsigned)((x_kv + n_heads) * blocks);
     if (eight) {
@@ -1600,7 +1658,20 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
           hkv,
                                             group, scale, x_kv, n_heads);
     }
-  } else {
+  } else if constexpr (!EDGE) {
+    auto kkv = attn_bwd_dkv_mfma_kernel<DH, false>;
+    auto kkv8 = attn_bwd_dkv_split_mfma_kernel<DH, false>;
+    auto kq1 = attn_bwd_dq_mfma_kernel<DH, 1, false>;
+    static bool configured = false;
+    if (!configured) {
+      PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kkv), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    smem_kv));
+      PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kkv8), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    smem_kv8));
+      PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kq1), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    smem_q));
+      configured = true;
+    }
     if (eight)
       kkv8<<<dim3(x_kv, blocks), 512, smem_kv8, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb,
           s,
@@ -1610,7 +1681,7 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
           h,
                                                          hkv, group, scale);
     if (dq_eight) {
-      auto kqs = attn_bwd_dq_split_mfma_kernel<DH, EDGE>;
+      auto kqs = attn_bwd_dq_split_mfma_kernel<DH, false>;
       static bool split_configured = false;
       if (!split_configured) {
         PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kqs), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1624,7 +1695,12 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
   }
   if (split) {
     size_t n = (size_t)s * (2 * hkv / 8);
-    attn_group_sum_kernel<DH><<<(unsigned)((n + 255) / 256), 256, 0, stream>>>(partials, dqkv, s, h, hkv, group);
+    const unsigned grid = (unsigned)((n + 255) / 256);
+    if (EDGE)
+      attn_group_sum_kernel<DH, float><<<grid, 256, 0, stream>>>((const float*)partials, dqkv, s, h + 2 * hkv, h, hkv,
+                                                                 n_parts);
+    else
+      attn_group_sum_kernel<DH, bf16><<<grid, 256, 0, stream>>>(partials, dqkv, s, h + 2 * hkv, h, hkv, n_parts);
   }
   return launch_ok("attention backward MFMA kernels");
 }
