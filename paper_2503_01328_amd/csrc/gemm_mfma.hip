@@ -38,7 +38,8 @@
 //
 // Results that are no whole tiles use a second form of the same kernel, EDGE: loads through buffer descriptors, guarded
 // stores.  A stage of C2's widths at 1733 rows: forward products 101, 133 and 73 us with the 64 x 64 tiles of
-// gemm_small.hip -> 54, 68 and 52 us, the four weight gradients 345 -> 261 us, the step 5.18 -> 3.96 ms.
+// gemm_small.hip -> 54, 68 and 52 us, the four weight gradients 345 -> 195 us (261 with every tile guarded), the step
+// 5.18 -> 3.68 ms.
 //
 // Workgroup ids are remapped so that the blocks that land on one XCD (ids equal
 // modulo 8) work on neighbouring tiles and share operand slices in that XCD's L2.
@@ -450,71 +451,76 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, const bf16* __res
   float* strip = reinterpret_cast<float*>(smem) + wave * (32 * STRIP_LD);
   int col = lane & 31, half = lane >> 5;
   auto inside = [&](int m, int n) { return m < M && n < N; };
+  auto epilogue = [&](auto guard_tag) __attribute__((always_inline)) {
+    constexpr bool GUARD = decltype(guard_tag)::value;  // the tile ends outside the result
 #pragma unroll
-  for (int i = 0; i < WTM; ++i) {
+    for (int i = 0; i < WTM; ++i) {
 #pragma unroll
-    for (int j = 0; j < WTN; ++j)
+      for (int j = 0; j < WTN; ++j)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        *reinterpret_cast<f32x4*>(strip + col * STRIP_LD + 32 * j + 8 * q + 4 * half) = v;
-      }
-    // (a wave reads back only what it wrote itself: program order is enough, no barrier)
-    int mrow0 = m0 + wm * (WTM * 32) + i * 32;
-    int ncol0 = n0 + wn * STRIP_N;
-    if (EPI == kEpiAccumulate) {
-      // fp32 read-modify-write of the strip: all loads of the old values are issued before the first
-      // add, so that a wave keeps 16 KiB in flight instead of one access at a time.
-      constexpr int LPR = STRIP_N / 4;       // lanes per row, 4 floats each
-      constexpr int NIT = 32 * LPR / 64;     // wave-wide accesses per strip; piece it * 64 + lane of the strip
-      static_assert(32 * LPR % 64 == 0, "strip is a whole number of wave-wide accesses");
-      f32x4 old[NIT];
-      float* cbase = ep.acc_f32 + (size_t)mrow0 * ep.ldc + ncol0;
-#pragma unroll
-      for (int it = 0; it < NIT; ++it) {
-        int piece = it * 64 + lane;
-        if (EDGE && !inside(mrow0 + piece / LPR, ncol0 + (piece % LPR) * 4)) continue;
-        old[it] = *reinterpret_cast<const f32x4*>(cbase + (size_t)(piece / LPR) * ep.ldc + (piece % LPR) * 4);
-      }
-#pragma unroll
-      for (int it = 0; it < NIT; ++it) {
-        int piece = it * 64 + lane;
-        int r = piece / LPR;
-        int c = (piece % LPR) * 4;
-        if (EDGE && !inside(mrow0 + r, ncol0 + c)) continue;
-        f32x4 v = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c);
-        *reinterpret_cast<f32x4*>(cbase + (size_t)r * ep.ldc + c) = old[it] + v;
-      }
-    } else {
-      constexpr int LPR = STRIP_N / 8;  // lanes per row, 8 values each
-      constexpr int NIT = 32 * LPR / 64;
-      static_assert(32 * LPR % 64 == 0, "strip is a whole number of wave-wide accesses");
-      // the strip's pieces of u (GeLU backward) or of the residual are all requested before the first use
-      bf16x8_t aux[NIT];
-      const bf16* aux_src = EPI == kEpiGeluBackward ? static_cast<const bf16*>(ep.gelu_u)
-                                                    : static_cast<const bf16*>(ep.residual);
-      if (aux_src) {
-        const bf16* abase = aux_src + (size_t)mrow0 * ep.ldc + ncol0;
+        for (int q = 0; q < 4; ++q) {
+          f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+          *reinterpret_cast<f32x4*>(strip + col * STRIP_LD + 32 * j + 8 * q + 4 * half) = v;
+        }
+      // (a wave reads back only what it wrote itself: program order is enough, no barrier)
+      int mrow0 = m0 + wm * (WTM * 32) + i * 32;
+      int ncol0 = n0 + wn * STRIP_N;
+      if (EPI == kEpiAccumulate) {
+        // fp32 read-modify-write of the strip: all loads of the old values are issued before the first
+        // add, so that a wave keeps 16 KiB in flight instead of one access at a time.
+        constexpr int LPR = STRIP_N / 4;       // lanes per row, 4 floats each
+        constexpr int NIT = 32 * LPR / 64;     // wave-wide accesses per strip; piece it * 64 + lane of the strip
+        static_assert(32 * LPR % 64 == 0, "strip is a whole number of wave-wide accesses");
+        f32x4 old[NIT];
+        float* cbase = ep.acc_f32 + (size_t)mrow0 * ep.ldc + ncol0;
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
           int piece = it * 64 + lane;
-          if (EDGE && !inside(mrow0 + piece / LPR, ncol0 + (piece % LPR) * 8)) continue;
-          aux[it] = *reinterpret_cast<const bf16x8_t*>(abase + (size_t)(piece / LPR) * ep.ldc + (piece % LPR) * 8);
+          if (GUARD && !inside(mrow0 + piece / LPR, ncol0 + (piece % LPR) * 4)) continue;
+          old[it] = *reinterpret_cast<const f32x4*>(cbase + (size_t)(piece / LPR) * ep.ldc + (piece % LPR) * 4);
+        }
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+          int piece = it * 64 + lane;
+          int r = piece / LPR;
+          int c = (piece % LPR) * 4;
+          if (GUARD && !inside(mrow0 + r, ncol0 + c)) continue;
+          f32x4 v = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c);
+          *reinterpret_cast<f32x4*>(cbase + (size_t)r * ep.ldc + c) = old[it] + v;
+        }
+      } else {
+        constexpr int LPR = STRIP_N / 8;  // lanes per row, 8 values each
+        constexpr int NIT = 32 * LPR / 64;
+        static_assert(32 * LPR % 64 == 0, "strip is a whole number of wave-wide accesses");
+        // the strip's pieces of u (GeLU backward) or of the residual are all requested before the first use
+        bf16x8_t aux[NIT];
+        const bf16* aux_src = EPI == kEpiGeluBackward ? static_cast<const bf16*>(ep.gelu_u)
+                                                      : static_cast<const bf16*>(ep.residual);
+        if (aux_src) {
+          const bf16* abase = aux_src + (size_t)mrow0 * ep.ldc + ncol0;
+#pragma unroll
+          for (int it = 0; it < NIT; ++it) {
+            int piece = it * 64 + lane;
+            if (GUARD && !inside(mrow0 + piece / LPR, ncol0 + (piece % LPR) * 8)) continue;
+            aux[it] = *reinterpret_cast<const bf16x8_t*>(abase + (size_t)(piece / LPR) * ep.ldc + (piece % LPR) * 8);
+          }
+        }
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+          int piece = it * 64 + lane;
+          int r = piece / LPR;
+          int c = (piece % LPR) * 8;
+          if (GUARD && !inside(mrow0 + r, ncol0 + c)) continue;
+          f32x4 v0 = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c);
+          f32x4 v1 = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c + 4);
+          float vv[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+          epilogue_row_piece<EPI>(ep, mrow0 + r, ncol0 + c, vv, aux[it]);
         }
       }
-#pragma unroll
-      for (int it = 0; it < NIT; ++it) {
-        int piece = it * 64 + lane;
-        int r = piece / LPR;
-        int c = (piece % LPR) * 8;
-        if (EDGE && !inside(mrow0 + r, ncol0 + c)) continue;
-        f32x4 v0 = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c);
-        f32x4 v1 = *reinterpret_cast<const f32x4*>(strip + r * STRIP_LD + c + 4);
-        float vv[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-        epilogue_row_piece<EPI>(ep, mrow0 + r, ncol0 + c, vv, aux[it]);
-      }
     }
-  }
+  };
+  if (!EDGE || (m0 + BM <= M && n0 + BN <= N)) epilogue(std::false_type());
+  else epilogue(std::true_type());
 #ifdef PO_PHASE_TIMING  // overwrites the first 16 bytes of the result: prologue, main loop, epilogue cycles, cycles per 10 ns
   __syncthreads();
   if (tile_m == 0 && tile_n == 0 && threadIdx.x == 0 && ep.out) {
