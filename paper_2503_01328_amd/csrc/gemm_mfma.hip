@@ -865,18 +865,15 @@ bool gemm_mfma_grouped_edge_accumulate(int n, const GemmProblem* p, hipStream_t 
 }
 
 // The four weight-gradient products of a layer of width h over s rows, us with 256 x 256 tiles / 64 x 64 tiles:
-//   h  512 ( 48 tiles of 256): s 100  23.8 /  9.0, s 1733   59 /  25, s 4000   94 /  45
-//   h 1024 (192):              s 100  35.9 / 26.3, s  700 46.7 / 44.0, s 1024 52.3 / 54.0, s 4000 110 / 144
-//   h 2048 (768):              s 100   100 /   90, s  300  115 /  111, s  512  127 /  133, s 4000 408 / 621
-//   h 4096 (3072):             s 100   581 /  519, s  300  619 /  604, s  512  664 /  690, s 1733 985 / 1275
+//   h  512 ( 48 tiles of 256): s 100  13.1 /  9.0, s 1733   40 /  25, s 4000   75 /  45
+//   h 1024 (192):              s 100  23.9 / 26.3, s  700 34.6 / 43.4, s 4000   97 / 144
+//   h 2048 (768):              s 100    73 /   90, s 1733  184 /  290, s 4000  341 / 623
+//   h 4096 (3072):             s 100   323 /  518, s 1733  721 / 1277
+// The line between, half a round, is where the small tiles' time, in proportion to the work, meets one round of large ones.
 bool gemm_small_group_is_faster(int n, const GemmProblem* p) {
   int64_t tiles = 0;
-  int K = 0;
-  for (int i = 0; i < n; ++i) {
-    tiles += (int64_t)ceil_div(p[i].M, 256) * ceil_div(p[i].N, 256);
-    K = p[i].K > K ? p[i].K : K;
-  }
-  return tiles <= 128 || K < (tiles <= 256 ? 896 : 384);
+  for (int i = 0; i < n; ++i) tiles += (int64_t)ceil_div(p[i].M, 256) * ceil_div(p[i].N, 256);
+  return tiles <= 128;
 }
 
 }  // namespace po
