@@ -628,9 +628,9 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
   const float c = scale * LOG2E;
 
   // K and V fragments of this wave's keys: B operands, column = key, contraction over the head dimension.
-  // With DH = 128 the last two V fragments live in LDS (a private 16-byte slot per lane and fragment)
+  // With DH = 128 the last two (EDGE: three) V fragments live in LDS (a private 16-byte slot per lane and fragment)
   // instead of registers: at two waves per SIMD the register file cannot hold them without spilling.
-  constexpr int V_IN_LDS = DH == 128 ? 2 : 0;
+  constexpr int V_IN_LDS = DH == 128 ? (EDGE ? 3 : 2) : 0;
   constexpr int V_IN_REG = KS - V_IN_LDS;
   char* vslot = smem + 2 * STAGE + (wave * V_IN_LDS * 64 + lane) * 16;
   bf16x8 kf[KS], vf[V_IN_REG > 0 ? V_IN_REG : 1];
@@ -834,6 +834,11 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
     __syncthreads();
   }
 
+  if (EDGE) {  // the lane id rebuilt rather than kept (and spilled) across the loop
+    lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    col = lane & 31;
+    half = lane >> 5;
+  }
   int key = kw0 + col;
   if (EDGE && key >= s) return;
 #pragma unroll
@@ -1600,7 +1605,7 @@ bool attention_forward_mfma(const void* qkv, void* o, float* lse, int s, int h, 
 template <int DH, bool EDGE>
 static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const bf16* d_o, bf16* dqkv, float* delta,
                        bf16* partials, int s, int h, int n_heads, int n_kv_heads, hipStream_t stream) {
-  constexpr int smem_kv = 2 * (2 * tile_bytes<DH>() + 512) + (DH == 128 ? 8192 : 0);  // + V fragments kept in LDS
+  constexpr int smem_kv = 2 * (2 * tile_bytes<DH>() + 512) + (DH == 128 ? (EDGE ? 12288 : 8192) : 0);  // + V in LDS
   constexpr int smem_q = 4 * tile_bytes<DH>();
   float scale = 1.0f / sqrtf((float)DH);
   int hkv = n_kv_heads * DH, group = n_heads / n_kv_heads;

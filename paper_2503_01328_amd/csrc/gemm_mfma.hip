@@ -535,9 +535,9 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, const bf16* __res
 // ---- the kernels -----------------------------------------------------------------
 // One tile per block.  XCD-aware remap: ids equal modulo 8 share an XCD; each XCD gets a contiguous run of tiles.
 template <int WTM, int WTN, bool TA, bool TB, int EPI, bool EDGE>
-__global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, const bf16* __restrict__ A, int lda,
-                                                        const bf16* __restrict__ B, int ldb, Epilogue ep,
-                                                        int tiles_m, int tiles_n) {
+__device__ __forceinline__ void gemm_block(int M, int N, int K, const bf16* __restrict__ A, int lda,
+                                           const bf16* __restrict__ B, int ldb, const Epilogue& ep, int tiles_m,
+                                           int tiles_n) {
   extern __shared__ __align__(16) char smem[];
   int n_tiles = tiles_m * tiles_n;
   int pid = blockIdx.x;
@@ -545,6 +545,19 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, con
   int tile_m, tile_n;
   tile_of(lin, tiles_m, tiles_n, tile_m, tile_n);
   gemm_tile<WTM, WTN, TA, TB, EPI, EDGE>(M, N, K, A, lda, B, ldb, ep, tile_m, tile_n, smem);
+}
+
+template <int WTM, int WTN, bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(256) void gemm_mfma_kernel(int K, const bf16* __restrict__ A, int lda,
+                                                        const bf16* __restrict__ B, int ldb, Epilogue ep,
+                                                        int tiles_m, int tiles_n) {
+  gemm_block<WTM, WTN, TA, TB, EPI, false>(0, 0, K, A, lda, B, ldb, ep, tiles_m, tiles_n);
+}
+template <int WTM, int WTN, bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(256) void gemm_edge_kernel(int M, int N, int K, const bf16* __restrict__ A, int lda,
+                                                        const bf16* __restrict__ B, int ldb, Epilogue ep,
+                                                        int tiles_m, int tiles_n) {
+  gemm_block<WTM, WTN, TA, TB, EPI, true>(M, N, K, A, lda, B, ldb, ep, tiles_m, tiles_n);
 }
 
 // Several independent GEMMs of one form in one launch: the 256 x 256 tiles of all problems are numbered one
@@ -564,7 +577,7 @@ struct GroupedArgs {
 };
 
 template <bool TA, bool TB, int EPI, bool EDGE>
-__global__ __launch_bounds__(256) void gemm_mfma_grouped_kernel(GroupedArgs g) {
+__device__ __forceinline__ void gemm_grouped_blocks(const GroupedArgs& g) {
   extern __shared__ __align__(16) char smem[];
   int pid = blockIdx.x, nb = gridDim.x;
   int slot = (nb % 8 == 0) ? (pid % 8) * (nb / 8) + pid / 8 : pid;  // an XCD's blocks take a run of tile numbers
@@ -585,6 +598,15 @@ __global__ __launch_bounds__(256) void gemm_mfma_grouped_kernel(GroupedArgs g) {
     }
     __syncthreads();  // the next tile's operand loads overwrite the epilogue strips of every wave
   }
+}
+
+template <bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(256) void gemm_mfma_grouped_kernel(GroupedArgs g) {
+  gemm_grouped_blocks<TA, TB, EPI, false>(g);
+}
+template <bool TA, bool TB, int EPI>
+__global__ __launch_bounds__(256) void gemm_edge_grouped_kernel(GroupedArgs g) {
+  gemm_grouped_blocks<TA, TB, EPI, true>(g);
 }
 
 // ---- host side ------------------------------------------------------------------
@@ -636,15 +658,21 @@ static bool launch_mfma_epi(int M, int N, int K, const bf16* A, int lda, const b
   constexpr int smem_ops = stages_of(WTM, WTN) * (BM + BN) * 128;
   constexpr int smem_epi = 4 * 32 * (WTN * 32 + 4) * 4;
   constexpr int smem = smem_ops > smem_epi ? smem_ops : smem_epi;
-  auto kern = gemm_mfma_kernel<WTM, WTN, TA, TB, EPI, EDGE>;
+  const void* kern;
+  if constexpr (EDGE) kern = reinterpret_cast<const void*>(gemm_edge_kernel<WTM, WTN, TA, TB, EPI>);
+  else kern = reinterpret_cast<const void*>(gemm_mfma_kernel<WTM, WTN, TA, TB, EPI>);
   static bool configured = false;  // per instantiation
   if (!configured) {
-    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  smem));
+    PO_HIP_OK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
     configured = true;
   }
   int tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
-  kern<<<tiles_m * tiles_n, 256, smem, stream>>>(M, N, K, A, lda, B, ldb, ep, tiles_m, tiles_n);
+  if constexpr (EDGE)
+    gemm_edge_kernel<WTM, WTN, TA, TB, EPI><<<tiles_m * tiles_n, 256, smem, stream>>>(M, N, K, A, lda, B, ldb, ep,
+                                                                                   tiles_m, tiles_n);
+  else
+    gemm_mfma_kernel<WTM, WTN, TA, TB, EPI><<<tiles_m * tiles_n, 256, smem, stream>>>(K, A, lda, B, ldb, ep, tiles_m,
+                                                                                   tiles_n);
   return launch_ok("gemm_mfma_kernel");
 }
 
@@ -796,7 +824,8 @@ bool gemm_mfma_grouped_supported(int n, const GemmProblem* p) {
 template <bool EDGE>
 static bool launch_grouped(GroupedArgs& g, hipStream_t stream) {
   constexpr int smem = stages_of(4, 4) * (256 + 256) * 128;
-  auto kern = gemm_mfma_grouped_kernel<true, true, kEpiAccumulate, EDGE>;
+  auto kern = EDGE ? gemm_edge_grouped_kernel<true, true, kEpiAccumulate>
+                   : gemm_mfma_grouped_kernel<true, true, kEpiAccumulate>;
   static bool configured = false;
   if (!configured) {
     PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
