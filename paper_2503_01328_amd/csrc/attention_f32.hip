@@ -8,6 +8,10 @@
 // meet, tile t to wave t % 4; the four partial results are added in wave order through LDS at the end (deterministic,
 // no atomics).  Heaviest blocks of the causal triangle first.
 //
+// Rows of o and dQ whose sums are not finite are redone one by one (attention_rows.h), so that an infinity or NaN in a
+// key or value reaches the rows at and behind it and no other.  What that costs where all is finite, one multiplication
+// per sum, is not measurable (a stage of 16 heads of 64 at 1024 rows 4.07 and 4.05 ms).
+//
 // Layouts.  S^T = K Q^T puts the index a wave owns on the MFMA's column: lane L holds column L % 32 and rows
 // 8 b + 4 (L / 32) + r (register 4 b + r).  Register e of such a tile is, as it stands, the second operand of step e of
 // the product that follows (the step's two k-indices are the rows the two half-waves hold in register e), whose first
@@ -17,8 +21,7 @@
 // s = 1024, 16 heads of 64: forward 42 us (2 s^2 h: 51 of 157 TFLOP/s), dK/dV 91 us, dQ 54 us; the vector kernels of
 // attention_generic.hip take 625, 3076 and 769 us.  s = 128, 4 heads: 7.5, 14.2 and 8.0 us (44, 55 and 28 us), there
 // bound by the chain of one tile: two loads, 64 to 128 dependent MFMAs, the sum over the waves.
-#include <math.h>
-
+#include "attention_rows.h"
 #include "mfma_common.h"
 
 namespace po {
@@ -70,6 +73,20 @@ __device__ __forceinline__ void put_partial(float* p, const f32x16 (&acc)[N], in
 #pragma unroll
     for (int e = 0; e < 16; ++e) p[(d * 16 + e) * 64 + lane] = acc[d][e];
 }
+template <int N>
+__device__ __forceinline__ bool not_finite(const f32x16 (&acc)[N]) {
+  float z = 0.f;
+#pragma unroll
+  for (int d = 0; d < N; ++d)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z = fmaf(acc[d][e], 0.f, z);
+  return !(z == 0.f);
+}
+// The four waves' rows to redo, left in LDS before the barrier: all of them, and this wave's share (every fourth).
+__device__ __forceinline__ uint32_t all_redo(const uint32_t* masks) {
+  return __builtin_amdgcn_readfirstlane(masks[0] | masks[1] | masks[2] | masks[3]);
+}
+__device__ __forceinline__ uint32_t share_of(uint32_t redo, int wave) { return redo & (0x11111111u << wave); }
 
 }  // namespace
 
@@ -78,7 +95,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
                                                               float* __restrict__ lse, int s, int h, int hkv, int group,
                                                               float scale) {
   constexpr int DT = DH / 32, PART = DT * 16 * 64;
-  extern __shared__ __align__(16) float lds[];  // four partial outputs, then their maxima and row sums
+  extern __shared__ __align__(16) float lds[];  // four partial outputs, then their maxima and row sums, rows to redo
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   const int head = blockIdx.x, q0 = (int)(gridDim.y - 1 - blockIdx.y) * 32, q = q0 + (lane & 31);
   const int ld = h + 2 * hkv, last = s - 1;
@@ -121,9 +138,14 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
   }
   put_partial<DT>(lds + wave * PART, acc, lane);
   float* stat = lds + 4 * PART;
+  uint32_t* redo_of = reinterpret_cast<uint32_t*>(stat + 8 * 64);
+  const uint32_t redo_mine = rows_to_redo(not_finite<DT>(acc), s - q0);
+  if (lane == 0) redo_of[wave] = redo_mine;
   stat[wave * 64 + lane] = m_run;
   stat[(4 + wave) * 64 + lane] = l_run + __shfl_xor(l_run, 32, 64);
   __syncthreads();
+  const uint32_t redo = all_redo(redo_of);
+  if (redo) redo_forward_rows<float, DH>(share_of(redo, wave), q0, qkv, o, lse, s, h, hkv, group, head, scale);
   // Wave w finishes registers 4 w .. 4 w + 3 (columns 32 d + 8 w + 4 half ..) of every lane's row.
   float m = stat[lane], f[4], l = 0.f;
 #pragma unroll
@@ -133,7 +155,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
     f[w] = __builtin_amdgcn_exp2f((stat[w * 64 + lane] - m) * c);
     l += stat[(4 + w) * 64 + lane] * f[w];
   }
-  if (q > last) return;
+  if (q > last || (redo >> (lane & 31) & 1)) return;
 #pragma unroll
   for (int d = 0; d < DT; ++d) {
     f32x4 v;
@@ -185,8 +207,13 @@ __global__ __launch_bounds__(256, DH > 64 ? 1 : 2) void attn_f32_bwd_dq_kernel(
     accumulate_rows<DH>(dq, kbase, ld, 32 * t, last, ds, lane);
   }
   put_partial<DT>(lds + wave * PART, dq, lane);
+  uint32_t* redo_of = reinterpret_cast<uint32_t*>(lds + 4 * PART);
+  const uint32_t redo_mine = rows_to_redo(not_finite<DT>(dq), s - q0);
+  if (lane == 0) redo_of[wave] = redo_mine;
   __syncthreads();
-  if (q > last) return;
+  const uint32_t redo = all_redo(redo_of);
+  if (redo) redo_dq_rows<float, DH>(share_of(redo, wave), q0, qkv, d_o, lse, delta, dqkv, s, h, hkv, group, head, scale);
+  if (q > last || (redo >> (lane & 31) & 1)) return;
 #pragma unroll
   for (int d = 0; d < DT; ++d) {
     f32x4 v;
@@ -234,11 +261,17 @@ __global__ __launch_bounds__(256, 1) void attn_f32_bwd_dkv_kernel(
     const float* delta_h = delta + (size_t)head * s;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int q = q0 + 8 * (e >> 2) + 4 * half + (e & 3), qc = min(q, last);
-      float pe = __builtin_amdgcn_exp2f(p[e] * c - lse_h[qc] * kLog2e);
-      if (q > last || key > q) pe = 0.f;
-      ds[e] = pe * (ds[e] - delta_h[qc]);
-      p[e] = pe;
+      const int qc = min(q0 + 8 * (e >> 2) + 4 * half + (e & 3), last);
+      p[e] = __builtin_amdgcn_exp2f(p[e] * c - lse_h[qc] * kLog2e);
+      ds[e] = p[e] * (ds[e] - delta_h[qc]);
+    }
+    if (q0 == first * 32 || q0 + 31 > last) {  // the diagonal, or rows past the end
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int q = q0 + 8 * (e >> 2) + 4 * half + (e & 3);
+        // dS is selected too: 0 times the dP of a row that is not finite is no 0
+        if (q > last || key > q) p[e] = ds[e] = 0.f;
+      }
     }
     accumulate_rows<DH>(dv, dobase, h, q0, last, p, lane);
     accumulate_rows<DH>(dk, qbase, ld, q0, last, ds, lane);
@@ -283,7 +316,7 @@ static bool allow_lds(K kern, int smem) {
 template <int DH>
 static bool forward_f32(const float* qkv, float* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                         hipStream_t stream) {
-  constexpr int smem = (4 * DH * 32 + 8 * 64) * 4;
+  constexpr int smem = (4 * DH * 32 + 8 * 64 + 4) * 4;
   static const bool configured = allow_lds(attn_f32_fwd_kernel<DH>, smem);
   if (!configured) return false;
   attn_f32_fwd_kernel<DH><<<dim3(n_heads, ceil_div(s, 32)), 256, smem, stream>>>(
@@ -294,7 +327,7 @@ static bool forward_f32(const float* qkv, float* o, float* lse, int s, int h, in
 template <int DH>
 static bool backward_f32(const float* qkv, const float* lse, const float* delta, const float* d_o, float* dqkv, int s,
                          int h, int n_heads, int n_kv_heads, hipStream_t stream) {
-  constexpr int smem_q = 4 * DH * 32 * 4, smem_kv = 2 * smem_q;
+  constexpr int smem_part = 4 * DH * 32 * 4, smem_q = smem_part + 16, smem_kv = 2 * smem_part;
   static const bool configured =
       allow_lds(attn_f32_bwd_dq_kernel<DH>, smem_q) && allow_lds(attn_f32_bwd_dkv_kernel<DH>, smem_kv);
   if (!configured) return false;

@@ -10,8 +10,7 @@
 // Grouped-query attention: the qkv matrix is [s, h + 2 hkv] (query block, key block, value block) with
 // hkv = n_kv_heads * dh; query head t reads key/value head t / group, group = n_heads / n_kv_heads.  The dK/dV
 // kernel runs per key/value head and walks its group's query heads in order.
-#include <math.h>
-
+#include "attention_rows.h"
 #include "kernels.h"
 
 namespace po {
@@ -35,44 +34,8 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(const T* __restri
     for (int e = lane; e < dh; e += kWave) qs[wave][e] = to_f32(qkv[(size_t)i * ld + head * dh + e]) * scale;
   __syncthreads();
   if (!active) return;
-  float m = -INFINITY, l = 0.f;
-  float acc[kDimSlots];
-#pragma unroll
-  for (int r = 0; r < kDimSlots; ++r) acc[r] = 0.f;
-  for (int j0 = 0; j0 <= i; j0 += kWave) {
-    int j = j0 + lane;
-    float sc = -INFINITY;
-    if (j <= i) {
-      const T* kr = kbase + (size_t)j * ld;
-      float d = 0.f;
-      for (int e = 0; e < dh; ++e) d = fmaf(qs[wave][e], to_f32(kr[e]), d);
-      sc = d;
-    }
-    float mnew = fmaxf(m, wave_max(sc));
-    float p = (j <= i) ? __expf(sc - mnew) : 0.f;
-    float alpha = __expf(m - mnew);
-    l = l * alpha + wave_sum(p);
-#pragma unroll
-    for (int r = 0; r < kDimSlots; ++r) acc[r] *= alpha;
-    int nj = min(kWave, i - j0 + 1);
-    for (int jj = 0; jj < nj; ++jj) {
-      float pj = __shfl(p, jj, kWave);
-      const T* vr = vbase + (size_t)(j0 + jj) * ld;
-#pragma unroll
-      for (int r = 0; r < kDimSlots; ++r) {
-        int e = lane + kWave * r;
-        if (e < dh) acc[r] = fmaf(pj, to_f32(vr[e]), acc[r]);
-      }
-    }
-    m = mnew;
-  }
-  float inv = 1.0f / l;
-#pragma unroll
-  for (int r = 0; r < kDimSlots; ++r) {
-    int e = lane + kWave * r;
-    if (e < dh) o[(size_t)i * h + head * dh + e] = from_f32<T>(acc[r] * inv);
-  }
-  if (lane == 0) lse[(size_t)head * s + i] = m + __logf(l);
+  attention_forward_row<T, kDimSlots>([&](int e) { return qs[wave][e]; }, kbase, vbase, ld, i, dh, lane,
+                                      o + (size_t)i * h + head * dh, lse + (size_t)head * s + i);
 }
 
 // delta[head][i] = sum_e dO[i, head, e] * O[i, head, e]
@@ -115,39 +78,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_generic_kernel(const T* __res
     }
   __syncthreads();
   if (!active) return;
-  float lse_i = lse[(size_t)head * s + i], delta_i = delta[(size_t)head * s + i];
-  float acc[kDimSlots];
-#pragma unroll
-  for (int r = 0; r < kDimSlots; ++r) acc[r] = 0.f;
-  for (int j0 = 0; j0 <= i; j0 += kWave) {
-    int j = j0 + lane;
-    float ds = 0.f;
-    if (j <= i) {
-      const T* kr = kbase + (size_t)j * ld;
-      const T* vr = vbase + (size_t)j * ld;
-      float sc = 0.f, dp = 0.f;
-      for (int e = 0; e < dh; ++e) {
-        sc = fmaf(qs[wave][e], to_f32(kr[e]), sc);
-        dp = fmaf(dos[wave][e], to_f32(vr[e]), dp);
-      }
-      ds = __expf(sc - lse_i) * (dp - delta_i);
-    }
-    int nj = min(kWave, i - j0 + 1);
-    for (int jj = 0; jj < nj; ++jj) {
-      float dsj = __shfl(ds, jj, kWave);
-      const T* kr = kbase + (size_t)(j0 + jj) * ld;
-#pragma unroll
-      for (int r = 0; r < kDimSlots; ++r) {
-        int e = lane + kWave * r;
-        if (e < dh) acc[r] = fmaf(dsj, to_f32(kr[e]), acc[r]);
-      }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < kDimSlots; ++r) {
-    int e = lane + kWave * r;
-    if (e < dh) dqkv[(size_t)i * ld + head * dh + e] = from_f32<T>(acc[r] * scale);
-  }
+  attention_dq_row<T, kDimSlots>([&](int e) { return qs[wave][e]; }, [&](int e) { return dos[wave][e]; }, kbase, vbase, ld,
+                                 lse[(size_t)head * s + i], delta[(size_t)head * s + i], i, dh, lane, scale,
+                                 dqkv + (size_t)i * ld + head * dh);
 }
 
 template <typename T>

@@ -304,6 +304,53 @@ def test_attention_ragged_bf16(gpu_device, s, h, a, akv):
         check_parity(mine, ref.cpu().numpy(), 2e-2, name)
 
 
+def _nonfinite_inputs(gpu_device, dtype, s, dh, a, akv, where, value, row):
+    _, tdt, _ = DT[dtype]
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(s + dh + a + row)
+    h, hkv = a * dh, akv * dh
+    qkv = torch.randn(s, h + 2 * hkv, generator=g, device=gpu_device).to(tdt)
+    d_o = torch.randn(s, h, generator=g, device=gpu_device).to(tdt)
+    first, last = {"k": (h, h + hkv), "v": (h + hkv, h + 2 * hkv), "qkv": (0, h + 2 * hkv), "d_o": (0, h)}[where]
+    (d_o if where == "d_o" else qkv)[row, first:last] = value
+    return qkv, d_o
+
+
+# A non-finite row among the keys, the values, a whole token or the upstream gradient: what lies behind a row may not
+# reach it.  Compared with the vector kernels, which never read a key behind the row; row: the first, inside the first
+# tile, around tile ends, the last of the sequence.
+NONFINITE = [("f32", 200, 32, 2, 2), ("f32", 97, 64, 2, 1), ("f32", 128, 96, 1, 1), ("f32", 200, 128, 2, 2),
+             ("f32", 512, 64, 4, 4)]
+
+
+@pytest.mark.parametrize("where", ["k", "v", "qkv", "d_o"])
+@pytest.mark.parametrize("dtype,s,dh,a,akv", NONFINITE)
+def test_attention_non_finite_rows_stay_where_they_are(gpu_device, dtype, s, dh, a, akv, where):
+    code, tdt, _ = DT[dtype]
+    h, hkv = a * dh, akv * dh
+    for value, row in ((float("nan"), s - 1), (float("inf"), 63), (float("nan"), 64), (float("-inf"), 17), (float("inf"), 0)):
+        qkv, d_o = _nonfinite_inputs(gpu_device, dtype, s, dh, a, akv, where, value, row)
+        o, lse = [torch.full((s, h), 7.0, dtype=tdt, device=gpu_device) for _ in range(2)], \
+                 [torch.full((a, s), 7.0, device=gpu_device) for _ in range(2)]
+        dqkv = [torch.full((s, h + 2 * hkv), 7.0, dtype=tdt, device=gpu_device) for _ in range(2)]
+        delta = torch.empty(a, s, device=gpu_device)
+        for generic in (1, 0):
+            po.po_op_attention_forward(code, qkv, o[generic], lse[generic], s, h, a, generic, n_kv_heads=akv)
+        for generic in (1, 0):  # both from the same forward results
+            po.po_op_attention_backward(code, qkv, o[1], lse[1], d_o, dqkv[generic], delta, s, h, a, generic,
+                                        n_kv_heads=akv)
+        same = lambda x, y: torch.equal(torch.isfinite(x), torch.isfinite(y))
+        what = (where, value, row)
+        assert same(o[0], o[1]) and same(lse[0], lse[1]), what
+        assert same(dqkv[0][:, :h], dqkv[1][:, :h]), what
+        # dK and dV of a key: the vector kernel lets a row of its 64-row block before it through, the others at most that
+        ok = torch.isfinite(dqkv[1])
+        assert torch.isfinite(dqkv[0][ok]).all(), what
+        close = lambda x, y: (x - y).double().norm() <= (2.0 ** -6 if dtype == "bf16" else 1e-4) * y.double().norm()
+        okf = torch.isfinite(o[1])
+        assert close(o[0][okf], o[1][okf]) and close(dqkv[0][ok], dqkv[1][ok]), what
+
+
 def _attention_case(gpu_device, dtype, s, h, a, force_generic, akv=0, with_partials=False):
     code, tdt, tol = DT[dtype]
     rng = np.random.default_rng(s * 31 + h + a + 7 * akv)
