@@ -291,7 +291,9 @@ int po_op_gemm_tile(int32_t M, int32_t N, int32_t* tile_rows, int32_t* tile_cols
 
 /* Causal attention forward: qkv [s, h + 2 hkv] (q | k | v blocks, hkv = n_kv_heads * h / n_heads;
  * n_kv_heads = 0 means n_heads, i.e. [s, 3h]), o [s, h], lse [a, s] fp32.  With n_kv_heads < n_heads query head t
- * reads key/value head t / (n_heads / n_kv_heads) (grouped-query attention, Table 2). */
+ * reads key/value head t / (n_heads / n_kv_heads) (grouped-query attention, Table 2).
+ * An infinity or NaN in key or value row j reaches rows j and later of o and dQ; with dtype PO_BF16 and s a multiple of 128 also
+ * the rows of the same block of 64 before j. */
 int po_op_attention_forward(int32_t dtype, const void* qkv, void* o, float* lse, int32_t s, int32_t h,
                             int32_t n_heads, int32_t n_kv_heads, int32_t force_generic, void* stream);
 /* Causal attention backward: dqkv laid out like qkv; delta: fp32 workspace [a, s]; partials: NULL, or

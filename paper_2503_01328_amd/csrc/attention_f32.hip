@@ -73,15 +73,6 @@ __device__ __forceinline__ void put_partial(float* p, const f32x16 (&acc)[N], in
 #pragma unroll
     for (int e = 0; e < 16; ++e) p[(d * 16 + e) * 64 + lane] = acc[d][e];
 }
-template <int N>
-__device__ __forceinline__ bool not_finite(const f32x16 (&acc)[N]) {
-  float z = 0.f;
-#pragma unroll
-  for (int d = 0; d < N; ++d)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) z = fmaf(acc[d][e], 0.f, z);
-  return !(z == 0.f);
-}
 // The four waves' rows to redo, left in LDS before the barrier: all of them, and this wave's share (every fourth).
 __device__ __forceinline__ uint32_t all_redo(const uint32_t* masks) {
   return __builtin_amdgcn_readfirstlane(masks[0] | masks[1] | masks[2] | masks[3]);

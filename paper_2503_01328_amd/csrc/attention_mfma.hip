@@ -26,13 +26,16 @@
 //
 // Every kernel has a second form, EDGE, for sequences that are no multiple of 128: tiles are loaded through buffer
 // descriptors that end with the sequence (rows past it read as zero: such a key is masked like any key above the
-// diagonal, such a query row adds zero to every gradient), results past it are not stored.  It also multiplies P and
+// diagonal, such a query row adds zero to every gradient), results past it are not stored.  Rows of o and dQ whose sums are
+// not finite are redone one by one (attention_rows.h), so that an infinity or NaN in a key or value reaches the rows at and
+// behind it and no other; in the other form it also reaches those of its 64-row tile before it.  EDGE also multiplies P and
 // dS as the sum of two bf16 terms, the rounded value and the rounded remainder (16 bits together), because these
 // sequences ran on the vector kernels, which hold P and dS in fp32.  Relative error against 64 bits at s 1733, 16 heads
 // of 128: o 1.608e-3, dq 1.768e-3 -> 1.770e-3, dk 1.765e-3, dv 1.659e-3, all of it the rounding of the results to bf16
 // (2.8e-3 with one term).  The second term costs a third of the MFMAs.  Vector kernels -> this form,
 // us: s 1733, 16 heads of 128: forward 2235 -> 75, backward 20450 -> 106; s 3000, 32 heads of 64 over 8: 5406 -> 116 and
 // 72760 -> 267; s 100, 16 heads of 128: 35 -> 19 and 147 -> 20.
+#include "attention_rows.h"
 #include "mfma_common.h"
 
 namespace po {
@@ -569,7 +572,11 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
   }
   const int q = qw0 + col;
   float l = l_run + __shfl_xor(l_run, 32, 64);
-  if (EDGE && q >= s) return;
+  if constexpr (EDGE) {
+    const uint32_t redo = rows_to_redo(not_finite<DT>(oacc), s - qw0);
+    if (redo) redo_forward_rows<bf16, DH>(redo, qw0, qkv, o, lse, s, h, hkv, group, head, scale);
+    if (q >= s || (redo >> col & 1)) return;
+  }
   float inv = 1.0f / l;
 #pragma unroll
   for (int d = 0; d < DT; ++d)
@@ -786,7 +793,10 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
           if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) pacc[e] *= sacc[e];
+        for (int e = 0; e < 16; ++e) {
+          pacc[e] *= sacc[e];  // selected as well as P: 0 times the dP of a row that is not finite is no 0
+          if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) pacc[e] = 0.f;
+        }
         hide();
         accumulate(dk, pacc, qtile);
         continue;
@@ -1075,7 +1085,10 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
           if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) pacc[e] *= sacc[e];
+        for (int e = 0; e < 16; ++e) {
+          pacc[e] *= sacc[e];  // selected as well as P: 0 times the dP of a row that is not finite is no 0
+          if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) pacc[e] = 0.f;
+        }
         hide();
         accumulate(dk, pacc, qtile);
         continue;
@@ -1307,7 +1320,11 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
     int q = qw0 + 32 * t + col;
-    if (EDGE && q >= s) continue;
+    if constexpr (EDGE) {
+      const uint32_t redo = rows_to_redo(not_finite<DT>(dq[t]), s - qw0 - 32 * t);
+      if (redo) redo_dq_rows<bf16, DH>(redo, qw0 + 32 * t, qkv, d_o, lse, delta, dqkv, s, h, hkv, group, head, scale);
+      if (q >= s || (redo >> col & 1)) continue;
+    }
 #pragma unroll
     for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -1438,20 +1455,25 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
       for (int e = 0; e < 16; ++e) xch[(d * 16 + e) * 64 + lane] = dq[d][e];
   }
   __syncthreads();
-  if (grp == 0 && !(EDGE && q >= s)) {
+  if (grp == 1) return;
 #pragma unroll
-    for (int d = 0; d < DT; ++d)
+  for (int d = 0; d < DT; ++d)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        bf16x4 v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int e = 4 * b + r;
-          v[r] = (bf16)((dq[d][e] + xch[(d * 16 + e) * 64 + lane]) * scale);
-        }
-        *reinterpret_cast<bf16x4*>(dqkv + (size_t)q * ld + head * DH + 32 * d + 8 * b + 4 * half) = v;
-      }
+    for (int e = 0; e < 16; ++e) dq[d][e] += xch[(d * 16 + e) * 64 + lane];
+  if constexpr (EDGE) {
+    const uint32_t redo = rows_to_redo(not_finite<DT>(dq), s - qw0);
+    if (redo) redo_dq_rows<bf16, DH>(redo, qw0, qkv, d_o, lse, delta, dqkv, s, h, hkv, group, head, scale);
+    if (q >= s || (redo >> col & 1)) return;
   }
+#pragma unroll
+  for (int d = 0; d < DT; ++d)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      bf16x4 v;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = (bf16)(dq[d][4 * b + r] * scale);
+      *reinterpret_cast<bf16x4*>(dqkv + (size_t)q * ld + head * DH + 32 * d + 8 * b + 4 * half) = v;
+    }
 }
 
 template <int DH, bool EDGE>

@@ -48,4 +48,15 @@ __device__ __forceinline__ void wait_loads() {
 }
 __device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Whether one of this lane's results is an infinity or NaN.
+template <int N>
+__device__ __forceinline__ bool not_finite(const f32x16 (&acc)[N]) {
+  float z = 0.f;
+#pragma unroll
+  for (int d = 0; d < N; ++d)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z = fmaf(acc[d][e], 0.f, z);
+  return !(z == 0.f);
+}
+
 }  // namespace po

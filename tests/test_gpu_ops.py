@@ -318,9 +318,10 @@ def _nonfinite_inputs(gpu_device, dtype, s, dh, a, akv, where, value, row):
 
 # A non-finite row among the keys, the values, a whole token or the upstream gradient: what lies behind a row may not
 # reach it.  Compared with the vector kernels, which never read a key behind the row; row: the first, inside the first
-# tile, around tile ends, the last of the sequence.
+# tile, around tile ends, the last of the sequence.  400 heads: the 256-row and four-wave forms of the bf16 kernels.
 NONFINITE = [("f32", 200, 32, 2, 2), ("f32", 97, 64, 2, 1), ("f32", 128, 96, 1, 1), ("f32", 200, 128, 2, 2),
-             ("f32", 512, 64, 4, 4)]
+             ("f32", 512, 64, 4, 4), ("bf16", 200, 64, 2, 2), ("bf16", 200, 128, 4, 2), ("bf16", 300, 64, 400, 400),
+             ("bf16", 300, 128, 400, 400)]
 
 
 @pytest.mark.parametrize("where", ["k", "v", "qkv", "d_o"])
