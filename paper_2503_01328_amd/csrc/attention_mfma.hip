@@ -28,13 +28,14 @@
 // descriptors that end with the sequence (rows past it read as zero: such a key is masked like any key above the
 // diagonal, such a query row adds zero to every gradient), results past it are not stored.  Rows of o and dQ whose sums are
 // not finite are redone one by one (attention_rows.h), so that an infinity or NaN in a key or value reaches the rows at and
-// behind it and no other; in the other form it also reaches those of its 64-row tile before it.  EDGE also multiplies P and
-// dS as the sum of two bf16 terms, the rounded value and the rounded remainder (16 bits together), because these
-// sequences ran on the vector kernels, which hold P and dS in fp32.  Relative error against 64 bits at s 1733, 16 heads
-// of 128: o 1.608e-3, dq 1.768e-3 -> 1.770e-3, dk 1.765e-3, dv 1.659e-3, all of it the rounding of the results to bf16
-// (2.8e-3 with one term).  The second term costs a third of the MFMAs.  Vector kernels -> this form,
-// us: s 1733, 16 heads of 128: forward 2235 -> 75, backward 20450 -> 106; s 3000, 32 heads of 64 over 8: 5406 -> 116 and
-// 72760 -> 267; s 100, 16 heads of 128: 35 -> 19 and 147 -> 20.
+// behind it and no other; in the other form it also reaches those of its 64-row tile before it.  EDGE also
+// multiplies P and dS as the sum of three bf16 terms that is the fp32 value itself (weights_of), because these sequences
+// ran on the vector kernels, which hold P and dS in fp32.  Relative error against 64 bits at s 1733, 16 heads of 128, vector
+// kernels and this form alike: o 1.608e-3, dq, dk, dv 1.661e-3, 1.660e-3, 1.659e-3, all of it the rounding of the results.
+// Two terms give the same there, but 1.5 to 15 % where probabilities that agree in 14 bits cancel (0.1 % with three).
+// MFMAs of a tile with one, two and three terms: forward 2 : 3 : 4, backward 7 : 10 : 13.  Vector kernels -> two terms -> this
+// form, us: s 1733, 16 heads of 128: forward 2235 -> 72 -> 73, backward 20450 -> 99 -> 116; s 3000, 32 heads of 64 over 8: 5406 -> 115 -> 126 and
+// 72760 -> 283 -> 315; s 100, 16 heads of 128: 35 -> 18 and 147 -> 18.
 #include "attention_rows.h"
 #include "mfma_common.h"
 
@@ -158,12 +159,45 @@ __device__ __forceinline__ bf16x8 pack_bf16x8(const f32x16& a, int first) {
   return r;
 }
 
-// What that rounding left over, as a second fragment.
-__device__ __forceinline__ bf16x8 pack_remainder(const f32x16& a, int first, const bf16x8& rounded) {
-  bf16x8 r;
+// Eight probabilities (or dS) as an operand: rounded to bf16 once, or (FULL) as the sum of three bf16 terms that is the
+// fp32 value itself: its upper 16 bits, those of what is left, and the rest, which has no more than eight significant bits.
+// Both differences are exact.
+template <bool FULL>
+struct Weights {
+  bf16x8 term[FULL ? 3 : 1];
+};
+// Pair p of the eight values: upper halves of two floats side by side in one register of each term.
+__device__ __forceinline__ void split_pair(Weights<true>& w, const f32x16& a, int first, int p) {
+  float x0 = a[first + 2 * p], x1 = a[first + 2 * p + 1];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = (bf16)(a[first + e] - (float)rounded[e]);
-  return r;
+  for (int k = 0; k < 3; ++k) {
+    const unsigned u0 = __builtin_bit_cast(unsigned, x0), u1 = __builtin_bit_cast(unsigned, x1);
+    u32x4 v = __builtin_bit_cast(u32x4, w.term[k]);
+    v[p] = __builtin_amdgcn_perm(u1, u0, 0x07060302);
+    w.term[k] = __builtin_bit_cast(bf16x8, v);
+    x0 -= __builtin_bit_cast(float, u0 & 0xffff0000u);
+    x1 -= __builtin_bit_cast(float, u1 & 0xffff0000u);
+  }
+}
+template <bool FULL>
+__device__ __forceinline__ Weights<FULL> weights_of(const f32x16& a, int first) {
+  Weights<FULL> w;
+  if constexpr (FULL) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) split_pair(w, a, first, p);
+  } else {
+    w.term[0] = pack_bf16x8(a, first);
+  }
+  return w;
+}
+// c += m^T w, the small terms first.
+template <bool FULL>
+__device__ __forceinline__ f32x16 multiply(const bf16x8& m, const Weights<FULL>& w, f32x16 c) {
+  if constexpr (FULL) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m, w.term[2], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m, w.term[1], c, 0, 0, 0);
+  }
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(m, w.term[0], c, 0, 0, 0);
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -241,7 +275,7 @@ __device__ __forceinline__ bf16x8 read_k_fragment(unsigned kb, int j, int kk) {
 // running reference maximum and row sum updated, output accumulators rescaled when the reference moved.
 template <int DH, bool EDGE, bool MASK>
 __device__ __forceinline__ void fwd_softmax(f32x16 (&sacc)[2], f32x16 (&oacc)[DH / 32], float& m_run, float& l_run,
-                                            bf16x8 (&pf)[2][2], bf16x8 (&pr)[2][2], int key0, int q, int lane,
+                                            Weights<EDGE> (&pf)[EDGE ? 2 : 4], int key0, int q, int lane,
                                             float c) {
   constexpr int DT = DH / 32;
   const int half = lane >> 5;
@@ -291,14 +325,7 @@ __device__ __forceinline__ void fwd_softmax(f32x16 (&sacc)[2], f32x16 (&oacc)[DH
       for (int e = 0; e < 16; ++e) oacc[d][e] *= alpha;
   }
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    pf[j][0] = pack_bf16x8(sacc[j], 0);
-    pf[j][1] = pack_bf16x8(sacc[j], 8);
-    if constexpr (EDGE) {
-      pr[j][0] = pack_remainder(sacc[j], 0, pf[j][0]);
-      pr[j][1] = pack_remainder(sacc[j], 8, pf[j][1]);
-    }
-  }
+  for (int js = 0; js < (EDGE ? 1 : 4); ++js) pf[js] = weights_of<EDGE>(sacc[js >> 1], 8 * (js & 1));
 }
 
 // A matrix slot: O^T += V^T P^T of the tile whose softmax just ended (PV), then the raw scores of the next tile
@@ -315,8 +342,8 @@ constexpr int q_in_regs() {
 template <int DH, bool EDGE, bool PV, bool SC>
 __device__ __forceinline__ void fwd_matrix_slot(const char* vtile, const char* ktile, unsigned q_addr,
                                                 const bf16x8 (&qreg)[q_in_regs<DH>() > 0 ? q_in_regs<DH>() : 1],
-                                                const FragmentOffsets<DH>& fo, const bf16x8 (&pf)[2][2],
-                                                const bf16x8 (&pr)[2][2], f32x16 (&oacc)[DH / 32], f32x16 (&sacc)[2]) {
+                                                const FragmentOffsets<DH>& fo, Weights<EDGE> (&pf)[EDGE ? 2 : 4],
+                                                f32x16 (&oacc)[DH / 32], f32x16 (&sacc)[2]) {
   constexpr int KS = DH / 16, DT = DH / 32, QR = q_in_regs<DH>();
   constexpr int NPV = PV ? 4 * DT : 0;  // P V MFMAs, one V fragment each
   constexpr int NSC = SC ? 2 * KS : 0;  // score MFMAs; step kk reads K(0, kk), K(1, kk) and, from QR on, Q(kk) first
@@ -356,19 +383,38 @@ __device__ __forceinline__ void fwd_matrix_slot(const char* vtile, const char* k
       ring_s[f % RS] = read_k_fragment<DH>(kb, w - 1, kk);
   };
   constexpr int PRE_S = SC ? (PV ? 3 : Idx::want(0)) : 0;  // requested during the last P V MFMAs
-  static_for<0, (AV < NPV ? AV : NPV)>(fetch_v);
-  if constexpr (!PV) static_for<0, PRE_S>(fetch_s);
-  __builtin_amdgcn_sched_barrier(0);
-  static_for<0, NPV>([&](auto mc) {
-    constexpr int m = decltype(mc)::value;
-    if constexpr (m + AV < NPV) fetch_v(std::integral_constant<int, m + AV>());
-    if constexpr (m + AV >= NPV && m + AV < NPV + PRE_S) fetch_s(std::integral_constant<int, m + AV - NPV>());
-    constexpr int js = m / DT, d = m % DT;
-    oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring_v[m % RV], pf[js >> 1][js & 1], oacc[d], 0, 0, 0);
-    if constexpr (EDGE)
-      oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring_v[m % RV], pr[js >> 1][js & 1], oacc[d], 0, 0, 0);
+  if constexpr (EDGE && PV) {
+    // P in three terms.  It stays in the score registers; the terms of 16 keys at a time are made between the MFMAs of the
+    // 16 before (the first by the softmax): all of them would need 48 registers.  Term by term over the output blocks, so
+    // that consecutive MFMAs still never wait for each other's accumulator.
+    constexpr int NT = 3 * DT, HELD = RV / DT;  // MFMAs and V fragments of 16 keys; how many of those fit the ring
+    static_assert(RV % DT == 0, "the ring holds whole sets of fragments");
+    static_for<0, RV>(fetch_v);
     __builtin_amdgcn_sched_barrier(0);
-  });
+    static_for<0, 4 * NT>([&](auto mc) {
+      constexpr int m = decltype(mc)::value, js = m / NT, i = m % NT, term = 2 - i / DT, d = i % DT, f = js * DT + d;
+      oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring_v[f % RV], pf[js & 1].term[term], oacc[d], 0, 0, 0);
+      if constexpr (term == 0 && f + HELD * DT < NPV) fetch_v(std::integral_constant<int, f + HELD * DT>());
+      if constexpr (js < 3)
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          if (p * NT / 4 == i) split_pair(pf[(js + 1) & 1], sacc[(js + 1) >> 1], 8 * ((js + 1) & 1), p);
+      if constexpr (4 * NT - m <= PRE_S) fetch_s(std::integral_constant<int, PRE_S - (4 * NT - m)>());
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  } else {
+    static_for<0, (AV < NPV ? AV : NPV)>(fetch_v);
+    if constexpr (!PV) static_for<0, PRE_S>(fetch_s);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NPV>([&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      if constexpr (m + AV < NPV) fetch_v(std::integral_constant<int, m + AV>());
+      if constexpr (m + AV >= NPV && m + AV < NPV + PRE_S) fetch_s(std::integral_constant<int, m + AV - NPV>());
+      constexpr int js = m / DT, d = m % DT;
+      oacc[d] = multiply<EDGE>(ring_v[m % RV], pf[js], oacc[d]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
   static_for<0, NSC>([&](auto mc) {
     constexpr int m = decltype(mc)::value;
     constexpr int lo = m == 0 ? PRE_S : Idx::want(m - 1), hi = Idx::want(m);
@@ -496,7 +542,7 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
   // this wave's Q rows: tile wrow / 2 of the Q area, rows 32 (wrow % 2) ..
   const unsigned q_addr = lds_address_of(smem + (wrow >> 1) * TBYTES) + fo.k + (wrow & 1) * 32 * DH * 2;
   f32x16 oacc[DT], sacc[2];
-  bf16x8 pf[2][2], pr[2][2];  // P and (EDGE) the remainders of its rounding
+  Weights<EDGE> pf[EDGE ? 2 : 4];  // P of 16 keys each
   float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
   for (int d = 0; d < DT; ++d)
@@ -519,12 +565,12 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
     const char* st = my_stages + (j % NST) * STAGE;
     __builtin_amdgcn_s_setprio(1);
     if constexpr (decltype(pv)::value || decltype(sc)::value)
-      fwd_matrix_slot<DH, EDGE, decltype(pv)::value, decltype(sc)::value>(st, st + TBYTES, q_addr, qreg, fo, pf, pr,
-                                                                          oacc, sacc);
+      fwd_matrix_slot<DH, EDGE, decltype(pv)::value, decltype(sc)::value>(st, st + TBYTES, q_addr, qreg, fo, pf, oacc,
+                                                                          sacc);
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
     if constexpr (decltype(sc)::value)
-      fwd_softmax<DH, EDGE, decltype(mask)::value>(sacc, oacc, m_run, l_run, pf, pr, (G * j + tg) * kKeysPerTile,
+      fwd_softmax<DH, EDGE, decltype(mask)::value>(sacc, oacc, m_run, l_run, pf, (G * j + tg) * kKeysPerTile,
                                                    qw0 + col, lane, c);
     if (last_barrier) __syncthreads();
   };
@@ -738,7 +784,7 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
         }
       }
       if constexpr (EDGE) {
-        // One product after the other, so that the two-term operands need no more registers than the other form:
+        // One product after the other, so that the three-term operands need no more registers than the other form:
         // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.  The lane id is hidden again before each, so that no LDS address is
         // carried from one to the next; with them in registers the fragments of K and V were spilled, and every reload
         // waited for the tile loads under way.
@@ -761,13 +807,10 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
         auto accumulate = [&](f32x16 (&to)[DT], const f32x16& w, const char* tile) __attribute__((always_inline)) {
 #pragma unroll
           for (int st = 0; st < 2; ++st) {
-            const bf16x8 hi = pack_bf16x8(w, 8 * st), lo = pack_remainder(w, 8 * st, hi);
+            const Weights<true> terms = weights_of<true>(w, 8 * st);
 #pragma unroll
-            for (int d = 0; d < DT; ++d) {
-              bf16x8 tr = read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane_l);
-              to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, lo, to[d], 0, 0, 0);
-              to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, hi, to[d], 0, 0, 0);
-            }
+            for (int d = 0; d < DT; ++d)
+              to[d] = multiply<true>(read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane_l), terms, to[d]);
             __builtin_amdgcn_sched_barrier(0);
           }
         };
@@ -1030,7 +1073,7 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
         }
       }
       if constexpr (EDGE) {
-        // One product after the other, so that the two-term operands need no more registers than the other form:
+        // One product after the other, so that the three-term operands need no more registers than the other form:
         // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.  The lane id is hidden again before each, so that no LDS address is
         // carried from one to the next; with them in registers the fragments of K and V were spilled, and every reload
         // waited for the tile loads under way.
@@ -1053,13 +1096,10 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
         auto accumulate = [&](f32x16 (&to)[DT], const f32x16& w, const char* tile) __attribute__((always_inline)) {
 #pragma unroll
           for (int st = 0; st < 2; ++st) {
-            const bf16x8 hi = pack_bf16x8(w, 8 * st), lo = pack_remainder(w, 8 * st, hi);
+            const Weights<true> terms = weights_of<true>(w, 8 * st);
 #pragma unroll
-            for (int d = 0; d < DT; ++d) {
-              bf16x8 tr = read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane_l);
-              to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, lo, to[d], 0, 0, 0);
-              to[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr, hi, to[d], 0, 0, 0);
-            }
+            for (int d = 0; d < DT; ++d)
+              to[d] = multiply<true>(read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane_l), terms, to[d]);
             __builtin_amdgcn_sched_barrier(0);
           }
         };
@@ -1279,7 +1319,7 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
           pacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, dof[t][kk], pacc[t], 0, 0, 0);
         }
       }
-      bf16x8 dsf[QT][2], dsr[QT][2];
+      Weights<EDGE> dsf[QT][2];
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
         int q = qw0 + 32 * t + col;
@@ -1293,12 +1333,8 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) pacc[t][e] = sacc[t][e] * (pacc[t][e] - delta_q[t]);
-        dsf[t][0] = pack_bf16x8(pacc[t], 0);
-        dsf[t][1] = pack_bf16x8(pacc[t], 8);
-        if constexpr (EDGE) {
-          dsr[t][0] = pack_remainder(pacc[t], 0, dsf[t][0]);
-          dsr[t][1] = pack_remainder(pacc[t], 8, dsf[t][1]);
-        }
+        dsf[t][0] = weights_of<EDGE>(pacc[t], 0);
+        dsf[t][1] = weights_of<EDGE>(pacc[t], 8);
       }
 #pragma unroll
       for (int d = 0; d < DT; ++d)
@@ -1306,11 +1342,7 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
         for (int st = 0; st < 2; ++st) {
           bf16x8 ktr = read_tr_fragment<DH>(ktile, 32 * j + 16 * st, 32 * d, lane);
 #pragma unroll
-          for (int t = 0; t < QT; ++t) {
-            if constexpr (EDGE)
-              dq[t][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr, dsr[t][st], dq[t][d], 0, 0, 0);
-            dq[t][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr, dsf[t][st], dq[t][d], 0, 0, 0);
-          }
+          for (int t = 0; t < QT; ++t) dq[t][d] = multiply<EDGE>(ktr, dsf[t][st], dq[t][d]);
         }
     }
     wait_tile_loads();
@@ -1429,18 +1461,13 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) pacc[e] = sacc[e] * (pacc[e] - delta_q);
-      bf16x8 dsf[2] = {pack_bf16x8(pacc, 0), pack_bf16x8(pacc, 8)}, dsr[2];
-      if constexpr (EDGE) {
-        dsr[0] = pack_remainder(pacc, 0, dsf[0]);
-        dsr[1] = pack_remainder(pacc, 8, dsf[1]);
-      }
+      Weights<EDGE> dsf[2] = {weights_of<EDGE>(pacc, 0), weights_of<EDGE>(pacc, 8)};
 #pragma unroll
       for (int d = 0; d < DT; ++d)
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
           bf16x8 ktr = read_tr_fragment<DH>(ktile, 32 * j + 16 * st, 32 * d, lane);
-          if constexpr (EDGE) dq[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr, dsr[st], dq[d], 0, 0, 0);
-          dq[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktr, dsf[st], dq[d], 0, 0, 0);
+          dq[d] = multiply<EDGE>(ktr, dsf[st], dq[d]);
         }
     }
     wait_tile_loads();
@@ -1635,8 +1662,8 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
   // Few key/value heads: one block per query head and a per-group sum afterwards (needs the [s, 2h] workspace),
   // once the direct launch would not fill the chip's 512 block slots.  Those partials are rounded to bf16; the EDGE
   // form, whose sums over a group have always been fp32, keeps fp32 partials of two (or the group's next divisor) query
-  // heads each, which fit the same workspace (s 3000, 32 heads of 64 over 8: 481 -> 305 us, then 267 with the eight-wave
-  // blocks; s 1000, 8 heads of 128 over 1: 377 -> 108).
+  // heads each, which fit the same workspace (without / with: s 3000, 32 heads of 64 over 8 455 / 313 us; s 1000, 8 heads of
+  // 128 over 1 449 / 123; s 1500, 64 heads of 64 over 8 444 / 169).
   const int blocks = ceil_div(s, 128);
   bool split = group > 1 && partials && (int64_t)n_kv_heads * blocks < 512;
   int hpb_split = 1;
@@ -1647,8 +1674,8 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
   const int n_parts = split ? group / hpb_split : 1;
   // At most one block per CU: the eight-wave kernel, which halves a wave's chain of tiles.  EDGE takes it up to three: the chain
   // is the longer part there, and one launch with the dQ blocks, of the same form, fills the chip beside it
-  // (256 / 512 / 768 / 1024 blocks of dK/dV at most, us: s 1300, 32 heads of 128 over 4 207 / 152 / 150 / 149; s 3000, 32
-  // heads of 128 over 8 495 / 425 / 424 / 423; s 2500, 40 heads of 64 226 / 214 / 214 / 243).
+  // (256 / 512 / 768 / 1024 blocks of dK/dV at most, us: s 3000, 32 heads of 64 over 8 365 / 314 / 313 / 314; s 3000, 32 heads of
+  // 128 over 8 592 / 501 / 501 / 501; s 2500, 40 heads of 64 251 / 249 / 249 / 272; s 2100, 60 heads of 64 272 / 272 / 273 / 302).
   constexpr int smem_kv8 = 4 * (2 * tile_bytes<DH>() + 512) + (DH == 128 ? 24576 : 0);
   bool eight = (int64_t)n_kv_heads * n_parts * blocks <= (EDGE ? 768 : 256);
   const bool dq_eight = EDGE ? eight : (int64_t)n_heads * blocks <= 256;  // one block per CU at most: the eight-wave kernel

@@ -304,6 +304,42 @@ def test_attention_ragged_bf16(gpu_device, s, h, a, akv):
         check_parity(mine, ref.cpu().numpy(), 2e-2, name)
 
 
+# P and dS enter the products with all 24 bits.  Rows of q come in pairs (2 i, 2 i + 1) and keys in pairs (2 j, 2 j + 1) whose
+# scores differ by 2^-11 / sqrt(dh) in the odd rows only, and everything P or dS is multiplied with has alternating
+# signs: results are differences of probabilities that agree in 14 bits.  With 16 bits they are 1.5 to 16 % off, with 24
+# below 0.1 %; the rounding of a result to bf16 is 2^-9, lse and score sums add less than that again.
+@pytest.mark.parametrize("generic", [0, 1])
+@pytest.mark.parametrize("a", [2, 400])
+@pytest.mark.parametrize("dh", [64, 128])
+def test_attention_ragged_bf16_keeps_probabilities_in_fp32(gpu_device, dh, a, generic):
+    s, h = 200, a * dh
+    i = torch.arange(s, dtype=torch.float64, device=gpu_device)
+    odd, sign, pair = i % 2, 1 - 2 * (i % 2), i // 2
+    q, k, v, g = (torch.zeros(s, dh, dtype=torch.float64, device=gpu_device) for _ in range(4))
+    q[:, 0], q[:, 2], q[:, 5] = odd, sign, 1
+    k[:, 0], k[:, 1], k[:, 5] = sign * 2.0 ** -11, sign, (-0.37 * (pair % 13)).bfloat16().double()
+    v[:, 3], v[:, 4] = 1, sign
+    g[:, 0], g[:, 3] = sign, 1  # dP = 1
+    lse_in = (0.3 + 0.013 * pair).float()  # the same for both rows of a pair
+    sc = (q @ k.T.contiguous() / dh ** 0.5).masked_fill(torch.ones(s, s, dtype=torch.bool, device=gpu_device).triu(1), -np.inf)
+    p, pb = torch.softmax(sc, 1), torch.exp(sc - lse_in.double()[:, None])
+    every = lambda x: x.bfloat16().repeat(1, a).contiguous()
+    qkv = torch.cat([every(q), every(k), every(v)], 1).contiguous()
+    o, lse = torch.empty(s, h, dtype=torch.bfloat16, device=gpu_device), torch.empty(a, s, device=gpu_device)
+    po.po_op_attention_forward(po.PO_BF16, qkv, o, lse, s, h, a, generic)
+    dqkv, delta = torch.empty_like(qkv), torch.empty(a, s, device=gpu_device)
+    po.po_op_attention_backward(po.PO_BF16, qkv, torch.zeros_like(o), lse_in.repeat(a, 1).contiguous(), every(g), dqkv,
+                                delta, s, h, a, generic)
+    def check(got, column, want, rows):  # every head holds the same
+        got = got.double().view(s, a, dh)[rows, :, column]
+        assert ((got - want[rows, None]) / want[rows, None]).abs().max() < 2.0 ** -7
+    odd_rows, even_rows = slice(1, None, 2), slice(0, None, 2)
+    check(o, 4, p @ sign, odd_rows)
+    check(dqkv[:, :h], 1, pb @ sign / dh ** 0.5, odd_rows)
+    check(dqkv[:, h:2 * h], 2, pb.T.contiguous() @ sign / dh ** 0.5, even_rows)
+    check(dqkv[:, 2 * h:], 0, pb.T.contiguous() @ sign, even_rows)
+
+
 def _nonfinite_inputs(gpu_device, dtype, s, dh, a, akv, where, value, row):
     _, tdt, _ = DT[dtype]
     g = torch.Generator(device=gpu_device)
