@@ -39,6 +39,8 @@ __device__ __forceinline__ f32x16 zero16() {
   for (int e = 0; e < 16; ++e) z[e] = 0.f;
   return z;
 }
+// exp(x scale).  Two multiplications: with scale log2(e) as one constant its rounding is the same in every term of a row.
+__device__ __forceinline__ float exp_scaled(float x, float scale) { return __builtin_amdgcn_exp2f(x * scale * kLog2e); }
 // Row `row` of a matrix: this half-wave's 16-byte pieces.
 template <int DH>
 __device__ __forceinline__ void load_pieces(f32x4 (&f)[DH / 8], const float* row, int half) {
@@ -92,7 +94,6 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
   const int ld = h + 2 * hkv, last = s - 1;
   const float* kbase = qkv + h + (head / group) * DH;
   const float* vbase = kbase + hkv;
-  const float c = scale * kLog2e;
   f32x4 qf[DH / 8];
   load_pieces<DH>(qf, qkv + (size_t)min(q, last) * ld + head * DH, half);
   f32x16 acc[DT];
@@ -113,10 +114,10 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, p[e]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    float alpha = __builtin_amdgcn_exp2f((m_run - mx) * c), sum = 0.f;
+    float alpha = exp_scaled(m_run - mx, scale), sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      p[e] = __builtin_amdgcn_exp2f((p[e] - mx) * c);
+      p[e] = exp_scaled(p[e] - mx, scale);
       sum += p[e];
     }
     m_run = mx;
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
   for (int w = 1; w < 4; ++w) m = fmaxf(m, stat[w * 64 + lane]);  // wave 0 has seen key 0: finite
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    f[w] = __builtin_amdgcn_exp2f((stat[w * 64 + lane] - m) * c);
+    f[w] = exp_scaled(stat[w * 64 + lane] - m, scale);
     l += stat[(4 + w) * 64 + lane] * f[w];
   }
   if (q > last || (redo >> (lane & 31) & 1)) return;
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
     }
     *reinterpret_cast<f32x4*>(o + (size_t)q * h + head * DH + 32 * d + 8 * wave + 4 * half) = v;
   }
-  if (wave == 0 && half == 0) lse[(size_t)head * s + q] = m * scale + __logf(l);
+  if (wave == 0 && half == 0) lse[(size_t)head * s + q] = fmaf(m, scale, __logf(l));
 }
 
 template <int DH>
@@ -173,11 +174,10 @@ __global__ __launch_bounds__(256, DH > 64 ? 1 : 2) void attn_f32_bwd_dq_kernel(
   const int ld = h + 2 * hkv, last = s - 1, qc = min(q, last);
   const float* kbase = qkv + h + (head / group) * DH;
   const float* vbase = kbase + hkv;
-  const float c = scale * kLog2e;
   f32x4 qf[DH / 8], dof[DH / 8];
   load_pieces<DH>(qf, qkv + (size_t)qc * ld + head * DH, half);
   load_pieces<DH>(dof, d_o + (size_t)qc * h + head * DH, half);
-  const float lse_q = lse[(size_t)head * s + qc] * kLog2e, delta_q = delta[(size_t)head * s + qc];
+  const float lse_q = lse[(size_t)head * s + qc], delta_q = delta[(size_t)head * s + qc];
   f32x16 dq[DT];
 #pragma unroll
   for (int d = 0; d < DT; ++d) dq[d] = zero16();
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256, DH > 64 ? 1 : 2) void attn_f32_bwd_dq_kernel(
     f32x16 ds = dot_tile<DH>(kf, dof);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      float pe = __builtin_amdgcn_exp2f(p[e] * c - lse_q);
+      float pe = __builtin_amdgcn_exp2f(fmaf(p[e], scale, -lse_q) * kLog2e);
       if (t == n_tiles - 1 && 32 * t + 8 * (e >> 2) + 4 * half + (e & 3) > q) pe = 0.f;
       ds[e] = pe * (ds[e] - delta_q);
     }
@@ -229,7 +229,6 @@ __global__ __launch_bounds__(256, 1) void attn_f32_bwd_dkv_kernel(
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   const int kv_head = blockIdx.x, first = blockIdx.y, key = first * 32 + (lane & 31);
   const int ld = h + 2 * hkv, last = s - 1;
-  const float c = scale * kLog2e;
   f32x4 kf[DH / 8], vf[DH / 8];
   const float* krow = qkv + (size_t)min(key, last) * ld + h + kv_head * DH;
   load_pieces<DH>(kf, krow, half);
@@ -253,7 +252,7 @@ __global__ __launch_bounds__(256, 1) void attn_f32_bwd_dkv_kernel(
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int qc = min(q0 + 8 * (e >> 2) + 4 * half + (e & 3), last);
-      p[e] = __builtin_amdgcn_exp2f(p[e] * c - lse_h[qc] * kLog2e);
+      p[e] = __builtin_amdgcn_exp2f(fmaf(p[e], scale, -lse_h[qc]) * kLog2e);
       ds[e] = p[e] * (ds[e] - delta_h[qc]);
     }
     if (q0 == first * 32 || q0 + 31 > last) {  // the diagonal, or rows past the end

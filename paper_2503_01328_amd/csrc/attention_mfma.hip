@@ -633,7 +633,8 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
       for (int r = 0; r < 4; ++r) v[r] = (bf16)(oacc[d][4 * b + r] * inv);
       *reinterpret_cast<bf16x4*>(o + (size_t)q * h + head * DH + 32 * d + 8 * b + 4 * half) = v;
     }
-  if (half == 0) lse[(size_t)head * s + q] = m_run * scale + __logf(l);
+  if (half == 0)  // EDGE: the reference as the exponents took it, rounded to fp32
+    lse[(size_t)head * s + q] = EDGE ? fmaf(m_run * c, 0.6931471805599453f, __logf(l)) : m_run * scale + __logf(l);
 }
 
 // ==================================================================================
