@@ -767,7 +767,7 @@ bool gemm_mfma_edge_supported(int ta, int tb, int M, int N, int K, const void* A
       lda < (ta ? M : K) || ldb < (tb ? K : N))
     return false;
   if (ta ? (tb || !ep.acc_f32 || M % 8 != 0) : (ep.acc_f32 != nullptr || K % kBK != 0)) return false;  // the forms below
-  if (!ta && !tb && ep.gelu_u) return false;
+  if (ep.gelu_u && (!tb || ep.bias || ep.residual)) return false;  // the GeLU-backward epilogue adds neither
   if (tb && ep.gelu_out && !ep.gelu_u) return false;
   const uintptr_t al = (uintptr_t)A | (uintptr_t)B | (uintptr_t)ep.out | (uintptr_t)ep.gelu_out | (uintptr_t)ep.gelu_u |
                        (uintptr_t)ep.residual | (uintptr_t)ep.acc_f32 | (uintptr_t)ep.bias;

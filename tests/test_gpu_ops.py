@@ -191,6 +191,28 @@ def test_gemm_small_edges(gpu_device, dtype, ta, tb, M, N, K):
     assert rel(acc, ref + 1.0) < sums + 2.0 ** -23
 
 
+# a GeLU backward is multiplied onto the sum of product, bias and residual: one row, few tiles, and results whose large tiles
+# end inside, whose kernel has no such epilogue and leaves these calls to the small tiles
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1, 64, 64), (200, 200, 128), (905, 4096, 1088), (1733, 8200, 128)])
+@pytest.mark.parametrize("with_bias,with_residual", [(1, 0), (0, 1), (1, 1)])
+def test_gemm_gelu_backward_of_a_sum(gpu_device, tb, M, N, K, with_bias, with_residual):
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(M + N + K)
+    rand = lambda *size: torch.randn(*size, generator=g, device=gpu_device).bfloat16()
+    A, B = rand(M, K), rand(*((N, K) if tb else (K, N)))
+    bias, res, u = 8 * rand(N), 8 * rand(M, N), rand(M, N)
+    ud = u.double().requires_grad_()
+    torch.nn.functional.gelu(ud, approximate="tanh").sum().backward()
+    ref = A.double() @ (B.double().t().contiguous() if tb else B.double())
+    ref = (ref + with_bias * bias.double() + with_residual * res.double()) * ud.grad
+    out, gel = torch.empty_like(u), torch.empty_like(u)
+    po.po_op_gemm(po.PO_BF16, 0, tb, M, N, K, A, K, B, B.shape[1], out=out, gelu_out=gel, gelu_u=u,
+                  bias=bias if with_bias else None, residual=res if with_residual else None)
+    # the rounding of the result to bf16 (2^-8 of it at most); the fp32 sums and the slope are far below
+    assert float((out.double() - ref).norm() / ref.norm()) < 2.0 ** -8
+
+
 def test_gemm_grouped_equals_single_launches_and_the_oracle(gpu_device):
     """Four weight-gradient products of different shapes in one launch: each accumulator equals, bit for bit, what
     the single launch of that product leaves, and the fp64 product within the bf16 tolerance.  Tile counts
