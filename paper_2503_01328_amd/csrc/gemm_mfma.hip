@@ -771,9 +771,11 @@ bool gemm_mfma_edge_supported(int ta, int tb, int M, int N, int K, const void* A
   if (tb && ep.gelu_out && !ep.gelu_u) return false;
   const uintptr_t al = (uintptr_t)A | (uintptr_t)B | (uintptr_t)ep.out | (uintptr_t)ep.gelu_out | (uintptr_t)ep.gelu_u |
                        (uintptr_t)ep.residual | (uintptr_t)ep.acc_f32 | (uintptr_t)ep.bias;
-  // offsets and sizes of the buffer descriptors fit 31 bits: 256 rows of a k-contiguous operand, all of a k-major one
-  const int64_t a_bytes = 2 * (ta ? (int64_t)K * lda : (int64_t)256 * lda + K);
-  const int64_t b_bytes = 2 * (tb ? (int64_t)256 * ldb + K : (int64_t)K * ldb);
+  // offsets and sizes of the buffer descriptors fit 31 bits: 256 rows of a k-contiguous operand, all of a k-major one and at
+  // least the rows of a whole slice, whose offsets a lane forms also where K ends before
+  const int64_t k_rows = K > kBK ? K : kBK;
+  const int64_t a_bytes = 2 * (ta ? k_rows * lda : (int64_t)256 * lda + K);
+  const int64_t b_bytes = 2 * (tb ? (int64_t)256 * ldb + K : k_rows * ldb);
   const int64_t limit = (int64_t)1 << 31;
   return N % 8 == 0 && lda % 8 == 0 && ldb % 8 == 0 && ep.ldc % 8 == 0 && al % 16 == 0 && a_bytes < limit &&
          b_bytes < limit;

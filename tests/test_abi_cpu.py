@@ -1,6 +1,7 @@
 """Host-only checks of the C ABI: the library loads, exports every declared
 symbol, and its pure-host entry points (schedule, parameter layout, Eq. 1, config
 validation) agree with the independent oracle models.  No GPU work is issued."""
+import ctypes
 import os
 import re
 
@@ -225,6 +226,30 @@ def test_gemm_tile_choice_fills_the_chip():
             bm, bn = tile(M, N)
             assert (bm, bn) in ((0, 0), (128, 128), (256, 192), (256, 256))
             assert bm == 0 or (M % bm == 0 and N % bn == 0)
+
+
+class _Epilogue(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("bias", "residual", "out", "gelu_out", "gelu_u", "acc_f32")] + \
+               [("ldc", ctypes.c_int)]
+
+
+def test_gemm_edge_kernel_leaves_offsets_beyond_31_bits_to_others():
+    """Host logic: a lane of the large-tile kernels for any size forms 32-bit byte offsets over a slice of 64 k, also where
+    K ends before; the leading dimension of a k-major operand has to leave them room."""
+    f = po.lib["_ZN2po24gemm_mfma_edge_supportedEiiiiiPKviS1_iRKNS_8EpilogueE"]
+    f.restype = ctypes.c_bool
+    f.argtypes = [ctypes.c_int] * 5 + [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_int,
+                                       ctypes.POINTER(_Epilogue)]
+    at = 1 << 20  # an aligned address; nothing is read
+    weight = lambda K, lda, ldb: f(1, 0, 256, 256, K, at, lda, at, ldb, _Epilogue(acc_f32=at, ldc=256))
+    forward = lambda K, lda, ldb: f(0, 0, 256, 256, K, at, lda, at, ldb, _Epilogue(out=at, ldc=256))
+    most = (1 << 24) - 8  # 64 rows of 2 * most bytes stay below 2^31
+    for K in (1, 8, 64):
+        assert weight(K, most, 256) and weight(K, 256, most)
+        for ld in (1 << 24, 1 << 25, (1 << 25) + 8, 1 << 26, (1 << 30) + 8):
+            assert not weight(K, ld, 256) and not weight(K, 256, ld)
+    assert forward(64, 64, most) and not forward(64, 64, 1 << 24) and not forward(64, 1 << 23, 256)
+    assert weight(4096, 1 << 17, 256) and not weight(4096, 1 << 18, 256)
 
 
 def test_hot_kernels_keep_their_accumulators_in_registers():
