@@ -297,18 +297,12 @@ bool attention_f32_supported(const void* qkv, const void* o, int s, int h, int n
   return (dh == 32 || dh == 64 || dh == 96 || dh == 128) && ((uintptr_t)qkv | (uintptr_t)o) % 16 == 0;
 }
 
-template <typename K>
-static bool allow_lds(K kern, int smem) {
-  PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-  return true;
-}
-
 template <int DH>
 static bool forward_f32(const float* qkv, float* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                         hipStream_t stream) {
   constexpr int smem = (4 * DH * 32 + 8 * 64 + 4) * 4;
-  static const bool configured = allow_lds(attn_f32_fwd_kernel<DH>, smem);
-  if (!configured) return false;
+  static LdsLimit lds;
+  if (!lds.allow(attn_f32_fwd_kernel<DH>, smem)) return false;
   attn_f32_fwd_kernel<DH><<<dim3(n_heads, ceil_div(s, 32)), 256, smem, stream>>>(
       qkv, o, lse, s, h, n_kv_heads * DH, n_heads / n_kv_heads, 1.0f / sqrtf((float)DH));
   return launch_ok("attn_f32_fwd_kernel");
@@ -318,9 +312,8 @@ template <int DH>
 static bool backward_f32(const float* qkv, const float* lse, const float* delta, const float* d_o, float* dqkv, int s,
                          int h, int n_heads, int n_kv_heads, hipStream_t stream) {
   constexpr int smem_part = 4 * DH * 32 * 4, smem_q = smem_part + 16, smem_kv = 2 * smem_part;
-  static const bool configured =
-      allow_lds(attn_f32_bwd_dq_kernel<DH>, smem_q) && allow_lds(attn_f32_bwd_dkv_kernel<DH>, smem_kv);
-  if (!configured) return false;
+  static LdsLimit lds_q, lds_kv;
+  if (!lds_q.allow(attn_f32_bwd_dq_kernel<DH>, smem_q) || !lds_kv.allow(attn_f32_bwd_dkv_kernel<DH>, smem_kv)) return false;
   const int hkv = n_kv_heads * DH, group = n_heads / n_kv_heads;
   const float scale = 1.0f / sqrtf((float)DH);
   attn_f32_bwd_dkv_kernel<DH><<<dim3(n_kv_heads, ceil_div(s, 32)), 256, smem_kv, stream>>>(qkv, d_o, lse, delta, dqkv, s,

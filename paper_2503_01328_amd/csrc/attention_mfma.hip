@@ -1616,14 +1616,8 @@ static bool launch_fwd(const bf16* qkv, bf16* o, float* lse, int s, int h, int n
   const bool big = (EDGE || s % 256 == 0) && (int64_t)n_heads * ceil_div(s, 256) >= 256;
   auto k1 = attn_fwd_roles_mfma_kernel<DH, 1, EDGE>;
   auto k2 = attn_fwd_roles_mfma_kernel<DH, 2, EDGE>;
-  static bool configured = false;
-  if (!configured) {
-    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(k1), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  smem));
-    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(k2), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  smem));
-    configured = true;
-  }
+  static LdsLimit lds1, lds2;
+  if (big ? !lds1.allow(k1, smem) : !lds2.allow(k2, smem)) return false;
   const float scale = 1.0f / sqrtf((float)DH);
   if (big)
     k1<<<dim3(n_heads, ceil_div(s, 256)), 576, smem, stream>>>(qkv, o, lse, s, h, n_kv_heads * DH,
@@ -1691,61 +1685,41 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
     if (eight) {
       constexpr int smem_f = smem_kv8 > smem_split ? smem_kv8 : smem_split;
       auto kf = attn_bwd_fused_mfma_kernel<DH, true, EDGE>;
-      static bool fused8_configured = false;
-      if (!fused8_configured) {
-        PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      smem_f));
-        fused8_configured = true;
-      }
+      static LdsLimit lds;
+      if (!lds.allow(kf, smem_f)) return false;
       kf<<<n_blocks, 512, smem_f, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, dqkv, s, h,
           hkv,
                                             group, scale, x_kv, n_heads);
     } else {
       constexpr int smem_f = smem_kv > smem_q ? smem_kv : smem_q;
       auto kf = attn_bwd_fused_mfma_kernel<DH, false, EDGE>;
-      static bool fused4_configured = false;
-      if (!fused4_configured) {
-        PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      smem_f));
-        fused4_configured = true;
-      }
+      static LdsLimit lds;
+      if (!lds.allow(kf, smem_f)) return false;
       kf<<<n_blocks, 256, smem_f, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, dqkv, s, h,
           hkv,
                                             group, scale, x_kv, n_heads);
     }
   } else if constexpr (!EDGE) {
-    auto kkv = attn_bwd_dkv_mfma_kernel<DH, false>;
-    auto kkv8 = attn_bwd_dkv_split_mfma_kernel<DH, false>;
-    auto kq1 = attn_bwd_dq_mfma_kernel<DH, 1, false>;
-    static bool configured = false;
-    if (!configured) {
-      PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kkv), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    smem_kv));
-      PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kkv8), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    smem_kv8));
-      PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kq1), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    smem_q));
-      configured = true;
-    }
-    if (eight)
-      kkv8<<<dim3(x_kv, blocks), 512, smem_kv8, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb,
-          s,
-                                                           h, hkv, group, scale);
-    else
-      kkv<<<dim3(x_kv, blocks), 256, smem_kv, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, s,
-          h,
-                                                         hkv, group, scale);
-    if (dq_eight) {
-      auto kqs = attn_bwd_dq_split_mfma_kernel<DH, false>;
-      static bool split_configured = false;
-      if (!split_configured) {
-        PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kqs), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      smem_split));
-        split_configured = true;
-      }
-      kqs<<<dim3(n_heads, blocks), 512, smem_split, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
+    static LdsLimit lds_kv, lds_kv8, lds_q, lds_q8;
+    if (eight) {
+      auto k = attn_bwd_dkv_split_mfma_kernel<DH, false>;
+      if (!lds_kv8.allow(k, smem_kv8)) return false;
+      k<<<dim3(x_kv, blocks), 512, smem_kv8, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, s, h, hkv,
+                                                       group, scale);
     } else {
-      kq1<<<dim3(n_heads, blocks), 256, smem_q, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
+      auto k = attn_bwd_dkv_mfma_kernel<DH, false>;
+      if (!lds_kv.allow(k, smem_kv)) return false;
+      k<<<dim3(x_kv, blocks), 256, smem_kv, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, s, h, hkv,
+                                                      group, scale);
+    }
+    if (dq_eight) {
+      auto k = attn_bwd_dq_split_mfma_kernel<DH, false>;
+      if (!lds_q8.allow(k, smem_split)) return false;
+      k<<<dim3(n_heads, blocks), 512, smem_split, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
+    } else {
+      auto k = attn_bwd_dq_mfma_kernel<DH, 1, false>;
+      if (!lds_q.allow(k, smem_q)) return false;
+      k<<<dim3(n_heads, blocks), 256, smem_q, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
     }
   }
   if (split) {

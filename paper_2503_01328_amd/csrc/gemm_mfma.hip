@@ -661,11 +661,8 @@ static bool launch_mfma_epi(int M, int N, int K, const bf16* A, int lda, const b
   const void* kern;
   if constexpr (EDGE) kern = reinterpret_cast<const void*>(gemm_edge_kernel<WTM, WTN, TA, TB, EPI>);
   else kern = reinterpret_cast<const void*>(gemm_mfma_kernel<WTM, WTN, TA, TB, EPI>);
-  static bool configured = false;  // per instantiation
-  if (!configured) {
-    PO_HIP_OK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-    configured = true;
-  }
+  static LdsLimit lds;  // per instantiation
+  if (!lds.allow(kern, smem)) return false;
   int tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
   if constexpr (EDGE)
     gemm_edge_kernel<WTM, WTN, TA, TB, EPI><<<tiles_m * tiles_n, 256, smem, stream>>>(M, N, K, A, lda, B, ldb, ep,
@@ -828,12 +825,8 @@ static bool launch_grouped(GroupedArgs& g, hipStream_t stream) {
   constexpr int smem = stages_of(4, 4) * (256 + 256) * 128;
   auto kern = EDGE ? gemm_edge_grouped_kernel<true, true, kEpiAccumulate>
                    : gemm_mfma_grouped_kernel<true, true, kEpiAccumulate>;
-  static bool configured = false;
-  if (!configured) {
-    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  smem));
-    configured = true;
-  }
+  static LdsLimit lds;
+  if (!lds.allow(kern, smem)) return false;
   int blocks = g.total_tiles < 256 ? g.total_tiles : 256;  // one block per CU; more tiles mean more rounds per block
   kern<<<blocks, 256, smem, stream>>>(g);
   return launch_ok("gemm_mfma_grouped_kernel");

@@ -365,18 +365,12 @@ bool gemm_small_supported(int dtype, int trans_a, int trans_b, int M, int N, int
          (int64_t)ldb * 64 * 4 < limit;
 }
 
-template <typename K>
-static bool allow_lds(K kern, int smem) {
-  PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-  return true;
-}
-
 template <typename T, int TM, int TN, int KG, bool TA, bool TB>
 static bool launch_small(SmallProblem& p, hipStream_t stream) {
   constexpr int smem = KG * 2 * 32 * (TM + TN) * 128;
   auto kern = gemm_small_kernel<T, TM, TN, KG, TA, TB>;
-  static const bool configured = allow_lds(kern, smem);  // per instantiation
-  if (!configured) return false;
+  static LdsLimit lds;  // per instantiation
+  if (!lds.allow(kern, smem)) return false;
   p.tiles_n = ceil_div(p.N, 32 * TN);
   kern<<<ceil_div(p.M, 32 * TM) * p.tiles_n, 64 * KG, smem, stream>>>(p);
   return launch_ok("gemm_small_kernel");
@@ -419,8 +413,8 @@ template <typename T, int TM, int TN, int KG>
 static bool launch_group(SmallGroup& g, hipStream_t stream) {
   constexpr int smem = KG * 2 * 32 * (TM + TN) * 128;
   auto kern = gemm_small_grouped_kernel<T, TM, TN, KG>;
-  static const bool configured = allow_lds(kern, smem);
-  if (!configured) return false;
+  static LdsLimit lds;
+  if (!lds.allow(kern, smem)) return false;
   int total = 0;
   for (int i = 0; i < g.n; ++i) {
     g.p[i].tiles_n = ceil_div(g.p[i].N, 32 * TN);

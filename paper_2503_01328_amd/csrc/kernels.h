@@ -3,6 +3,8 @@
 // when the arguments do not fit what the kernel assumes.
 #pragma once
 
+#include <atomic>
+
 #include "po_common.h"
 
 namespace po {
@@ -151,6 +153,24 @@ bool attention_backward(int dtype, const void* qkv, const void* o, const float* 
       return false;                                                                      \
     }                                                                                    \
   } while (0)
+
+// The dynamic LDS a kernel may ask for: set once per kernel (a static object beside its launch) and device.  A call that
+// fails leaves its error text and the next one tries again.
+class LdsLimit {
+  std::atomic<uint64_t> devices_{0};  // one bit per device it has been set on
+
+ public:
+  template <typename Kernel>
+  bool allow(Kernel kern, int bytes) {
+    int device = 0;
+    PO_HIP_OK(hipGetDevice(&device));
+    const uint64_t bit = device < 64 ? (uint64_t)1 << device : 0;
+    if (devices_.load(std::memory_order_relaxed) & bit) return true;
+    PO_HIP_OK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    devices_.fetch_or(bit, std::memory_order_relaxed);
+    return true;
+  }
+};
 
 // hipGetLastError is sticky per thread: an error left behind by an earlier, unrelated HIP call
 // (of this library or of the host program) must not be blamed on the next launch.

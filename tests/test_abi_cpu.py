@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from oracle import schedule_oracle as sch
 from paper_2503_01328_amd import binding as po
@@ -250,6 +251,24 @@ def test_gemm_edge_kernel_leaves_offsets_beyond_31_bits_to_others():
             assert not weight(K, ld, 256) and not weight(K, 256, ld)
     assert forward(64, 64, most) and not forward(64, 64, 1 << 24) and not forward(64, 1 << 23, 256)
     assert weight(4096, 1 << 17, 256) and not weight(4096, 1 << 18, 256)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="forces launches to fail by having no GPU")
+@pytest.mark.parametrize("call", ["gemm f32", "gemm bf16", "edge", "attention f32", "attention bf16"])
+def test_a_launch_that_cannot_be_set_up_says_so_every_time(call):
+    """Without a GPU the LDS size of a kernel cannot be set.  Each such call fails with its own text, and a later one tries
+    again instead of remembering the failure."""
+    at = 1 << 20  # never read: the call fails on the host
+    act = {"gemm f32": lambda: po.po_op_gemm(po.PO_F32, 0, 0, 64, 64, 64, at, 64, at, 64, out=at, stream=0),
+           "gemm bf16": lambda: po.po_op_gemm(po.PO_BF16, 0, 0, 256, 256, 256, at, 256, at, 256, out=at, stream=0),
+           "edge": lambda: po.po_op_gemm(po.PO_BF16, 0, 0, 1736, 8200, 128, at, 128, at, 8200, out=at, stream=0),
+           "attention f32": lambda: po.po_op_attention_forward(po.PO_F32, at, at, at, 64, 64, 1, stream=0),
+           "attention bf16": lambda: po.po_op_attention_forward(po.PO_BF16, at, at, at, 100, 64, 1, stream=0)}[call]
+    for _ in range(2):
+        with pytest.raises(po.PipeOffloadError, match="failed"):
+            act()
+        with pytest.raises(po.PipeOffloadError, match="unknown dtype"):  # leaves another text behind
+            po.po_op_gemm(7, 0, 0, 64, 64, 64, at, 64, at, 64, out=at, stream=0)
 
 
 def test_hot_kernels_keep_their_accumulators_in_registers():
