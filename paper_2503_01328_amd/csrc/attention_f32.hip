@@ -293,6 +293,7 @@ __global__ __launch_bounds__(256, 1) void attn_f32_bwd_dkv_kernel(
 // ---- host side -------------------------------------------------------------------------------------------------
 bool attention_f32_supported(const void* qkv, const void* o, int s, int h, int n_heads, int n_kv_heads) {
   if (s <= 0 || h <= 0 || n_heads <= 0 || h % n_heads != 0 || n_kv_heads <= 0 || n_heads % n_kv_heads != 0) return false;
+  if (s > 32 * kMaxGridY) return false;
   const int dh = h / n_heads;
   return (dh == 32 || dh == 64 || dh == 96 || dh == 128) && ((uintptr_t)qkv | (uintptr_t)o) % 16 == 0;
 }

@@ -1604,6 +1604,7 @@ __global__ __launch_bounds__(256) void attn_delta_mfma_path_kernel(const bf16* _
 // ==================================================================================
 bool attention_mfma_supported(int s, int h, int n_heads, int n_kv_heads) {
   if (n_heads <= 0 || h % n_heads != 0 || n_kv_heads <= 0 || n_heads % n_kv_heads != 0) return false;
+  if (s % 128 != 0 && s > 128 * kMaxGridY) return false;
   int dh = h / n_heads;
   return (dh == 64 || dh == 128) && s >= 1;
 }

@@ -154,6 +154,10 @@ bool attention_backward(int dtype, const void* qkv, const void* o, const float* 
     }                                                                                    \
   } while (0)
 
+// Blocks in the second dimension of a grid.  The attention kernels that tile the rows there leave longer sequences to the
+// vector kernels, which have them in the first.
+constexpr int kMaxGridY = 65535;
+
 // The dynamic LDS a kernel may ask for: set once per kernel (a static object beside its launch) and device.  A call that
 // fails leaves its error text and the next one tries again.
 class LdsLimit {

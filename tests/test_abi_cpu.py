@@ -253,6 +253,16 @@ def test_gemm_edge_kernel_leaves_offsets_beyond_31_bits_to_others():
     assert weight(4096, 1 << 17, 256) and not weight(4096, 1 << 18, 256)
 
 
+def test_attention_longer_than_a_grid_goes_to_the_vector_kernels():
+    """Host logic: the matrix-core kernels count tiles of rows in the second grid dimension, which ends at 65535."""
+    f32, bf16 = (po.lib[n] for n in ("_ZN2po23attention_f32_supportedEPKvS1_iiii", "_ZN2po24attention_mfma_supportedEiiii"))
+    f32.restype = bf16.restype = ctypes.c_bool
+    f32.argtypes = [ctypes.c_void_p] * 2 + [ctypes.c_int] * 4
+    bf16.argtypes = [ctypes.c_int] * 4
+    assert f32(1 << 20, 1 << 20, 32 * 65535, 64, 1, 1) and not f32(1 << 20, 1 << 20, 32 * 65535 + 1, 64, 1, 1)
+    assert bf16(128 * 65535 - 1, 64, 1, 1) and not bf16(128 * 65535 + 1, 64, 1, 1)
+
+
 @pytest.mark.skipif(torch.cuda.is_available(), reason="forces launches to fail by having no GPU")
 @pytest.mark.parametrize("call", ["gemm f32", "gemm bf16", "edge", "attention f32", "attention bf16"])
 def test_a_launch_that_cannot_be_set_up_says_so_every_time(call):
