@@ -323,8 +323,12 @@ struct StreamPool {
   static bool lease(int device, hipStream_t* out) {
     std::lock_guard<std::mutex> g(lock());
     StreamPool& p = of(device);
-    if (p.idle.empty()) {
-      if (hipStreamCreateWithFlags(out, hipStreamNonBlocking) == hipSuccess) return true;  // at the default priority
+    if (p.idle.empty()) {  // a stage may be driven while another device is current: the stream is made on its own
+      int current = device;
+      bool ok = hipGetDevice(&current) == hipSuccess && (current == device || hipSetDevice(device) == hipSuccess);
+      ok = ok && hipStreamCreateWithFlags(out, hipStreamNonBlocking) == hipSuccess;  // at the default priority
+      if (current != device) (void)hipSetDevice(current);
+      if (ok) return true;
       (void)hipGetLastError();
       *out = nullptr;
       return false;
