@@ -362,6 +362,51 @@ def test_attention_ragged_bf16_keeps_probabilities_in_fp32(gpu_device, dh, a, ge
     check(dqkv[:, 2 * h:], 0, pb.T.contiguous() @ sign, even_rows)
 
 
+def _attention_64(qkv, d_o, o, lse, dh, a, akv):
+    """o and lse in 64 bits, and the gradients that follow in 64 bits from the given o and lse."""
+    s, h, hkv, group = len(qkv), a * dh, akv * dh, a // akv
+    q, k, v = (x.double() for x in (qkv[:, :h], qkv[:, h:h + hkv], qkv[:, h + hkv:]))
+    want = dict(o=torch.zeros_like(d_o, dtype=torch.float64), lse=torch.zeros_like(lse, dtype=torch.float64),
+                dqkv=torch.zeros_like(qkv, dtype=torch.float64))
+    future = torch.ones(s, s, dtype=torch.bool, device=qkv.device).triu(1)
+    for t in range(a):
+        c, ck = slice(t * dh, (t + 1) * dh), slice(t // group * dh, (t // group + 1) * dh)
+        sc = (q[:, c] @ k[:, ck].T.contiguous() / dh ** 0.5).masked_fill(future, -np.inf)
+        want["o"][:, c], want["lse"][t] = torch.softmax(sc, 1) @ v[:, ck], torch.logsumexp(sc, 1)
+        p, up = torch.exp(sc - lse[t].double()[:, None]), d_o[:, c].double()
+        ds = p * (up @ v[:, ck].T.contiguous() - (up * o[:, c].double()).sum(1, keepdim=True)) / dh ** 0.5
+        want["dqkv"][:, c] = ds @ k[:, ck]
+        want["dqkv"][:, h:h + hkv][:, ck] += ds.T.contiguous() @ q[:, c]
+        want["dqkv"][:, h + hkv:][:, ck] += p.T.contiguous() @ up
+    return want
+
+
+# The workspace of a ragged grouped backward: fp32 partials of two query heads, or of the group's next divisor, inside [s, 2h]
+# bf16.  Groups of 4, 6, 8 (two heads each), 9 (three), and of 2, 3, 5, which have no such divisor; both head sizes;
+# eight-wave blocks, and in the last case (800 of them) the four-wave ones.  Nothing behind the workspace is written, an
+# unaligned one is not used.  2^-8: the rounding of the results to bf16.
+@pytest.mark.parametrize("s,dh,a,akv,parts", [(200, 64, 8, 2, 2), (130, 128, 6, 1, 3), (257, 64, 9, 1, 3), (65, 128, 16, 2, 4),
+                                              (300, 128, 9, 1, 3), (200, 64, 4, 2, 0), (131, 128, 6, 2, 0), (70, 64, 5, 1, 0),
+                                              (130, 64, 800, 200, 2)])
+def test_attention_ragged_bf16_group_partials(gpu_device, s, dh, a, akv, parts):
+    h, hkv = a * dh, akv * dh
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(s + a)
+    qkv = torch.randn(s, h + 2 * hkv, generator=g, device=gpu_device).bfloat16()
+    d_o = torch.randn(s, h, generator=g, device=gpu_device).bfloat16()
+    o, lse, delta = torch.empty_like(d_o), torch.empty(a, s, device=gpu_device), torch.empty(a, s, device=gpu_device)
+    po.po_op_attention_forward(po.PO_BF16, qkv, o, lse, s, h, a, n_kv_heads=akv)
+    want = _attention_64(qkv, d_o, o, lse, dh, a, akv)["dqkv"]
+    for offset in (0, 4):
+        room = torch.full((s * 2 * h + 4096,), float("nan"), dtype=torch.bfloat16, device=gpu_device)
+        work, dqkv = room[offset:], torch.full_like(qkv, float("nan"))
+        po.po_op_attention_backward(po.PO_BF16, qkv, o, lse, d_o, dqkv, delta, s, h, a, n_kv_heads=akv, partials=work)
+        for part in (slice(0, h), slice(h, h + hkv), slice(h + hkv, h + 2 * hkv)):
+            assert (dqkv[:, part].double() - want[:, part]).norm() < 2.0 ** -8 * want[:, part].norm()
+        used = 0 if offset else s * 2 * parts * hkv  # floats
+        assert not torch.isnan(room[:2 * used].view(torch.float32)).any() and torch.isnan(room[2 * used:]).all()
+
+
 # What the matrix-core kernels put in place of the vector kernels is no further from the truth: 2-norm errors against 64 bits,
 # the backward from the same o and lse.  A twentieth is what such an error differs by between two draws of the inputs.
 @pytest.mark.parametrize("dtype,s,dh,a,akv", [("f32", 100, 64, 64, 64), ("f32", 333, 32, 64, 64), ("f32", 333, 96, 32, 32),
@@ -369,7 +414,7 @@ def test_attention_ragged_bf16_keeps_probabilities_in_fp32(gpu_device, dh, a, ge
                                               ("bf16", 300, 128, 40, 40), ("bf16", 300, 64, 32, 8)])
 def test_attention_errors_are_no_larger_than_the_vector_kernels(gpu_device, dtype, s, dh, a, akv):
     code, tdt, _ = DT[dtype]
-    h, hkv, group = a * dh, akv * dh, a // akv
+    h, hkv = a * dh, akv * dh
     g = torch.Generator(device=gpu_device)
     g.manual_seed(s)
     qkv = torch.randn(s, h + 2 * hkv, generator=g, device=gpu_device).to(tdt)
@@ -380,19 +425,7 @@ def test_attention_errors_are_no_larger_than_the_vector_kernels(gpu_device, dtyp
     o, lse, delta = got[1]["o"], got[1]["lse"], torch.empty(a, s, device=gpu_device)
     for generic in (1, 0):
         po.po_op_attention_backward(code, qkv, o, lse, d_o, got[generic]["dqkv"], delta, s, h, a, generic, n_kv_heads=akv)
-    q, k, v = (x.double() for x in (qkv[:, :h], qkv[:, h:h + hkv], qkv[:, h + hkv:]))
-    want = dict(o=torch.zeros_like(d_o, dtype=torch.float64), lse=torch.zeros(a, s, dtype=torch.float64, device=gpu_device),
-                dqkv=torch.zeros_like(qkv, dtype=torch.float64))
-    future = torch.ones(s, s, dtype=torch.bool, device=gpu_device).triu(1)
-    for t in range(a):
-        c, ck = slice(t * dh, (t + 1) * dh), slice(t // group * dh, (t // group + 1) * dh)
-        sc = (q[:, c] @ k[:, ck].T.contiguous() / dh ** 0.5).masked_fill(future, -np.inf)
-        want["o"][:, c], want["lse"][t] = torch.softmax(sc, 1) @ v[:, ck], torch.logsumexp(sc, 1)
-        p, up = torch.exp(sc - lse[t].double()[:, None]), d_o[:, c].double()
-        ds = p * (up @ v[:, ck].T.contiguous() - (up * o[:, c].double()).sum(1, keepdim=True)) / dh ** 0.5
-        want["dqkv"][:, c] = ds @ k[:, ck]
-        want["dqkv"][:, h:h + hkv][:, ck] += ds.T.contiguous() @ q[:, c]
-        want["dqkv"][:, h + hkv:][:, ck] += p.T.contiguous() @ up
+    want = _attention_64(qkv, d_o, o, lse, dh, a, akv)
     parts = dict(dq=slice(0, h), dk=slice(h, h + hkv), dv=slice(h + hkv, h + 2 * hkv))
     for name in ("o", "lse", *parts):
         pick = lambda r: r["dqkv"][:, parts[name]] if name in parts else r[name]

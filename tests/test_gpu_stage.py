@@ -532,8 +532,10 @@ def test_short_gap_units_are_not_offloaded(gpu_device):
 @pytest.mark.parametrize("shape,tol", [
     (syn.StageShape(2, 1, 128, 4, 512, 96, vocab=40, dtype="f32", pipeline_degree=2, n_microbatches=3, n_kv_heads=2), 1e-4),
     (syn.StageShape(2, 1, 512, 4, 1024, 256, dtype="bf16", pipeline_degree=3, n_microbatches=4, n_kv_heads=1), 2e-2),
-    (syn.StageShape(2, 1, 256, 4, 1024, 384, dtype="bf16", pipeline_degree=2, n_microbatches=3, n_kv_heads=2), 2e-2)],
-    ids=["f32-generic", "bf16-mfma-dh128", "bf16-mfma-dh64"])
+    (syn.StageShape(2, 1, 256, 4, 1024, 384, dtype="bf16", pipeline_degree=2, n_microbatches=3, n_kv_heads=2), 2e-2),
+    # a sequence that ends inside a tile, groups of four: fp32 partials of two query heads in the stage's workspace
+    (syn.StageShape(2, 1, 512, 8, 1024, 200, dtype="bf16", pipeline_degree=2, n_microbatches=3, n_kv_heads=2), 2e-2)],
+    ids=["f32-generic", "bf16-mfma-dh128", "bf16-mfma-dh64", "bf16-ragged-dh64"])
 def test_stage_with_grouped_query_attention(gpu_device, shape, tol):
     m = shape.n_microbatches
     snaps = {}
