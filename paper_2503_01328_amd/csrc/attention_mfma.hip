@@ -34,8 +34,8 @@
 // kernels and this form alike: o 1.608e-3, dq, dk, dv 1.661e-3, 1.660e-3, 1.659e-3, all of it the rounding of the results.
 // Two terms give the same there, but 1.5 to 15 % where probabilities that agree in 14 bits cancel (0.1 % with three).
 // MFMAs of a tile with one, two and three terms: forward 2 : 3 : 4, backward 7 : 10 : 13.  Vector kernels -> two terms -> this
-// form, us: s 1733, 16 heads of 128: forward 2235 -> 72 -> 73, backward 20450 -> 99 -> 116; s 3000, 32 heads of 64 over 8: 5406 -> 115 -> 126 and
-// 72760 -> 283 -> 315; s 100, 16 heads of 128: 35 -> 18 and 147 -> 18.
+// form, us: s 1733, 16 heads of 128: forward 2235 -> 73 -> 74, backward 20450 -> 100 -> 112; s 3000, 32 heads of 64 over 8: 5406 -> 115 -> 125 and
+// 72760 -> 278 -> 307; s 100, 16 heads of 128: 35 -> 18 and 147 -> 18.
 #include "attention_rows.h"
 #include "mfma_common.h"
 
@@ -244,9 +244,6 @@ struct FragmentOffsets {
     k = (unsigned)tile_offset<DH>(lane & 31, lane >> 5);
   }
 };
-__device__ __forceinline__ unsigned lds_address_of(const char* p) {
-  return (unsigned)(size_t)((const __attribute__((address_space(3))) char*)p);
-}
 // V fragment (contraction over keys 16 js .. 16 js + 15, output block d) and row fragment (rows 32 j + lane % 32,
 // head-dimension step kk) from the bases above; `vlo`, `vhi`, `kb` already include the tile's LDS address (tiles
 // start at multiples of their size, so XOR and add commute with it).
@@ -356,8 +353,8 @@ __device__ __forceinline__ void fwd_matrix_slot(const char* vtile, const char* k
   // from carrying some twenty of them across the tile loop, which at 168 registers a wave would cost spills.
   unsigned off_lo = fo.v_lo, off_hi = fo.v_hi, off_k = fo.k;
   asm volatile("" : "+v"(off_lo), "+v"(off_hi), "+v"(off_k), "+v"(q_addr));
-  const unsigned vlo = lds_address_of(vtile) + off_lo, vhi = lds_address_of(vtile) + off_hi;
-  const unsigned kb = lds_address_of(ktile) + off_k;
+  const unsigned vlo = lds_byte(vtile) + off_lo, vhi = lds_byte(vtile) + off_hi;
+  const unsigned kb = lds_byte(ktile) + off_k;
   bf16x8 ring_v[RV], ring_s[RS];
   auto fetch_v = [&](auto fc) {
     constexpr int f = decltype(fc)::value;
@@ -476,7 +473,7 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
 #pragma unroll
       for (int q = 0; q < PIECES; ++q) {
         const bf16* src = base + (size_t)(row0 + (q >> 2) * ROWS_PER_4K) * ld;
-        unsigned lds_addr = lds_address_of(tile + q * 1024);
+        unsigned lds_addr = lds_byte(tile + q * 1024);
         if constexpr (EDGE)
           buffer_to_lds(lds_addr, lane_off[q & 3], rows_buffer<DH>(src, ld, s - row0 - (q >> 2) * ROWS_PER_4K));
         else
@@ -540,7 +537,7 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
   FragmentOffsets<DH> fo;
   fo.init(lane);
   // this wave's Q rows: tile wrow / 2 of the Q area, rows 32 (wrow % 2) ..
-  const unsigned q_addr = lds_address_of(smem + (wrow >> 1) * TBYTES) + fo.k + (wrow & 1) * 32 * DH * 2;
+  const unsigned q_addr = lds_byte(smem + (wrow >> 1) * TBYTES) + fo.k + (wrow & 1) * 32 * DH * 2;
   f32x16 oacc[DT], sacc[2];
   Weights<EDGE> pf[EDGE ? 2 : 4];  // P of 16 keys each
   float m_run = -INFINITY, l_run = 0.f;
@@ -654,6 +651,81 @@ __device__ __forceinline__ void store_partial(bf16* out, size_t row, int ld_out,
   f32x4 w = {v[0], v[1], v[2], v[3]};
   *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out) + row * ld_out + column) = w;
 }
+// EDGE: rows 32 j .. 32 j + 31 of a query tile (sequence rows qs0 ..) against a wave's 32 keys from kw0 on; `lane` and what
+// follows from it are the hidden ones of the loop (see there), key and key_half the wave's own.
+// One product after the other, so that the three-term operands need no more registers than the other form:
+// S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.  The lane id is hidden again before each, so that no LDS address is
+// carried from one to the next; with them in registers the fragments of K and V were spilled, and every reload
+// waited for the tile loads under way.
+template <int DH, int V_IN_REG>
+__device__ __forceinline__ void dkv_edge_half(int j, int qs0, int kw0, int key, int key_half, float c, const char* qtile,
+                                              const char* dotile, const float* st_lse, const float* st_delta,
+                                              const char* vslot, const bf16x8 (&kf)[DH / 16],
+                                              const bf16x8 (&vf)[V_IN_REG > 0 ? V_IN_REG : 1], int& lane,
+                                              f32x16 (&dk)[DH / 32], f32x16 (&dv)[DH / 32]) {
+  constexpr int KS = DH / 16, DT = DH / 32;
+  int col = lane & 31, half = lane >> 5;
+  auto hide = [&]() __attribute__((always_inline)) {
+    asm volatile("" : "+v"(lane));
+    col = lane & 31, half = lane >> 5;
+  };
+  auto start_from = [&](f32x16& acc, const float* stat) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {  // accumulator row 8 b + 4 half + r is query row 32 j + that
+      f32x4 v = *reinterpret_cast<const f32x4*>(stat + 32 * j + 8 * b + 4 * half);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[4 * b + r] = v[r];
+    }
+  };
+  f32x16 sacc, pacc;
+  start_from(sacc, st_lse);
+  hide();
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+        read_row_fragment<DH>(qtile, 32 * j + col, 2 * kk + half), kf[kk], sacc, 0, 0, 0);
+    if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    sacc[e] = fast_exp2(sacc[e] * c);
+    if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * key_half + (e & 3)) sacc[e] = 0.f;
+  }
+  auto accumulate = [&](f32x16 (&to)[DT], const f32x16& w, const char* tile) __attribute__((always_inline)) {
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const Weights<true> terms = weights_of<true>(w, 8 * st);
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+        to[d] = multiply<true>(read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane), terms, to[d]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  __builtin_amdgcn_sched_barrier(0);
+  hide();
+  accumulate(dv, sacc, dotile);
+  hide();
+  start_from(pacc, st_delta);
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    bf16x8 vb;
+    if (kk < V_IN_REG)
+      vb = vf[kk];
+    else
+      vb = *reinterpret_cast<const bf16x8*>(vslot + (kk - V_IN_REG) * 1024);
+    pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+        read_row_fragment<DH>(dotile, 32 * j + col, 2 * kk + half), vb, pacc, 0, 0, 0);
+    if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    pacc[e] *= sacc[e];  // selected as well as P: 0 times the dP of a row that is not finite is no 0
+    if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * key_half + (e & 3)) pacc[e] = 0.f;
+  }
+  hide();
+  accumulate(dk, pacc, qtile);
+}
+
 // The backward kernels are written as block functions: bx, by and gy stand for blockIdx.x, blockIdx.y and gridDim.y,
 // so that a kernel of its own (the thin wrapper after each function) and the one-launch kernel further down, which
 // numbers its blocks itself, run the same code.
@@ -773,6 +845,10 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
     for (int j = 0; j < 2; ++j) {  // 32-row halves of the query tile, one at a time (keeps registers low)
       int qs0 = q0 + 32 * j;
       if (qs0 + 31 < kw0) continue;  // every row of this half is above every key of this wave
+      if constexpr (EDGE) {
+        dkv_edge_half<DH, V_IN_REG>(j, qs0, kw0, key, half, c, qtile, dotile, st_lse, st_delta, vslot_l, kf, vf, lane_l, dk, dv);
+        continue;
+      }
       f32x16 sacc, pacc;
 #pragma unroll
       for (int b = 0; b < 4; ++b) {  // accumulator row 8 b + 4 half + r is query row 32 j + that
@@ -781,69 +857,8 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           sacc[4 * b + r] = l4[r];
-          if (!EDGE) pacc[4 * b + r] = d4[r];
+          pacc[4 * b + r] = d4[r];
         }
-      }
-      if constexpr (EDGE) {
-        // One product after the other, so that the three-term operands need no more registers than the other form:
-        // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.  The lane id is hidden again before each, so that no LDS address is
-        // carried from one to the next; with them in registers the fragments of K and V were spilled, and every reload
-        // waited for the tile loads under way.
-        auto hide = [&]() __attribute__((always_inline)) {
-          asm volatile("" : "+v"(lane_l));
-          col_l = lane_l & 31, half_l = lane_l >> 5;
-        };
-        hide();
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              read_row_fragment<DH>(qtile, 32 * j + col_l, 2 * kk + half_l), kf[kk], sacc, 0, 0, 0);
-          if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          sacc[e] = fast_exp2(sacc[e] * c);
-          if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) sacc[e] = 0.f;
-        }
-        auto accumulate = [&](f32x16 (&to)[DT], const f32x16& w, const char* tile) __attribute__((always_inline)) {
-#pragma unroll
-          for (int st = 0; st < 2; ++st) {
-            const Weights<true> terms = weights_of<true>(w, 8 * st);
-#pragma unroll
-            for (int d = 0; d < DT; ++d)
-              to[d] = multiply<true>(read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane_l), terms, to[d]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        };
-        __builtin_amdgcn_sched_barrier(0);
-        hide();
-        accumulate(dv, sacc, dotile);
-        hide();
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          f32x4 d4 = *reinterpret_cast<const f32x4*>(st_delta + 32 * j + 8 * b + 4 * half_l);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) pacc[4 * b + r] = d4[r];
-        }
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-          bf16x8 vb;
-          if (kk < V_IN_REG)
-            vb = vf[kk];
-          else
-            vb = *reinterpret_cast<const bf16x8*>(vslot_l + (kk - V_IN_REG) * 1024);
-          pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              read_row_fragment<DH>(dotile, 32 * j + col_l, 2 * kk + half_l), vb, pacc, 0, 0, 0);
-          if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          pacc[e] *= sacc[e];  // selected as well as P: 0 times the dP of a row that is not finite is no 0
-          if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) pacc[e] = 0.f;
-        }
-        hide();
-        accumulate(dk, pacc, qtile);
-        continue;
       }
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
@@ -922,12 +937,12 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
     }
 }
 
-template <int DH, bool EDGE>
+template <int DH>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dkv_mfma_kernel(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ out, int ld_out, int out_k0, int out_v_delta, int hpb, int s, int h, int hkv, int group,
     float scale) {
-  attn_bwd_dkv_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group, scale,
+  attn_bwd_dkv_mfma_block<DH, false>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group, scale,
       (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y);
 }
 
@@ -1062,6 +1077,10 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
     for (int j = 0; j < 2; ++j) {  // 32-row halves of the query tile, one at a time (keeps registers low)
       int qs0 = q0 + 32 * j;
       if (!active || qs0 + 31 < kw0) continue;  // nothing to do, or every row of this half is above every key
+      if constexpr (EDGE) {
+        dkv_edge_half<DH, V_IN_REG>(j, qs0, kw0, key, half, c, qtile, dotile, st_lse, st_delta, vslot_l, kf, vf, lane_l, dk, dv);
+        continue;
+      }
       f32x16 sacc, pacc;
 #pragma unroll
       for (int b = 0; b < 4; ++b) {  // accumulator row 8 b + 4 half + r is query row 32 j + that
@@ -1070,69 +1089,8 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           sacc[4 * b + r] = l4[r];
-          if (!EDGE) pacc[4 * b + r] = d4[r];
+          pacc[4 * b + r] = d4[r];
         }
-      }
-      if constexpr (EDGE) {
-        // One product after the other, so that the three-term operands need no more registers than the other form:
-        // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.  The lane id is hidden again before each, so that no LDS address is
-        // carried from one to the next; with them in registers the fragments of K and V were spilled, and every reload
-        // waited for the tile loads under way.
-        auto hide = [&]() __attribute__((always_inline)) {
-          asm volatile("" : "+v"(lane_l));
-          col_l = lane_l & 31, half_l = lane_l >> 5;
-        };
-        hide();
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              read_row_fragment<DH>(qtile, 32 * j + col_l, 2 * kk + half_l), kf[kk], sacc, 0, 0, 0);
-          if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          sacc[e] = fast_exp2(sacc[e] * c);
-          if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) sacc[e] = 0.f;
-        }
-        auto accumulate = [&](f32x16 (&to)[DT], const f32x16& w, const char* tile) __attribute__((always_inline)) {
-#pragma unroll
-          for (int st = 0; st < 2; ++st) {
-            const Weights<true> terms = weights_of<true>(w, 8 * st);
-#pragma unroll
-            for (int d = 0; d < DT; ++d)
-              to[d] = multiply<true>(read_tr_fragment<DH>(tile, 32 * j + 16 * st, 32 * d, lane_l), terms, to[d]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        };
-        __builtin_amdgcn_sched_barrier(0);
-        hide();
-        accumulate(dv, sacc, dotile);
-        hide();
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          f32x4 d4 = *reinterpret_cast<const f32x4*>(st_delta + 32 * j + 8 * b + 4 * half_l);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) pacc[4 * b + r] = d4[r];
-        }
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-          bf16x8 vb;
-          if (kk < V_IN_REG)
-            vb = vf[kk];
-          else
-            vb = *reinterpret_cast<const bf16x8*>(vslot_l + (kk - V_IN_REG) * 1024);
-          pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              read_row_fragment<DH>(dotile, 32 * j + col_l, 2 * kk + half_l), vb, pacc, 0, 0, 0);
-          if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          pacc[e] *= sacc[e];  // selected as well as P: 0 times the dP of a row that is not finite is no 0
-          if (qs0 < kw0 + 31 && key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) pacc[e] = 0.f;
-        }
-        hide();
-        accumulate(dk, pacc, qtile);
-        continue;
       }
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
@@ -1226,12 +1184,12 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
   }
 }
 
-template <int DH, bool EDGE>
+template <int DH>
 __global__ __launch_bounds__(512, 1) void attn_bwd_dkv_split_mfma_kernel(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ out, int ld_out, int out_k0, int out_v_delta, int hpb, int s, int h, int hkv, int group,
     float scale) {
-  attn_bwd_dkv_split_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group,
+  attn_bwd_dkv_split_mfma_block<DH, false>(qkv, d_o, lse, delta, out, ld_out, out_k0, out_v_delta, hpb, s, h, hkv, group,
       scale, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y);
 }
 
@@ -1370,11 +1328,11 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
   }
 }
 
-template <int DH, int QT, bool EDGE>
+template <int DH, int QT>
 __global__ __launch_bounds__(256, QT == 1 ? 2 : 1) void attn_bwd_dq_mfma_kernel(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ dqkv, int s, int h, int hkv, int group, float scale) {
-  attn_bwd_dq_mfma_block<DH, QT, EDGE>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, (int)blockIdx.x,
+  attn_bwd_dq_mfma_block<DH, QT, false>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, (int)blockIdx.x,
       (int)blockIdx.y, (int)gridDim.y);
 }
 
@@ -1504,11 +1462,11 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
     }
 }
 
-template <int DH, bool EDGE>
+template <int DH>
 __global__ __launch_bounds__(512, 1) void attn_bwd_dq_split_mfma_kernel(const bf16* __restrict__ qkv,
     const bf16* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ dqkv, int s, int h, int hkv, int group, float scale) {
-  attn_bwd_dq_split_mfma_block<DH, EDGE>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, (int)blockIdx.x,
+  attn_bwd_dq_split_mfma_block<DH, false>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale, (int)blockIdx.x,
       (int)blockIdx.y, (int)gridDim.y);
 }
 
@@ -1703,22 +1661,22 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
   } else if constexpr (!EDGE) {
     static LdsLimit lds_kv, lds_kv8, lds_q, lds_q8;
     if (eight) {
-      auto k = attn_bwd_dkv_split_mfma_kernel<DH, false>;
+      auto k = attn_bwd_dkv_split_mfma_kernel<DH>;
       if (!lds_kv8.allow(k, smem_kv8)) return false;
       k<<<dim3(x_kv, blocks), 512, smem_kv8, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, s, h, hkv,
                                                        group, scale);
     } else {
-      auto k = attn_bwd_dkv_mfma_kernel<DH, false>;
+      auto k = attn_bwd_dkv_mfma_kernel<DH>;
       if (!lds_kv.allow(k, smem_kv)) return false;
       k<<<dim3(x_kv, blocks), 256, smem_kv, stream>>>(qkv, d_o, lse, delta, kv_out, kv_ld, kv_k0, kv_vd, kv_hpb, s, h, hkv,
                                                       group, scale);
     }
     if (dq_eight) {
-      auto k = attn_bwd_dq_split_mfma_kernel<DH, false>;
+      auto k = attn_bwd_dq_split_mfma_kernel<DH>;
       if (!lds_q8.allow(k, smem_split)) return false;
       k<<<dim3(n_heads, blocks), 512, smem_split, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
     } else {
-      auto k = attn_bwd_dq_mfma_kernel<DH, 1, false>;
+      auto k = attn_bwd_dq_mfma_kernel<DH, 1>;
       if (!lds_q.allow(k, smem_q)) return false;
       k<<<dim3(n_heads, blocks), 256, smem_q, stream>>>(qkv, d_o, lse, delta, dqkv, s, h, hkv, group, scale);
     }

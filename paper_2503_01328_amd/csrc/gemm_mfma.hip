@@ -74,10 +74,6 @@ __device__ __forceinline__ int kmajor_unit(int u, int k) {
   return u ^ (k & MASK);
 }
 
-// Byte address of a pointer into the block's LDS as the hardware counts it (the generic -> LDS conversion and
-// its null check happen here, once, instead of at every load).
-__device__ __forceinline__ unsigned lds_address(const void* p) { return (unsigned)(size_t)PO_LDS3(p); }
-
 // The slice is R * 128 bytes = R / 8 wave-wide loads of 1 KiB; wave w issues pieces w, w + 4, w + 8, ...
 // What a lane fetches for piece u never changes from slice to slice except for a step that is the same for every
 // lane, so the lane keeps one 32-bit byte offset per piece and the wave one 64-bit slice pointer in scalar
@@ -122,7 +118,7 @@ struct SliceLoader {
   // Piece u of the slice at `slice` -> LDS at lds_wave + 4096 u (lds_wave: the LDS address of this wave's piece 0
   // in the target stage).  Issued as inline assembly on purpose: through the builtin the compiler treats every
   // later LDS read as dependent on the load and waits for it at once, which would undo the double buffering.
-  // The caller waits (wait_slice_loads) before the barrier that publishes the slice.
+  // The caller waits (wait_loads) before the barrier that publishes the slice.
   __device__ __forceinline__ void issue(int u, unsigned lds_wave) const {
     unsigned dst = lds_wave + 4096u * u;
     if constexpr (EDGE) buffer_to_lds(dst, voff[u], buffer_of(slice, (unsigned)max(left, 0)));
@@ -134,12 +130,6 @@ struct SliceLoader {
     if (EDGE) left -= (int)step;
   }
 };
-
-// Waits until at most N of this wave's loads are outstanding (they complete in issue order).
-template <int N>
-__device__ __forceinline__ void wait_slice_loads() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 
 // ---- LDS -> MFMA fragment: 32 rows (row0 + lane % 32), k = 16 kk + 8 (lane / 32) + 0..7 ----
 template <int R, bool KMAJOR>
@@ -295,7 +285,7 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, const bf16* __res
   LoaderB lb;
   la.init(a_base, lda, M - m0, K, wave, lane);
   lb.init(b_base, ldb, N - n0, K, wave, lane);
-  const unsigned lds0 = uniform((int)lds_address(smem)) + 1024u * wave;  // this wave's piece 0 of stage 0, operand A
+  const unsigned lds0 = uniform((int)lds_byte(smem)) + 1024u * wave;  // this wave's piece 0 of stage 0, operand A
   // Load q (0 .. PER_SLICE - 1, A's pieces first) of the slice the loaders point at, into stage `st`.
   auto issue_load = [&](int q, unsigned st) {
     unsigned base = lds0 + st * STAGE;
@@ -317,10 +307,10 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, const bf16* __res
       next_slice();
     }
     // slice 0 has landed when at most ahead - 1 slices are still in flight
-    if (ahead >= 4) wait_slice_loads<3 * PER_SLICE>();
-    else if (ahead == 3) wait_slice_loads<2 * PER_SLICE>();
-    else if (ahead == 2) wait_slice_loads<PER_SLICE>();
-    else wait_slice_loads<0>();
+    if (ahead >= 4) wait_loads<3 * PER_SLICE>();
+    else if (ahead == 3) wait_loads<2 * PER_SLICE>();
+    else if (ahead == 2) wait_loads<PER_SLICE>();
+    else wait_loads<0>();
   }
   __syncthreads();
 #ifdef PO_PHASE_TIMING
@@ -374,7 +364,7 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, const bf16* __res
       if (MORE && kk == 1) {
         // slice kt + 1 complete (in steady state NSTAGE - 2 younger slices may stay in flight; the tail slices
         // simply wait for everything), own reads of stage kt % NSTAGE complete, then the barrier
-        wait_slice_loads<(ISSUE ? NSTAGE - 2 : 0) * PER_SLICE>();
+        wait_loads<(ISSUE ? NSTAGE - 2 : 0) * PER_SLICE>();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);

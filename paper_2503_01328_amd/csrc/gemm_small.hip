@@ -388,7 +388,8 @@ static bool launch_trans(int ta, int tb, SmallProblem& p, hipStream_t stream) {
 template <typename T>
 static bool launch_form(SmallForm f, int ta, int tb, SmallProblem& p, hipStream_t stream) {
   if (f.edge == 32) {
-    if (f.waves == 8) return launch_trans<T, 1, 1, 8>(ta, tb, p, stream);
+    if constexpr (sizeof(T) == 4)  // small_form gives fp32 alone eight
+      if (f.waves == 8) return launch_trans<T, 1, 1, 8>(ta, tb, p, stream);
     return launch_trans<T, 1, 1, 4>(ta, tb, p, stream);
   }
   if (f.waves == 4) return launch_trans<T, 2, 2, 4>(ta, tb, p, stream);
@@ -428,7 +429,8 @@ static bool launch_group(SmallGroup& g, hipStream_t stream) {
 template <typename T>
 static bool group_form(SmallForm f, SmallGroup& g, hipStream_t stream) {
   if (f.edge == 32) {
-    if (f.waves == 8) return launch_group<T, 1, 1, 8>(g, stream);
+    if constexpr (sizeof(T) == 4)
+      if (f.waves == 8) return launch_group<T, 1, 1, 8>(g, stream);
     return launch_group<T, 1, 1, 4>(g, stream);
   }
   if (f.waves == 4) return launch_group<T, 2, 2, 4>(g, stream);

@@ -14,7 +14,8 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-// Byte address of a pointer into the block's LDS as the hardware counts it.
+// Byte address of a pointer into the block's LDS as the hardware counts it (the generic -> LDS conversion and its null
+// check happen here, once, instead of at every load).
 __device__ __forceinline__ unsigned lds_byte(const void* p) {
   return (unsigned)(size_t)((const void __attribute__((address_space(3)))*)p);
 }
