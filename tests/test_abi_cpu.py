@@ -299,11 +299,18 @@ def test_hot_kernels_keep_their_accumulators_in_registers():
     # GEMM: three tiles x four operand layouts x four epilogues; attention: the forward kernel in its two block
     # shapes, the two backward kernels, their eight-wave forms and the one-launch form of both, two head dimensions
     assert len(gemm) == 48 and len(attn) >= 16
-    for name, v in {**gemm, **grouped, **attn}.items():
+    # results of any size: three tiles x (two forward and two input-gradient epilogues, weight gradients) and the grouped
+    # launch; the small tiles, 32 x 32 with four waves (fp32 also eight) and 64 x 64 with four, two and one, x four layouts
+    # and the grouped launch, two types; fp32 attention: three kernels, four head sizes
+    edge = {k: v for k, v in usage.items() if "gemm_edge_kernel" in k or "gemm_edge_grouped_kernel" in k}
+    small = {k: v for k, v in usage.items() if "gemm_small_kernel" in k or "gemm_small_grouped_kernel" in k}
+    f32 = {k: v for k, v in usage.items() if "attn_f32_" in k}
+    assert len(edge) == 16 and len(small) == 9 * 5 and len(f32) == 12
+    for name, v in {**gemm, **grouped, **attn, **edge, **small, **f32}.items():
         assert v["ScratchSize"] == 0, (name, v)
     for name, v in attn.items():
         assert v["Occupancy"] >= 2, (name, v)
-    for name, v in gemm.items():
+    for name, v in {**gemm, **edge}.items():
         assert v["VGPRs"] + v["AGPRs"] <= 512
 
 
