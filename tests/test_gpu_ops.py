@@ -381,6 +381,29 @@ def _attention_64(qkv, d_o, o, lse, dh, a, akv):
     return want
 
 
+# Short sequences stay with the vector kernels, bit for bit; one row more and a call goes to the matrix cores.
+@pytest.mark.parametrize("dtype,dh,forward,backward", [("f32", 32, 4, 6), ("f32", 64, 9, 12), ("f32", 96, 13, 18),
+                                                       ("f32", 128, 18, 24)])
+def test_attention_of_few_rows_runs_on_the_vector_kernels(gpu_device, dtype, dh, forward, backward):
+    code, tdt, _ = DT[dtype]
+    a, akv = 4, 2
+    h, hkv = a * dh, akv * dh
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(dh)
+    for s in sorted({1, forward, forward + 1, backward, backward + 1}):
+        qkv = torch.randn(s, h + 2 * hkv, generator=g, device=gpu_device).to(tdt)
+        d_o = torch.randn(s, h, generator=g, device=gpu_device).to(tdt)
+        o, lse, grad = ([torch.zeros(*size, dtype=t, device=gpu_device) for _ in range(2)]
+                        for size, t in (((s, h), tdt), ((a, s), torch.float32), ((s, h + 2 * hkv), tdt)))
+        delta = torch.empty(a, s, device=gpu_device)
+        for generic in (1, 0):
+            po.po_op_attention_forward(code, qkv, o[generic], lse[generic], s, h, a, generic, n_kv_heads=akv)
+        for generic in (1, 0):
+            po.po_op_attention_backward(code, qkv, o[1], lse[1], d_o, grad[generic], delta, s, h, a, generic,
+                                        n_kv_heads=akv)
+        assert torch.equal(o[0], o[1]) == (s <= forward) and torch.equal(grad[0], grad[1]) == (s <= backward), s
+
+
 # The workspace of a ragged grouped backward: fp32 partials of two query heads, or of the group's next divisor, inside [s, 2h]
 # bf16.  Groups of 4, 6, 8 (two heads each), 9 (three), and of 2, 3, 5, which have no such divisor; both head sizes;
 # eight-wave blocks, and in the last case (800 of them) the four-wave ones.  Nothing behind the workspace is written, an
