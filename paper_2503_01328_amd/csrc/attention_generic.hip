@@ -206,9 +206,11 @@ static bool vectors_or_refused(int s, uintptr_t addresses) { return s % 128 == 0
 
 bool attention_forward(int dtype, const void* qkv, void* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                        bool force_generic, hipStream_t stream) {
-  // Up to 40 rows the vector kernel's forward is the faster one: 8.7 against 10.6 us at 32 rows and 12 against 10.7 at 48
-  // with heads of 64, 12.4 against 17.1 and 16.8 against 17.4 with heads of 128 (2 to 32 heads alike).  Its backward never is.
-  if (dtype == kBF16 && !force_generic && s > 40 && attention_mfma_supported(s, h, n_heads, n_kv_heads) &&
+  // At few rows the vector kernel's forward is the faster one, vector / matrix cores in us (2 to 32 heads alike): heads of 64 at
+  // 41 and 48 rows 10.0 / 10.6 and 11.1 / 10.6, of 128 at 41, 48 and 56 rows 14.8 / 17.5, 16.5 / 17.5 and 18.5 / 17.5.  Its
+  // backward never is (8 rows: 15.5 / 10.3 and 24.6 / 14.4).
+  const int few = h == 64 * (int64_t)n_heads ? 43 : 51;
+  if (dtype == kBF16 && !force_generic && s > few && attention_mfma_supported(s, h, n_heads, n_kv_heads) &&
       vectors_or_refused(s, (uintptr_t)qkv | (uintptr_t)o))
     return attention_forward_mfma(qkv, o, lse, s, h, n_heads, n_kv_heads, stream);
   // fp32, vector / matrix cores at few rows (1 to 32 heads alike), us: heads of 32 at 4 rows 4.4 / 4.4; of 64 at 8 and 12 rows
