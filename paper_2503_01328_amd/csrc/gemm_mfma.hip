@@ -742,6 +742,10 @@ static double pick_edge_tile(int M, int N, int K, int& wtm, int& wtn) {
 bool gemm_small_is_faster(int M, int N, int K) {
   int wtm, wtn;
   pick_tile(M, N, wtm, wtn);
+  // Whole large tiles whose few slices are all on their way at once win, which the estimates below do not see.  512 x 1024,
+  // K 64 / 128 / 192 / 256, GeLU epilogue, us: large 5.5 / 5.7 / 6.3 / 6.6, small 6.2 / 6.8 / 7.3 / 5.6; 2048 x 2048, K 128:
+  // 5.4 and 7.1.
+  if (wtm && K % kBK == 0 && K < 4 * kBK) return false;
   const double big = wtm && K % kBK == 0 ? tile_us(M, N, K, wtm, wtn) : pick_edge_tile(M, N, K, wtm = 0, wtn);
   const double small4 = launch_us(M, N, K, 64, 64, 256, 4.0, 0.17, 0.17);  // a tile's K over four waves
   const double small1 = launch_us(M, N, K, 64, 64, 1024, 3.5, 0.6, 0.75);

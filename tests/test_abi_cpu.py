@@ -263,6 +263,15 @@ def test_attention_longer_than_a_grid_goes_to_the_vector_kernels():
     assert bf16(128 * 65535 - 1, 64, 1, 1) and not bf16(128 * 65535 + 1, 64, 1, 1)
 
 
+def test_whole_tiles_of_few_slices_stay_with_the_large_tiles():
+    """Host logic: results of whole 128 x 128 tiles take the small ones from K = 256 on where those fill the chip better."""
+    f = po.lib["_ZN2po20gemm_small_is_fasterEiii"]
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 3
+    for M, N in ((128, 128), (256, 1024), (512, 512), (512, 2048), (1024, 1024), (2048, 512)):
+        assert not any(f(M, N, K) for K in (64, 128, 192)) and f(M, N, 256)
+    assert f(100, 2048, 64) and f(512, 512, 200)  # no whole tiles, no whole slices
+
+
 @pytest.mark.skipif(torch.cuda.is_available(), reason="forces launches to fail by having no GPU")
 @pytest.mark.parametrize("call", ["gemm f32", "gemm bf16", "edge", "attention f32", "attention bf16"])
 def test_a_launch_that_cannot_be_set_up_says_so_every_time(call):
