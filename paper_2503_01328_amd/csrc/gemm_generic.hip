@@ -113,10 +113,22 @@ bool gemm_generic(int dtype, int trans_a, int trans_b, int M, int N, int K, cons
   return launch_ok("gemm_generic_kernel");
 }
 
+// Whether the vector kernel beats the 64 x 64 matrix-core tiles: a K that fills no more than a chunk or two of them (128 bytes
+// of a row each, loaded and multiplied whole) under many tiles.  vector / matrix cores, us, fp32 weight gradients: 1024 x 512,
+// K 1 / 16 / 24 7.0 / 8.6, 7.6 / 8.5, 9.9 / 8.5 (fewer tiles: 256 x 1024, K 16 7.6 / 5.0); 4096 x 4096, K 16 / 32 / 40 / 64
+// 40.8 / 51.0, 48.3 / 51.0, 53.4 / 64.9, 64.8 / 65.3; 4096 x 2048, K 32 / 40 30.5 / 28.5, 34.4 / 36.1.  Forward products alike (2048 x 512,
+// K 4 6.3 / 8.2).  bf16, 1032 x 4104, K 8 / 24 7.9 / 9.6, 10.0 / 9.6; its weight gradients have better kernels.
+static bool vector_is_faster(int dtype, int trans_a, int M, int N, int K) {
+  const int64_t tiles = (int64_t)ceil_div(M, 64) * ceil_div(N, 64);
+  if (dtype == kBF16) return !trans_a && K <= 16 && tiles >= 1024;
+  return K <= 48 && tiles >= (K <= 16 ? 128 : K <= 32 ? 4096 : 2048);
+}
+
 bool gemm(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
           const Epilogue& ep, bool force_generic, hipStream_t stream) {
   if (force_generic) return gemm_generic(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
-  const bool small = gemm_small_supported(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb);
+  const bool small = gemm_small_supported(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb) &&
+                     !vector_is_faster(dtype, trans_a, M, N, K);
   if (dtype == kBF16) {
     // bf16 by size.  Whole tiles: the large tiles, or the small ones where those leave most of the chip idle, for the
     // forward and the input gradients (512 x 512, K 512: 11.8 -> 5 us); a weight gradient on its own stays with the large

@@ -191,6 +191,27 @@ def test_gemm_small_edges(gpu_device, dtype, ta, tb, M, N, K):
     assert rel(acc, ref + 1.0) < sums + 2.0 ** -23
 
 
+# Short K under many tiles stays with the vector kernel, bit for bit; on the other side of the line the order of the sums is
+# another one.
+@pytest.mark.parametrize("dtype,ta,M,N,K,vector", [("f32", 1, 1024, 512, 16, 1), ("f32", 1, 1024, 512, 20, 0),
+                                                   ("f32", 1, 448, 1024, 16, 0), ("f32", 0, 520, 1000, 12, 1),
+                                                   ("f32", 1, 4096, 4096, 32, 1), ("f32", 1, 4096, 2048, 40, 1),
+                                                   ("f32", 1, 4096, 2048, 52, 0), ("f32", 1, 4096, 1984, 40, 0),
+                                                   ("bf16", 0, 2048, 2056, 16, 1), ("bf16", 0, 2048, 2056, 24, 0)])
+def test_gemm_of_short_k_runs_on_the_vector_kernel(gpu_device, dtype, ta, M, N, K, vector):
+    code, tdt, _ = DT[dtype]
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(M + N + K)
+    A = torch.randn(*((K, M) if ta else (M, K)), generator=g, device=gpu_device).to(tdt)
+    B = torch.randn(K, N, generator=g, device=gpu_device).to(tdt)
+    out = [torch.zeros(M, N, device=gpu_device) for _ in range(2)]
+    for generic in (1, 0):  # accumulated: fp32 results in either type
+        po.po_op_gemm(code, ta, 0, M, N, K, A, A.shape[1], B, N, acc_f32=out[generic], force_generic=generic)
+    assert torch.equal(out[0], out[1]) == bool(vector)
+    want = (A.double().t().contiguous() if ta else A.double()) @ B.double()
+    assert (out[0].double() - want).norm() < (2.0 ** -24 * K ** 0.5 + 2.0 ** -23) * want.norm()
+
+
 # a GeLU backward is multiplied onto the sum of product, bias and residual: one row, few tiles, and results whose large tiles
 # end inside, whose kernel has no such epilogue and leaves these calls to the small tiles
 @pytest.mark.parametrize("tb", [0, 1])
