@@ -221,7 +221,11 @@ int po_stage_backward_weight(po_stage* st, int32_t mb, int32_t chunk);
  * host memory on the offload stream once its forward has finished, and releases their
  * device slabs (Section 4.2; Appendix C buffer management).  The copies are issued from
  * the highest of those layers down: the reload brings layers back in the same order, and
- * the layer the backward needs first should not be the one that leaves last. */
+ * the layer the backward needs first should not be the one that leaves last.
+ * Single calls always copy by the DMA engine, which leaves the compute units alone; the library cannot see whether the rest
+ * of the program is bound by its copies, as po_run_schedule can, which then copies by kernel.  For about a second per
+ * 10 GB of device memory that any process on the GPU frees, the driver clears it on the engine of the copies to the host
+ * and those run at three quarters of their rate. */
 int po_offload(po_stage* st, int32_t mb, int32_t chunk, float ratio);
 
 /* Asynchronously brings an offloaded unit back on the reload stream, top layer first;
@@ -277,8 +281,9 @@ int po_op_gemm(int32_t dtype, int32_t trans_a, int32_t trans_b, int32_t M, int32
  * acc_f32[i] [M[i], N[i]] += A[i]^T B[i] with A[i] DEVICE [K[i], M[i]] (row stride lda[i]) and B[i] DEVICE
  * [K[i], N[i]] (row stride ldb[i]); acc_f32[i] DEVICE fp32 with row stride ldc[i].  The arrays themselves are HOST
  * arrays of length n.  Every M[i], N[i] must be a multiple of 256 and every K[i] of 64, else PO_E_INVAL (use
- * po_op_gemm per product then).  Each product equals po_op_gemm(trans_a = 1, trans_b = 0, acc_f32) bit for bit;
- * the stage runs the four parameter-gradient products of a layer this way (Section 3.1's W pass). */
+ * po_op_gemm per product then).  Each product equals po_op_gemm(trans_a = 1, trans_b = 0, acc_f32) bit for bit.  The
+ * stage runs the four parameter-gradient products of a layer in one launch as well (Section 3.1's W pass): these kernels where
+ * every product is whole tiles, others of any size where not or where there are few tiles. */
 int po_op_gemm_grouped(int32_t n, const int32_t* M, const int32_t* N, const int32_t* K, const void* const* A,
                        const int32_t* lda, const void* const* B, const int32_t* ldb, float* const* acc_f32,
                        const int32_t* ldc, void* stream);
@@ -297,8 +302,10 @@ int po_op_gemm_tile(int32_t M, int32_t N, int32_t* tile_rows, int32_t* tile_cols
 int po_op_attention_forward(int32_t dtype, const void* qkv, void* o, float* lse, int32_t s, int32_t h,
                             int32_t n_heads, int32_t n_kv_heads, int32_t force_generic, void* stream);
 /* Causal attention backward: dqkv laid out like qkv; delta: fp32 workspace [a, s]; partials: NULL, or
- * a [s, 2h] workspace of dtype that lets grouped-query shapes with few key/value heads compute dK/dV per query
- * head and add the groups up afterwards (same result up to the rounding of the per-head terms). */
+ * a workspace of 2 s h elements of dtype, contents unspecified afterwards.  In bf16 it lets grouped-query shapes with few
+ * key/value heads compute dK/dV in parts and add the groups up afterwards: with s a multiple of 128 per query head, the parts
+ * rounded to bf16 (same result up to that rounding); else in fp32 per two query heads, or the group's next divisor, where
+ * the group has one and the workspace is 16-byte aligned (the same sums in another order).  Unused otherwise. */
 int po_op_attention_backward(int32_t dtype, const void* qkv, const void* o, const float* lse, const void* d_o,
                              void* dqkv, float* delta, void* partials, int32_t s, int32_t h, int32_t n_heads,
                              int32_t n_kv_heads, int32_t force_generic, void* stream);

@@ -18,8 +18,8 @@
 // operand is then 32 consecutive floats of row 8 b + 4 (L / 32) + r.  For the products over the head dimension a
 // half-wave takes elements 8 kk + 4 (L / 32) + j in step (kk, j): a 16-byte load feeds four steps.
 //
-// s = 1024, 16 heads of 64: forward 42 us (2 s^2 h: 51 of 157 TFLOP/s), dK/dV 91 us, dQ 54 us; the vector kernels of
-// attention_generic.hip take 625, 3076 and 769 us.  s = 128, 4 heads: 7.5, 14.2 and 8.0 us (44, 55 and 28 us), there
+// s = 1024, 16 heads of 64: forward 38 us (2 s^2 h: 56 of 157 TFLOP/s), dK/dV 87 us, dQ 54 us; the vector kernels of
+// attention_generic.hip take 625, 3076 and 769 us.  s = 128, 4 heads: 7.6, 12.8 and 9.1 us (44, 55 and 28 us), there
 // bound by the chain of one tile: two loads, 64 to 128 dependent MFMAs, the sum over the waves.
 #include "attention_rows.h"
 #include "mfma_common.h"

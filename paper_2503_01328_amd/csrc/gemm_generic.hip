@@ -132,7 +132,7 @@ bool gemm(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* 
   if (dtype == kBF16) {
     // bf16 by size.  Whole tiles: the large tiles, or the small ones where those leave most of the chip idle, for the
     // forward and the input gradients (512 x 512, K 512: 11.8 -> 5 us); a weight gradient on its own stays with the large
-    // ones, bit for bit what a group of them gives.
+    // ones, bit for bit what po_op_gemm_grouped gives (a stage's group of few tiles takes the small ones).
     const bool few = small && (trans_a || gemm_mfma_edge_supported(trans_a, trans_b, M, N, K, A, lda, B, ldb, ep)) &&
                      gemm_small_is_faster(M, N, K);
     if (gemm_mfma_supported(trans_a, trans_b, M, N, K, lda, ldb, ep.ldc) && (trans_a || !few))

@@ -134,8 +134,9 @@ bool attention_backward_f32(const float* qkv, const float* lse, const float* del
 bool attention_mfma_supported(int s, int h, int n_heads, int n_kv_heads);
 bool attention_forward_mfma(const void* qkv, void* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                             hipStream_t stream);
-// partials: optional [s, 2h] workspace of the dtype; with it, grouped-query shapes with few key/value heads run
-// dK/dV per query head and add the groups up afterwards.
+// partials: optional workspace of 4 s h bytes; with it, grouped-query shapes with few key/value heads run dK/dV per query head
+// (s a multiple of 128: bf16 partials) or per two query heads or the group's next divisor (else: fp32 partials, if it is
+// 16-byte aligned and the group has such a divisor) and add the groups up afterwards.
 bool attention_backward_mfma(const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                              float* delta, void* partials, int s, int h, int n_heads, int n_kv_heads,
                              hipStream_t stream);

@@ -879,7 +879,8 @@ static int copy_slab(const po_stage* st, char* dst, const char* src, size_t byte
 
 // Whether a schedule's copies (both directions share about 97 GB/s) take longer than its compute at the rates that whole
 // steps reach.  C2 with every unit offloaded: 55 against 27 ms; C3's widths with half of them 24 against 30, C4's 55
-// against 80 (there the copy kernel costs 45.5 instead of 37.7 and 111 instead of 90 ms per step).
+// against 80 (there the copy kernel costs 45.5 instead of 37.7 and 111 instead of 90 ms per step).  The estimate has no time
+// per launch: a stage of small launches with everything offloaded counts as bound by its copies too, and copies by kernel.
 static bool copies_bound(const po_stage* st, const std::vector<po_op>& ops) {
   const po_config& c = st->cfg;
   double moved = 0., passes = 0.;

@@ -1,8 +1,8 @@
 """Summarises two rocprofv3 --pmc runs of bench.py (FETCH_SIZE, then WRITE_SIZE) into the HBM traffic per launch.
 
     cd /tmp && export TMPDIR=/tmp && cd <repo>
-    rocprofv3 --pmc FETCH_SIZE -d gpurun_out/pmc_fetch -o f --output-format csv -- python3 bench.py --steps 1 --warmup 1 --no-cpu-baseline --no-frontier --no-secondary --no-auto-ratio
-    rocprofv3 --pmc WRITE_SIZE -d gpurun_out/pmc_write -o w --output-format csv -- python3 bench.py --steps 1 --warmup 1 --no-cpu-baseline --no-frontier --no-secondary --no-auto-ratio
+    rocprofv3 --pmc FETCH_SIZE -d out/pmc_fetch -o f --output-format csv -- python3 bench.py --steps 1 --warmup 1 --no-cpu-baseline --no-frontier --no-secondary --no-auto-ratio
+    rocprofv3 --pmc WRITE_SIZE -d out/pmc_write -o w --output-format csv -- python3 bench.py --steps 1 --warmup 1 --no-cpu-baseline --no-frontier --no-secondary --no-auto-ratio
     python3 -m paper_2503_01328_amd.profile_traffic C2 <fetch counter csv> <write counter csv>
 
 Both counters read KiB per dispatch.  They are scaled by what they read for a plain copy kernel of known size in
@@ -59,8 +59,8 @@ def main():
     cfg = "" if workload == "C2" else f" --config {workload}"
     L = [f"# HBM traffic per launch, workload {workload} (rocprofv3 --pmc), tree at {commit}", "",
          "Commands (on the MI355X box, from the repository root; one counter per run):", "",
-         f"    rocprofv3 --pmc FETCH_SIZE -d gpurun_out/pmc_fetch -o f --output-format csv -- python3 bench.py{cfg} {flags}",
-         f"    rocprofv3 --pmc WRITE_SIZE -d gpurun_out/pmc_write -o w --output-format csv -- python3 bench.py{cfg} {flags}",
+         f"    rocprofv3 --pmc FETCH_SIZE -d out/pmc_fetch -o f --output-format csv -- python3 bench.py{cfg} {flags}",
+         f"    rocprofv3 --pmc WRITE_SIZE -d out/pmc_write -o w --output-format csv -- python3 bench.py{cfg} {flags}",
          f"    python3 -m paper_2503_01328_amd.profile_traffic {workload} <fetch counter csv> <write counter csv>", "",
          f"Calibration: `po::copy16_kernel` copies exactly {copy_kib:.0f} KiB (one [s, h] bf16 stage input) per launch in "
          f"this workload. FETCH_SIZE reads {F[ck][1] / F[ck][0]:.0f} KiB for it and WRITE_SIZE {W[ck][1] / W[ck][0]:.0f} "
