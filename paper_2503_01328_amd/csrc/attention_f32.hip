@@ -8,7 +8,7 @@
 // meet, tile t to wave t % 4; the four partial results are added in wave order through LDS at the end (deterministic,
 // no atomics).  Heaviest blocks of the causal triangle first.
 //
-// Rows of o and dQ whose sums are not finite are redone one by one (attention_rows.h), so that an infinity or NaN in a
+// Rows of o and dQ whose sums are not finite, without a NaN of their own, are redone one by one (attention_rows.h), so that an infinity or NaN in a
 // key or value reaches the rows at and behind it and no other.  What that costs where all is finite, one multiplication
 // per sum, is not measurable (a stage of 16 heads of 64 at 1024 rows 4.07 and 4.05 ms).
 //
@@ -114,10 +114,11 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, p[e]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    float alpha = exp_scaled(m_run - mx, scale), sum = 0.f;
+    const float ref = mx == -INFINITY ? 0.f : mx;  // scores that are all -inf add nothing, instead of inf - inf
+    float alpha = exp_scaled(m_run - ref, scale), sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      p[e] = exp_scaled(p[e] - mx, scale);
+      p[e] = exp_scaled(p[e] - ref, scale);
       sum += p[e];
     }
     m_run = mx;
@@ -136,8 +137,6 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
   stat[wave * 64 + lane] = m_run;
   stat[(4 + wave) * 64 + lane] = l_run + __shfl_xor(l_run, 32, 64);
   __syncthreads();
-  const uint32_t redo = all_redo(redo_of);
-  if (redo) redo_forward_rows<float, DH>(share_of(redo, wave), q0, qkv, o, lse, s, h, hkv, group, head, scale);
   // Wave w finishes registers 4 w .. 4 w + 3 (columns 32 d + 8 w + 4 half ..) of every lane's row.
   float m = stat[lane], f[4], l = 0.f;
 #pragma unroll
@@ -147,6 +146,8 @@ __global__ __launch_bounds__(256, 2) void attn_f32_fwd_kernel(const float* __res
     f[w] = exp_scaled(stat[w * 64 + lane] - m, scale);
     l += stat[(4 + w) * 64 + lane] * f[w];
   }
+  const uint32_t redo = all_redo(redo_of) & rows_to_redo(!is_nan(l), 32);
+  if (redo) redo_forward_rows<float, DH>(share_of(redo, wave), q0, qkv, o, lse, s, h, hkv, group, head, scale);
   if (q > last || (redo >> (lane & 31) & 1)) return;
 #pragma unroll
   for (int d = 0; d < DT; ++d) {
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(256, DH > 64 ? 1 : 2) void attn_f32_bwd_dq_kernel(
   }
   put_partial<DT>(lds + wave * PART, dq, lane);
   uint32_t* redo_of = reinterpret_cast<uint32_t*>(lds + 4 * PART);
-  const uint32_t redo_mine = rows_to_redo(not_finite<DT>(dq), s - q0);
+  const uint32_t redo_mine = rows_to_redo(not_finite<DT>(dq) && !is_nan(lse_q + delta_q), s - q0);
   if (lane == 0) redo_of[wave] = redo_mine;
   __syncthreads();
   const uint32_t redo = all_redo(redo_of);

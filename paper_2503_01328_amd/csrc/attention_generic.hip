@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(const T* __restri
     for (int e = lane; e < dh; e += kWave) qs[wave][e] = to_f32(qkv[(size_t)i * ld + head * dh + e]) * scale;
   __syncthreads();
   if (!active) return;
-  attention_forward_row<T, kDimSlots>([&](int e) { return qs[wave][e]; }, kbase, vbase, ld, i, dh, lane,
+  attention_forward_row<T, kDimSlots, 1>([&](int e) { return qs[wave][e]; }, kbase, vbase, ld, i, dh, lane,
                                       o + (size_t)i * h + head * dh, lse + (size_t)head * s + i);
 }
 
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_generic_kernel(const T* __res
     }
   __syncthreads();
   if (!active) return;
-  attention_dq_row<T, kDimSlots>([&](int e) { return qs[wave][e]; }, [&](int e) { return dos[wave][e]; }, kbase, vbase, ld,
+  attention_dq_row<T, kDimSlots, 1>([&](int e) { return qs[wave][e]; }, [&](int e) { return dos[wave][e]; }, kbase, vbase, ld,
                                  lse[(size_t)head * s + i], delta[(size_t)head * s + i], i, dh, lane, scale,
                                  dqkv + (size_t)i * ld + head * dh);
 }

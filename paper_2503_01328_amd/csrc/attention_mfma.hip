@@ -27,7 +27,7 @@
 // Every kernel has a second form, EDGE, for sequences that are no multiple of 128: tiles are loaded through buffer
 // descriptors that end with the sequence (rows past it read as zero: such a key is masked like any key above the
 // diagonal, such a query row adds zero to every gradient), results past it are not stored.  Rows of o and dQ whose sums are
-// not finite are redone one by one (attention_rows.h), so that an infinity or NaN in a key or value reaches the rows at and
+// not finite, without a NaN of their own, are redone one by one (attention_rows.h), so that an infinity or NaN in a key or value reaches the rows at and
 // behind it and no other; in the other form it also reaches those of its 64-row tile before it.  EDGE also
 // multiplies P and dS as the sum of three bf16 terms that is the fp32 value itself (weights_of), because these sequences
 // ran on the vector kernels, which hold P and dS in fp32.  Relative error against 64 bits at s 1733, 16 heads of 128, vector
@@ -301,8 +301,10 @@ __device__ __forceinline__ void fwd_softmax(f32x16 (&sacc)[2], f32x16 (&oacc)[DH
   constexpr float kLazyLog2 = 8.0f;
   const bool outgrown = __builtin_amdgcn_ballot_w64((mx - m_run) * c > kLazyLog2) != 0;
   float m_new = outgrown ? fmaxf(m_run, mx) : m_run;
-  float alpha = fast_exp2((m_run - m_new) * c);
-  float mc = m_new * c;
+  // EDGE: a first tile whose visible scores are all -inf adds nothing, instead of inf - inf
+  const float m_ref = EDGE && m_new == -INFINITY ? 0.f : m_new;
+  float alpha = fast_exp2((m_run - m_ref) * c);
+  float mc = m_ref * c;
   float sum = 0.f;
 #pragma unroll
   for (int j = 0; j < 2; ++j)
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
   const int q = qw0 + col;
   float l = l_run + __shfl_xor(l_run, 32, 64);
   if constexpr (EDGE) {
-    const uint32_t redo = rows_to_redo(not_finite<DT>(oacc), s - qw0);
+    const uint32_t redo = rows_to_redo(not_finite<DT>(oacc) && !is_nan(l), s - qw0);
     if (redo) redo_forward_rows<bf16, DH>(redo, qw0, qkv, o, lse, s, h, hkv, group, head, scale);
     if (q >= s || (redo >> col & 1)) return;
   }
@@ -1312,7 +1314,7 @@ __device__ __forceinline__ void attn_bwd_dq_mfma_block(const bf16* __restrict__ 
   for (int t = 0; t < QT; ++t) {
     int q = qw0 + 32 * t + col;
     if constexpr (EDGE) {
-      const uint32_t redo = rows_to_redo(not_finite<DT>(dq[t]), s - qw0 - 32 * t);
+      const uint32_t redo = rows_to_redo(not_finite<DT>(dq[t]) && !is_nan(lse_q[t] + delta_q[t]), s - qw0 - 32 * t);
       if (redo) redo_dq_rows<bf16, DH>(redo, qw0 + 32 * t, qkv, d_o, lse, delta, dqkv, s, h, hkv, group, head, scale);
       if (q >= s || (redo >> col & 1)) continue;
     }
@@ -1447,7 +1449,7 @@ __device__ __forceinline__ void attn_bwd_dq_split_mfma_block(const bf16* __restr
 #pragma unroll
     for (int e = 0; e < 16; ++e) dq[d][e] += xch[(d * 16 + e) * 64 + lane];
   if constexpr (EDGE) {
-    const uint32_t redo = rows_to_redo(not_finite<DT>(dq), s - qw0);
+    const uint32_t redo = rows_to_redo(not_finite<DT>(dq) && !is_nan(lse_q + delta_q), s - qw0);
     if (redo) redo_dq_rows<bf16, DH>(redo, qw0, qkv, d_o, lse, delta, dqkv, s, h, hkv, group, head, scale);
     if (q >= s || (redo >> col & 1)) return;
   }

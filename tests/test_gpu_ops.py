@@ -383,6 +383,29 @@ def test_attention_ragged_bf16_keeps_probabilities_in_fp32(gpu_device, dh, a, ge
     check(dqkv[:, 2 * h:], 0, pb.T.contiguous() @ sign, even_rows)
 
 
+# Keys no row may attend to, by scores of -inf: a whole tile of them, the first or one that starts a wave's or a group's
+# share of the tiles, adds nothing.  (Row i of a query of ones against keys of -inf; rows that see no other key are NaN.)
+@pytest.mark.parametrize("first,last", [(0, 40), (0, 64), (32, 64), (64, 128), (96, 160)])
+@pytest.mark.parametrize("dtype,s,dh,a", [("f32", 200, 64, 2), ("f32", 200, 128, 1), ("bf16", 300, 64, 2),
+                                          ("bf16", 300, 128, 400)])
+def test_attention_keys_of_minus_infinity_add_nothing(gpu_device, dtype, s, dh, a, first, last):
+    code, tdt, _ = DT[dtype]
+    h = a * dh
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(first + last + s)
+    qkv = torch.randn(s, 3 * h, generator=g, device=gpu_device).to(tdt)
+    qkv[:, :h] = 1
+    qkv[first:last, h:2 * h] = float("-inf")
+    o, lse = torch.empty(s, h, dtype=tdt, device=gpu_device), torch.empty(a, s, device=gpu_device)
+    po.po_op_attention_forward(code, qkv, o, lse, s, h, a)
+    k, v = qkv[:, h:h + dh].double(), qkv[:, 2 * h:2 * h + dh].double()
+    sc = (k.sum(1) / dh ** 0.5).expand(s, s).masked_fill(torch.ones(s, s, dtype=torch.bool, device=gpu_device).triu(1), -np.inf)
+    want, sees = torch.softmax(sc, 1) @ v, slice(0 if first else last, s)
+    assert (o[sees, :dh].double() - want[sees]).norm() < (2.0 ** -8 if dtype == "bf16" else 1e-6) * want[sees].norm()
+    assert (lse[0, sees] - torch.logsumexp(sc, 1)[sees]).abs().max() < 1e-5
+    assert not torch.isfinite(o[:sees.start]).any() and not torch.isfinite(lse[:, :sees.start]).any()
+
+
 def _attention_64(qkv, d_o, o, lse, dh, a, akv):
     """o and lse in 64 bits, and the gradients that follow in 64 bits from the given o and lse."""
     s, h, hkv, group = len(qkv), a * dh, akv * dh, a // akv
