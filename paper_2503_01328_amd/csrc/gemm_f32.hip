@@ -1,0 +1,277 @@
+// fp32 GEMM on v_mfma_f32_32x32x2_f32 (full fp32 products and sums, 256 flop/clk/CU: 157 TFLOP/s at 2.4 GHz) for results
+// that give every CU a tile; smaller ones have gemm_small.hip.
+//
+// An MFMA takes 64 cycles, so operands are cheap to supply and what decides is that no SIMD's matrix core waits.  The waves
+// of a block share each chunk of K (32 k, 128 bytes of a row) through a ring of NST LDS stages.  A wave that issues a tile load
+// is held until the memory pipeline has taken it, so two waves of the block do nothing else, one per operand (one for both
+// cannot feed 64 x 64 tiles: a chunk's 16 loads take it longer than the chunk's MFMAs); the computing waves only read
+// fragments, each behind an MFMA of the step before its own, and multiply.  The one barrier per chunk stands where the last of the
+// chunk's fragments are in registers and a quarter of its MFMAs is still to come.  LDS is small enough (48 to 72 KB) that two
+// or three blocks share a CU: one's first loads and last stores run under the other's MFMAs.
+//
+// A block: WK groups of WM x WN computing waves, a wave TM x TN tiles of 32 x 32.  Group g owns every WK-th chunk; the
+// groups' partial tiles are added in group order through LDS (always the same order: deterministic).  Chunks past K and
+// rows past M or N read as zero (the buffer descriptors end with the operand), the epilogue stores only what is inside.
+//
+// Measured against tiles of 64 x 64 whose four waves each took every fourth chunk of K and loaded it themselves (us):
+// 1024 x 4096, K 1024 92 -> 68 (127 TFLOP/s); 2048 x 2048, K 8192 553 -> 484 (142); 777 x 640, K 2560 47 -> 31;
+// 512 x 2560, K 5120 175 -> 140; 4096 x 1536, K 512 75 -> 53.  What is left: the barrier (a SIMD's pipe runs dry while the last
+// wave arrives) and the last, partly filled round of tiles.
+#include <string.h>
+
+#include "gemm_tile.h"
+
+namespace po {
+
+template <int TM_, int TN_, int WM_, int WN_, int WK_, int NST_>
+struct F32Form {
+  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, WK = WK_, NST = NST_;
+  static constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN, GW = WM * WN, WAVES = GW * WK;  // computing waves
+  static constexpr int THREADS = 64 * (WAVES + 2);
+  static constexpr int STAGE = (BM + BN) * 128, LD = BN + 4;
+  static constexpr int RING = NST * STAGE > BM * LD * 4 ? NST * STAGE : BM * LD * 4;  // of a group; later its partial tile
+  static constexpr int SMEM = WK * RING;
+};
+
+template <typename Form, bool TA, bool TB>
+__device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* smem) {
+  constexpr int TM = Form::TM, TN = Form::TN, WN = Form::WN, WK = Form::WK, NST = Form::NST;
+  constexpr int BM = Form::BM, BN = Form::BN, GW = Form::GW, KU = MfmaOf<float>::KU;
+  using OpA = Operand<float, BM, TA>;
+  using OpB = Operand<float, BN, TB>;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = wave / GW, w = wave % GW, wm = w / WN, wn = w % WN;
+  const int M = p.M, N = p.N, K = p.K;
+  int m0, n0;
+  place_of_tile(tile, (M + BM - 1) / BM, p.tiles_n, m0, n0);
+  m0 *= BM;
+  n0 *= BN;
+
+  const int chunks = ((K + KU - 1) / KU + WK - 1) / WK;  // of every group; the last ones may be empty
+  // a wave with a single tile adds even and odd pairs of k apart: half as long a chain of roundings
+  constexpr int CH = TM * TN == 1 ? 2 : 1;
+  f32x16 acc[CH][TM][TN];
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[c][i][j][e] = 0.f;
+  // Loader waves: one for A, one for B.
+  auto loader = [&](auto op, const float* ptr, int ld, int row0, int rows, int offset) {
+    using Op = decltype(op);
+    constexpr int LOADS = WK * Op::LOADS;  // of a chunk of every group
+    Op x[WK];
+#pragma unroll
+    for (int g = 0; g < WK; ++g) x[g].init(ptr, ld, row0, rows, K, g, WK, lane);
+    const unsigned ring = __builtin_amdgcn_readfirstlane((int)lds_byte(smem)) + offset;
+    int k_left = K;
+    auto issue = [&](unsigned stage) {
+#pragma unroll
+      for (int g = 0; g < WK; ++g) x[g].issue(ring + g * Form::RING + stage, k_left - g * KU, lane);
+      k_left -= WK * KU;
+    };
+#pragma unroll
+    for (int i = 0; i < NST; ++i) issue(i * Form::STAGE);
+    wait_loads<(LOADS * (NST - 1) < 63 ? LOADS * (NST - 1) : 63)>();
+    asm volatile("s_barrier" ::: "memory");
+    unsigned stage = 0;
+    for (int t = 0; t < chunks; ++t) {
+      wait_loads<(LOADS * (NST - 2) < 63 ? LOADS * (NST - 2) : 63)>();
+      asm volatile("s_barrier" ::: "memory");
+      issue(stage);
+      stage = stage + Form::STAGE == NST * Form::STAGE ? 0 : stage + Form::STAGE;
+    }
+    wait_loads<0>();  // the empty chunks behind the last one write zeros into the ring
+  };
+  if (wave == Form::WAVES) {
+    loader(OpA(), static_cast<const float*>(p.A), p.lda, m0, M, 0);
+  } else if (wave == Form::WAVES + 1) {
+    loader(OpB(), static_cast<const float*>(p.B), p.ldb, n0, N, OpA::BYTES);
+  } else {
+    const char* ring = smem + group * Form::RING;
+    f32x4 fa[2][TM], fb[2][TN];
+    // fragment x of the next eight k: A's TM, then B's TN
+    auto read = [&](int x, unsigned stage, int kk, int buf) {
+      const char* sa = ring + stage;
+      if (x < TM) fa[buf][x] = fragment<BM, TA>((const float*)nullptr, sa, 32 * (wm * TM + x), kk, lane);
+      else fb[buf][x - TM] = fragment<BN, TB>((const float*)nullptr, sa + OpA::BYTES, 32 * (wn * TN + x - TM), kk, lane);
+    };
+    asm volatile("s_barrier" ::: "memory");
+    unsigned stage = 0;
+#pragma unroll
+    for (int x = 0; x < TM + TN; ++x) {
+      read(x, 0, 0, 0);
+    }
+    for (int t = 0; t < chunks; ++t) {
+      const unsigned next = stage + Form::STAGE == NST * Form::STAGE ? 0 : stage + Form::STAGE;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        if (kk == 3) {  // this wave has the last fragments of the chunk; when all have them the stage is free
+          wait_lds_reads();
+          asm volatile("s_barrier" ::: "memory");
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < 4 * TM * TN; ++x) {
+          const int e = x / (TM * TN), i = x / TN % TM, j = x % TN;
+          acc[e % CH][i][j] =
+              __builtin_amdgcn_mfma_f32_32x32x2f32(fb[kk & 1][j][e], fa[kk & 1][i][e], acc[e % CH][i][j], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (x < TM + TN) {
+            read(x, kk < 3 ? stage : next, (kk + 1) & 3, (kk + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+      stage = next;
+    }
+    wait_lds_reads();
+  }
+  __syncthreads();
+
+  constexpr int LD = Form::LD;
+  float* part = reinterpret_cast<float*>(smem + group * Form::RING);
+  if (wave < Form::WAVES) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            v[e] = CH == 2 ? acc[0][i][j][4 * q + e] + acc[CH - 1][i][j][4 * q + e] : acc[0][i][j][4 * q + e];
+          *reinterpret_cast<f32x4*>(part + (32 * (wm * TM + i) + (lane & 31)) * LD + 32 * (wn * TN + j) + 8 * q +
+                                    4 * (lane >> 5)) = v;
+        }
+  }
+  __syncthreads();
+  constexpr int PER_ROW = BN / 4;
+#pragma unroll 4
+  for (int piece = threadIdx.x; piece < BM * PER_ROW; piece += Form::THREADS) {
+    int r = piece / PER_ROW, c = piece % PER_ROW * 4;
+    if (m0 + r >= M || n0 + c >= N) continue;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < WK; ++g) {
+      f32x4 x = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(smem + g * Form::RING) + r * LD + c);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] += x[k];
+    }
+    if (p.vec && n0 + c + 4 <= N) {
+      epilogue_vector<float>(p.ep, m0 + r, n0 + c, v);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (n0 + c + i < N) epilogue_store<float>(p.ep, m0 + r, n0 + c + i, v[i]);
+    }
+  }
+}
+
+template <typename Form, bool TA, bool TB>
+__global__ __launch_bounds__(Form::THREADS) void gemm_small_kernel(SmallProblem p) {
+  extern __shared__ __align__(16) char smem[];
+  f32_tile<Form, TA, TB>(p, tile_of_block(), smem);
+}
+
+template <typename Form>
+__global__ __launch_bounds__(Form::THREADS) void gemm_small_grouped_kernel(SmallGroup g) {
+  extern __shared__ __align__(16) char smem[];
+  const int lin = tile_of_block();
+  SmallProblem p = g.p[0];  // constant indices only: a run-time index would send the arguments through memory
+#pragma unroll
+  for (int i = 1; i < kMaxSmallGroup; ++i)
+    if (i < g.n && lin >= g.p[i].first_tile) p = g.p[i];
+  f32_tile<Form, true, true>(p, lin - p.first_tile, smem);
+}
+
+template <typename Form, bool TA, bool TB>
+static bool launch_one(SmallProblem& p, hipStream_t stream) {
+  auto kern = gemm_small_kernel<Form, TA, TB>;
+  static LdsLimit lds;  // per instantiation
+  if (!lds.allow(kern, Form::SMEM)) return false;
+  p.tiles_n = ceil_div(p.N, Form::BN);
+  kern<<<ceil_div(p.M, Form::BM) * p.tiles_n, Form::THREADS, Form::SMEM, stream>>>(p);
+  return launch_ok("gemm_small_kernel (fp32)");
+}
+template <typename Form>
+static bool launch_trans(int ta, int tb, SmallProblem& p, hipStream_t stream) {
+  // kernel flag TB means "B is n-contiguous", i.e. trans_b == 0
+  if (!ta && !tb) return launch_one<Form, false, true>(p, stream);
+  if (!ta && tb) return launch_one<Form, false, false>(p, stream);
+  if (ta && !tb) return launch_one<Form, true, true>(p, stream);
+  return launch_one<Form, true, false>(p, stream);
+}
+template <typename Form>
+static bool launch_group(SmallGroup& g, hipStream_t stream) {
+  auto kern = gemm_small_grouped_kernel<Form>;
+  static LdsLimit lds;
+  if (!lds.allow(kern, Form::SMEM)) return false;
+  int total = 0;
+  for (int i = 0; i < g.n; ++i) {
+    g.p[i].tiles_n = ceil_div(g.p[i].N, Form::BN);
+    g.p[i].first_tile = total;
+    total += ceil_div(g.p[i].M, Form::BM) * g.p[i].tiles_n;
+  }
+  kern<<<total, Form::THREADS, Form::SMEM, stream>>>(g);
+  return launch_ok("gemm_small_grouped_kernel (fp32)");
+}
+
+// ---- which tile -----------------------------------------------------------------------------------------------------
+// Form 0: 32 x 64, two groups of two waves; 1: 64 x 64, four waves; 2: 128 x 64, four waves of 64 x 32.  Big tiles use
+// a fragment twice and spend less of their time at barriers, small ones fill the last round better.  A launch takes as long as its fullest
+// CU: rounds of tiles times (start + per chunk of K), in us, fitted to 260 random products of 20 to 6000 rows, columns and k
+// (within 9 % of each; the choice is within 1.5 % of the best form on average):
+//   1024 x 1024, K 1024: 23.3 22.4 38.1    1024 x 4096, K 1024: 81.2 79.0 67.6    777 x 640, K 2560: 30.7 46.6 84.3
+//   1500 x 1536, K 1536: 71.7 73.9 97.7    4608 x 1536, K 1500:  191  170  180    4096 x 512, K 512: 24.8 22.2 22.7
+using Form32x64 = F32Form<1, 1, 1, 2, 2, 3>;
+using Form64x64 = F32Form<1, 1, 2, 2, 1, 3>;
+using Form128x64 = F32Form<2, 1, 2, 2, 1, 2>;
+static double round_time(int form, int64_t tiles, int K) {
+  static const double start[3] = {1.43, 1.33, 1.92}, chunk[3] = {0.547, 0.509, 0.959};
+  const int chunks = form == 0 ? ceil_div(ceil_div(K, 32), 2) : ceil_div(K, 32);
+  // few rounds: whole ones; many: the blocks of a CU no longer end together
+  const double rounds = tiles < 1024 ? (double)ceil_div64(tiles, 256) : (double)tiles / 256 + 0.5;
+  return rounds * (start[form] + chunk[form] * chunks);
+}
+static int best_form(const int64_t* tiles, int K) {
+  int best = 0;
+  for (int f = 1; f < 3; ++f)
+    if (round_time(f, tiles[f], K) < round_time(best, tiles[best], K)) best = f;
+  return best;
+}
+static void count_tiles(int M, int N, int64_t* tiles) {
+  tiles[0] += (int64_t)ceil_div(M, 32) * ceil_div(N, 64);
+  tiles[1] += (int64_t)ceil_div(M, 64) * ceil_div(N, 64);
+  tiles[2] += (int64_t)ceil_div(M, 128) * ceil_div(N, 64);
+}
+
+bool gemm_f32(int ta, int tb, SmallProblem& p, hipStream_t stream) {
+  int64_t tiles[3] = {0, 0, 0};
+  count_tiles(p.M, p.N, tiles);
+  switch (best_form(tiles, p.K)) {
+    case 0: return launch_trans<Form32x64>(ta, tb, p, stream);
+    case 1: return launch_trans<Form64x64>(ta, tb, p, stream);
+    default: return launch_trans<Form128x64>(ta, tb, p, stream);
+  }
+}
+
+bool gemm_f32_grouped(SmallGroup& g, hipStream_t stream) {
+  int64_t tiles[3] = {0, 0, 0};
+  int K = g.p[0].K;
+  for (int i = 0; i < g.n; ++i) {
+    count_tiles(g.p[i].M, g.p[i].N, tiles);
+    K = min(K, g.p[i].K);
+  }
+  switch (best_form(tiles, K)) {
+    case 0: return launch_group<Form32x64>(g, stream);
+    case 1: return launch_group<Form64x64>(g, stream);
+    default: return launch_group<Form128x64>(g, stream);
+  }
+}
+
+}  // namespace po

@@ -114,10 +114,10 @@ bool gemm_generic(int dtype, int trans_a, int trans_b, int M, int N, int K, cons
 }
 
 // Whether the vector kernel beats the 64 x 64 matrix-core tiles: a K that fills no more than a chunk or two of them (128 bytes
-// of a row each, loaded and multiplied whole) under many tiles.  vector / matrix cores, us, fp32 weight gradients: 1024 x 512,
-// K 1 / 16 / 24 7.0 / 8.6, 7.6 / 8.5, 9.9 / 8.5 (fewer tiles: 256 x 1024, K 16 7.6 / 5.0); 4096 x 4096, K 16 / 32 / 40 / 64
-// 40.8 / 51.0, 48.3 / 51.0, 53.4 / 64.9, 64.8 / 65.3; 4096 x 2048, K 32 / 40 30.5 / 28.5, 34.4 / 36.1.  Forward products alike (2048 x 512,
-// K 4 6.3 / 8.2).  bf16, 1032 x 4104, K 8 / 24 7.9 / 9.6, 10.0 / 9.6; its weight gradients have better kernels.
+// of a row each, loaded and multiplied whole) under many tiles.  vector / matrix cores, us: fp32 weight gradients 1024 x 512,
+// K 16 / 20 8.3 / 5.0, 10.3 / 5.0; 4096 x 4096, K 16 / 32 / 48 / 52 43 / 41, 50 / 41, 58 / 42, 62 / 42; 4096 x 2048, K 32 / 40 32 / 20,
+// 36 / 21: since fp32 has larger tiles the line only keeps these few products (a K no layer has) on one kernel, bit for bit.
+// bf16, 1032 x 4104, K 8 / 24 7.9 / 9.6, 10.0 / 9.6; its weight gradients have better kernels.
 static bool vector_is_faster(int dtype, int trans_a, int M, int N, int K) {
   const int64_t tiles = (int64_t)ceil_div(M, 64) * ceil_div(N, 64);
   if (dtype == kBF16) return !trans_a && K <= 16 && tiles >= 1024;

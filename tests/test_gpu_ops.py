@@ -191,6 +191,31 @@ def test_gemm_small_edges(gpu_device, dtype, ta, tb, M, N, K):
     assert rel(acc, ref + 1.0) < sums + 2.0 ** -23
 
 
+# fp32 results that give every CU a tile: each of the three tiles (32 x 64 with two groups of waves, 64 x 64, 128 x 64) with
+# one chunk of K (32), chunks that leave a group without a last one, a K that ends inside a chunk and one that ends with it,
+# results that end inside a tile and with it, and rows of operands that are longer than what is used of them.
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(548, 572, 132), (548, 572, 160), (544, 576, 516), (960, 964, 4), (1024, 1024, 32),
+                                   (964, 964, 100), (1028, 964, 4), (1024, 1088, 64), (1028, 964, 292)])
+def test_gemm_f32_tiles(gpu_device, ta, tb, M, N, K):
+    """Bounds as in test_gemm_small_edges."""
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(M + N + K + ta)
+    def rand(rows, cols):  # NaNs between the rows and behind the last one
+        t = torch.full((rows * (cols + 8) + 70000,), float("nan"), device=gpu_device)[:rows * (cols + 8)].view(rows, cols + 8)
+        t[:, :cols] = torch.randn(rows, cols, generator=g, device=gpu_device)
+        return t[:, :cols]
+    A, B = rand(*((K, M) if ta else (M, K))), rand(*((N, K) if tb else (K, N)))
+    ref = (A.t() if ta else A).double() @ (B.t() if tb else B).double()
+    sums = 2.0 ** -24 * K ** 0.5 + 2.0 ** -23
+    got = torch.full((M, N), 7.0, device=gpu_device)
+    bias = torch.randn(N, generator=g, device=gpu_device)
+    po.po_op_gemm(po.PO_F32, ta, tb, M, N, K, A, A.stride(0), B, B.stride(0), bias=bias, out=got)
+    assert (got.double() - ref - bias.double()).norm() < sums * (ref + bias.double()).norm()
+    po.po_op_gemm(po.PO_F32, ta, tb, M, N, K, A, A.stride(0), B, B.stride(0), acc_f32=got)
+    assert (got.double() - 2 * ref - bias.double()).norm() < 2 * sums * (2 * ref + bias.double()).norm()
+
+
 # Short K under many tiles stays with the vector kernel, bit for bit; on the other side of the line the order of the sums is
 # another one.
 @pytest.mark.parametrize("dtype,ta,M,N,K,vector", [("f32", 1, 1024, 512, 16, 1), ("f32", 1, 1024, 512, 20, 0),
