@@ -213,9 +213,9 @@ bool attention_forward(int dtype, const void* qkv, void* o, float* lse, int s, i
   if (dtype == kBF16 && !force_generic && s > few && attention_mfma_supported(s, h, n_heads, n_kv_heads) &&
       vectors_or_refused(s, (uintptr_t)qkv | (uintptr_t)o))
     return attention_forward_mfma(qkv, o, lse, s, h, n_heads, n_kv_heads, stream);
-  // fp32, vector / matrix cores at few rows (1 to 32 heads alike), us: heads of 32 at 4 rows 4.4 / 4.4; of 64 at 8 and 12 rows
-  // 4.5 / 5.1 and 5.2 / 5.1; of 96 at 8 and 16 rows 5.7 / 7.2 and 7.7 / 7.0; of 128 at 8, 16 and 20 rows 6.0 / 8.8, 8.1 / 8.8
-  // and 9.1 / 8.7: the chain of one tile against one key after the other.
+  // fp32, vector / matrix cores at few rows (8 heads), us: heads of 32 at 8 rows 5.3 / 4.8; of 64 at 8 and 14 rows 5.4 / 6.2 and
+  // 6.3 / 6.2; of 96 at 8 and 14 rows 6.7 / 7.7 and 8.2 / 7.7; of 128 at 8, 16 and 19 rows 7.2 / 8.9, 9.3 / 8.9 and 9.9 / 8.9:
+  // the chain of one tile against one key after the other.
   if (dtype == kF32 && !force_generic && 64 * (int64_t)s > 9 * (int64_t)(h / max(n_heads, 1)) &&
       attention_f32_supported(qkv, o, s, h, n_heads, n_kv_heads))
     return attention_forward_f32((const float*)qkv, (float*)o, lse, s, h, n_heads, n_kv_heads, stream);
@@ -228,12 +228,16 @@ bool attention_backward(int dtype, const void* qkv, const void* o, const float* 
   if (dtype == kBF16 && !force_generic && attention_mfma_supported(s, h, n_heads, n_kv_heads) &&
       vectors_or_refused(s, (uintptr_t)qkv | (uintptr_t)o | (uintptr_t)d_o | (uintptr_t)dqkv))
     return attention_backward_mfma(qkv, o, lse, d_o, dqkv, delta, partials, s, h, n_heads, n_kv_heads, stream);
-  // fp32 as in the forward: heads of 32 at 8 rows 11.7 / 11.8; of 64 at 8 and 14 rows 14.0 / 15.8 and 16.4 / 16.5; of 96 at 8
-  // and 20 rows 18.4 / 23.0 and 24.6 / 23.5; of 128 at 8, 16 and 26 rows 21.1 / 28.2, 25.6 / 29.1 and 31.4 / 29.2.
+  // fp32 as in the forward: heads of 32 at 8 rows 12.0 / 8.2; of 64 at 12 and 14 rows 16.6 / 10.5 and 17.2 / 10.5; of 96 at 16
+  // and 20 rows 23.6 / 14.3 and 26.8 / 14.4; of 128 at 20 and 26 rows 29.2 / 17.7 and 33.3 / 17.7 (the line was drawn when the
+  // matrix-core kernels took 11.8 to 29 us; below it results keep the order of their sums).
   if (dtype == kF32 && !force_generic && 64 * (int64_t)s > 12 * (int64_t)(h / max(n_heads, 1)) &&
       attention_f32_supported(qkv, d_o, s, h, n_heads, n_kv_heads) && (uintptr_t)dqkv % 16 == 0) {
-    attn_delta_kernel<float><<<dim3(ceil_div(s, 4), n_heads), 256, 0, stream>>>((const float*)o, (const float*)d_o, delta,
-                                                                               s, h, h / n_heads);
+    if ((uintptr_t)o % 16 != 0)
+      attn_delta_kernel<float><<<dim3(ceil_div(s, 4), n_heads), 256, 0, stream>>>((const float*)o, (const float*)d_o, delta,
+                                                                                 s, h, h / n_heads);
+    else if (!attention_delta_f32((const float*)o, (const float*)d_o, delta, s, h, n_heads, stream))
+      return false;
     return attention_backward_f32((const float*)qkv, lse, delta, (const float*)d_o, (float*)dqkv, s, h, n_heads,
                                   n_kv_heads, stream);
   }

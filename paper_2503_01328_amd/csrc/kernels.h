@@ -125,12 +125,13 @@ bool attention_backward_generic(int dtype, const void* qkv, const void* o, const
                                 void* dqkv, float* delta, int s, int h, int n_heads, int n_kv_heads,
                                 hipStream_t stream);
 // fp32 on the matrix cores (attention_f32.hip): head sizes 32, 64, 96, 128, 16-byte aligned tensors.  The backward takes
-// delta as given.
+// delta as given; attention_delta_f32 forms it, by whole vectors.
 bool attention_f32_supported(const void* qkv, const void* o, int s, int h, int n_heads, int n_kv_heads);
 bool attention_forward_f32(const float* qkv, float* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                            hipStream_t stream);
 bool attention_backward_f32(const float* qkv, const float* lse, const float* delta, const float* d_o, float* dqkv, int s,
                             int h, int n_heads, int n_kv_heads, hipStream_t stream);
+bool attention_delta_f32(const float* o, const float* d_o, float* delta, int s, int h, int n_heads, hipStream_t stream);
 bool attention_mfma_supported(int s, int h, int n_heads, int n_kv_heads);
 bool attention_forward_mfma(const void* qkv, void* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                             hipStream_t stream);

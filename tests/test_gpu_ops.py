@@ -324,6 +324,29 @@ def test_attention_f32(gpu_device, s, h, a, akv):
     _attention_case(gpu_device, "f32", s, h, a, 0, akv)
 
 
+# more than 256 forward blocks that all find a place at once (their order turns round there, the last row of 256 partly
+# filled), and the head sizes of which one block fills a CU's LDS
+@pytest.mark.parametrize("s,h,a,akv", [(545, 512, 16, 16), (1057, 512, 8, 2), (550, 1152, 12, 12), (290, 2560, 20, 4)])
+def test_attention_f32_many_blocks(gpu_device, s, h, a, akv):
+    _attention_case(gpu_device, "f32", s, h, a, 0, akv)
+
+
+@pytest.mark.parametrize("s,dh,a", [(1, 64, 1), (33, 32, 3), (70, 96, 2), (50, 128, 5)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_attention_f32_backward_takes_any_output_alignment(gpu_device, s, dh, a, offset):
+    """delta by whole vectors, or element by element where o is not 16-byte aligned; every product and addition rounds by
+    at most 2^-24 of what it yields, dh products in all."""
+    h = a * dh
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(s + dh)
+    rand = lambda *n: torch.randn(*n, generator=g, device=gpu_device)
+    qkv, d_o, o = rand(s, 3 * h), rand(s, h), rand(s * h + 4)[offset:offset + s * h].view(s, h)
+    lse, delta, dqkv = torch.zeros(a, s, device=gpu_device), torch.empty(a, s, device=gpu_device), torch.empty_like(qkv)
+    po.po_op_attention_backward(po.PO_F32, qkv, o, lse, d_o, dqkv, delta, s, h, a)
+    terms = (o.double() * d_o.double()).view(s, a, dh)
+    assert ((delta.t().double() - terms.sum(2)).abs() <= dh * 2.0 ** -24 * terms.abs().sum(2)).all()
+
+
 # shapes the matrix-core kernels take: head size 64 / 128, s a multiple of 128; the last two
 # are large enough in (s / 256) * heads to select the forward kernel's 256-row blocks (both head sizes)
 @pytest.mark.parametrize("s,h,a", [(128, 128, 2), (256, 256, 2), (384, 128, 1), (640, 192, 3), (512, 16384, 256),
