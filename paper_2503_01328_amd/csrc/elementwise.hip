@@ -1,6 +1,6 @@
 // HBM-bound kernels of the stage: LayerNorm forward / recompute+backward,
 // deterministic column reductions (bias and LayerNorm parameter gradients),
-// embedding, activation pack/unpack, fills and copies.
+// embedding, activation pack/unpack, fills.
 //
 // LayerNorm rows are reduced with wavefront (64-lane) shuffles: one wave owns
 // one row, lanes read 16 bytes each, so a row of h elements is covered by
@@ -25,7 +25,8 @@ void set_error(const char* fmt, ...) {
 const char* get_error() { return g_error; }
 
 // --------------------------------------------------------------------------
-// LayerNorm forward: y = (x - mean) * rstd * gain + shift, one wave per row.
+// LayerNorm forward: y = (x - mean) * rstd * gain + shift, one wave per row.  copy (may be null): x as well, for a caller
+// that keeps it (2048 rows of 2048: a copy kernel of its own took 18 us at the start of a pass).
 // --------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ void row_stats(const T* xr, int h, int lane, float eps, float& mean, float& rstd) {
@@ -49,10 +50,10 @@ __device__ __forceinline__ void row_stats(const T* xr, int h, int lane, float ep
   rstd = 1.0f / sqrtf(wave_sum(sq) / (float)h + eps);
 }
 
-template <typename T>
+template <typename T, bool COPY>
 __global__ __launch_bounds__(256) void ln_forward_kernel(const T* __restrict__ x, const T* __restrict__ gain,
                                                          const T* __restrict__ shift, T* __restrict__ y, int rows,
-                                                         int h, float eps) {
+                                                         int h, float eps, T* __restrict__ copy) {
   constexpr int V = Vec16<T>::N;
   int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   int lane = threadIdx.x & 63;
@@ -67,15 +68,16 @@ __global__ __launch_bounds__(256) void ln_forward_kernel(const T* __restrict__ x
     for (int i = 0; i < V; ++i)
       o.v[i] = from_f32<T>((to_f32(v.v[i]) - mean) * rstd * to_f32(g.v[i]) + to_f32(b.v[i]));
     store16(yr + c, o);
+    if (COPY) store16(copy + (size_t)row * h + c, v);
   }
 }
 
 // Same arithmetic in the same order with the row held in registers: VPL 16-byte vectors per lane, one pass
 // over memory.  Used when h is VPL * 64 vectors exactly.
-template <typename T, int VPL>
+template <typename T, int VPL, bool COPY>
 __global__ __launch_bounds__(256) void ln_forward_cached_kernel(const T* __restrict__ x, const T* __restrict__ gain,
                                                                 const T* __restrict__ shift, T* __restrict__ y,
-                                                                int rows, int h, float eps) {
+                                                                int rows, int h, float eps, T* __restrict__ copy) {
   constexpr int V = Vec16<T>::N;
   int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   int lane = threadIdx.x & 63;
@@ -108,6 +110,7 @@ __global__ __launch_bounds__(256) void ln_forward_cached_kernel(const T* __restr
     for (int i = 0; i < V; ++i)
       o.v[i] = from_f32<T>((to_f32(xv[j].v[i]) - mean) * rstd * to_f32(g.v[i]) + to_f32(b.v[i]));
     store16(yr + c, o);
+    if (COPY) store16(copy + (size_t)row * h + c, xv[j]);
   }
 }
 
@@ -133,35 +136,33 @@ static int cached_vpl(int h) {
     default: CALL(16); break;    \
   }
 
+template <typename T, bool COPY>
+static bool ln_forward(const void* x, const void* gain, const void* shift, void* y, int rows, int h, float eps,
+                       hipStream_t stream, void* copy) {
+  dim3 grid(ceil_div(rows, 4)), block(256);
+  if (const int vpl = cached_vpl<T>(h)) {
+#define PO_LNF(N) ln_forward_cached_kernel<T, N, COPY><<<grid, block, 0, stream>>>( \
+      (const T*)x, (const T*)gain, (const T*)shift, (T*)y, rows, h, eps, (T*)copy)
+    PO_VPL_SWITCH(vpl, PO_LNF)
+#undef PO_LNF
+    return launch_ok("ln_forward_cached_kernel");
+  }
+  ln_forward_kernel<T, COPY><<<grid, block, 0, stream>>>((const T*)x, (const T*)gain, (const T*)shift, (T*)y, rows, h, eps,
+                                                         (T*)copy);
+  return launch_ok("ln_forward_kernel");
+}
+
 bool layernorm_forward(int dtype, const void* x, const void* gain, const void* shift, void* y, int rows, int h,
-                       float eps, hipStream_t stream) {
+                       float eps, hipStream_t stream, void* copy) {
   if (rows <= 0 || h <= 0 || h % 8 != 0) {
     set_error("layernorm_forward: rows=%d h=%d (h must be a positive multiple of 8)", rows, h);
     return false;
   }
-  dim3 grid(ceil_div(rows, 4)), block(256);
-  int vpl = dtype == kF32 ? cached_vpl<float>(h) : cached_vpl<bf16>(h);
-  if (vpl) {
-#define PO_LNF_F32(N) ln_forward_cached_kernel<float, N><<<grid, block, 0, stream>>>( \
-      (const float*)x, (const float*)gain, (const float*)shift, (float*)y, rows, h, eps)
-#define PO_LNF_BF16(N) ln_forward_cached_kernel<bf16, N><<<grid, block, 0, stream>>>( \
-      (const bf16*)x, (const bf16*)gain, (const bf16*)shift, (bf16*)y, rows, h, eps)
-    if (dtype == kF32) {
-      PO_VPL_SWITCH(vpl, PO_LNF_F32)
-    } else {
-      PO_VPL_SWITCH(vpl, PO_LNF_BF16)
-    }
-#undef PO_LNF_F32
-#undef PO_LNF_BF16
-    return launch_ok("ln_forward_cached_kernel");
-  }
   if (dtype == kF32)
-    ln_forward_kernel<float><<<grid, block, 0, stream>>>((const float*)x, (const float*)gain, (const float*)shift,
-                                                         (float*)y, rows, h, eps);
-  else
-    ln_forward_kernel<bf16><<<grid, block, 0, stream>>>((const bf16*)x, (const bf16*)gain, (const bf16*)shift,
-                                                        (bf16*)y, rows, h, eps);
-  return launch_ok("ln_forward_kernel");
+    return copy ? ln_forward<float, true>(x, gain, shift, y, rows, h, eps, stream, copy)
+                : ln_forward<float, false>(x, gain, shift, y, rows, h, eps, stream, copy);
+  return copy ? ln_forward<bf16, true>(x, gain, shift, y, rows, h, eps, stream, copy)
+              : ln_forward<bf16, false>(x, gain, shift, y, rows, h, eps, stream, copy);
 }
 
 // --------------------------------------------------------------------------
@@ -169,8 +170,8 @@ bool layernorm_forward(int dtype, const void* x, const void* gain, const void* s
 //   xhat = (x - mean) rstd ; dxhat = dn * gain
 //   dx = dres + rstd (dxhat - mean(dxhat) - xhat mean(dxhat xhat))
 //   dgain += colsum(dn * xhat) ; dshift += colsum(dn)
-// Kernel 1 (wave per row) writes dx and the row statistics; kernel 2 builds
-// per-row-chunk column partials; kernel 3 adds them in a fixed tree.
+// The rows kernel (wave per row) writes dx and the row statistics; the column
+// reductions below form the parameter gradients from those.
 // --------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void ln_backward_rows_kernel(const T* __restrict__ dn, const T* __restrict__ x,
@@ -320,90 +321,6 @@ __global__ __launch_bounds__(256, (ln_backward_waves<T, VPL>())) void ln_backwar
   }
 }
 
-// Block: 256 threads = 4 waves; a lane owns 2 adjacent columns of a 128-column
-// tile; wave w walks rows chunk_start + w, + 4, ...  Partials: [chunk][2][h].
-template <typename T>
-__global__ __launch_bounds__(256) void ln_backward_cols_kernel(const T* __restrict__ dn, const T* __restrict__ x,
-                                                               const float* __restrict__ stats,
-                                                               float* __restrict__ partials, int rows, int h,
-                                                               int rows_per_chunk) {
-  __shared__ float red[4][128][2];
-  int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int col = blockIdx.x * 128 + lane * 2;
-  int r0 = blockIdx.y * rows_per_chunk;
-  int r1 = min(rows, r0 + rows_per_chunk);
-  float g0 = 0.f, g1 = 0.f, b0 = 0.f, b1 = 0.f;
-  if (col < h) {
-    for (int r = r0 + wave; r < r1; r += 4) {
-      float mean = stats[2 * r], rstd = stats[2 * r + 1];
-      float d0 = to_f32(dn[(size_t)r * h + col]), d1 = to_f32(dn[(size_t)r * h + col + 1]);
-      float x0 = to_f32(x[(size_t)r * h + col]), x1 = to_f32(x[(size_t)r * h + col + 1]);
-      g0 += d0 * (x0 - mean) * rstd;
-      g1 += d1 * (x1 - mean) * rstd;
-      b0 += d0;
-      b1 += d1;
-    }
-  }
-  red[wave][lane * 2][0] = g0;
-  red[wave][lane * 2 + 1][0] = g1;
-  red[wave][lane * 2][1] = b0;
-  red[wave][lane * 2 + 1][1] = b1;
-  __syncthreads();
-  if (threadIdx.x < 128) {
-    int c = blockIdx.x * 128 + threadIdx.x;
-    if (c < h) {
-      float sg = 0.f, sb = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        sg += red[w][threadIdx.x][0];
-        sb += red[w][threadIdx.x][1];
-      }
-      partials[((size_t)blockIdx.y * 2 + 0) * h + c] = sg;
-      partials[((size_t)blockIdx.y * 2 + 1) * h + c] = sb;
-    }
-  }
-}
-
-// Sums up to 64 chunk partials per column in a fixed tree: a block owns 64 columns, thread (part, c) adds the
-// chunks part, part + 4, ... in that order (its loads are independent, so they are all in flight together), and
-// thread c of part 0 adds the four parts in order.  Partials are laid out [chunk][N_OUT][n]; plane o is added
-// into out0 (o = 0) or out1 (o = 1).
-template <int N_OUT>
-__global__ __launch_bounds__(256) void chunk_partials_final_kernel(const float* __restrict__ partials,
-                                                                   float* __restrict__ out0,
-                                                                   float* __restrict__ out1, int n, int n_chunks) {
-  __shared__ float red[N_OUT][4][64];
-  int part = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int c = blockIdx.x * 64 + lane;
-  float acc[N_OUT];
-#pragma unroll
-  for (int o = 0; o < N_OUT; ++o) acc[o] = 0.f;
-  if (c < n) {
-    float v[N_OUT][16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      int k = part + 4 * i;
-#pragma unroll
-      for (int o = 0; o < N_OUT; ++o) v[o][i] = k < n_chunks ? partials[((size_t)k * N_OUT + o) * n + c] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-#pragma unroll
-      for (int o = 0; o < N_OUT; ++o) acc[o] += v[o][i];
-  }
-#pragma unroll
-  for (int o = 0; o < N_OUT; ++o) red[o][part][lane] = acc[o];
-  __syncthreads();
-  if (part == 0 && c < n) {
-#pragma unroll
-    for (int o = 0; o < N_OUT; ++o) {
-      float s = ((red[o][0][lane] + red[o][1][lane]) + red[o][2][lane]) + red[o][3][lane];
-      float* out = o == 0 ? out0 : out1;
-      out[c] += s;
-    }
-  }
-}
-
 static int reduce_chunks(int rows) { return max(1, min(64, ceil_div(rows, 32))); }
 
 size_t layernorm_backward_workspace(int rows, int h) {
@@ -421,9 +338,7 @@ bool layernorm_backward(int dtype, const void* dn, const void* x, const void* ga
   }
   float* stats = workspace;
   float* partials = workspace + (size_t)rows * 2;
-  int n_chunks = reduce_chunks(rows);
-  int rows_per_chunk = ceil_div(rows, n_chunks);
-  dim3 g1(ceil_div(rows, 4)), g2(ceil_div(h, 128), n_chunks), g3(ceil_div(h, 64));
+  dim3 g1(ceil_div(rows, 4));
   int vpl = dtype == kF32 ? cached_vpl<float>(h) : cached_vpl<bf16>(h);
   if ((parts & kLnInputGrad) && vpl) {
 #define PO_LNB_F32(N) ln_backward_rows_cached_kernel<float, N><<<g1, 256, 0, stream>>>( \
@@ -450,13 +365,8 @@ bool layernorm_backward(int dtype, const void* dn, const void* x, const void* ga
     if (n_out && !layernorm_forward(dtype, x, gain, shift, n_out, rows, h, eps, stream)) return false;
   }
   if (parts & kLnParamGrad) {  // dgain, dshift from (dn, x) and the statistics an input-gradient call left
-    if (dtype == kF32)
-      ln_backward_cols_kernel<float><<<g2, 256, 0, stream>>>((const float*)dn, (const float*)x, stats, partials,
-                                                             rows, h, rows_per_chunk);
-    else
-      ln_backward_cols_kernel<bf16><<<g2, 256, 0, stream>>>((const bf16*)dn, (const bf16*)x, stats, partials, rows,
-                                                            h, rows_per_chunk);
-    chunk_partials_final_kernel<2><<<g3, 256, 0, stream>>>(partials, dgain, dshift, h, n_chunks);
+    const ReduceJob job{dn, x, stats, dgain, dshift, partials, h};
+    if (!column_reductions(dtype, &job, 1, rows, stream)) return false;
   }
   return launch_ok("layernorm_backward kernels");
 }
@@ -464,32 +374,6 @@ bool layernorm_backward(int dtype, const void* dn, const void* x, const void* ga
 // --------------------------------------------------------------------------
 // acc[n] += sum over rows of x[r, n]   (bias gradients)
 // --------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict__ x, float* __restrict__ partials,
-                                                             int rows, int n, int rows_per_chunk) {
-  __shared__ float red[4][128];
-  int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int col = blockIdx.x * 128 + lane * 2;
-  int r0 = blockIdx.y * rows_per_chunk;
-  int r1 = min(rows, r0 + rows_per_chunk);
-  float a0 = 0.f, a1 = 0.f;
-  if (col < n) {
-    for (int r = r0 + wave; r < r1; r += 4) {
-      a0 += to_f32(x[(size_t)r * n + col]);
-      a1 += to_f32(x[(size_t)r * n + col + 1]);
-    }
-  }
-  red[wave][lane * 2] = a0;
-  red[wave][lane * 2 + 1] = a1;
-  __syncthreads();
-  if (threadIdx.x < 128) {
-    int c = blockIdx.x * 128 + threadIdx.x;
-    if (c < n)
-      partials[(size_t)blockIdx.y * n + c] =
-          red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
-  }
-}
-
 size_t colsum_workspace(int rows, int n) { return (size_t)reduce_chunks(rows) * n * sizeof(float); }
 
 bool colsum_accumulate(int dtype, const void* x, float* acc, float* workspace, int rows, int n,
@@ -498,15 +382,8 @@ bool colsum_accumulate(int dtype, const void* x, float* acc, float* workspace, i
     set_error("colsum_accumulate: rows=%d n=%d workspace=%p (n must be even)", rows, n, (void*)workspace);
     return false;
   }
-  int n_chunks = reduce_chunks(rows);
-  int rows_per_chunk = ceil_div(rows, n_chunks);
-  dim3 g(ceil_div(n, 128), n_chunks);
-  if (dtype == kF32)
-    colsum_partial_kernel<float><<<g, 256, 0, stream>>>((const float*)x, workspace, rows, n, rows_per_chunk);
-  else
-    colsum_partial_kernel<bf16><<<g, 256, 0, stream>>>((const bf16*)x, workspace, rows, n, rows_per_chunk);
-  chunk_partials_final_kernel<1><<<ceil_div(n, 64), 256, 0, stream>>>(workspace, acc, nullptr, n, n_chunks);
-  return launch_ok("colsum kernels");
+  const ReduceJob job{x, nullptr, nullptr, acc, nullptr, workspace, n};
+  return column_reductions(dtype, &job, 1, rows, stream);
 }
 
 // --------------------------------------------------------------------------
@@ -583,7 +460,7 @@ __global__ __launch_bounds__(256) void reduce_batch_partial_kernel(ReduceBatch b
   int r0 = blockIdx.y * rows_per_chunk;
   int r1 = min(rows, r0 + rows_per_chunk);
   const T* a = static_cast<const T*>(job.a);
-  if (job.x == nullptr) {  // plain column sum, as colsum_partial_kernel
+  if (job.x == nullptr) {  // plain column sum
     float a0 = 0.f, a1 = 0.f;
     if (col < n) {
       for (int r = r0 + wave; r < r1; r += 4) {
@@ -600,7 +477,7 @@ __global__ __launch_bounds__(256) void reduce_batch_partial_kernel(ReduceBatch b
         job.partials[(size_t)blockIdx.y * n + c] =
             red[0][threadIdx.x][0] + red[1][threadIdx.x][0] + red[2][threadIdx.x][0] + red[3][threadIdx.x][0];
     }
-  } else {  // LayerNorm gain / shift partials, as ln_backward_cols_kernel
+  } else {  // LayerNorm gain / shift partials
     const T* x = static_cast<const T*>(job.x);
     const float* stats = job.stats;
     float g0 = 0.f, g1 = 0.f, b0 = 0.f, b1 = 0.f;
@@ -702,7 +579,10 @@ __global__ __launch_bounds__(256) void reduce_batch_partial_vec_kernel(ReduceBat
   }
 }
 
-// The fixed tree of chunk_partials_final_kernel, per job with one or two output planes.
+// Sums up to 64 chunk partials per column in a fixed tree: a block owns 64 columns of a job, thread (part, c) adds the
+// chunks part, part + 4, ... in that order (its loads are independent, so they are all in flight together), and
+// thread c of part 0 adds the four parts in order.  Partials are laid out [chunk][planes][n], one plane for a sum, two
+// for a LayerNorm.
 __global__ __launch_bounds__(256) void reduce_batch_final_kernel(ReduceBatch b, int n_chunks) {
   __shared__ float red[2][4][64];
   int j = 0;
@@ -737,7 +617,106 @@ __global__ __launch_bounds__(256) void reduce_batch_final_kernel(ReduceBatch b, 
   }
 }
 
+// Few rows: one launch instead of two and no partials in memory.  A block of sixteen waves owns 64 columns of a job over ALL
+// rows, a lane one 16-byte vector of a row, 128 (fp32: 64) rows at once; the loads of four rows are in flight per lane and
+// added before they join the column's sum.  Bound by the round trips of a lane's rows, hence the many waves.
+template <typename T>
+__global__ __launch_bounds__(1024) void reduce_batch_direct_kernel(ReduceBatch b, int rows) {
+  constexpr int V = Vec16<T>::N, LPR = 64 / V, SLOTS = 1024 / LPR;
+  __shared__ float red[16][2][64];
+  int j = 0;
+  while (j + 1 < b.n_jobs && (int)blockIdx.x >= b.first64[j + 1]) ++j;
+  const ReduceJob& job = b.job[j];
+  const int n = job.n, col0 = ((int)blockIdx.x - b.first64[j]) * 64;
+  const int cl = (int)threadIdx.x % LPR * V, slot = threadIdx.x / LPR;
+  const bool inside = col0 + cl < n, ln = job.x != nullptr;
+  const T* a = static_cast<const T*>(job.a) + col0 + cl;
+  const T* x = static_cast<const T*>(job.x) + col0 + cl;
+  float s0[V], s1[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) s0[i] = s1[i] = 0.f;
+  if (inside && !ln) {
+    constexpr int AT_ONCE = 4;
+    for (int r0 = slot; r0 < rows; r0 += AT_ONCE * SLOTS) {
+      Vec16<T> d[AT_ONCE];
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u) d[u] = load16(a + (size_t)min(r0 + u * SLOTS, rows - 1) * n);
+      float p[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) p[i] = 0.f;
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u)
+        if (r0 + u * SLOTS < rows)
+#pragma unroll
+          for (int i = 0; i < V; ++i) p[i] += to_f32(d[u].v[i]);
+#pragma unroll
+      for (int i = 0; i < V; ++i) s0[i] += p[i];
+    }
+  } else if (inside) {
+    constexpr int AT_ONCE = 4;
+    const float* stats = job.stats;
+    for (int r0 = slot; r0 < rows; r0 += AT_ONCE * SLOTS) {
+      Vec16<T> d[AT_ONCE], xv[AT_ONCE];
+      float mean[AT_ONCE], rstd[AT_ONCE];
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u) {
+        const size_t r = min(r0 + u * SLOTS, rows - 1);
+        d[u] = load16(a + r * n);
+        xv[u] = load16(x + r * n);
+        mean[u] = stats[2 * r];
+        rstd[u] = stats[2 * r + 1];
+      }
+      float p0[V], p1[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) p0[i] = p1[i] = 0.f;
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u)
+        if (r0 + u * SLOTS < rows)
+#pragma unroll
+          for (int i = 0; i < V; ++i) {
+            const float dv = to_f32(d[u].v[i]);
+            p0[i] += dv * (to_f32(xv[u].v[i]) - mean[u]) * rstd[u];
+            p1[i] += dv;
+          }
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        s0[i] += p0[i];
+        s1[i] += p1[i];
+      }
+    }
+  }
+#pragma unroll
+  for (int m = LPR; m < kWave; m <<= 1)
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      s0[i] += __shfl_xor(s0[i], m);
+      if (ln) s1[i] += __shfl_xor(s1[i], m);
+    }
+  if ((threadIdx.x & 63) < LPR)
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      red[threadIdx.x >> 6][0][cl + i] = s0[i];
+      red[threadIdx.x >> 6][1][cl + i] = s1[i];
+    }
+  __syncthreads();
+  const int c = threadIdx.x & 63, plane = threadIdx.x >> 6;
+  if (plane < (ln ? 2 : 1) && col0 + c < n) {
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) part[q] += red[4 * k + q][plane][c];
+    (plane ? job.out1 : job.out0)[col0 + c] += (part[0] + part[1]) + (part[2] + part[3]);
+  }
+}
+
 size_t column_reductions_workspace(int rows, int n) { return (size_t)reduce_chunks(rows) * n * sizeof(float); }
+
+// Whether one launch over all rows beats partials per chunk of rows and their sum.  two / one, us: column sums of 3328
+// columns, 100 / 512 / 4096 rows, bf16 5.8 / 4.5, 6.0 / 4.8, 8.6 / 11.4, fp32 5.7 / 3.7, 6.0 / 4.2, 14.3 / 18.7; of 26624, 100 rows
+// 6.1 / 6.7, fp32 6.1 / 4.3.  LayerNorm backward of 1024 columns, 100 / 512 / 1024 rows 10.0 / 9.2, 10.5 / 10.5, 11.1 / 12.5, fp32
+// 10.4 / 8.5, 11.0 / 10.6, 11.7 / 13.9: the round trips of its two tensors' rows are what a block without chunks waits for.
+static bool one_launch(int dtype, int rows, int blocks) { return rows <= 512 && (dtype == kF32 || blocks <= 256); }
 
 bool column_reductions(int dtype, const ReduceJob* jobs, int n_jobs, int rows, hipStream_t stream) {
   if (n_jobs < 1 || n_jobs > kMaxReduceJobs || rows <= 0 || !jobs) {
@@ -771,6 +750,11 @@ bool column_reductions(int dtype, const ReduceJob* jobs, int n_jobs, int rows, h
   bool vec = true;  // 16-byte loads need whole vectors per row and aligned rows
   for (int j = 0; j < n_jobs; ++j)
     vec = vec && jobs[j].n % v == 0 && (uintptr_t)jobs[j].a % 16 == 0 && (uintptr_t)jobs[j].x % 16 == 0;
+  if (vec && one_launch(dtype, rows, b.first64[n_jobs])) {
+    if (dtype == kF32) reduce_batch_direct_kernel<float><<<b.first64[n_jobs], 1024, 0, stream>>>(b, rows);
+    else reduce_batch_direct_kernel<bf16><<<b.first64[n_jobs], 1024, 0, stream>>>(b, rows);
+    return launch_ok("reduce_batch_direct_kernel");
+  }
   if (vec && dtype == kF32)
     reduce_batch_partial_vec_kernel<float><<<g, 256, 0, stream>>>(b, rows, rows_per_chunk);
   else if (vec)
@@ -798,20 +782,31 @@ __global__ void embedding_forward_kernel(const int32_t* __restrict__ tok, const 
     x[(size_t)p * h + c] = from_f32<T>(to_f32(wte[(size_t)t * h + c]) + to_f32(wpe[(size_t)p * h + c]));
 }
 
+// Block `row` < vocab finds the positions of its token 256 at a time (one comparison a thread) and adds their gradients in
+// position order.
 template <typename T>
-__global__ void embedding_backward_kernel(const int32_t* __restrict__ tok, const T* __restrict__ dx,
-                                          float* __restrict__ dwte, float* __restrict__ dwpe, int s, int h,
-                                          int vocab) {
-  int row = blockIdx.x;
-  if (row < vocab) {
-    for (int p = 0; p < s; ++p) {
-      int t = min(max(tok[p], 0), vocab - 1);
-      if (t != row) continue;  // uniform across the block
-      for (int c = threadIdx.x; c < h; c += blockDim.x) dwte[(size_t)row * h + c] += to_f32(dx[(size_t)p * h + c]);
-    }
-  } else {
-    int p = row - vocab;
-    for (int c = threadIdx.x; c < h; c += blockDim.x) dwpe[(size_t)p * h + c] += to_f32(dx[(size_t)p * h + c]);
+__global__ __launch_bounds__(256) void embedding_backward_kernel(const int32_t* __restrict__ tok, const T* __restrict__ dx,
+                                                                 float* __restrict__ dwte, float* __restrict__ dwpe, int s,
+                                                                 int h, int vocab) {
+  __shared__ uint64_t hits[4];
+  const int row = blockIdx.x;
+  if (row >= vocab) {
+    const int p = row - vocab;
+    for (int c = threadIdx.x; c < h; c += 256) dwpe[(size_t)p * h + c] += to_f32(dx[(size_t)p * h + c]);
+    return;
+  }
+  for (int p0 = 0; p0 < s; p0 += 256) {
+    const int at = p0 + (int)threadIdx.x;
+    const bool hit = at < s && min(max(tok[at], 0), vocab - 1) == row;
+    const uint64_t mask = __ballot(hit);
+    if ((threadIdx.x & 63) == 0) hits[threadIdx.x >> 6] = mask;
+    if (!__syncthreads_or(hit)) continue;
+    for (int w = 0; w < 4; ++w)
+      for (uint64_t m = hits[w]; m; m &= m - 1) {
+        const int p = p0 + 64 * w + __ffsll((unsigned long long)m) - 1;
+        for (int c = threadIdx.x; c < h; c += 256) dwte[(size_t)row * h + c] += to_f32(dx[(size_t)p * h + c]);
+      }
+    __syncthreads();
   }
 }
 
@@ -946,7 +941,7 @@ bool dropout_apply(int dtype, const void* x, const void* residual, void* out, in
 }
 
 // --------------------------------------------------------------------------
-// Fill / copy
+// Fill
 // --------------------------------------------------------------------------
 __global__ void fill_u32_kernel(uint32_t* p, uint32_t pattern, size_t n) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -964,29 +959,6 @@ bool fill_u32(void* p, uint32_t pattern, size_t bytes, hipStream_t stream) {
   int grid = (int)min((size_t)4096, (n + 255) / 256);
   fill_u32_kernel<<<grid, 256, 0, stream>>>((uint32_t*)p, pattern, n);
   return launch_ok("fill_u32_kernel");
-}
-
-__global__ __launch_bounds__(256) void copy16_kernel(uint4* __restrict__ dst, const uint4* __restrict__ src,
-                                                     size_t n) {
-  size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x;
-  uint4 v[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-    if (i + u * 256 < n) v[u] = src[i + u * 256];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-    if (i + u * 256 < n) dst[i + u * 256] = v[u];
-}
-
-bool copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t stream) {
-  if (bytes % 16 != 0 || ((uintptr_t)dst | (uintptr_t)src) % 16 != 0) {
-    set_error("copy_bytes: %zu bytes / pointers must be multiples of 16", bytes);
-    return false;
-  }
-  if (bytes == 0) return true;
-  size_t n = bytes / 16;
-  copy16_kernel<<<(unsigned)((n + 1023) / 1024), 256, 0, stream>>>((uint4*)dst, (const uint4*)src, n);
-  return launch_ok("copy16_kernel");
 }
 
 // --------------------------------------------------------------------------

@@ -13,8 +13,9 @@ void set_error(const char* fmt, ...);
 const char* get_error();
 
 // ---- elementwise / normalisation (elementwise.hip) -------------------------
+// copy (may be null): where x goes too.
 bool layernorm_forward(int dtype, const void* x, const void* gain, const void* shift, void* y, int rows, int h,
-                       float eps, hipStream_t stream);
+                       float eps, hipStream_t stream, void* copy = nullptr);
 size_t layernorm_backward_workspace(int rows, int h);
 // parts: kLnInputGrad writes dx (= dres + LayerNorm input gradient) and the row statistics into the workspace;
 // kLnParamGrad adds the gain / shift gradients, reading the statistics an earlier or the same call left there.
@@ -29,9 +30,9 @@ bool colsum_accumulate(int dtype, const void* x, float* acc, float* workspace, i
 // The same with the partials in a device array built into the library (no workspace, nothing allocated);
 // n <= 32768.  Calls that overlap on one GPU share that array and race.
 bool colsum_accumulate_static(int dtype, const void* x, float* acc, int rows, int n, hipStream_t stream);
-// Several column reductions over the same number of rows in two launches (all partial sums, then all final
-// sums) instead of two per tensor: the bias gradients and LayerNorm gain / shift gradients of one layer.
-// Per job the arithmetic and its order are those of colsum_accumulate / layernorm_backward(kLnParamGrad).
+// Several column reductions over the same number of rows in one launch or two (all partial sums, then all final
+// sums) instead of as many per tensor: the bias gradients and LayerNorm gain / shift gradients of one layer.
+// colsum_accumulate and layernorm_backward(kLnParamGrad) are such reductions of one tensor.
 struct ReduceJob {
   const void* a;       // [rows, n] of dtype: the tensor summed over rows, or dn of a LayerNorm
   const void* x;       // LayerNorm input [rows, n]; null: plain column sum
@@ -49,7 +50,6 @@ bool embedding_forward(int dtype, const int32_t* tok, const void* wte, const voi
 bool embedding_backward(int dtype, const int32_t* tok, const void* dx, float* dwte, float* dwpe, int s, int h,
                         int vocab, hipStream_t stream);
 bool fill_u32(void* p, uint32_t pattern, size_t bytes, hipStream_t stream);
-bool copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t stream);
 
 constexpr int kMaxPackSegments = 48;
 bool pack_segments(const void* const* seg_ptrs, const uint64_t* seg_bytes, int n_seg, void* packed,

@@ -588,9 +588,11 @@ static DropoutSite site_of(const po_stage* st, int layer, int site, int mb) {
   return d;
 }
 
+// x_in: null, or the layer input that is not in the slab yet (the first LayerNorm reads it and leaves a copy there).
 // before_out: null, or the event to wait for before y_out is written (it lies in a slab whose last user has to end
 // first); `span` is the pass's timed span.
-static int layer_forward(po_stage* st, int layer, int mb, char* slab, void* y_out, hipEvent_t before_out, size_t* span) {
+static int layer_forward(po_stage* st, int layer, int mb, char* slab, const void* x_in, void* y_out, hipEvent_t before_out,
+                         size_t* span) {
   const po_config& c = st->cfg;
   const ParamLayout& pl = st->pl;
   const SlabLayout& sl = st->sl;
@@ -603,7 +605,8 @@ static int layer_forward(po_stage* st, int layer, int mb, char* slab, void* y_ou
   char* u = slab + sl.off_u;
   float* lse = (float*)(slab + sl.off_lse);
 
-  PO_K(layernorm_forward(dt, x, st->P(layer, pl.ln1_g), st->P(layer, pl.ln1_b), st->w_n, s, h, c.ln_eps, q));
+  PO_K(layernorm_forward(dt, x_in ? x_in : x, st->P(layer, pl.ln1_g), st->P(layer, pl.ln1_b), st->w_n, s, h, c.ln_eps, q,
+                         x_in ? x : nullptr));
   const int wq = qkv_width_of(c);  // h + 2 hkv
   Epilogue e = make_ep(wq);
   e.bias = st->P(layer, pl.b_qkv);
@@ -820,13 +823,14 @@ int stage_forward(po_stage* st, int mb, int chunk, const void* x_in, void* y_out
     PO_K(embedding_forward(c.dtype, (const int32_t*)x_in, st->params + (size_t)st->pl.emb_wte * st->E,
                            st->params + (size_t)st->pl.emb_wpe * st->E, slab0 + st->sl.off_x, c.seq, c.hidden,
                            c.vocab, st->compute));
-  } else {
-    PO_K(copy_bytes(slab0 + st->sl.off_x, x_in, st->sl.sz_x, st->compute));
+  } else if ((uintptr_t)x_in % 16 != 0) {
+    set_error("forward: x_in=%p is not 16-byte aligned", x_in);
+    return PO_E_INVAL;
   }
   for (int l = 0; l < st->Lu; ++l) {
     char* slab = st->dev_pool.bufs[u.layers[l].dev].ptr;
     void* out = (l + 1 < st->Lu) ? (void*)(st->dev_pool.bufs[u.layers[l + 1].dev].ptr + st->sl.off_x) : y_out;
-    rc = layer_forward(st, chunk * st->Lu + l, mb, slab, out, l + 1 < st->Lu ? slab_free[l + 1] : nullptr, &span);
+    rc = layer_forward(st, chunk * st->Lu + l, mb, slab, l == 0 && !embed ? x_in : nullptr, out, l + 1 < st->Lu ? slab_free[l + 1] : nullptr, &span);
     if (rc) return rc;
   }
   rc = span_end(st, st->compute, span);

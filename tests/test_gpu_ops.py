@@ -668,6 +668,30 @@ def test_colsum_accumulate(gpu_device, dtype, rows, n):
     assert max_rel_err(_np(acc) - acc0, x.astype(np.float64).sum(0)) < 1e-4
 
 
+# one launch over all rows (up to 512; bf16 up to 256 blocks of 64 columns) and the two of more: rows that leave lanes, waves and
+# a lane's four rows without work, a last block of few columns, rows that are no whole vectors
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,h", [(1, 8), (63, 72), (129, 200), (511, 64), (512, 136), (513, 136), (30, 16384), (30, 16392)])
+def test_column_reductions_of_few_rows(gpu_device, dtype, rows, h):
+    """Against fp64.  Each sum has `rows` terms, which no order of additions rounds by more than rows * 2^-24 of their
+    magnitudes' sum; a LayerNorm gain's terms are off by the statistics' rounding too, 2^-20 of theirs."""
+    code, tdt, _ = DT[dtype]
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(rows + h)
+    rand = lambda *n: torch.randn(*n, generator=g, device=gpu_device).to(tdt)
+    x, dn, dres, gain = rand(rows, h), rand(rows, h), rand(rows, h), rand(h)
+    words = max(po.po_op_layernorm_backward_workspace(rows, h), po.po_op_colsum_workspace(rows, h)) // 4
+    ws = torch.full((words,), float("nan"), device=gpu_device)
+    out = torch.zeros(3, h, device=gpu_device)
+    po.po_op_colsum_accumulate(code, dn, out[0], ws, rows, h)
+    po.po_op_layernorm_backward(code, dn, x, gain, dres, torch.empty_like(x), out[1], out[2], ws, rows, h, 1e-5)
+    d64, x64 = dn.double(), x.double()
+    xhat = (x64 - x64.mean(1, keepdim=True)) / (x64.var(1, keepdim=True, unbiased=False) + 1e-5).sqrt()
+    for got, terms, extra in ((out[0], d64, 0.0), (out[2], d64, 0.0), (out[1], d64 * xhat, 2.0 ** -20)):
+        bound = (rows * 2.0 ** -24 + extra) * (terms.abs().sum(0) + d64.abs().sum(0))
+        assert ((got.double() - terms.sum(0)).abs() <= bound).all()
+
+
 def test_pack_unpack_roundtrip_is_bit_exact(gpu_device):
     rng = np.random.default_rng(0)
     sizes = [16, 4096 + 16, 0, 1 << 20, 48, 3 * 16384 + 32]  # bytes, multiples of 16, one empty

@@ -71,6 +71,16 @@ def test_config1_tiny_gpt_fp32_against_oracle_with_full_offload(gpu_device):
         _assert_bit_identical(with_offload, _snapshot(r))
 
 
+@pytest.mark.parametrize("seq,vocab", [(256, 3), (300, 7), (520, 600)])
+def test_embedding_gradients_of_repeated_tokens(gpu_device, seq, vocab):
+    """Positions are compared with a token 256 at a time: one full group, a rest, tokens that occur in several or in none."""
+    shape = syn.StageShape(1, 1, 64, 1, 64, seq, vocab=vocab, dtype="f32", pipeline_degree=1, n_microbatches=2)
+    with StageRunner(shape) as r:
+        r.make_inputs()
+        r.run(po.PO_SCHED_1F1B, 0.0)
+        _compare(shape, r.results(), _oracle(shape, r, 2), 1e-4)
+
+
 SMALL_BF16 = syn.StageShape(2, 1, 256, 2, 1024, 384, dtype="bf16", pipeline_degree=3, n_microbatches=5)
 SMALL_BF16_RAGGED = syn.StageShape(1, 1, 192, 3, 320, 200, dtype="bf16", pipeline_degree=2, n_microbatches=3)
 
