@@ -35,7 +35,8 @@
 // Two terms give the same there, but 1.5 to 15 % where probabilities that agree in 14 bits cancel (0.1 % with three).
 // MFMAs of a tile with one, two and three terms: forward 2 : 3 : 4, backward 7 : 10 : 13.  Vector kernels -> two terms -> this
 // form, us: s 1733, 16 heads of 128: forward 2235 -> 73 -> 74, backward 20450 -> 100 -> 112; s 3000, 32 heads of 64 over 8: 5406 -> 115 -> 125 and
-// 72760 -> 278 -> 307; s 100, 16 heads of 128: 35 -> 18 and 147 -> 18.
+// 72760 -> 278 -> 307; s 100, 16 heads of 128: 35 -> 18 and 147 -> 18.  Since then (one buffer descriptor per tile, heads of 64 with
+// both products of a half tile open at once) 46 and 120, 92 and 278, 10.3 and 18.7.
 #include "attention_rows.h"
 #include "mfma_common.h"
 
@@ -93,13 +94,15 @@ __device__ __forceinline__ void load_tile_async(const bf16* __restrict__ base, i
   constexpr int PER_WAVE = tile_bytes<DH>() / (1024 * WAVES);
   constexpr int ROWS_PER_LOAD = 1024 * WAVES / (DH * 2);  // rows the WAVES waves cover with one load each
   static_assert(ROWS_PER_LOAD % 16 == 0, "swz must not change between the loads of a lane");
+  i32x4 rows{};  // one descriptor per tile: forming it takes some fifteen instructions
+  if constexpr (EDGE) rows = rows_buffer<DH>(base + (size_t)row0 * ld, ld, s - row0);
 #pragma unroll
   for (int u = 0; u < PER_WAVE; ++u) {
     const bf16* src = base + (size_t)(row0 + u * ROWS_PER_LOAD) * ld;
     unsigned lds_addr =
         (unsigned)(size_t)((void __attribute__((address_space(3)))*)(tile + (u * WAVES + wave) * 1024));
     if constexpr (EDGE)
-      buffer_to_lds(lds_addr, lane_offset, rows_buffer<DH>(src, ld, s - row0 - u * ROWS_PER_LOAD));
+      buffer_to_lds(lds_addr, lane_offset + (unsigned)(u * ROWS_PER_LOAD * ld) * 2u, rows);
     else
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr),
                    "v"(lane_offset), "s"(src)
@@ -464,27 +467,57 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
   // Slots are numbered 0 .. 2 n_it + 1, each ends with a barrier.  Group 0: matrix slot j in slot 2 j, softmax of
   // tile j in slot 2 j + 1.  Group 1: the same one slot later.
 
+  const bf16* qbase = qkv + head * DH;
+  const bf16* kbase = qkv + h + (head / group) * DH;
+  const bf16* vbase = kbase + hkv;
+  const int tile_last = nkv - 1;
+  // Piece q (1 KiB) of the tile whose first row is at src (EDGE: `rows`, its buffer); off: the lane's offset in pieces
+  // q mod 4.
+  auto load_piece = [&](const bf16* src, const i32x4& rows, char* tile, int q, unsigned off) __attribute__((always_inline)) {
+    const unsigned lds_addr = lds_byte(tile + q * 1024);
+    const int row = (q >> 2) * ROWS_PER_4K;
+    if constexpr (EDGE)
+      buffer_to_lds(lds_addr, off + (unsigned)(row * ld) * 2u, rows);
+    else
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off),
+                   "s"(src + (size_t)row * ld)
+                   : "memory");
+  };
+  // The compute waves' share of the tile from row0 on: pieces `wave`, `wave` + 8, ...
+  auto load_share = [&](const bf16* base, int row0, char* tile, unsigned off) __attribute__((always_inline)) {
+    const bf16* src = base + (size_t)row0 * ld;
+    i32x4 rows{};
+    if constexpr (EDGE) rows = rows_buffer<DH>(src, ld, s - row0);
+#pragma unroll
+    for (int q = 0; q < PIECES / 8; ++q) load_piece(src, rows, tile, 8 * q + wave, off);
+  };
+  // Q and the first K tiles (stage 0 has no V) are loaded by the compute waves, which have nothing else to do yet: the loader
+  // alone took 4 us for them and the stages after them (100 rows, 16 heads of 128 19.3 -> 15.2 us; 128 rows 9.7 -> 9.0).  256-row
+  // blocks of whole tiles do not gain (4096 rows, 32 heads of 128 143 / 144) and leave it to the loader.
+  constexpr bool SHARE = EDGE || G == 2;
+
   if (wave == 8) {  // the loader
-    const bf16* qbase = qkv + head * DH;
-    const bf16* kbase = qkv + h + (head / group) * DH;
-    const bf16* vbase = qkv + h + hkv + (head / group) * DH;
     unsigned lane_off[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) lane_off[i] = tile_lane_offset<DH>(ld, i, lane);
-    auto load_tile = [&](const bf16* base, int row0, char* tile) {
+    // EDGE: one descriptor per tile and a register of offset for each of its pieces, so that a piece is three instructions as
+    // in the other form.  With a descriptor per piece the loader set the pace of the whole block (s 1733, 16 heads of 128
+    // 73.7 -> 45.9 us; s 3000, 32 heads of 64 over 8 114 -> 92; s 100, 16 heads of 128 15.2 -> 10.3).
+    unsigned piece_off[EDGE ? PIECES : 1];
+    if constexpr (EDGE)
 #pragma unroll
-      for (int q = 0; q < PIECES; ++q) {
-        const bf16* src = base + (size_t)(row0 + (q >> 2) * ROWS_PER_4K) * ld;
-        unsigned lds_addr = lds_byte(tile + q * 1024);
-        if constexpr (EDGE)
-          buffer_to_lds(lds_addr, lane_off[q & 3], rows_buffer<DH>(src, ld, s - row0 - (q >> 2) * ROWS_PER_4K));
-        else
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr),
-                       "v"(lane_off[q & 3]), "s"(src)
-                       : "memory");
+      for (int q = 0; q < PIECES; ++q) piece_off[q] = lane_off[q & 3] + (unsigned)((q >> 2) * ROWS_PER_4K * ld) * 2u;
+    auto load_tile = [&](const bf16* base, int row0, char* tile) {
+      const bf16* src = base + (size_t)row0 * ld;
+      if constexpr (EDGE) {
+        const i32x4 rows = rows_buffer<DH>(src, ld, s - row0);
+#pragma unroll
+        for (int q = 0; q < PIECES; ++q) buffer_to_lds(lds_byte(tile + q * 1024), piece_off[q], rows);
+      } else {
+#pragma unroll
+        for (int q = 0; q < PIECES; ++q) load_piece(src, i32x4(), tile, q, lane_off[q & 3]);
       }
     };
-    const int tile_last = nkv - 1;
     // A tile that does not exist is replaced by the nearest one that does, so that every stage is the same number
     // of loads and the waits below can count them.
     auto load_stage = [&](int g, int j) {
@@ -497,13 +530,15 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
       if (DH == 128) asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
       else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
     };
-#pragma unroll
-    for (int t = 0; t < BQ / 64; ++t) load_tile(qbase, q0 + 64 * t, smem + t * TBYTES);
     if (G == 1) {
       // Stage j is read in slots 2 j and 2 j + 1; its buffer (j mod 3) takes stage j + 3 from slot 2 j + 2 on.
-      load_stage(0, 0);
+      if (!SHARE) {
+#pragma unroll
+        for (int t = 0; t < BQ / 64; ++t) load_tile(qbase, q0 + 64 * t, smem + t * TBYTES);
+        load_stage(0, 0);
+      }
       load_stage(0, 1);
-      wait_tile_loads_opaque();
+      if (!SHARE) wait_tile_loads_opaque();
       __syncthreads();
       for (int g = 0; g <= 2 * n_it + 1; ++g) {
         if ((g & 1) == 0) load_stage(0, g / 2 + 2);  // its buffer held stage g / 2 - 1, last read in slot g - 1
@@ -514,11 +549,8 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
       // Group 0's stage j is read in slot 2 j, group 1's in slot 2 j + 1; a buffer (j mod 2 of its group) takes
       // the group's stage j + 2 in the slot after.  Every slot: what the next slot reads must have arrived (only
       // the stage issued in the slot before may still be on its way), then one stage is issued.
-      load_stage(0, 0);
-      load_stage(1, 0);
       load_stage(0, 1);
       load_stage(1, 1);
-      wait_tile_loads_opaque();
       __syncthreads();
       for (int g = 0; g <= 2 * n_it + 1; ++g) {
         wait_all_but_one_stage();
@@ -555,6 +587,15 @@ __global__ __launch_bounds__(576, 1) void attn_fwd_roles_mfma_kernel(const bf16*
   constexpr int QR = q_in_regs<DH>();
   bf16x8 qreg[QR > 0 ? QR : 1];
 
+  if (SHARE) {
+    const unsigned off = tile_lane_offset<DH>(ld, wave & 3, lane);
+#pragma unroll
+    for (int t = 0; t < BQ / 64; ++t) load_share(qbase, q0 + 64 * t, smem + t * TBYTES, off);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      load_share(kbase, min(g, tile_last) * kKeysPerTile, stages + g * NST * STAGE + TBYTES, off);
+    wait_tile_loads_opaque();
+  }
   __syncthreads();                // Q and the first stages are there
 #pragma unroll
   for (int kk = 0; kk < QR; ++kk) qreg[kk] = read_k_fragment<DH>(q_addr, 0, kk);
@@ -653,12 +694,13 @@ __device__ __forceinline__ void store_partial(bf16* out, size_t row, int ld_out,
   f32x4 w = {v[0], v[1], v[2], v[3]};
   *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out) + row * ld_out + column) = w;
 }
-// EDGE: rows 32 j .. 32 j + 31 of a query tile (sequence rows qs0 ..) against a wave's 32 keys from kw0 on; `lane` and what
+// EDGE, heads of 128: rows 32 j .. 32 j + 31 of a query tile (sequence rows qs0 ..) against a wave's 32 keys from kw0 on; `lane` and what
 // follows from it are the hidden ones of the loop (see there), key and key_half the wave's own.
 // One product after the other, so that the three-term operands need no more registers than the other form:
 // S, P, dV += P^T dO, then dP, dS, dK += dS^T Q.  The lane id is hidden again before each, so that no LDS address is
 // carried from one to the next; with them in registers the fragments of K and V were spilled, and every reload
-// waited for the tile loads under way.
+// waited for the tile loads under way.  Heads of 64 have the registers to leave both products open, as the other form does
+// (s 3000, 32 heads of 64 over 8 308 -> 278 us, s 777, 10 heads 41.9 -> 36.7).
 template <int DH, int V_IN_REG>
 __device__ __forceinline__ void dkv_edge_half(int j, int qs0, int kw0, int key, int key_half, float c, const char* qtile,
                                               const char* dotile, const float* st_lse, const float* st_delta,
@@ -847,7 +889,7 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
     for (int j = 0; j < 2; ++j) {  // 32-row halves of the query tile, one at a time (keeps registers low)
       int qs0 = q0 + 32 * j;
       if (qs0 + 31 < kw0) continue;  // every row of this half is above every key of this wave
-      if constexpr (EDGE) {
+      if constexpr (EDGE && DH == 128) {
         dkv_edge_half<DH, V_IN_REG>(j, qs0, kw0, key, half, c, qtile, dotile, st_lse, st_delta, vslot_l, kf, vf, lane_l, dk, dv);
         continue;
       }
@@ -884,16 +926,21 @@ __device__ __forceinline__ void attn_bwd_dkv_mfma_block(const bf16* __restrict__
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) pacc[e] *= sacc[e];
-      bf16x8 pf[2] = {pack_bf16x8(sacc, 0), pack_bf16x8(sacc, 8)};
-      bf16x8 dsf[2] = {pack_bf16x8(pacc, 0), pack_bf16x8(pacc, 8)};
+      if (EDGE && need_mask) {  // dS is selected too: 0 times the dP of a row that is not finite is no 0
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) pacc[e] = 0.f;
+      }
+      const Weights<EDGE> pf[2] = {weights_of<EDGE>(sacc, 0), weights_of<EDGE>(sacc, 8)};
+      const Weights<EDGE> dsf[2] = {weights_of<EDGE>(pacc, 0), weights_of<EDGE>(pacc, 8)};
 #pragma unroll
       for (int d = 0; d < DT; ++d)
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
           bf16x8 dot = read_tr_fragment<DH>(dotile, 32 * j + 16 * st, 32 * d, lane_l);
           bf16x8 qtr = read_tr_fragment<DH>(qtile, 32 * j + 16 * st, 32 * d, lane_l);
-          dv[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dot, pf[st], dv[d], 0, 0, 0);
-          dk[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qtr, dsf[st], dk[d], 0, 0, 0);
+          dv[d] = multiply<EDGE>(dot, pf[st], dv[d]);
+          dk[d] = multiply<EDGE>(qtr, dsf[st], dk[d]);
         }
     }
     if (more) {
@@ -1079,7 +1126,7 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
     for (int j = 0; j < 2; ++j) {  // 32-row halves of the query tile, one at a time (keeps registers low)
       int qs0 = q0 + 32 * j;
       if (!active || qs0 + 31 < kw0) continue;  // nothing to do, or every row of this half is above every key
-      if constexpr (EDGE) {
+      if constexpr (EDGE && DH == 128) {
         dkv_edge_half<DH, V_IN_REG>(j, qs0, kw0, key, half, c, qtile, dotile, st_lse, st_delta, vslot_l, kf, vf, lane_l, dk, dv);
         continue;
       }
@@ -1116,16 +1163,21 @@ __device__ __forceinline__ void attn_bwd_dkv_split_mfma_block(const bf16* __rest
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) pacc[e] *= sacc[e];
-      bf16x8 pf[2] = {pack_bf16x8(sacc, 0), pack_bf16x8(sacc, 8)};
-      bf16x8 dsf[2] = {pack_bf16x8(pacc, 0), pack_bf16x8(pacc, 8)};
+      if (EDGE && need_mask) {  // dS is selected too: 0 times the dP of a row that is not finite is no 0
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (key > qs0 + 8 * (e >> 2) + 4 * half + (e & 3)) pacc[e] = 0.f;
+      }
+      const Weights<EDGE> pf[2] = {weights_of<EDGE>(sacc, 0), weights_of<EDGE>(sacc, 8)};
+      const Weights<EDGE> dsf[2] = {weights_of<EDGE>(pacc, 0), weights_of<EDGE>(pacc, 8)};
 #pragma unroll
       for (int d = 0; d < DT; ++d)
 #pragma unroll
         for (int st = 0; st < 2; ++st) {
           bf16x8 dot = read_tr_fragment<DH>(dotile, 32 * j + 16 * st, 32 * d, lane_l);
           bf16x8 qtr = read_tr_fragment<DH>(qtile, 32 * j + 16 * st, 32 * d, lane_l);
-          dv[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dot, pf[st], dv[d], 0, 0, 0);
-          dk[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qtr, dsf[st], dk[d], 0, 0, 0);
+          dv[d] = multiply<EDGE>(dot, pf[st], dv[d]);
+          dk[d] = multiply<EDGE>(qtr, dsf[st], dk[d]);
         }
     }
     if (more) {
