@@ -292,11 +292,14 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, const bf16* __res
     if (q < LoaderA::PER_WAVE) la.issue(q, base);
     else lb.issue(q - LoaderA::PER_WAVE, base + A_BYTES);
   };
-  // Both operands with k contiguous (input gradients): the rows of a slice are a whole row apart, 32 KiB at K = 16384, and
-  // 256 blocks walking K in step ask the same few memory channels for all of them.  Each XCD's blocks begin an eighth of K
-  // further on (blocks of one XCD stay in step: they share their slices in its L2): 4096 x 4096, K 16384 450 -> 399 us, K 12288
-  // and below, 2048 rows and 5120 columns within 1 %.  The other forms read one operand along its rows and gain nothing.
-  constexpr bool ROTATE = !TA && !TB;
+  // The rows of a k-contiguous operand's slice are a whole row apart (32 KiB at K = 16384), and 256 blocks walking K in step
+  // ask the same few memory channels for all of them.  Each XCD's blocks begin an eighth of K further on (blocks of one XCD stay
+  // in step: they share their slices in its L2).  Input gradients, warm operands: 4096 x 4096, K 16384 450 -> 399 us, others
+  // within 1 %.  Forward products with warm weights gain nothing (1733 x 2048, K 8192 63 / 65), but a stage's weights come from
+  // memory: with the 128 x 128 tiles, all of them in one round, a step of C2's stage without offload 27.2 -> 26.9 ms and the
+  // ragged one 3.51 -> 3.48; the larger tiles of several rounds do not gain (C4's widths 90.4 -> 90.6).  Weight gradients keep one order of K
+  // in every tile, so that a group equals its single launches bit for bit.
+  constexpr bool ROTATE = !TA && (!TB || WTM == 2);
   int at = ROTATE ? (int)((int64_t)(blockIdx.x & 7) * nk / 8) : 0;
   if (ROTATE) {
     la.advance(at);
