@@ -825,12 +825,13 @@ int stage_forward(po_stage* st, int mb, int chunk, const void* x_in, void* y_out
                            c.vocab, st->compute));
   } else if ((uintptr_t)x_in % 16 != 0) {
     set_error("forward: x_in=%p is not 16-byte aligned", x_in);
-    return PO_E_INVAL;
+    return PO_E_HIP;
   }
   for (int l = 0; l < st->Lu; ++l) {
     char* slab = st->dev_pool.bufs[u.layers[l].dev].ptr;
     void* out = (l + 1 < st->Lu) ? (void*)(st->dev_pool.bufs[u.layers[l + 1].dev].ptr + st->sl.off_x) : y_out;
-    rc = layer_forward(st, chunk * st->Lu + l, mb, slab, l == 0 && !embed ? x_in : nullptr, out, l + 1 < st->Lu ? slab_free[l + 1] : nullptr, &span);
+    rc = layer_forward(st, chunk * st->Lu + l, mb, slab, l == 0 && !embed ? x_in : nullptr, out,
+                       l + 1 < st->Lu ? slab_free[l + 1] : nullptr, &span);
     if (rc) return rc;
   }
   rc = span_end(st, st->compute, span);

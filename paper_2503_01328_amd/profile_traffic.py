@@ -5,8 +5,9 @@
     rocprofv3 --pmc WRITE_SIZE -d out/pmc_write -o w --output-format csv -- python3 bench.py --steps 1 --warmup 1 --no-cpu-baseline --no-frontier --no-secondary --no-auto-ratio
     python3 -m paper_2503_01328_amd.profile_traffic C2 <fetch counter csv> <write counter csv>
 
-Both counters read KiB per dispatch.  They are scaled by what they read for a plain copy kernel of known size in
-the same run (po::copy16_kernel copies one [s, h] stage input per launch).  Writes the table to
+Both counters read KiB per dispatch.  They are scaled by what they read for a kernel of known traffic in the same
+run: the LayerNorm that opens a pass reads one [s, h] stage input and writes it twice, normalised and as it is (its
+gain and shift, a few KiB per XCD, are not counted).  Writes the table to
 profiles/hbm_traffic_<workload>.md and the average over all bf16 matrix-core GEMM launches, with the commit the
 tree is at, to profiles/gemm_hbm_traffic.txt, which bench.py reads for roofline.traffic.
 """
@@ -39,9 +40,9 @@ def main():
     workload, fetch_csv, write_csv = sys.argv[1:4]
     shape = syn.CONFIGS[workload]
     F, W = _load(fetch_csv, "FETCH_SIZE"), _load(write_csv, "WRITE_SIZE")
-    ck = [k for k in F if "copy16" in k[0]][0]
-    copy_kib = shape.seq * shape.hidden * 2 / 1024.0
-    fs, ws = copy_kib / (F[ck][1] / F[ck][0]), copy_kib / (W[ck][1] / W[ck][0])
+    ck = [k for k in F if "ln_forward" in k[0] and ("Lb1E" in k[0] or "true>" in k[0])][0]  # the copying form
+    in_kib = shape.seq * shape.hidden * 2 / 1024.0
+    fs, ws = in_kib / (F[ck][1] / F[ck][0]), 2 * in_kib / (W[ck][1] / W[ck][0])
     rows, gemm_n, gemm_b = [], 0, 0.0
     for k in F:
         if k not in W:
@@ -62,9 +63,9 @@ def main():
          f"    rocprofv3 --pmc FETCH_SIZE -d out/pmc_fetch -o f --output-format csv -- python3 bench.py{cfg} {flags}",
          f"    rocprofv3 --pmc WRITE_SIZE -d out/pmc_write -o w --output-format csv -- python3 bench.py{cfg} {flags}",
          f"    python3 -m paper_2503_01328_amd.profile_traffic {workload} <fetch counter csv> <write counter csv>", "",
-         f"Calibration: `po::copy16_kernel` copies exactly {copy_kib:.0f} KiB (one [s, h] bf16 stage input) per launch in "
-         f"this workload. FETCH_SIZE reads {F[ck][1] / F[ck][0]:.0f} KiB for it and WRITE_SIZE {W[ck][1] / W[ck][0]:.0f} "
-         f"KiB, so readings are scaled by {fs:.3f} (fetch) and {ws:.3f} (write).", "",
+         f"Calibration: the LayerNorm at the start of a pass reads {in_kib:.0f} KiB (one [s, h] bf16 stage input) and "
+         f"writes {2 * in_kib:.0f} (its result and a copy of the input) per launch. FETCH_SIZE reads "
+         f"{F[ck][1] / F[ck][0]:.0f} KiB for it and WRITE_SIZE {W[ck][1] / W[ck][0]:.0f} KiB, so readings are scaled by {fs:.3f} (fetch) and {ws:.3f} (write).", "",
          f"All bf16 MFMA GEMM launches of the run ({gemm_n}): scaled traffic {avg / 2 ** 20:.1f} MiB per launch on "
          f"average ({avg:.0f} bytes: the `roofline.traffic` figure of bench.py, read from "
          f"`profiles/gemm_hbm_traffic.txt`). The counters sit at the L2's far side, so what the infinity cache serves "
