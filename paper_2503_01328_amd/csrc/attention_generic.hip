@@ -206,9 +206,9 @@ static bool vectors_or_refused(int s, uintptr_t addresses) { return s % 128 == 0
 
 bool attention_forward(int dtype, const void* qkv, void* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                        bool force_generic, hipStream_t stream) {
-  // At few rows the vector kernel's forward is the faster one, vector / matrix cores in us (2 to 32 heads alike): heads of 64 at
-  // 41 and 48 rows 10.0 / 10.6 and 11.1 / 10.6, of 128 at 41, 48 and 56 rows 14.8 / 17.5, 16.5 / 17.5 and 18.5 / 17.5.  Its
-  // backward never is (8 rows: 15.5 / 10.3 and 24.6 / 14.4).
+  // Vector / matrix cores in us, 16 heads: of 64 at 44, 52 and 100 rows 11.1 / 7.3, 12.5 / 7.6 and 23.4 / 7.6, of 128 at 52, 64 and
+  // 100 rows 18.3 / 8.8, 21.4 / 8.9 and 35.4 / 9.5.  The line was drawn when the matrix-core kernel took 10.6 and 17.5 us at any
+  // of these; below it results keep the order of their sums.  The backward has none (8 rows: 15.5 / 10.3 and 24.6 / 14.4).
   const int few = h == 64 * (int64_t)n_heads ? 43 : 51;
   if (dtype == kBF16 && !force_generic && s > few && attention_mfma_supported(s, h, n_heads, n_kv_heads) &&
       vectors_or_refused(s, (uintptr_t)qkv | (uintptr_t)o))
