@@ -125,9 +125,9 @@ struct SliceLoader {
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff[u]), "s"(slice)
                  : "memory");
   }
-  __device__ __forceinline__ void advance(int64_t slices = 1) {
-    slice += slices * step;
-    if (EDGE) left -= (int)(slices * step);
+  __device__ __forceinline__ void advance() {
+    slice += step;
+    if (EDGE) left -= (int)step;
   }
 };
 
@@ -292,28 +292,9 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, const bf16* __res
     if (q < LoaderA::PER_WAVE) la.issue(q, base);
     else lb.issue(q - LoaderA::PER_WAVE, base + A_BYTES);
   };
-  // The rows of a k-contiguous operand's slice are a whole row apart (32 KiB at K = 16384), and 256 blocks walking K in step
-  // ask the same few memory channels for all of them.  Each XCD's blocks begin an eighth of K further on (blocks of one XCD stay
-  // in step: they share their slices in its L2).  Input gradients, warm operands: 4096 x 4096, K 16384 450 -> 399 us, others
-  // within 1 %.  Forward products with warm weights gain nothing (1733 x 2048, K 8192 63 / 65), but a stage's weights come from
-  // memory: with the 128 x 128 tiles, all of them in one round, a step of C2's stage without offload 27.2 -> 26.9 ms and the
-  // ragged one 3.51 -> 3.48; the larger tiles of several rounds do not gain (C4's widths 90.4 -> 90.6).  Weight gradients keep one order of K
-  // in every tile, so that a group equals its single launches bit for bit.
-  constexpr bool ROTATE = !TA && (!TB || WTM == 2);
-  int at = ROTATE ? (int)((int64_t)(blockIdx.x & 7) * nk / 8) : 0;
-  if (ROTATE) {
-    la.advance(at);
-    lb.advance(at);
-  }
   auto next_slice = [&]() {
-    int64_t by = 1;
-    if (ROTATE) {
-      const bool last = at + 1 == nk;
-      by = last ? 1 - nk : 1;
-      at = last ? 0 : at + 1;
-    }
-    la.advance(by);
-    lb.advance(by);
+    la.advance();
+    lb.advance();
   };
 #ifdef PO_PHASE_TIMING  // measurement build only (gemm_phases.py): cycle counts of the three phases of tile (0, 0)
   const long long tim0 = __builtin_readcyclecounter(), wal0 = wall_clock64();

@@ -191,6 +191,24 @@ def test_gemm_small_edges(gpu_device, dtype, ta, tb, M, N, K):
     assert rel(acc, ref + 1.0) < sums + 2.0 ** -23
 
 
+# Equal rows of A give equal rows of the result, whichever tile they lie in and whichever XCD works on it: whole tiles of 128, 256
+# and 256 x 192, tiles that end inside, and both sizes of small tiles, forward, input-gradient and weight-gradient layouts.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(2048, 2048, 2048), (1736, 2048, 8192), (4096, 4096, 4096), (4096, 3072, 4096),
+                                   (104, 1024, 1024), (520, 1536, 1024)])
+def test_gemm_row_does_not_depend_on_its_place(gpu_device, dtype, ta, tb, M, N, K):
+    code, tdt, _ = DT[dtype]
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(M + N + K)
+    rand = lambda *size: torch.randn(*size, generator=g, device=gpu_device).to(tdt)
+    row, B = rand(K), rand(*((N, K) if tb else (K, N)))
+    A = row[:, None].repeat(1, M) if ta else row.repeat(M, 1)
+    out = torch.zeros(M, N, dtype=torch.float32 if ta else tdt, device=gpu_device)
+    po.po_op_gemm(code, ta, tb, M, N, K, A, A.shape[1], B, B.shape[1], **{"acc_f32" if ta else "out": out})
+    assert torch.equal(out, out[:1].expand(M, N))
+
+
 # fp32 results that give every CU a tile: each of the three tiles (32 x 64 with two groups of waves, 64 x 64, 128 x 64) with
 # one chunk of K (32), chunks that leave a group without a last one, a K that ends inside a chunk and one that ends with it,
 # results that end inside a tile and with it, and rows of operands that are longer than what is used of them.
