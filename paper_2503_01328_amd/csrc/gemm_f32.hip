@@ -1,21 +1,27 @@
 // fp32 GEMM on v_mfma_f32_32x32x2_f32 (full fp32 products and sums, 256 flop/clk/CU: 157 TFLOP/s at 2.4 GHz) for results
-// that give every CU a tile; smaller ones have gemm_small.hip.
+// of more tiles than one round of 32 x 32 ones; smaller ones have gemm_small.hip.
 //
 // An MFMA takes 64 cycles, so operands are cheap to supply and what decides is that no SIMD's matrix core waits.  The waves
 // of a block share each chunk of K (32 k, 128 bytes of a row) through a ring of NST LDS stages.  A wave that issues a tile load
 // is held until the memory pipeline has taken it, so two waves of the block do nothing else, one per operand (one for both
 // cannot feed 64 x 64 tiles: a chunk's 16 loads take it longer than the chunk's MFMAs); the computing waves only read
 // fragments, each behind an MFMA of the step before its own, and multiply.  The one barrier per chunk stands where the last of the
-// chunk's fragments are in registers and a quarter of its MFMAs is still to come.  LDS is small enough (48 to 72 KB) that two
-// or three blocks share a CU: one's first loads and last stores run under the other's MFMAs.
+// chunk's fragments are in registers and a quarter of its MFMAs is still to come.  Two or three blocks share a CU: one's
+// first loads and last stores run under the other's MFMAs.  LDS has room for them (48 to 72 KB a block); the registers have up to
+// 80 a wave, since the first SIMD takes two of a block's six waves (three of ten): four accumulators kept to the end
+// instead of two and a sum (90 registers) cost 5 to 15 % wherever a CU gets more than two tiles.
 //
-// A block: WK groups of WM x WN computing waves, a wave TM x TN tiles of 32 x 32.  Group g owns every WK-th chunk; the
+// A block: WK groups of WM x WN computing waves, a wave one tile of 32 x 32.  Group g owns every WK-th chunk; the
 // groups' partial tiles are added in group order through LDS (always the same order: deterministic).  Chunks past K and
 // rows past M or N read as zero (the buffer descriptors end with the operand), the epilogue stores only what is inside.
 //
-// Measured against tiles of 64 x 64 whose four waves each took every fourth chunk of K and loaded it themselves (us):
-// 1024 x 4096, K 1024 92 -> 68 (127 TFLOP/s); 2048 x 2048, K 8192 553 -> 484 (142); 777 x 640, K 2560 47 -> 31;
-// 512 x 2560, K 5120 175 -> 140; 4096 x 1536, K 512 75 -> 53.  What is left: the barrier (a SIMD's pipe runs dry while the last
+// Rounding: every sum is formed in at least four chains of a quarter of K (eight of an eighth in 32 x 64 tiles).  Against 64 bits,
+// normal operands, K 512 / 1024 / 8192: 2.1e-7, 2.9e-7, 8.1e-7; one chain has twice, two have 1.4 times that, and with operands of one
+// sign 3.7 and 1.9 times.
+//
+// Measured against tiles of 64 x 64 whose four waves each took every fourth chunk of K and loaded it themselves, the same
+// chains (us): 1024 x 4096, K 1024 81 -> 71 (121 TFLOP/s); 2048 x 2048, K 8192 552 -> 502 (137); 777 x 640, K 2560 46 -> 25;
+// 512 x 2560, K 5120 174 -> 124; 4096 x 1536, K 512 71 -> 54.  What is left: the barrier (a SIMD's pipe runs dry while the last
 // wave arrives) and the last, partly filled round of tiles.
 #include <string.h>
 
@@ -23,10 +29,10 @@
 
 namespace po {
 
-template <int TM_, int TN_, int WM_, int WN_, int WK_, int NST_>
+template <int WM_, int WN_, int WK_, int NST_>
 struct F32Form {
-  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_, WK = WK_, NST = NST_;
-  static constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN, GW = WM * WN, WAVES = GW * WK;  // computing waves
+  static constexpr int WM = WM_, WN = WN_, WK = WK_, NST = NST_;
+  static constexpr int BM = 32 * WM, BN = 32 * WN, GW = WM * WN, WAVES = GW * WK;  // computing waves
   static constexpr int THREADS = 64 * (WAVES + 2);
   static constexpr int STAGE = (BM + BN) * 128, LD = BN + 4;
   static constexpr int RING = NST * STAGE > BM * LD * 4 ? NST * STAGE : BM * LD * 4;  // of a group; later its partial tile
@@ -35,7 +41,7 @@ struct F32Form {
 
 template <typename Form, bool TA, bool TB>
 __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* smem) {
-  constexpr int TM = Form::TM, TN = Form::TN, WN = Form::WN, WK = Form::WK, NST = Form::NST;
+  constexpr int WN = Form::WN, WK = Form::WK, NST = Form::NST;
   constexpr int BM = Form::BM, BN = Form::BN, GW = Form::GW, KU = MfmaOf<float>::KU;
   using OpA = Operand<float, BM, TA>;
   using OpB = Operand<float, BN, TB>;
@@ -48,17 +54,10 @@ __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* 
   n0 *= BN;
 
   const int chunks = ((K + KU - 1) / KU + WK - 1) / WK;  // of every group; the last ones may be empty
-  // a wave with a single tile adds even and odd pairs of k apart: half as long a chain of roundings
-  constexpr int CH = TM * TN == 1 ? 2 : 1;
-  f32x16 acc[CH][TM][TN];
+  // Four chains of additions: even and odd pairs of k, the first and the second half of the chunks.
+  f32x16 acc[2], first_half;
 #pragma unroll
-  for (int c = 0; c < CH; ++c)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[c][i][j][e] = 0.f;
+  for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.f;
   // Loader waves: one for A, one for B.
   auto loader = [&](auto op, const float* ptr, int ld, int row0, int rows, int offset) {
     using Op = decltype(op);
@@ -92,42 +91,48 @@ __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* 
     loader(OpB(), static_cast<const float*>(p.B), p.ldb, n0, N, OpA::BYTES);
   } else {
     const char* ring = smem + group * Form::RING;
-    f32x4 fa[2][TM], fb[2][TN];
-    // fragment x of the next eight k: A's TM, then B's TN
-    auto read = [&](int x, unsigned stage, int kk, int buf) {
-      const char* sa = ring + stage;
-      if (x < TM) fa[buf][x] = fragment<BM, TA>((const float*)nullptr, sa, 32 * (wm * TM + x), kk, lane);
-      else fb[buf][x - TM] = fragment<BN, TB>((const float*)nullptr, sa + OpA::BYTES, 32 * (wn * TN + x - TM), kk, lane);
+    f32x4 fa[2], fb[2];
+    auto read_a = [&](unsigned stage, int kk, int buf) {
+      fa[buf] = fragment<BM, TA>((const float*)nullptr, ring + stage, 32 * wm, kk, lane);
+    };
+    auto read_b = [&](unsigned stage, int kk, int buf) {
+      fb[buf] = fragment<BN, TB>((const float*)nullptr, ring + stage + OpA::BYTES, 32 * wn, kk, lane);
     };
     asm volatile("s_barrier" ::: "memory");
     unsigned stage = 0;
+    read_a(0, 0, 0);
+    read_b(0, 0, 0);
+    auto multiply_chunks = [&](int n) __attribute__((always_inline)) {
+      for (int t = 0; t < n; ++t) {
+        const unsigned next = stage + Form::STAGE == NST * Form::STAGE ? 0 : stage + Form::STAGE;
 #pragma unroll
-    for (int x = 0; x < TM + TN; ++x) {
-      read(x, 0, 0, 0);
-    }
-    for (int t = 0; t < chunks; ++t) {
-      const unsigned next = stage + Form::STAGE == NST * Form::STAGE ? 0 : stage + Form::STAGE;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        if (kk == 3) {  // this wave has the last fragments of the chunk; when all have them the stage is free
-          wait_lds_reads();
-          asm volatile("s_barrier" ::: "memory");
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int x = 0; x < 4 * TM * TN; ++x) {
-          const int e = x / (TM * TN), i = x / TN % TM, j = x % TN;
-          acc[e % CH][i][j] =
-              __builtin_amdgcn_mfma_f32_32x32x2f32(fb[kk & 1][j][e], fa[kk & 1][i][e], acc[e % CH][i][j], 0, 0, 0);
+        for (int kk = 0; kk < 4; ++kk) {
+          if (kk == 3) {  // this wave has the last fragments of the chunk; when all have them the stage is free
+            wait_lds_reads();
+            asm volatile("s_barrier" ::: "memory");
+          }
           __builtin_amdgcn_sched_barrier(0);
-          if (x < TM + TN) {
-            read(x, kk < 3 ? stage : next, (kk + 1) & 3, (kk + 1) & 1);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            acc[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[kk & 1][e], fa[kk & 1][e], acc[e & 1], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (e == 0) read_a(kk < 3 ? stage : next, (kk + 1) & 3, (kk + 1) & 1);
+            if (e == 1) read_b(kk < 3 ? stage : next, (kk + 1) & 3, (kk + 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
+        stage = next;
       }
-      stage = next;
+    };
+    const int half = chunks >= 4 ? chunks / 2 : 0;
+    multiply_chunks(half);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      first_half[e] = acc[0][e] + acc[1][e];
+      asm volatile("" : "+v"(first_half[e]));  // here: left to itself the compiler keeps all four chains to the end
+      acc[0][e] = acc[1][e] = 0.f;
     }
+    multiply_chunks(chunks - half);
     wait_lds_reads();
   }
   __syncthreads();
@@ -136,18 +141,12 @@ __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* 
   float* part = reinterpret_cast<float*>(smem + group * Form::RING);
   if (wave < Form::WAVES) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int q = 0; q < 4; ++q) {
+      f32x4 v;
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            v[e] = CH == 2 ? acc[0][i][j][4 * q + e] + acc[CH - 1][i][j][4 * q + e] : acc[0][i][j][4 * q + e];
-          *reinterpret_cast<f32x4*>(part + (32 * (wm * TM + i) + (lane & 31)) * LD + 32 * (wn * TN + j) + 8 * q +
-                                    4 * (lane >> 5)) = v;
-        }
+      for (int e = 0; e < 4; ++e) v[e] = first_half[4 * q + e] + (acc[0][4 * q + e] + acc[1][4 * q + e]);
+      *reinterpret_cast<f32x4*>(part + (32 * wm + (lane & 31)) * LD + 32 * wn + 8 * q + 4 * (lane >> 5)) = v;
+    }
   }
   __syncthreads();
   constexpr int PER_ROW = BN / 4;
@@ -222,20 +221,22 @@ static bool launch_group(SmallGroup& g, hipStream_t stream) {
 }
 
 // ---- which tile -----------------------------------------------------------------------------------------------------
-// Form 0: 32 x 64, two groups of two waves; 1: 64 x 64, four waves; 2: 128 x 64, four waves of 64 x 32.  Big tiles use
-// a fragment twice and spend less of their time at barriers, small ones fill the last round better.  A launch takes as long as its fullest
-// CU: rounds of tiles times (start + per chunk of K), in us, fitted to 260 random products of 20 to 6000 rows, columns and k
-// (within 9 % of each; the choice is within 1.5 % of the best form on average):
-//   1024 x 1024, K 1024: 23.3 22.4 38.1    1024 x 4096, K 1024: 81.2 79.0 67.6    777 x 640, K 2560: 30.7 46.6 84.3
-//   1500 x 1536, K 1536: 71.7 73.9 97.7    4608 x 1536, K 1500:  191  170  180    4096 x 512, K 512: 24.8 22.2 22.7
-using Form32x64 = F32Form<1, 1, 1, 2, 2, 3>;
-using Form64x64 = F32Form<1, 1, 2, 2, 1, 3>;
-using Form128x64 = F32Form<2, 1, 2, 2, 1, 2>;
+// Form 0: 32 x 64, two groups of two waves; 1: 64 x 64, four waves; 2: 128 x 64, eight waves.  Small tiles fill the last
+// round better, big ones read an operand less often, and the last also has fewer blocks to start and end.  A launch takes as long
+// as its fullest CU: rounds of tiles times (start + per chunk of K), in us, fitted to 100 products of 32 to 6000 rows, columns and
+// k: 6 % off on average, 26 % at most (the least launches); the choice is within 0.5 % of the best form on average and 9 % at most.
+// Forms 0, 1 and 2, us:
+//   1024 x 1024, K 1024: 24.0 23.2 36.0    1024 x 4096, K 1024: 84.5 79.0 77.2    780 x 640, K 2560: 26.7 43.9 79.9
+//   1500 x 1536, K 1536: 68.8 73.5 93.9    4608 x 1536, K 1500:  192  189  208    4096 x 512, K 512: 23.0 20.7 20.5
+//   2004 x 2936, K  788:  110 90.2 78.8    4096 x 4096, K 4096: 1060 1010 1059    2072 x 4480, K 472: 108 91.5 96.0
+using Form32x64 = F32Form<1, 2, 2, 3>;
+using Form64x64 = F32Form<2, 2, 1, 3>;
+using Form128x64 = F32Form<4, 2, 1, 2>;
 static double round_time(int form, int64_t tiles, int K) {
-  static const double start[3] = {1.43, 1.33, 1.92}, chunk[3] = {0.547, 0.509, 0.959};
+  static const double start[3] = {1.34, 1.19, 2.11}, chunk[3] = {0.517, 0.493, 0.936}, last[3] = {0.60, 0.63, 1.0};
   const int chunks = form == 0 ? ceil_div(ceil_div(K, 32), 2) : ceil_div(K, 32);
   // few rounds: whole ones; many: the blocks of a CU no longer end together
-  const double rounds = tiles < 1024 ? (double)ceil_div64(tiles, 256) : (double)tiles / 256 + 0.5;
+  const double rounds = tiles <= 768 ? (double)ceil_div64(tiles, 256) : (double)tiles / 256 + last[form];
   return rounds * (start[form] + chunk[form] * chunks);
 }
 static int best_form(const int64_t* tiles, int K) {

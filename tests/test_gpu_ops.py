@@ -234,6 +234,25 @@ def test_gemm_f32_tiles(gpu_device, ta, tb, M, N, K):
     assert (got.double() - 2 * ref - bias.double()).norm() < 2 * sums * (2 * ref + bias.double()).norm()
 
 
+# The length of fp32 chains of additions: each of the three tiles, K that ends with a chunk of 32 and inside one.
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K,chains", [(640, 512, 1024, 8), (780, 640, 2560, 4), (1024, 1024, 1024, 4), (2056, 2008, 328, 4),
+                                          (1024, 4096, 1024, 4), (2004, 2936, 788, 4), (2048, 2048, 8192, 4)])
+def test_gemm_f32_sums_in_short_chains(gpu_device, ta, tb, M, N, K, chains):
+    """A chain of n additions of equal terms of random sign leaves the sum of n roundings, the i-th of sqrt(i) terms: n / sqrt(2)
+    roundings of a term, over its chains sqrt(K n / 2), and relative to the sum of K terms sqrt(n / 2), n = K / chains.  The
+    additions of the chains' sums add sqrt(chains / 2).  A rounding is 2^-24 of the value at most and 0.42 of that (root of the
+    mean square) over values of any size; 0.5 leaves a fifth.  Half as many chains are 1.4 times as far off."""
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(M + N + K + ta)
+    rand = lambda *size: torch.randn(*size, generator=g, device=gpu_device)
+    A, B = rand(*((K, M) if ta else (M, K))), rand(*((N, K) if tb else (K, N)))
+    got = torch.zeros(M, N, device=gpu_device)
+    po.po_op_gemm(po.PO_F32, ta, tb, M, N, K, A, A.shape[1], B, B.shape[1], acc_f32=got)
+    ref = (A.t() if ta else A).double() @ (B.t() if tb else B).double()
+    assert (got.double() - ref).norm() < 0.5 * 2.0 ** -24 * (K / chains / 2 + chains / 2) ** 0.5 * ref.norm()
+
+
 # Short K under many tiles stays with the vector kernel, bit for bit; on the other side of the line the order of the sums is
 # another one.
 @pytest.mark.parametrize("dtype,ta,M,N,K,vector", [("f32", 1, 1024, 512, 16, 1), ("f32", 1, 1024, 512, 20, 0),
