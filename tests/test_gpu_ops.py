@@ -384,6 +384,23 @@ def test_attention_f32_backward_takes_any_output_alignment(gpu_device, s, dh, a,
     assert ((delta.t().double() - terms.sum(2)).abs() <= dh * 2.0 ** -24 * terms.abs().sum(2)).all()
 
 
+@pytest.mark.parametrize("dh", [32, 64, 96, 128])
+def test_attention_f32_delta_is_a_tree_of_additions(gpu_device, dh):
+    """Every level of a tree of additions leaves, over all its nodes, one rounding of the whole sum: sqrt(levels) in all, one level
+    for the products.  A rounding is 2^-24 of the value at most, and at most half of that as the root of the mean square over a
+    sum's values of any size and sign (1 / sqrt(3) of it at the lower end of a binade, half as much at the upper)."""
+    s, a = 2048, 16
+    h = a * dh
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(dh)
+    rand = lambda *n: torch.randn(*n, generator=g, device=gpu_device)
+    qkv, d_o, o = rand(s, 3 * h), rand(s, h), rand(s, h)
+    lse, delta, dqkv = torch.full((a, s), 9.0, device=gpu_device), torch.empty(a, s, device=gpu_device), torch.empty_like(qkv)
+    po.po_op_attention_backward(po.PO_F32, qkv, o, lse, d_o, dqkv, delta, s, h, a)
+    want = (o.double() * d_o.double()).view(s, a, dh).sum(2).t()
+    assert (delta.double() - want).norm() < 0.5 * 2.0 ** -24 * (1 + np.log2(dh)) ** 0.5 * want.norm()
+
+
 # shapes the matrix-core kernels take: head size 64 / 128, s a multiple of 128; the last two
 # are large enough in (s / 256) * heads to select the forward kernel's 256-row blocks (both head sizes)
 @pytest.mark.parametrize("s,h,a", [(128, 128, 2), (256, 256, 2), (384, 128, 1), (640, 192, 3), (512, 16384, 256),
