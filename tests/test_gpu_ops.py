@@ -746,6 +746,41 @@ def test_column_reductions_of_few_rows(gpu_device, dtype, rows, h):
         assert ((got.double() - terms.sum(0)).abs() <= bound).all()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,h", [(100, 26624), (520, 4096), (1024, 4096), (3000, 4096)])
+def test_layernorm_gain_gradient_rounds_no_more_than_a_plain_order(gpu_device, dtype, rows, h):
+    """Against fp64, beside the same terms added in fp32 in a plain order: chunks of some 32 rows in four chains each, the chunks in
+    four chains.  Orders of the same quality differ by chance, over 4 x h columns by 1 / sqrt(8 h): half a percent at most; two
+    percent is four times that."""
+    code, tdt, _ = DT[dtype]
+    err = [0.0, 0.0]
+    chunks = max(1, min(64, -(-rows // 32)))
+    per_chunk = -(-rows // chunks)
+    def four_chains(t):  # along the first dimension
+        acc = torch.zeros(4, *t.shape[1:], device=gpu_device)
+        for i in range(0, t.shape[0], 4):
+            n = min(4, t.shape[0] - i)
+            acc[:n] += t[i:i + n]
+        return ((acc[0] + acc[1]) + acc[2]) + acc[3]
+    for seed in range(4):
+        g = torch.Generator(device=gpu_device)
+        g.manual_seed(rows + h + seed)
+        rand = lambda *n: torch.randn(*n, generator=g, device=gpu_device).to(tdt)
+        x, dn, dres, gain = rand(rows, h), rand(rows, h), rand(rows, h), rand(h)
+        ws = torch.empty(po.po_op_layernorm_backward_workspace(rows, h) // 4, device=gpu_device)
+        out = torch.zeros(2, h, device=gpu_device)
+        po.po_op_layernorm_backward(code, dn, x, gain, dres, torch.empty_like(x), out[0], out[1], ws, rows, h, 1e-5)
+        mean = x.double().mean(1, keepdim=True)
+        rstd = (x.double().var(1, keepdim=True, unbiased=False) + 1e-5).rsqrt()
+        want = (dn.double() * (x.double() - mean) * rstd).sum(0)
+        mean32, rstd32 = ws[:2 * rows].view(rows, 2).split(1, 1)  # the kernel's, whose own rounding is not in question
+        terms = dn.float() * (x.float() - mean32) * rstd32
+        plain = four_chains(torch.stack([four_chains(t) for t in terms.split(per_chunk)]))
+        for k, got in enumerate((out[0], plain)):
+            err[k] += float((got.double() - want).square().sum())
+    assert err[0] ** 0.5 <= 1.02 * err[1] ** 0.5
+
+
 def test_pack_unpack_roundtrip_is_bit_exact(gpu_device):
     rng = np.random.default_rng(0)
     sizes = [16, 4096 + 16, 0, 1 << 20, 48, 3 * 16384 + 32]  # bytes, multiples of 16, one empty
