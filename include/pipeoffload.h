@@ -196,7 +196,8 @@ int po_bind_params(po_stage* st, const void* params, float* grads);
  * x_in: DEVICE [s, h] of cfg.dtype, or int32 tokens [s] when vocab > 0 and chunk == 0.  A token array is read
  * again by the unit's backward (the embedding gradient scatters by token): it must stay valid and unchanged until
  * that backward (po_stage_backward, or po_stage_backward_weight under a split schedule) has run on the device.
- * Activation inputs are copied into the unit's slab and may be reused as soon as the forward has run.
+ * Activation inputs are copied into the unit's slab and may be reused as soon as the forward has run; one that is
+ * not 16-byte aligned is refused (PO_E_HIP) and leaves the unit as it was.
  * y_out: DEVICE [s, h].  The unit becomes RESIDENT. */
 int po_stage_forward(po_stage* st, int32_t mb, int32_t chunk, const void* x_in, void* y_out);
 

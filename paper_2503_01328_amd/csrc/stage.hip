@@ -790,6 +790,12 @@ int stage_forward(po_stage* st, int mb, int chunk, const void* x_in, void* y_out
     set_error("forward of unit (mb %d, chunk %d) that is still in flight", mb, chunk);
     return PO_E_STATE;
   }
+  const bool embed = c.vocab > 0 && chunk == 0;
+  if (!embed && (uintptr_t)x_in % 16 != 0) {
+    st->units.erase(unit_key(mb, chunk));
+    set_error("forward: x_in=%p is not 16-byte aligned", x_in);
+    return PO_E_HIP;
+  }
   u.layers.assign(st->Lu, UnitLayer());
   // A slab still on its way to the host is waited for right before the first kernel that writes it, not before the
   // whole pass: the slabs of an offloaded unit come free one by one, and layer 0 starts with the first of them.
@@ -817,15 +823,11 @@ int stage_forward(po_stage* st, int mb, int chunk, const void* x_in, void* y_out
   size_t span;
   rc = span_begin(st, st->compute, 0, &span);
   if (rc) return rc;
-  bool embed = c.vocab > 0 && chunk == 0;
   char* slab0 = st->dev_pool.bufs[u.layers[0].dev].ptr;
   if (embed) {
     PO_K(embedding_forward(c.dtype, (const int32_t*)x_in, st->params + (size_t)st->pl.emb_wte * st->E,
                            st->params + (size_t)st->pl.emb_wpe * st->E, slab0 + st->sl.off_x, c.seq, c.hidden,
                            c.vocab, st->compute));
-  } else if ((uintptr_t)x_in % 16 != 0) {
-    set_error("forward: x_in=%p is not 16-byte aligned", x_in);
-    return PO_E_HIP;
   }
   for (int l = 0; l < st->Lu; ++l) {
     char* slab = st->dev_pool.bufs[u.layers[l].dev].ptr;

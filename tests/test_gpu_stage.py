@@ -230,6 +230,28 @@ def test_interleaved_schedule_chunks_and_residency(gpu_device):
         _assert_bit_identical(base, v)
 
 
+def test_refused_input_leaves_the_unit_as_it_was(gpu_device):
+    """A pass whose input is not 16-byte aligned is refused before it holds a slab: the same unit runs afterwards, in a pool
+    of one unit's slabs."""
+    shape = syn.StageShape(2, 1, 128, 2, 512, 64, dtype="f32", pipeline_degree=2, n_microbatches=1)
+    with StageRunner(shape) as r:
+        r.make_inputs()
+        r.run(po.PO_SCHED_1F1B, 0.0)
+        want = _snapshot(r)
+        r.zero_grads()
+        st, before = r.stage, po.po_get_stats(r.stage)
+        shifted = torch.empty(r.x[0].numel() + 4, device=gpu_device)[1:1 + r.x[0].numel()].view_as(r.x[0]).copy_(r.x[0])
+        for _ in range(3):
+            with pytest.raises(po.PipeOffloadError, match="not 16-byte aligned") as e:
+                po.po_stage_forward(st, 0, 0, shifted, r.y[0])
+            assert e.value.code == po.PO_E_HIP
+        po.po_stage_forward(st, 0, 0, r.x[0], r.y[0])
+        po.po_stage_backward(st, 0, 0, r.dy[0], r.dx[0])
+        po.po_synchronize(st)
+        _assert_bit_identical(want, _snapshot(r))
+        assert po.po_get_stats(st)["pool_bytes_allocated"] == before["pool_bytes_allocated"]
+
+
 def test_manual_calls_partial_ratio_and_state_errors(gpu_device):
     shape = syn.StageShape(4, 1, 128, 2, 512, 64, dtype="f32", pipeline_degree=2, n_microbatches=2)
     with StageRunner(shape) as r:
