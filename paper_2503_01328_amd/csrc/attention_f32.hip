@@ -437,6 +437,8 @@ bool attention_f32_supported(const void* qkv, const void* o, int s, int h, int n
   if (s <= 0 || h <= 0 || n_heads <= 0 || h % n_heads != 0 || n_kv_heads <= 0 || n_heads % n_kv_heads != 0) return false;
   if (s > 32 * kMaxGridY) return false;
   const int dh = h / n_heads;
+  // a lane's offset in a tile of 32 rows fits 32 bits
+  if (((int64_t)h + 2 * (int64_t)n_kv_heads * dh) * (4 * 32) > (int64_t)1 << 32) return false;
   return (dh == 32 || dh == 64 || dh == 96 || dh == 128) && ((uintptr_t)qkv | (uintptr_t)o) % 16 == 0;
 }
 

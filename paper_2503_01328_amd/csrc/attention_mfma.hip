@@ -1618,6 +1618,8 @@ bool attention_mfma_supported(int s, int h, int n_heads, int n_kv_heads) {
   if (n_heads <= 0 || h % n_heads != 0 || n_kv_heads <= 0 || n_heads % n_kv_heads != 0) return false;
   if (s % 128 != 0 && s > 128 * kMaxGridY) return false;
   int dh = h / n_heads;
+  // ragged: a lane's offset in a tile of 64 rows fits 32 bits
+  if (s % 128 != 0 && ((int64_t)h + 2 * (int64_t)n_kv_heads * dh) * (2 * 64) > (int64_t)1 << 32) return false;
   return (dh == 64 || dh == 128) && s >= 1;
 }
 

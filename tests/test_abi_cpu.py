@@ -263,6 +263,22 @@ def test_attention_longer_than_a_grid_goes_to_the_vector_kernels():
     assert bf16(128 * 65535 - 1, 64, 1, 1) and not bf16(128 * 65535 + 1, 64, 1, 1)
 
 
+def test_attention_of_rows_beyond_32_bit_offsets_goes_to_the_vector_kernels():
+    """Host logic: the fp32 kernels address 32 rows of 4-byte elements, the ragged bf16 ones 64 rows of 2-byte ones, by 32-bit
+    offsets from a tile's first row."""
+    f32, bf16 = (po.lib[n] for n in ("_ZN2po23attention_f32_supportedEPKvS1_iiii", "_ZN2po24attention_mfma_supportedEiiii"))
+    f32.restype = bf16.restype = ctypes.c_bool
+    f32.argtypes = [ctypes.c_void_p] * 2 + [ctypes.c_int] * 4
+    bf16.argtypes = [ctypes.c_int] * 4
+    at, most = 1 << 20, (1 << 25) - 128  # and two columns of keys and values of 64
+    heads = most // 64
+    for s in (5, 32, 100):
+        assert f32(at, at, s, most, heads, 1) and not f32(at, at, s, most + 64, heads + 1, 1)
+        assert not f32(at, at, s, most // 2 + 64, heads // 2 + 1, heads // 2 + 1)
+        assert bf16(s, most, heads, 1) and not bf16(s, most + 64, heads + 1, 1)
+    assert bf16(128, most + 64, heads + 1, 1)
+
+
 def test_whole_tiles_of_few_slices_stay_with_the_large_tiles():
     """Host logic: results of whole 128 x 128 tiles take the small ones from K = 256 on where those fill the chip better."""
     f = po.lib["_ZN2po20gemm_small_is_fasterEiii"]
