@@ -436,6 +436,8 @@ __global__ __launch_bounds__(256) void attn_f32_delta_kernel(const float* __rest
 bool attention_f32_supported(const void* qkv, const void* o, int s, int h, int n_heads, int n_kv_heads) {
   if (s <= 0 || h <= 0 || n_heads <= 0 || h % n_heads != 0 || n_kv_heads <= 0 || n_heads % n_kv_heads != 0) return false;
   if (s > 32 * kMaxGridY) return false;
+  // the backward's blocks, 256 threads each, in one dimension of a grid
+  if (((int64_t)n_heads + n_kv_heads) * ceil_div(s, 32) >= (int64_t)1 << 24) return false;
   const int dh = h / n_heads;
   // a lane's offset in a tile of 32 rows fits 32 bits
   if (((int64_t)h + 2 * (int64_t)n_kv_heads * dh) * (4 * 32) > (int64_t)1 << 32) return false;

@@ -261,6 +261,10 @@ def test_attention_longer_than_a_grid_goes_to_the_vector_kernels():
     bf16.argtypes = [ctypes.c_int] * 4
     assert f32(1 << 20, 1 << 20, 32 * 65535, 64, 1, 1) and not f32(1 << 20, 1 << 20, 32 * 65535 + 1, 64, 1, 1)
     assert bf16(128 * 65535 - 1, 64, 1, 1) and not bf16(128 * 65535 + 1, 64, 1, 1)
+    # fp32: all blocks (32 rows of a head or of a key/value head, 256 threads) in one dimension of 2^32 threads
+    assert f32(1 << 20, 1 << 20, 32 * 16, 32 * ((1 << 20) - 2), (1 << 20) - 2, 1)
+    assert not f32(1 << 20, 1 << 20, 32 * 16, 32 * ((1 << 20) - 1), (1 << 20) - 1, 1)
+    assert f32(1 << 20, 1 << 20, 32 * 65535, 32 * 128, 128, 128) and not f32(1 << 20, 1 << 20, 32 * 65535, 32 * 256, 256, 4)
 
 
 def test_attention_of_rows_beyond_32_bit_offsets_goes_to_the_vector_kernels():
