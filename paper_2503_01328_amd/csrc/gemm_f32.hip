@@ -239,22 +239,23 @@ static double round_time(int form, int64_t tiles, int K) {
   const double rounds = tiles <= 768 ? (double)ceil_div64(tiles, 256) : (double)tiles / 256 + last[form];
   return rounds * (start[form] + chunk[form] * chunks);
 }
-static int best_form(const int64_t* tiles, int K) {
-  int best = 0;
-  for (int f = 1; f < 3; ++f)
-    if (round_time(f, tiles[f], K) < round_time(best, tiles[best], K)) best = f;
-  return best;
-}
 static void count_tiles(int M, int N, int64_t* tiles) {
   tiles[0] += (int64_t)ceil_div(M, 32) * ceil_div(N, 64);
   tiles[1] += (int64_t)ceil_div(M, 64) * ceil_div(N, 64);
   tiles[2] += (int64_t)ceil_div(M, 128) * ceil_div(N, 64);
 }
+// The form of one launch for n products (the smallest K counts).
+int gemm_f32_form(int n, const int* M, const int* N, int K) {
+  int64_t tiles[3] = {0, 0, 0};
+  for (int i = 0; i < n; ++i) count_tiles(M[i], N[i], tiles);
+  int best = 0;
+  for (int f = 1; f < 3; ++f)
+    if (round_time(f, tiles[f], K) < round_time(best, tiles[best], K)) best = f;
+  return best;
+}
 
 bool gemm_f32(int ta, int tb, SmallProblem& p, hipStream_t stream) {
-  int64_t tiles[3] = {0, 0, 0};
-  count_tiles(p.M, p.N, tiles);
-  switch (best_form(tiles, p.K)) {
+  switch (gemm_f32_form(1, &p.M, &p.N, p.K)) {
     case 0: return launch_trans<Form32x64>(ta, tb, p, stream);
     case 1: return launch_trans<Form64x64>(ta, tb, p, stream);
     default: return launch_trans<Form128x64>(ta, tb, p, stream);
@@ -262,13 +263,13 @@ bool gemm_f32(int ta, int tb, SmallProblem& p, hipStream_t stream) {
 }
 
 bool gemm_f32_grouped(SmallGroup& g, hipStream_t stream) {
-  int64_t tiles[3] = {0, 0, 0};
-  int K = g.p[0].K;
+  int M[kMaxSmallGroup], N[kMaxSmallGroup], K = g.p[0].K;
   for (int i = 0; i < g.n; ++i) {
-    count_tiles(g.p[i].M, g.p[i].N, tiles);
+    M[i] = g.p[i].M;
+    N[i] = g.p[i].N;
     K = min(K, g.p[i].K);
   }
-  switch (best_form(tiles, K)) {
+  switch (gemm_f32_form(g.n, M, N, K)) {
     case 0: return launch_group<Form32x64>(g, stream);
     case 1: return launch_group<Form64x64>(g, stream);
     default: return launch_group<Form128x64>(g, stream);

@@ -201,5 +201,6 @@ __device__ __forceinline__ int tile_of_block() {
 // gemm_f32.hip: fp32 problems whose operands gemm_small has checked.
 bool gemm_f32(int trans_a, int trans_b, SmallProblem& p, hipStream_t stream);
 bool gemm_f32_grouped(SmallGroup& g, hipStream_t stream);
+int gemm_f32_form(int n, const int* M, const int* N, int K);  // 0: 32 x 64 tiles, 1: 64 x 64, 2: 128 x 64
 
 }  // namespace po

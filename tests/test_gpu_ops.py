@@ -2,6 +2,8 @@
 
 Tolerances (max |got - ref| / max |ref| per tensor): 1e-4 in fp32, 2e-2 in bf16.
 The oracle is fed the values the kernel is fed (bf16-rounded where bf16)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -209,12 +211,31 @@ def test_gemm_row_does_not_depend_on_its_place(gpu_device, dtype, ta, tb, M, N, 
     assert torch.equal(out, out[:1].expand(M, N))
 
 
-# fp32 results that give every CU a tile: each of the three tiles (32 x 64 with two groups of waves, 64 x 64, 128 x 64) with
-# one chunk of K (32), chunks that leave a group without a last one, a K that ends inside a chunk and one that ends with it,
-# results that end inside a tile and with it, and rows of operands that are longer than what is used of them.
+# fp32 results of more tiles than one round of 32 x 32 ones: 128 x 64, 64 x 64 and 32 x 64 tiles (two groups of waves, never for
+# one chunk of K) with one chunk (32) and part of one, as many as there are stages, one more, a first and a second half, chunks
+# that leave a group without a last one, a K that ends inside a chunk and one that ends with it, results that end inside a tile
+# and with it, and rows of operands that are longer than what is used of them.
+F32_TILES = {2: [(1028, 964, 20), (1028, 1088, 32), (1024, 1088, 64), (1028, 964, 100), (1028, 964, 132), (1028, 964, 292)],
+             1: [(964, 964, 28), (1024, 1024, 32), (964, 964, 60), (964, 964, 100), (960, 1024, 128), (964, 964, 132), (964, 964, 292)],
+             0: [(484, 1020, 36), (512, 1024, 64), (484, 1020, 100), (548, 572, 132), (548, 572, 160), (484, 1020, 224), (544, 576, 516)],
+             None: [(960, 964, 4), (1028, 964, 4)]}  # so short a K stays with the vector kernel
+
+
+def test_gemm_f32_tiles_cover_every_tile():
+    form = po.lib["_ZN2po13gemm_f32_formEiPKiS1_i"]
+    form.restype, form.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int), ctypes.c_int]
+    for want in (0, 1, 2):
+        for M, N, K in F32_TILES[want]:
+            assert form(1, ctypes.c_int(M), ctypes.c_int(N), K) == want, (M, N, K)
+    # the weight gradients of a layer (QKV, output projection, FC1, FC2) in one launch: the fp32 stages of
+    # test_grouped_weight_gradients_of_any_shape
+    four = lambda *v: (ctypes.c_int * 4)(*v)
+    group = lambda h, f, seq: form(4, four(h, h, h, f), four(3 * h, h, f, h), seq)
+    assert [group(192, 768, 200), group(512, 1536, 37), group(1024, 2048, 300), group(384, 1536, 100)] == [0, 1, 1, 2]
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
-@pytest.mark.parametrize("M,N,K", [(548, 572, 132), (548, 572, 160), (544, 576, 516), (960, 964, 4), (1024, 1024, 32),
-                                   (964, 964, 100), (1028, 964, 4), (1024, 1088, 64), (1028, 964, 292)])
+@pytest.mark.parametrize("M,N,K", [shape for shapes in F32_TILES.values() for shape in shapes])
 def test_gemm_f32_tiles(gpu_device, ta, tb, M, N, K):
     """Bounds as in test_gemm_small_edges."""
     g = torch.Generator(device=gpu_device)
@@ -232,6 +253,10 @@ def test_gemm_f32_tiles(gpu_device, ta, tb, M, N, K):
     assert (got.double() - ref - bias.double()).norm() < sums * (ref + bias.double()).norm()
     po.po_op_gemm(po.PO_F32, ta, tb, M, N, K, A, A.stride(0), B, B.stride(0), acc_f32=got)
     assert (got.double() - 2 * ref - bias.double()).norm() < 2 * sums * (2 * ref + bias.double()).norm()
+    acc = [torch.zeros(M, N, device=gpu_device) for _ in range(2)]
+    for generic in (0, 1):  # the matrix cores add in another order
+        po.po_op_gemm(po.PO_F32, ta, tb, M, N, K, A, A.stride(0), B, B.stride(0), acc_f32=acc[generic], force_generic=generic)
+    assert torch.equal(acc[0], acc[1]) == ((M, N, K) in F32_TILES[None])
 
 
 # The length of fp32 chains of additions: each of the three tiles, K that ends with a chunk of 32 and inside one.

@@ -97,8 +97,10 @@ def test_bf16_stage_against_oracle(gpu_device, shape):
     syn.StageShape(1, 1, 448, 7, 1024, 200, dtype="bf16", pipeline_degree=2, n_microbatches=2),
     syn.StageShape(1, 1, 512, 8, 1536, 37, dtype="f32", pipeline_degree=2, n_microbatches=2),
     syn.StageShape(1, 1, 1024, 8, 2048, 300, dtype="f32", pipeline_degree=2, n_microbatches=2),
+    syn.StageShape(1, 1, 192, 3, 768, 200, dtype="f32", pipeline_degree=2, n_microbatches=2),
+    syn.StageShape(1, 1, 384, 6, 1536, 100, dtype="f32", pipeline_degree=2, n_microbatches=2),
     syn.StageShape(1, 1, 1088, 17, 4096, 905, dtype="bf16", pipeline_degree=2, n_microbatches=2)],
-    ids=["bf16-64-tiles", "f32-64-tiles-short", "f32-64-tiles-long", "bf16-256-tiles-that-end-inside"])
+    ids=["bf16-64-tiles", "f32-64-tiles-short", "f32-64-tiles-long", "f32-32x64-tiles", "f32-128x64-tiles", "bf16-256-tiles-that-end-inside"])
 def test_grouped_weight_gradients_of_any_shape(gpu_device, shape):
     """The one launch of a layer's four weight-gradient products where the shapes are no whole 256 x 256 tiles."""
     with StageRunner(shape) as r:
