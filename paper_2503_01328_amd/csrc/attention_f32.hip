@@ -1,8 +1,8 @@
 // fp32 causal attention on the matrix cores (v_mfma_f32_32x32x2_f32: full fp32 products and sums), forward and
 // backward, any sequence length, head sizes 32, 64, 96 and 128.
 //
-// What counts is that every SIMD has two waves with MFMAs to issue (one takes 64 cycles, 2048 a product of two 32-row tiles over 64
-// columns) and that no chain is long.  Every wave works on its own, no barrier in the loops: its two tiles of 32 keys (query
+// What counts is that a SIMD has waves with MFMAs to issue (one takes 64 cycles, 2048 a product of two 32-row tiles over 64
+// columns; two waves up to heads of 64, of whose blocks a CU's LDS holds two, one for heads of 96 and 128) and that no chain is long.  Every wave works on its own, no barrier in the loops: its two tiles of 32 keys (query
 // rows) go HBM -> LDS directly into a place of its own, from which it reads 16-byte pieces of rows for the products over the head
 // dimension and 32 consecutive floats of a row for the others.  (Read from global memory into registers instead, the compiler kept
 // one or two loads in flight, a memory round trip per four MFMAs.)  A block owns only 32 rows (query rows in forward and dQ,

@@ -208,7 +208,7 @@ bool attention_forward(int dtype, const void* qkv, void* o, float* lse, int s, i
                        bool force_generic, hipStream_t stream) {
   // Vector / matrix cores in us, 16 heads: of 64 at 44, 52 and 100 rows 11.1 / 7.3, 12.5 / 7.6 and 23.4 / 7.6, of 128 at 52, 64 and
   // 100 rows 18.3 / 8.8, 21.4 / 8.9 and 35.4 / 9.5.  The line was drawn when the matrix-core kernel took 10.6 and 17.5 us at any
-  // of these; below it results keep the order of their sums.  The backward has none (8 rows: 15.5 / 10.3 and 24.6 / 14.4).
+  // of these and has not been moved since.  The backward has none (8 rows: 15.5 / 10.3 and 24.6 / 14.4).
   const int few = h == 64 * (int64_t)n_heads ? 43 : 51;
   if (dtype == kBF16 && !force_generic && s > few && attention_mfma_supported(s, h, n_heads, n_kv_heads) &&
       vectors_or_refused(s, (uintptr_t)qkv | (uintptr_t)o))
@@ -230,7 +230,7 @@ bool attention_backward(int dtype, const void* qkv, const void* o, const float* 
     return attention_backward_mfma(qkv, o, lse, d_o, dqkv, delta, partials, s, h, n_heads, n_kv_heads, stream);
   // fp32 as in the forward: heads of 32 at 8 rows 12.0 / 8.2; of 64 at 12 and 14 rows 16.6 / 10.5 and 17.2 / 10.5; of 96 at 16
   // and 20 rows 23.6 / 14.3 and 26.8 / 14.4; of 128 at 20 and 26 rows 29.2 / 17.7 and 33.3 / 17.7 (the line was drawn when the
-  // matrix-core kernels took 11.8 to 29 us; below it results keep the order of their sums).
+  // matrix-core kernels took 11.8 to 29 us and has not been moved since).
   if (dtype == kF32 && !force_generic && 64 * (int64_t)s > 12 * (int64_t)(h / max(n_heads, 1)) &&
       attention_f32_supported(qkv, d_o, s, h, n_heads, n_kv_heads) && (uintptr_t)dqkv % 16 == 0) {
     if ((uintptr_t)o % 16 != 0)

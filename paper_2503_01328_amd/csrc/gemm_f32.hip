@@ -43,6 +43,7 @@ template <typename Form, bool TA, bool TB>
 __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* smem) {
   constexpr int WN = Form::WN, WK = Form::WK, NST = Form::NST;
   constexpr int BM = Form::BM, BN = Form::BN, GW = Form::GW, KU = MfmaOf<float>::KU;
+  static_assert(BM <= kMaxSmallRows && BN <= kMaxSmallRows, "gemm_small_supported bounds a lane's offset");
   using OpA = Operand<float, BM, TA>;
   using OpB = Operand<float, BN, TB>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -172,13 +173,13 @@ __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* 
 }
 
 template <typename Form, bool TA, bool TB>
-__global__ __launch_bounds__(Form::THREADS) void gemm_small_kernel(SmallProblem p) {
+__global__ __launch_bounds__(Form::THREADS) void gemm_f32_kernel(SmallProblem p) {
   extern __shared__ __align__(16) char smem[];
   f32_tile<Form, TA, TB>(p, tile_of_block(), smem);
 }
 
 template <typename Form>
-__global__ __launch_bounds__(Form::THREADS) void gemm_small_grouped_kernel(SmallGroup g) {
+__global__ __launch_bounds__(Form::THREADS) void gemm_f32_grouped_kernel(SmallGroup g) {
   extern __shared__ __align__(16) char smem[];
   const int lin = tile_of_block();
   SmallProblem p = g.p[0];  // constant indices only: a run-time index would send the arguments through memory
@@ -190,12 +191,12 @@ __global__ __launch_bounds__(Form::THREADS) void gemm_small_grouped_kernel(Small
 
 template <typename Form, bool TA, bool TB>
 static bool launch_one(SmallProblem& p, hipStream_t stream) {
-  auto kern = gemm_small_kernel<Form, TA, TB>;
+  auto kern = gemm_f32_kernel<Form, TA, TB>;
   static LdsLimit lds;  // per instantiation
   if (!lds.allow(kern, Form::SMEM)) return false;
   p.tiles_n = ceil_div(p.N, Form::BN);
   kern<<<ceil_div(p.M, Form::BM) * p.tiles_n, Form::THREADS, Form::SMEM, stream>>>(p);
-  return launch_ok("gemm_small_kernel (fp32)");
+  return launch_ok("gemm_f32_kernel");
 }
 template <typename Form>
 static bool launch_trans(int ta, int tb, SmallProblem& p, hipStream_t stream) {
@@ -207,7 +208,7 @@ static bool launch_trans(int ta, int tb, SmallProblem& p, hipStream_t stream) {
 }
 template <typename Form>
 static bool launch_group(SmallGroup& g, hipStream_t stream) {
-  auto kern = gemm_small_grouped_kernel<Form>;
+  auto kern = gemm_f32_grouped_kernel<Form>;
   static LdsLimit lds;
   if (!lds.allow(kern, Form::SMEM)) return false;
   int total = 0;
@@ -217,7 +218,7 @@ static bool launch_group(SmallGroup& g, hipStream_t stream) {
     total += ceil_div(g.p[i].M, Form::BM) * g.p[i].tiles_n;
   }
   kern<<<total, Form::THREADS, Form::SMEM, stream>>>(g);
-  return launch_ok("gemm_small_grouped_kernel (fp32)");
+  return launch_ok("gemm_f32_grouped_kernel");
 }
 
 // ---- which tile -----------------------------------------------------------------------------------------------------

@@ -113,12 +113,13 @@ bool gemm_generic(int dtype, int trans_a, int trans_b, int M, int N, int K, cons
   return launch_ok("gemm_generic_kernel");
 }
 
-// Whether the vector kernel beats the 64 x 64 matrix-core tiles: a K that fills no more than a chunk or two of them (128 bytes
-// of a row each, loaded and multiplied whole) under many tiles.  vector / matrix cores, us: fp32 weight gradients 1024 x 512,
-// K 16 / 20 8.3 / 5.0, 10.3 / 5.0; 4096 x 4096, K 16 / 32 / 48 / 52 43 / 41, 50 / 41, 58 / 42, 62 / 42; 4096 x 2048, K 32 / 40 32 / 20,
-// 36 / 21: since fp32 has larger tiles the line only keeps these few products (a K no layer has) on one kernel, bit for bit.
-// bf16, 1032 x 4104, K 8 / 24 7.9 / 9.6, 10.0 / 9.6; its weight gradients have better kernels.
-static bool vector_is_faster(int dtype, int trans_a, int M, int N, int K) {
+// Products that stay with the vector kernel: a K that fills no more than a chunk or two (128 bytes of a row each, loaded and
+// multiplied whole) under many tiles.  bf16, vector / 64 x 64 matrix-core tiles, us: 1032 x 4104, K 8 / 24 7.9 / 9.6, 10.0 / 9.6; its
+// weight gradients have better kernels.  fp32: the line was drawn against 64 x 64 tiles whose waves loaded for themselves (weight
+// gradients 4096 x 4096, K 16 / 32 40.8 / 51.0, 48.3 / 51.0) and has not been moved since; the tiles of today are faster on both
+// sides of it: 1024 x 512, K 16 / 20 7.5 / 3.4, 9.5 / 3.5; 4096 x 4096, K 16 / 32 / 48 / 52 42 / 35, 49 / 34, 58 / 42, 63 / 42;
+// 4096 x 2048, K 32 / 40 31 / 20, 35 / 23.
+static bool stays_with_vector_kernel(int dtype, int trans_a, int M, int N, int K) {
   const int64_t tiles = (int64_t)ceil_div(M, 64) * ceil_div(N, 64);
   if (dtype == kBF16) return !trans_a && K <= 16 && tiles >= 1024;
   return K <= 48 && tiles >= (K <= 16 ? 128 : K <= 32 ? 4096 : 2048);
@@ -128,7 +129,7 @@ bool gemm(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* 
           const Epilogue& ep, bool force_generic, hipStream_t stream) {
   if (force_generic) return gemm_generic(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb, ep, stream);
   const bool small = gemm_small_supported(dtype, trans_a, trans_b, M, N, K, A, lda, B, ldb) &&
-                     !vector_is_faster(dtype, trans_a, M, N, K);
+                     !stays_with_vector_kernel(dtype, trans_a, M, N, K);
   if (dtype == kBF16) {
     // bf16 by size.  Whole tiles: the large tiles, or the small ones where those leave most of the chip idle, for the
     // forward and the input gradients (512 x 512, K 512: 11.8 -> 5 us); a weight gradient on its own stays with the large

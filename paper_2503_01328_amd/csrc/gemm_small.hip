@@ -24,6 +24,7 @@ namespace po {
 template <typename T, int TM, int TN, int KG, bool TA, bool TB>
 __device__ __forceinline__ void small_tile(const SmallProblem& p, int tile, char* smem) {
   constexpr int BM = 32 * TM, BN = 32 * TN, KU = MfmaOf<T>::KU;
+  static_assert(BM <= kMaxSmallRows && BN <= kMaxSmallRows, "gemm_small_supported bounds a lane's offset");
   using OpA = Operand<T, BM, TA>;
   using OpB = Operand<T, BN, TB>;
   constexpr int STAGE = OpA::BYTES + OpB::BYTES, LOADS = OpA::LOADS + OpB::LOADS;
@@ -165,8 +166,8 @@ static SmallForm small_form(int dtype, int64_t tiles64, int K) {
 }
 // fp32 results for which 32 x 32 tiles beat the larger ones of gemm_f32.hip: few enough for one round of the CUs (a short K
 // is over before a larger tile's first chunks have arrived).  32 x 32 / best larger, us, 32 x 32 tiles in brackets:
-//   300 x 512, K 512 6.2 / 9.1 (160); 354 x 652, K 1844 15.8 / 21.7 (252); 1272 x 216, K 226 6.5 / 7.2 (280);
-//   636 x 496, K 314 7.7 / 7.4 (320); 516 x 712, K 772 14.2 / 12.0 (391); 680 x 572, K 68 5.3 / 6.2 (396)
+//   300 x 512, K 512 5.4 / 8.2 (160); 356 x 652, K 1844 15.1 / 20.3 (252); 1272 x 216, K 228 5.4 / 6.3 (280);
+//   636 x 496, K 316 6.8 / 6.8 (320); 516 x 712, K 772 13.4 / 11.3 (391); 680 x 572, K 68 3.9 / 5.2 (396)
 static bool f32_few_tiles(int64_t tiles32, int K) { return tiles32 <= 288 || (tiles32 < 448 && K < 128); }
 
 static bool vector_epilogue(int dtype, const Epilogue& ep) {
@@ -178,11 +179,12 @@ static bool vector_epilogue(int dtype, const Epilogue& ep) {
 bool gemm_small_supported(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda,
                           const void* B, int ldb) {
   const int v = dtype == kF32 ? 4 : 8;  // elements of a 16-byte load
-  // rows of both operands are whole 16-byte pieces; a lane's offset (up to 64 rows) fits 32 bits
-  const int64_t limit = (int64_t)1 << 31;
+  // rows of both operands are whole 16-byte pieces; a lane's offset (less than kMaxSmallRows rows of up to 4 bytes an element)
+  // fits 32 bits and the largest buffer
+  const int64_t limit = (int64_t)1 << 32;
   return M > 0 && N > 0 && K > 0 && lda % v == 0 && ldb % v == 0 && (trans_a ? M : K) % v == 0 &&
-         (trans_b ? K : N) % v == 0 && ((uintptr_t)A | (uintptr_t)B) % 16 == 0 && (int64_t)lda * 64 * 4 < limit &&
-         (int64_t)ldb * 64 * 4 < limit;
+         (trans_b ? K : N) % v == 0 && ((uintptr_t)A | (uintptr_t)B) % 16 == 0 && (int64_t)lda * kMaxSmallRows * 4 < limit &&
+         (int64_t)ldb * kMaxSmallRows * 4 < limit;
 }
 
 template <typename T, int TM, int TN, int KG, bool TA, bool TB>

@@ -180,6 +180,7 @@ struct SmallProblem {
   int vec;                  // every row of the result and its operands starts on a 16-byte boundary
 };
 
+constexpr int kMaxSmallRows = 128;  // of an operand's tile: the largest row or k whose offset a lane forms is one less
 constexpr int kMaxSmallGroup = 4;
 struct SmallGroup {
   SmallProblem p[kMaxSmallGroup];

@@ -329,18 +329,22 @@ def test_hot_kernels_keep_their_accumulators_in_registers():
     # shapes, the two backward kernels, their eight-wave forms and the one-launch form of both, two head dimensions
     assert len(gemm) == 48 and len(attn) >= 16
     # results of any size: three tiles x (two forward and two input-gradient epilogues, weight gradients) and the grouped
-    # launch; the small tiles, 32 x 32 with four waves (fp32 also eight) and 64 x 64 with four, two and one, x four layouts
-    # and the grouped launch, two types; fp32 attention: three kernels, four head sizes
+    # launch; the small tiles, bf16 32 x 32 with four waves and 64 x 64 with four, two and one, fp32 32 x 32 with four and eight, x
+    # four layouts and the grouped launch; larger fp32 results: three tiles x the same; fp32 attention: forward, backward and
+    # delta, four head sizes
     edge = {k: v for k, v in usage.items() if "gemm_edge_kernel" in k or "gemm_edge_grouped_kernel" in k}
     small = {k: v for k, v in usage.items() if "gemm_small_kernel" in k or "gemm_small_grouped_kernel" in k}
+    gemm_f32 = {k: v for k, v in usage.items() if "gemm_f32_kernel" in k or "gemm_f32_grouped_kernel" in k}
     f32 = {k: v for k, v in usage.items() if "attn_f32_" in k}
-    assert len(edge) == 16 and len(small) == 9 * 5 and len(f32) == 12
-    for name, v in {**gemm, **grouped, **attn, **edge, **small, **f32}.items():
+    assert len(edge) == 16 and len(small) == 6 * 5 and len(gemm_f32) == 3 * 5 and len(f32) == 12
+    for name, v in {**gemm, **grouped, **attn, **edge, **small, **gemm_f32, **f32}.items():
         assert v["ScratchSize"] == 0, (name, v)
     for name, v in attn.items():
         assert v["Occupancy"] >= 2, (name, v)
     for name, v in {**gemm, **edge}.items():
         assert v["VGPRs"] + v["AGPRs"] <= 512
+    for name, v in gemm_f32.items():  # two waves of each of three blocks on a SIMD
+        assert v["Occupancy"] >= 6, (name, v)
 
 
 def test_trace_viewer_reads_the_span_file(tmp_path):
