@@ -172,16 +172,23 @@ __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* 
   }
 }
 
+// The tile of a block of a grid of gemm_f32_grid; of a second dimension the last blocks have none.
+__device__ __forceinline__ int tile_of_f32_block() {
+  return gridDim.y == 1 ? tile_of_block() : (int)(blockIdx.y * gridDim.x + blockIdx.x);
+}
+
 template <typename Form, bool TA, bool TB>
 __global__ __launch_bounds__(Form::THREADS) void gemm_f32_kernel(SmallProblem p) {
   extern __shared__ __align__(16) char smem[];
-  f32_tile<Form, TA, TB>(p, tile_of_block(), smem);
+  const int tile = tile_of_f32_block();
+  if (tile < (p.M + Form::BM - 1) / Form::BM * p.tiles_n) f32_tile<Form, TA, TB>(p, tile, smem);
 }
 
 template <typename Form>
 __global__ __launch_bounds__(Form::THREADS) void gemm_f32_grouped_kernel(SmallGroup g) {
   extern __shared__ __align__(16) char smem[];
-  const int lin = tile_of_block();
+  const int lin = tile_of_f32_block();
+  if (lin >= g.tiles) return;
   SmallProblem p = g.p[0];  // constant indices only: a run-time index would send the arguments through memory
 #pragma unroll
   for (int i = 1; i < kMaxSmallGroup; ++i)
@@ -189,13 +196,18 @@ __global__ __launch_bounds__(Form::THREADS) void gemm_f32_grouped_kernel(SmallGr
   f32_tile<Form, true, true>(p, lin - p.first_tile, smem);
 }
 
+// A dimension of a grid ends at 2^32 threads.
+dim3 gemm_f32_grid(int64_t tiles, int threads) {
+  const unsigned y = (unsigned)ceil_div64(tiles * threads, (int64_t)1 << 31);
+  return dim3((unsigned)ceil_div64(tiles, y), y);
+}
 template <typename Form, bool TA, bool TB>
 static bool launch_one(SmallProblem& p, hipStream_t stream) {
   auto kern = gemm_f32_kernel<Form, TA, TB>;
   static LdsLimit lds;  // per instantiation
   if (!lds.allow(kern, Form::SMEM)) return false;
   p.tiles_n = ceil_div(p.N, Form::BN);
-  kern<<<ceil_div(p.M, Form::BM) * p.tiles_n, Form::THREADS, Form::SMEM, stream>>>(p);
+  kern<<<gemm_f32_grid(ceil_div(p.M, Form::BM) * p.tiles_n, Form::THREADS), Form::THREADS, Form::SMEM, stream>>>(p);
   return launch_ok("gemm_f32_kernel");
 }
 template <typename Form>
@@ -217,7 +229,8 @@ static bool launch_group(SmallGroup& g, hipStream_t stream) {
     g.p[i].first_tile = total;
     total += ceil_div(g.p[i].M, Form::BM) * g.p[i].tiles_n;
   }
-  kern<<<total, Form::THREADS, Form::SMEM, stream>>>(g);
+  g.tiles = total;
+  kern<<<gemm_f32_grid(total, Form::THREADS), Form::THREADS, Form::SMEM, stream>>>(g);
   return launch_ok("gemm_f32_grouped_kernel");
 }
 

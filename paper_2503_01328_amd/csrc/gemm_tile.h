@@ -184,7 +184,7 @@ constexpr int kMaxSmallRows = 128;  // of an operand's tile: the largest row or 
 constexpr int kMaxSmallGroup = 4;
 struct SmallGroup {
   SmallProblem p[kMaxSmallGroup];
-  int n;
+  int n, tiles;  // tiles: of all of them (set by gemm_f32.hip, whose grid may have blocks without one)
 };
 // Tiles in groups of eight rows, so that a run of them is compact in both dimensions.
 __device__ __forceinline__ void place_of_tile(int tile, int tiles_m, int tiles_n, int& m, int& n) {
@@ -202,6 +202,7 @@ __device__ __forceinline__ int tile_of_block() {
 // gemm_f32.hip: fp32 problems whose operands gemm_small has checked.
 bool gemm_f32(int trans_a, int trans_b, SmallProblem& p, hipStream_t stream);
 bool gemm_f32_grouped(SmallGroup& g, hipStream_t stream);
+dim3 gemm_f32_grid(int64_t tiles, int threads);
 int gemm_f32_form(int n, const int* M, const int* N, int K);  // 0: 32 x 64 tiles, 1: 64 x 64, 2: 128 x 64
 
 }  // namespace po

@@ -283,6 +283,21 @@ def test_attention_of_rows_beyond_32_bit_offsets_goes_to_the_vector_kernels():
     assert bf16(128, most + 64, heads + 1, 1)
 
 
+def test_fp32_gemm_grids_end_below_the_limit_of_a_dimension():
+    """Host logic: blocks of 384 and 640 threads pass 2^32 threads at fewer tiles than smaller blocks did; the rest goes to the
+    second dimension."""
+    class Dim3(ctypes.Structure):
+        _fields_ = [(n, ctypes.c_uint32) for n in "xyz"]
+    f = po.lib["_ZN2po13gemm_f32_gridEli"]
+    f.restype, f.argtypes = Dim3, [ctypes.c_int64, ctypes.c_int]
+    for threads in (384, 640):
+        for tiles in (1, 256, 3000000, 1 << 24, (1 << 26) + 1, (1 << 31) - 1):
+            g = f(tiles, threads)
+            assert g.x * threads < 1 << 32 and g.y <= 65535 and g.z == 1
+            assert tiles <= g.x * g.y < tiles + g.y
+            assert g.y == 1 or tiles * threads > 1 << 31
+
+
 def test_whole_tiles_of_few_slices_stay_with_the_large_tiles():
     """Host logic: results of whole 128 x 128 tiles take the small ones from K = 256 on where those fill the chip better."""
     f = po.lib["_ZN2po20gemm_small_is_fasterEiii"]
