@@ -13,7 +13,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libpipeoffload.so")
 RESOURCES = os.path.join(PKG, "kernel_resources.json")  # per kernel: registers, scratch bytes per lane, occupancy
-SOURCES = ["elementwise.hip", "gemm_generic.hip", "gemm_mfma.hip", "gemm_small.hip", "gemm_f32.hip", "attention_generic.hip", "attention_f32.hip", "attention_mfma.hip",
+SOURCES = ["elementwise.hip", "gemm_generic.hip", "gemm_mfma.hip", "gemm_small.hip", "gemm_f32.hip", "attention_generic.hip", "attention_f32.hip", "attention_few.hip", "attention_mfma.hip",
            "schedule.cpp", "stage.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -206,9 +206,9 @@ static bool vectors_or_refused(int s, uintptr_t addresses) { return s % 128 == 0
 
 bool attention_forward(int dtype, const void* qkv, void* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                        bool force_generic, hipStream_t stream) {
-  // Vector / matrix cores in us, 16 heads: of 64 at 44, 52 and 100 rows 11.1 / 7.3, 12.5 / 7.6 and 23.4 / 7.6, of 128 at 52, 64 and
-  // 100 rows 18.3 / 8.8, 21.4 / 8.9 and 35.4 / 9.5.  The line was drawn when the matrix-core kernel took 10.6 and 17.5 us at any
-  // of these and has not been moved since.  The backward has none (8 rows: 15.5 / 10.3 and 24.6 / 14.4).
+  // Vector / matrix cores in us, 16 heads: of 64 at 16, 43 and 51 rows 6.6 / 4.0, 11.3 / 4.1 and 12.6 / 4.1, of 128 at 16, 51 and
+  // 64 rows 9.1 / 5.2, 18.4 / 5.4 and 21.7 / 5.3.  The line was drawn when the matrix-core kernel took 10.6 and 17.5 us at any
+  // of these and has not been moved since.  The backward has none (8 rows: 15.5 / 7.1 and 24.6 / 9.5).
   const int few = h == 64 * (int64_t)n_heads ? 43 : 51;
   if (dtype == kBF16 && !force_generic && s > few && attention_mfma_supported(s, h, n_heads, n_kv_heads) &&
       vectors_or_refused(s, (uintptr_t)qkv | (uintptr_t)o))

@@ -36,33 +36,14 @@
 // MFMAs of a tile with one, two and three terms: forward 2 : 3 : 4, backward 7 : 10 : 13.  Vector kernels -> two terms -> this
 // form, us: s 1733, 16 heads of 128: forward 2235 -> 73 -> 74, backward 20450 -> 100 -> 112; s 3000, 32 heads of 64 over 8: 5406 -> 115 -> 125 and
 // 72760 -> 278 -> 307; s 100, 16 heads of 128: 35 -> 18 and 147 -> 18.  Since then (one buffer descriptor per tile, heads of 64 with
-// both products of a half tile open at once) 46 and 120, 92 and 278, 10.3 and 18.7.
+// both products of a half tile open at once) 46 and 120, 92 and 278, 10.3 and 18.7; s 100 goes to attention_few.hip, 6.0 and 10.9.
 #include "attention_rows.h"
-#include "mfma_common.h"
+#include "attention_tile.h"
 
 namespace po {
 
-#define LDS_AS3(p) ((s16x4 __attribute__((address_space(3)))*)(p))
-
 constexpr int kKeysPerTile = 64;
 
-// ---- LDS tile --------------------------------------------------------------------
-// [64 rows][DH] bf16, unpadded: the 16-byte chunk c of row r sits at chunk position c ^ swz(r).
-// One tile serves both kinds of MFMA operand reads without bank conflicts:
-//  * ds_read_b128 "row" fragments (contraction over the head dimension): 16 lanes read the same
-//    chunk of 16 consecutive rows; swz is a bijection of those rows onto the 16 chunk positions
-//    of a 256-byte bank line (for DH = 64 two rows share a line and the row parity picks the half);
-//  * transposing reads (contraction over the tile's rows): a half-wave reads 64 contiguous bytes
-//    of four consecutive rows; swz sends them to the four different 64-byte quarters of a line.
-template <int DH>
-__device__ __forceinline__ int swz(int r) {
-  if (DH == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
-  return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-}
-template <int DH>
-__device__ __forceinline__ int tile_offset(int row, int chunk) {
-  return row * (DH * 2) + ((chunk ^ swz<DH>(row)) << 4);
-}
 template <int DH> constexpr int tile_bytes() { return kKeysPerTile * DH * 2; }
 
 // HBM -> LDS without a register stop: a wave-level global_load_lds_dwordx4 writes 1 KiB of the tile
@@ -122,88 +103,6 @@ __device__ __forceinline__ void wait_tile_loads() {
 // of two waves per SIMD, their extra waits cost nothing measurable, and the different schedule the visible wait
 // gives the compiler makes it spill.
 __device__ __forceinline__ void wait_tile_loads_opaque() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Fragment whose contraction index is the tile's row: lane (column c = lane % 32 of the
-// 32-wide block starting at col0, half = lane / 32) receives rows
-// {row0 + 4 half + 0..3} and {row0 + 4 half + 8 + 0..3} of column col0 + c.
-// Within a group of 16 lanes, the transposing read hands lane i element (i % 4) of the
-// four addresses supplied by lanes i / 4, 4 + i / 4, 8 + i / 4, 12 + i / 4 of the group.
-template <int DH>
-__device__ __forceinline__ bf16x8 read_tr_fragment(const char* tile, int row0, int col0, int lane) {
-  int i = lane & 15;
-  int grp = lane >> 4;
-  int half = grp >> 1;
-  int r = row0 + 4 * half + (i >> 2);
-  int c = col0 + 16 * (grp & 1) + 4 * (i & 3);
-  int inner = (c & 7) * 2;
-  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_AS3(tile + tile_offset<DH>(r, c >> 3) + inner));
-  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_AS3(tile + tile_offset<DH>(r + 8, c >> 3) + inner));
-  union {
-    struct {
-      s16x4 a, b;
-    } s;
-    bf16x8 v;
-  } u;
-  u.s.a = lo;
-  u.s.b = hi;
-  return u.v;
-}
-
-template <int DH>
-__device__ __forceinline__ bf16x8 read_row_fragment(const char* tile, int row, int chunk) {
-  return *reinterpret_cast<const bf16x8*>(tile + tile_offset<DH>(row, chunk));
-}
-
-// Eight consecutive accumulator values -> bf16 operand fragment.
-__device__ __forceinline__ bf16x8 pack_bf16x8(const f32x16& a, int first) {
-  bf16x8 r;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = (bf16)a[first + e];
-  return r;
-}
-
-// Eight probabilities (or dS) as an operand: rounded to bf16 once, or (FULL) as the sum of three bf16 terms that is the
-// fp32 value itself: its upper 16 bits, those of what is left, and the rest, which has no more than eight significant bits.
-// Both differences are exact.
-template <bool FULL>
-struct Weights {
-  bf16x8 term[FULL ? 3 : 1];
-};
-// Pair p of the eight values: upper halves of two floats side by side in one register of each term.
-__device__ __forceinline__ void split_pair(Weights<true>& w, const f32x16& a, int first, int p) {
-  float x0 = a[first + 2 * p], x1 = a[first + 2 * p + 1];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const unsigned u0 = __builtin_bit_cast(unsigned, x0), u1 = __builtin_bit_cast(unsigned, x1);
-    u32x4 v = __builtin_bit_cast(u32x4, w.term[k]);
-    v[p] = __builtin_amdgcn_perm(u1, u0, 0x07060302);
-    w.term[k] = __builtin_bit_cast(bf16x8, v);
-    x0 -= __builtin_bit_cast(float, u0 & 0xffff0000u);
-    x1 -= __builtin_bit_cast(float, u1 & 0xffff0000u);
-  }
-}
-template <bool FULL>
-__device__ __forceinline__ Weights<FULL> weights_of(const f32x16& a, int first) {
-  Weights<FULL> w;
-  if constexpr (FULL) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) split_pair(w, a, first, p);
-  } else {
-    w.term[0] = pack_bf16x8(a, first);
-  }
-  return w;
-}
-// c += m^T w, the small terms first.
-template <bool FULL>
-__device__ __forceinline__ f32x16 multiply(const bf16x8& m, const Weights<FULL>& w, f32x16 c) {
-  if constexpr (FULL) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m, w.term[2], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m, w.term[1], c, 0, 0, 0);
-  }
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(m, w.term[0], c, 0, 0, 0);
-}
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // ==================================================================================
 // Forward: S^T = K Q^T, online softmax, O^T += V^T P^T per 64-key tile, a wave owning 32 query rows.
@@ -1653,6 +1552,8 @@ bool attention_forward_mfma(const void* qkv, void* o, float* lse, int s, int h, 
   }
   const bf16* q = (const bf16*)qkv;
   bf16* out = (bf16*)o;
+  if (attention_few_forward_is_faster(s, h, n_heads, n_kv_heads))
+    return attention_few_forward(q, out, lse, s, h, n_heads, n_kv_heads, stream);
   if (s % 128 == 0) {
     if (h / n_heads == 128) return launch_fwd<128, false>(q, out, lse, s, h, n_heads, n_kv_heads, stream);
     return launch_fwd<64, false>(q, out, lse, s, h, n_heads, n_kv_heads, stream);
@@ -1668,6 +1569,11 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
   constexpr int smem_q = 4 * tile_bytes<DH>();
   float scale = 1.0f / sqrtf((float)DH);
   int hkv = n_kv_heads * DH, group = n_heads / n_kv_heads;
+  auto sum_groups = [&](const auto* parts, int n_parts) {
+    const size_t n = (size_t)s * (2 * hkv / 8);
+    attn_group_sum_kernel<DH><<<(unsigned)((n + 255) / 256), 256, 0, stream>>>(parts, dqkv, s, h + 2 * hkv, h, hkv, n_parts);
+    return launch_ok("attention backward MFMA kernels");
+  };
   attn_delta_mfma_path_kernel<DH><<<(unsigned)(((size_t)s * h / 8 + 255) / 256), 256, 0, stream>>>(o, d_o, delta, s, h);
   // Few key/value heads: one block per query head and a per-group sum afterwards (needs the [s, 2h] workspace),
   // once the direct launch would not fill the chip's 512 block slots.  Those partials are rounded to bf16; the EDGE
@@ -1680,6 +1586,13 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
   if (EDGE) {
     for (hpb_split = 2; hpb_split < group && group % hpb_split != 0;) ++hpb_split;
     split = split && hpb_split < group && (uintptr_t)partials % 16 == 0;
+  }
+  // Blocks of 32 rows sum a group in fp32 in one block, except where EDGE keeps partial results.
+  const int few_hpb = EDGE && split ? hpb_split : group;
+  if (attention_few_backward_is_faster(s, h, n_heads, n_kv_heads, few_hpb)) {
+    float* few_partials = EDGE && split ? reinterpret_cast<float*>(partials) : nullptr;
+    if (!attention_few_backward(qkv, lse, delta, d_o, dqkv, few_partials, few_hpb, s, h, n_heads, n_kv_heads, stream)) return false;
+    return !few_partials || sum_groups(few_partials, group / hpb_split);
   }
   const int n_parts = split ? group / hpb_split : 1;
   // At most one block per CU: the eight-wave kernel, which halves a wave's chain of tiles.  EDGE takes it up to three: the chain
@@ -1738,13 +1651,8 @@ static bool launch_bwd(const bf16* qkv, const bf16* o, const float* lse, const b
     }
   }
   if (split) {
-    size_t n = (size_t)s * (2 * hkv / 8);
-    const unsigned grid = (unsigned)((n + 255) / 256);
-    if (EDGE)
-      attn_group_sum_kernel<DH, float><<<grid, 256, 0, stream>>>((const float*)partials, dqkv, s, h + 2 * hkv, h, hkv,
-                                                                 n_parts);
-    else
-      attn_group_sum_kernel<DH, bf16><<<grid, 256, 0, stream>>>(partials, dqkv, s, h + 2 * hkv, h, hkv, n_parts);
+    if constexpr (EDGE) return sum_groups(reinterpret_cast<const float*>(partials), n_parts);
+    else return sum_groups(partials, n_parts);
   }
   return launch_ok("attention backward MFMA kernels");
 }

@@ -141,6 +141,15 @@ bool attention_forward_mfma(const void* qkv, void* o, float* lse, int s, int h, 
 bool attention_backward_mfma(const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,
                              float* delta, void* partials, int s, int h, int n_heads, int n_kv_heads,
                              hipStream_t stream);
+// bf16 in blocks of 32 rows (attention_few.hip) for launches that blocks of 128 rows would leave most of the chip idle: shapes and
+// pointers that attention_*_mfma have checked, where *_is_faster says so.  The backward takes delta as given.
+bool attention_few_forward_is_faster(int s, int h, int n_heads, int n_kv_heads);
+bool attention_few_forward(const bf16* qkv, bf16* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
+                           hipStream_t stream);
+// A dK/dV block walks hpb query heads; partials: null (hpb is the whole group), or where their fp32 results go.
+bool attention_few_backward_is_faster(int s, int h, int n_heads, int n_kv_heads, int hpb);
+bool attention_few_backward(const bf16* qkv, const float* lse, const float* delta, const bf16* d_o, bf16* dqkv,
+                            float* partials, int hpb, int s, int h, int n_heads, int n_kv_heads, hipStream_t stream);
 bool attention_forward(int dtype, const void* qkv, void* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                        bool force_generic, hipStream_t stream);
 bool attention_backward(int dtype, const void* qkv, const void* o, const float* lse, const void* d_o, void* dqkv,

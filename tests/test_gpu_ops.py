@@ -552,6 +552,31 @@ def _attention_64(qkv, d_o, o, lse, dh, a, akv):
     return want
 
 
+# Blocks of 32 rows: one tile and less, ends around a tile, more tiles than a block's waves have stages (8 x 2 with heads of 64,
+# 4 x 2 with heads of 128), groups, and both sides of the line to the 128-row blocks.  Against 64 bits: P, dS and the results
+# are rounded to bf16 (2^-9 each); what lies behind the results stays.
+@pytest.mark.parametrize("s,dh,a,akv", [(128, 64, 2, 2), (640, 64, 4, 1), (512, 64, 30, 30), (512, 64, 31, 31), (20, 64, 3, 3),
+                                        (44, 64, 2, 1), (97, 64, 8, 1), (545, 64, 4, 2), (777, 64, 25, 25), (128, 128, 2, 2),
+                                        (512, 128, 4, 2), (384, 128, 24, 24), (384, 128, 25, 25), (31, 128, 2, 1),
+                                        (65, 128, 3, 3), (300, 128, 4, 1), (129, 128, 70, 70)])
+def test_attention_blocks_of_32_rows(gpu_device, s, dh, a, akv):
+    h, hkv = a * dh, akv * dh
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(s + dh + a)
+    bf = lambda *size: torch.randn(*size, generator=g, device=gpu_device).bfloat16()
+    qkv, d_o = bf(s, h + 2 * hkv), bf(s, h)
+    o, dqkv = (torch.full((s + 40, n), 7.0, dtype=torch.bfloat16, device=gpu_device) for n in (h, h + 2 * hkv))
+    lse, delta = torch.full((a * s + 40,), 7.0, device=gpu_device), torch.empty(a, s, device=gpu_device)
+    po.po_op_attention_forward(po.PO_BF16, qkv, o, lse, s, h, a, n_kv_heads=akv)
+    po.po_op_attention_backward(po.PO_BF16, qkv, o, lse, d_o, dqkv, delta, s, h, a, n_kv_heads=akv)
+    assert (o[s:] == 7).all() and (dqkv[s:] == 7).all() and (lse[a * s:] == 7).all()
+    want = _attention_64(qkv, d_o, o[:s], lse[:a * s].view(a, s), dh, a, akv)
+    err = lambda got, ref: ((got.double() - ref).norm() / ref.norm()).item()
+    assert err(o[:s], want["o"]) < 2.0 ** -8 and (lse[:a * s].view(a, s) - want["lse"]).abs().max() < 1e-5
+    for part in (slice(0, h), slice(h, h + hkv), slice(h + hkv, h + 2 * hkv)):
+        assert err(dqkv[:s, part], want["dqkv"][:, part]) < 2.0 ** -7, part
+
+
 # Short sequences stay with the vector kernels, bit for bit; one row more and a call goes to the matrix cores (the bf16
 # backward always does).
 @pytest.mark.parametrize("dtype,dh,forward,backward", [("f32", 32, 4, 6), ("f32", 64, 9, 12), ("f32", 96, 13, 18),
