@@ -11,7 +11,7 @@
 #include <stdarg.h>
 #include <stdio.h>
 
-#include "kernels.h"
+#include "column_sums.h"
 
 namespace po {
 
@@ -440,13 +440,6 @@ bool colsum_accumulate_static(int dtype, const void* x, float* acc, int rows, in
 // --------------------------------------------------------------------------
 // Batched column reductions: the jobs' column blocks are laid end to end on grid.x
 // --------------------------------------------------------------------------
-struct ReduceBatch {
-  ReduceJob job[kMaxReduceJobs];
-  int first128[kMaxReduceJobs + 1];  // first 128-column block of job j on the partial kernel's grid.x
-  int first64[kMaxReduceJobs + 1];   // first 64-column block of job j on the final kernel's grid.x
-  int n_jobs;
-};
-
 template <typename T>
 __global__ __launch_bounds__(256) void reduce_batch_partial_kernel(ReduceBatch b, int rows, int rows_per_chunk) {
   __shared__ float red[4][128][2];
@@ -620,97 +613,11 @@ __global__ __launch_bounds__(256) void reduce_batch_final_kernel(ReduceBatch b, 
   }
 }
 
-// Few rows: one launch instead of two and no partials in memory.  A block of sixteen waves owns 64 columns of a job over ALL
-// rows, a lane one 16-byte vector of a row, 128 (fp32: 64) rows at once; the loads of four rows are in flight per lane and
-// added before they join the column's sum.  Bound by the round trips of a lane's rows, hence the many waves.
+// Few rows: one launch instead of two and no partials in memory.  Bound by the round trips of a lane's rows, hence sixteen waves.
 template <typename T>
 __global__ __launch_bounds__(1024) void reduce_batch_direct_kernel(ReduceBatch b, int rows) {
-  constexpr int V = Vec16<T>::N, LPR = 64 / V, SLOTS = 1024 / LPR;
-  __shared__ float red[16][2][64];
-  int j = 0;
-  while (j + 1 < b.n_jobs && (int)blockIdx.x >= b.first64[j + 1]) ++j;
-  const ReduceJob& job = b.job[j];
-  const int n = job.n, col0 = ((int)blockIdx.x - b.first64[j]) * 64;
-  const int cl = (int)threadIdx.x % LPR * V, slot = threadIdx.x / LPR;
-  const bool inside = col0 + cl < n, ln = job.x != nullptr;
-  const T* a = static_cast<const T*>(job.a) + col0 + cl;
-  const T* x = static_cast<const T*>(job.x) + col0 + cl;
-  float s0[V], s1[V];
-#pragma unroll
-  for (int i = 0; i < V; ++i) s0[i] = s1[i] = 0.f;
-  if (inside && !ln) {
-    constexpr int AT_ONCE = 4;
-    for (int r0 = slot; r0 < rows; r0 += AT_ONCE * SLOTS) {
-      Vec16<T> d[AT_ONCE];
-#pragma unroll
-      for (int u = 0; u < AT_ONCE; ++u) d[u] = load16(a + (size_t)min(r0 + u * SLOTS, rows - 1) * n);
-      float p[V];
-#pragma unroll
-      for (int i = 0; i < V; ++i) p[i] = 0.f;
-#pragma unroll
-      for (int u = 0; u < AT_ONCE; ++u)
-        if (r0 + u * SLOTS < rows)
-#pragma unroll
-          for (int i = 0; i < V; ++i) p[i] += to_f32(d[u].v[i]);
-#pragma unroll
-      for (int i = 0; i < V; ++i) s0[i] += p[i];
-    }
-  } else if (inside) {
-    constexpr int AT_ONCE = 4;
-    const float* stats = job.stats;
-    for (int r0 = slot; r0 < rows; r0 += AT_ONCE * SLOTS) {
-      Vec16<T> d[AT_ONCE], xv[AT_ONCE];
-      float mean[AT_ONCE], rstd[AT_ONCE];
-#pragma unroll
-      for (int u = 0; u < AT_ONCE; ++u) {
-        const size_t r = min(r0 + u * SLOTS, rows - 1);
-        d[u] = load16(a + r * n);
-        xv[u] = load16(x + r * n);
-        mean[u] = stats[2 * r];
-        rstd[u] = stats[2 * r + 1];
-      }
-      float p0[V], p1[V];
-#pragma unroll
-      for (int i = 0; i < V; ++i) p0[i] = p1[i] = 0.f;
-#pragma unroll
-      for (int u = 0; u < AT_ONCE; ++u)
-        if (r0 + u * SLOTS < rows)
-#pragma unroll
-          for (int i = 0; i < V; ++i) {
-            const float dv = to_f32(d[u].v[i]);
-            p0[i] += dv * (to_f32(xv[u].v[i]) - mean[u]) * rstd[u];
-            p1[i] += dv;
-          }
-#pragma unroll
-      for (int i = 0; i < V; ++i) {
-        s0[i] += p0[i];
-        s1[i] += p1[i];
-      }
-    }
-  }
-#pragma unroll
-  for (int m = LPR; m < kWave; m <<= 1)
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      s0[i] += __shfl_xor(s0[i], m);
-      if (ln) s1[i] += __shfl_xor(s1[i], m);
-    }
-  if ((threadIdx.x & 63) < LPR)
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      red[threadIdx.x >> 6][0][cl + i] = s0[i];
-      red[threadIdx.x >> 6][1][cl + i] = s1[i];
-    }
-  __syncthreads();
-  const int c = threadIdx.x & 63, plane = threadIdx.x >> 6;
-  if (plane < (ln ? 2 : 1) && col0 + c < n) {
-    float part[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) part[q] += red[4 * k + q][plane][c];
-    (plane ? job.out1 : job.out0)[col0 + c] += (part[0] + part[1]) + (part[2] + part[3]);
-  }
+  __shared__ float red[16 * 128];
+  column_sums_block<T, 1024, 64, 4>(b, blockIdx.x, rows, red);
 }
 
 size_t column_reductions_workspace(int rows, int n) { return (size_t)reduce_chunks(rows) * n * sizeof(float); }
@@ -721,12 +628,11 @@ size_t column_reductions_workspace(int rows, int n) { return (size_t)reduce_chun
 // 10.4 / 8.5, 11.0 / 10.6, 11.7 / 13.9: the round trips of its two tensors' rows are what a block without chunks waits for.
 static bool one_launch(int dtype, int rows, int blocks) { return rows <= 512 && (dtype == kF32 || blocks <= 256); }
 
-bool column_reductions(int dtype, const ReduceJob* jobs, int n_jobs, int rows, hipStream_t stream) {
-  if (n_jobs < 1 || n_jobs > kMaxReduceJobs || rows <= 0 || !jobs) {
-    set_error("column_reductions: n_jobs=%d rows=%d", n_jobs, rows);
+bool make_reduce_batch(const ReduceJob* jobs, int n_jobs, ReduceBatch& b) {
+  if (n_jobs < 1 || n_jobs > kMaxReduceJobs || !jobs) {
+    set_error("column_reductions: n_jobs=%d", n_jobs);
     return false;
   }
-  ReduceBatch b;
   b.n_jobs = n_jobs;
   b.first128[0] = b.first64[0] = 0;
   for (int j = 0; j < n_jobs; ++j) {
@@ -746,13 +652,27 @@ bool column_reductions(int dtype, const ReduceJob* jobs, int n_jobs, int rows, h
     b.first128[j + 1] = b.first128[n_jobs];
     b.first64[j + 1] = b.first64[n_jobs];
   }
+  return true;
+}
+
+bool column_sums_vectors(int dtype, const ReduceJob* jobs, int n_jobs) {
+  const int v = dtype == kF32 ? 4 : 8;
+  for (int j = 0; j < n_jobs; ++j)
+    if (jobs[j].n % v != 0 || (uintptr_t)jobs[j].a % 16 != 0 || (uintptr_t)jobs[j].x % 16 != 0) return false;
+  return true;
+}
+
+bool column_reductions(int dtype, const ReduceJob* jobs, int n_jobs, int rows, hipStream_t stream) {
+  if (rows <= 0) {
+    set_error("column_reductions: n_jobs=%d rows=%d", n_jobs, rows);
+    return false;
+  }
+  ReduceBatch b;
+  if (!make_reduce_batch(jobs, n_jobs, b)) return false;
   int n_chunks = reduce_chunks(rows);
   int rows_per_chunk = ceil_div(rows, n_chunks);
   dim3 g(b.first128[n_jobs], n_chunks);
-  const int v = dtype == kF32 ? 4 : 8;
-  bool vec = true;  // 16-byte loads need whole vectors per row and aligned rows
-  for (int j = 0; j < n_jobs; ++j)
-    vec = vec && jobs[j].n % v == 0 && (uintptr_t)jobs[j].a % 16 == 0 && (uintptr_t)jobs[j].x % 16 == 0;
+  const bool vec = column_sums_vectors(dtype, jobs, n_jobs);
   if (vec && one_launch(dtype, rows, b.first64[n_jobs])) {
     if (dtype == kF32) reduce_batch_direct_kernel<float><<<b.first64[n_jobs], 1024, 0, stream>>>(b, rows);
     else reduce_batch_direct_kernel<bf16><<<b.first64[n_jobs], 1024, 0, stream>>>(b, rows);

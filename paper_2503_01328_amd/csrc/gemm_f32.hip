@@ -173,8 +173,8 @@ __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* 
 }
 
 // The tile of a block of a grid of gemm_f32_grid; of a second dimension the last blocks have none.
-__device__ __forceinline__ int tile_of_f32_block() {
-  return gridDim.y == 1 ? tile_of_block() : (int)(blockIdx.y * gridDim.x + blockIdx.x);
+__device__ __forceinline__ int tile_of_f32_block(int before = 0) {
+  return gridDim.y == 1 ? tile_of_block(before) : (int)(blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 template <typename Form, bool TA, bool TB>
@@ -184,10 +184,18 @@ __global__ __launch_bounds__(Form::THREADS) void gemm_f32_kernel(SmallProblem p)
   if (tile < (p.M + Form::BM - 1) / Form::BM * p.tiles_n) f32_tile<Form, TA, TB>(p, tile, smem);
 }
 
-template <typename Form>
-__global__ __launch_bounds__(Form::THREADS) void gemm_f32_grouped_kernel(SmallGroup g) {
+template <typename Form, typename... Sums>
+__global__ __launch_bounds__(Form::THREADS) void gemm_f32_grouped_kernel(SmallGroup g, Sums... sums) {
   extern __shared__ __align__(16) char smem[];
-  const int lin = tile_of_f32_block();
+  int before = 0;
+  if constexpr (sizeof...(Sums) > 0) {  // column sums in the first blocks (of a grid of one dimension)
+    before = (sums.blocks, ...);
+    if ((int)blockIdx.x < before) {
+      (column_sums_block<float, Form::THREADS, 64, 4>(sums.batch, blockIdx.x, sums.rows, reinterpret_cast<float*>(smem)), ...);
+      return;
+    }
+  }
+  const int lin = tile_of_f32_block(before);
   if (lin >= g.tiles) return;
   SmallProblem p = g.p[0];  // constant indices only: a run-time index would send the arguments through memory
 #pragma unroll
@@ -218,9 +226,9 @@ static bool launch_trans(int ta, int tb, SmallProblem& p, hipStream_t stream) {
   if (ta && !tb) return launch_one<Form, true, true>(p, stream);
   return launch_one<Form, true, false>(p, stream);
 }
-template <typename Form>
-static bool launch_group(SmallGroup& g, hipStream_t stream) {
-  auto kern = gemm_f32_grouped_kernel<Form>;
+template <typename Form, typename... Sums>
+static bool launch_group(SmallGroup& g, hipStream_t stream, const Sums&... sums) {
+  auto kern = gemm_f32_grouped_kernel<Form, Sums...>;
   static LdsLimit lds;
   if (!lds.allow(kern, Form::SMEM)) return false;
   int total = 0;
@@ -230,7 +238,7 @@ static bool launch_group(SmallGroup& g, hipStream_t stream) {
     total += ceil_div(g.p[i].M, Form::BM) * g.p[i].tiles_n;
   }
   g.tiles = total;
-  kern<<<gemm_f32_grid(total, Form::THREADS), Form::THREADS, Form::SMEM, stream>>>(g);
+  kern<<<gemm_f32_grid(total + (0 + ... + sums.blocks), Form::THREADS), Form::THREADS, Form::SMEM, stream>>>(g, sums...);
   return launch_ok("gemm_f32_grouped_kernel");
 }
 
@@ -276,18 +284,24 @@ bool gemm_f32(int ta, int tb, SmallProblem& p, hipStream_t stream) {
   }
 }
 
-bool gemm_f32_grouped(SmallGroup& g, hipStream_t stream) {
+template <typename... Sums>
+static bool group_form(int form, SmallGroup& g, hipStream_t stream, const Sums&... sums) {
+  switch (form) {
+    case 0: return launch_group<Form32x64>(g, stream, sums...);
+    case 1: return launch_group<Form64x64>(g, stream, sums...);
+    default: return launch_group<Form128x64>(g, stream, sums...);
+  }
+}
+
+bool gemm_f32_grouped(SmallGroup& g, const GroupSums* sums, hipStream_t stream) {
   int M[kMaxSmallGroup], N[kMaxSmallGroup], K = g.p[0].K;
   for (int i = 0; i < g.n; ++i) {
     M[i] = g.p[i].M;
     N[i] = g.p[i].N;
     K = min(K, g.p[i].K);
   }
-  switch (gemm_f32_form(g.n, M, N, K)) {
-    case 0: return launch_group<Form32x64>(g, stream);
-    case 1: return launch_group<Form64x64>(g, stream);
-    default: return launch_group<Form128x64>(g, stream);
-  }
+  const int form = gemm_f32_form(g.n, M, N, K);
+  return sums ? group_form(form, g, stream, *sums) : group_form(form, g, stream);
 }
 
 }  // namespace po

@@ -2,7 +2,7 @@
 // 16-byte vectors, unaligned operands) and what force_generic asks for.  64x64 block tile,
 // 16-deep k slices staged through LDS as fp32, each thread owns a 4x4 micro-tile.
 // All bounds are checked, so any M, N, K >= 1 and any leading dimension works.
-#include "kernels.h"
+#include "column_sums.h"
 
 namespace po {
 
@@ -150,9 +150,34 @@ bool gemm_grouped_supported(int dtype, int n, const GemmProblem* p) {
          (dtype == kBF16 && (gemm_mfma_grouped_supported(n, p) || gemm_mfma_grouped_edge_supported(n, p)));
 }
 
+static bool group_is_small(int dtype, int n, const GemmProblem* p) {
+  return gemm_small_grouped_supported(dtype, n, p) &&
+         (dtype == kF32 || gemm_small_group_is_faster(n, p) ||
+          !(gemm_mfma_grouped_supported(n, p) || gemm_mfma_grouped_edge_supported(n, p)));
+}
+
+// The sums' blocks come first and run beside the tiles; what is saved is the launch (or two) and what those took alone.  A block
+// sums all rows of its columns, a chain that outlasts the tiles where a bf16 product's K is long, and in fp32 one
+// whose rounding grows beyond that of partial sums (against 64 bits 9.5e-8 both at 1024 rows, 1.03e-7 and 1.01e-7 at 1400, 1.4e-7 and
+// 1.1e-7 at 4096).  Two layers of width h and s
+// rows, 2 or 4 microbatches, launches of their own / in passing, us: bf16 h 512, s 256 893 / 823, s 512 936 / 875, s 1000
+// 1433 / 1397, s 2048 1714 / 1709, s 4096 1556 / 1620; h 256, s 1024 988 / 966, s 2048 1270 / 1268, s 4096 1004 / 1045; fp32 h 256, s 128
+// 1251 / 1210, h 1024, s 1024 3233 / 3177.
+bool gemm_grouped_takes_sums(int dtype, int n, const GemmProblem* p, const ReduceJob* jobs, int n_jobs, int rows) {
+  int64_t blocks = 0;  // at most, of at most 640 threads: a grid of one dimension
+  for (int j = 0; j < n_jobs; ++j) blocks += ceil_div(jobs[j].n, 32);
+  for (int i = 0; i < n; ++i) blocks += (int64_t)ceil_div(p[i].M, 32) * ceil_div(p[i].N, 32);
+  return rows <= (dtype == kF32 ? 1024 : 1536) && blocks * 640 < (int64_t)1 << 31 && group_is_small(dtype, n, p) &&
+         column_sums_vectors(dtype, jobs, n_jobs);
+}
+
+bool gemm_grouped_accumulate_with_sums(int dtype, int n, const GemmProblem* p, const ReduceJob* jobs, int n_jobs, int rows,
+                                       hipStream_t stream) {
+  return gemm_small_grouped_accumulate(dtype, n, p, stream, jobs, n_jobs, rows);
+}
+
 bool gemm_grouped_accumulate(int dtype, int n, const GemmProblem* p, hipStream_t stream) {
-  const bool small = gemm_small_grouped_supported(dtype, n, p);
-  if (dtype == kBF16 && !(small && gemm_small_group_is_faster(n, p))) {
+  if (dtype == kBF16 && !group_is_small(dtype, n, p)) {
     if (gemm_mfma_grouped_supported(n, p)) return gemm_mfma_grouped_accumulate(n, p, stream);
     if (gemm_mfma_grouped_edge_supported(n, p)) return gemm_mfma_grouped_edge_accumulate(n, p, stream);
   }

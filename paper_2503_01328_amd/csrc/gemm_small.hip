@@ -130,11 +130,25 @@ __global__ __launch_bounds__(64 * KG) void gemm_small_kernel(SmallProblem p) {
   small_tile<T, TM, TN, KG, TA, TB>(p, tile_of_block(), smem);
 }
 
+// Columns of a column-sum block: half of the 64 where a block has few waves, each of whose rounds over the rows is a chain of
+// memory round trips.
+template <int KG>
+constexpr int kSumColumns = KG <= 2 ? 32 : 64;
+
 // The four weight-gradient products of a layer in one launch: the tiles of all of them one product after the other.
-template <typename T, int TM, int TN, int KG>
-__global__ __launch_bounds__(64 * KG) void gemm_small_grouped_kernel(SmallGroup g) {
+// SUMS: and its column sums, in blocks of their own before the others, which hide them.
+template <typename T, int TM, int TN, int KG, typename... Sums>
+__global__ __launch_bounds__(64 * KG) void gemm_small_grouped_kernel(SmallGroup g, Sums... sums) {
   extern __shared__ __align__(16) char smem[];
-  const int lin = tile_of_block();
+  int before = 0;
+  if constexpr (sizeof...(Sums) > 0) {
+    before = (sums.blocks, ...);
+    if ((int)blockIdx.x < before) {
+      (column_sums_block<T, 64 * KG, kSumColumns<KG>, 4>(sums.batch, blockIdx.x, sums.rows, reinterpret_cast<float*>(smem)), ...);
+      return;
+    }
+  }
+  const int lin = tile_of_block(before);
   SmallProblem p = g.p[0];  // constant indices only: a run-time index would send the arguments through memory
 #pragma unroll
   for (int i = 1; i < kMaxSmallGroup; ++i)
@@ -230,10 +244,10 @@ bool gemm_small(int dtype, int ta, int tb, int M, int N, int K, const void* A, i
   return launch_form(dtype, f, ta, tb, p, stream);
 }
 
-template <typename T, int TM, int TN, int KG>
-static bool launch_group(SmallGroup& g, hipStream_t stream) {
+template <typename T, int TM, int TN, int KG, typename... Sums>
+static bool launch_group(SmallGroup& g, hipStream_t stream, Sums... sums) {
   constexpr int smem = KG * 2 * 32 * (TM + TN) * 128;
-  auto kern = gemm_small_grouped_kernel<T, TM, TN, KG>;
+  auto kern = gemm_small_grouped_kernel<T, TM, TN, KG, Sums...>;
   static LdsLimit lds;
   if (!lds.allow(kern, smem)) return false;
   int total = 0;
@@ -242,16 +256,19 @@ static bool launch_group(SmallGroup& g, hipStream_t stream) {
     g.p[i].first_tile = total;
     total += ceil_div(g.p[i].M, 32 * TM) * g.p[i].tiles_n;
   }
-  kern<<<total, 64 * KG, smem, stream>>>(g);
+  ((sums.blocks *= 64 / kSumColumns<KG>), ...);
+  kern<<<total + (0 + ... + sums.blocks), 64 * KG, smem, stream>>>(g, sums...);
   return launch_ok("gemm_small_grouped_kernel");
 }
 
-static bool group_form(int dtype, SmallForm f, SmallGroup& g, hipStream_t stream) {
-  if (dtype == kF32) return f.waves == 8 ? launch_group<float, 1, 1, 8>(g, stream) : launch_group<float, 1, 1, 4>(g, stream);
-  if (f.edge == 32) return launch_group<bf16, 1, 1, 4>(g, stream);
-  if (f.waves == 4) return launch_group<bf16, 2, 2, 4>(g, stream);
-  if (f.waves == 2) return launch_group<bf16, 2, 2, 2>(g, stream);
-  return launch_group<bf16, 2, 2, 1>(g, stream);
+template <typename... Sums>
+static bool group_form(int dtype, SmallForm f, SmallGroup& g, hipStream_t stream, const Sums&... sums) {
+  if (dtype == kF32)
+    return f.waves == 8 ? launch_group<float, 1, 1, 8>(g, stream, sums...) : launch_group<float, 1, 1, 4>(g, stream, sums...);
+  if (f.edge == 32) return launch_group<bf16, 1, 1, 4>(g, stream, sums...);
+  if (f.waves == 4) return launch_group<bf16, 2, 2, 4>(g, stream, sums...);
+  if (f.waves == 2) return launch_group<bf16, 2, 2, 2>(g, stream, sums...);
+  return launch_group<bf16, 2, 2, 1>(g, stream, sums...);
 }
 
 bool gemm_small_grouped_supported(int dtype, int n, const GemmProblem* prob) {
@@ -265,7 +282,8 @@ bool gemm_small_grouped_supported(int dtype, int n, const GemmProblem* prob) {
   return true;
 }
 
-bool gemm_small_grouped_accumulate(int dtype, int n, const GemmProblem* prob, hipStream_t stream) {
+bool gemm_small_grouped_accumulate(int dtype, int n, const GemmProblem* prob, hipStream_t stream, const ReduceJob* jobs,
+                                   int n_jobs, int rows) {
   if (!gemm_small_grouped_supported(dtype, n, prob)) {
     set_error("gemm_small_grouped: %d problems, or a shape, stride or pointer the kernel does not take", n);
     return false;
@@ -286,12 +304,18 @@ bool gemm_small_grouped_accumulate(int dtype, int n, const GemmProblem* prob, hi
     tiles32 += (int64_t)ceil_div(q.M, 32) * ceil_div(q.N, 32);
     K = min(K, q.K);
   }
-  if (dtype == kF32 && !f32_few_tiles(tiles32, K)) return gemm_f32_grouped(g, stream);
+  GroupSums sums;
+  if (n_jobs > 0) {
+    if (!make_reduce_batch(jobs, n_jobs, sums.batch)) return false;
+    sums.rows = rows;
+    sums.blocks = sums.batch.first64[n_jobs];
+  }
+  if (dtype == kF32 && !f32_few_tiles(tiles32, K)) return gemm_f32_grouped(g, n_jobs > 0 ? &sums : nullptr, stream);
   SmallForm f = small_form(dtype, tiles64, K);
   // a group of bf16 products does best with one wave per tile from 512 on:
   // width 512, 100 / 512 / 4000 rows 9.0 / 12.4 / 44.8 us against 10.7 / 14.5 / 49.9 with two
   if (dtype == kBF16 && tiles64 >= 512) f.waves = 1;
-  return group_form(dtype, f, g, stream);
+  return n_jobs > 0 ? group_form(dtype, f, g, stream, sums) : group_form(dtype, f, g, stream);
 }
 
 }  // namespace po

@@ -2,6 +2,7 @@
 // LDS, fragments out of it, the epilogue on one vector, a tile's place.
 #pragma once
 
+#include "column_sums.h"
 #include "mfma_common.h"
 
 namespace po {
@@ -193,15 +194,22 @@ __device__ __forceinline__ void place_of_tile(int tile, int tiles_m, int tiles_n
   n = at / rows;
 }
 
-// Block ids equal modulo 8 share an XCD: each XCD gets a run of neighbouring tiles (and their operands its L2).
-__device__ __forceinline__ int tile_of_block() {
-  const int n = gridDim.x, pid = blockIdx.x;
+// Column sums that a group's launch does beside its products, in its first `blocks` blocks.
+struct GroupSums {
+  ReduceBatch batch;
+  int rows, blocks;
+};
+
+// Block ids equal modulo 8 share an XCD: each XCD gets a run of neighbouring tiles (and their operands its L2).  The first
+// `before` blocks have no tile.
+__device__ __forceinline__ int tile_of_block(int before = 0) {
+  const int n = gridDim.x - before, pid = blockIdx.x - before;
   return n % 8 == 0 ? (pid % 8) * (n / 8) + pid / 8 : pid;
 }
 
 // gemm_f32.hip: fp32 problems whose operands gemm_small has checked.
 bool gemm_f32(int trans_a, int trans_b, SmallProblem& p, hipStream_t stream);
-bool gemm_f32_grouped(SmallGroup& g, hipStream_t stream);
+bool gemm_f32_grouped(SmallGroup& g, const GroupSums* sums, hipStream_t stream);
 dim3 gemm_f32_grid(int64_t tiles, int threads);
 int gemm_f32_form(int n, const int* M, const int* N, int K);  // 0: 32 x 64 tiles, 1: 64 x 64, 2: 128 x 64
 

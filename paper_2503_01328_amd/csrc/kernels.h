@@ -101,10 +101,17 @@ bool gemm_small(int dtype, int trans_a, int trans_b, int M, int N, int K, const 
                 int ldb, const Epilogue& ep, hipStream_t stream);
 // The counterpart of gemm_mfma_grouped_accumulate for its shapes and types.
 bool gemm_small_grouped_supported(int dtype, int n, const GemmProblem* p);
-bool gemm_small_grouped_accumulate(int dtype, int n, const GemmProblem* p, hipStream_t stream);
+// jobs: column sums over `rows` rows that the same launch does (column_sums_vectors).
+bool gemm_small_grouped_accumulate(int dtype, int n, const GemmProblem* p, hipStream_t stream,
+                                   const ReduceJob* jobs = nullptr, int n_jobs = 0, int rows = 0);
 // Several weight-gradient products in one launch of whichever of those kernels takes them and is the fastest.
 bool gemm_grouped_supported(int dtype, int n, const GemmProblem* p);
 bool gemm_grouped_accumulate(int dtype, int n, const GemmProblem* p, hipStream_t stream);
+// Whether that launch does a layer's column sums in passing (gemm_grouped_accumulate_with_sums), and cheaper than
+// column_reductions would.  The sums come out the same up to the order of additions.
+bool gemm_grouped_takes_sums(int dtype, int n, const GemmProblem* p, const ReduceJob* jobs, int n_jobs, int rows);
+bool gemm_grouped_accumulate_with_sums(int dtype, int n, const GemmProblem* p, const ReduceJob* jobs, int n_jobs, int rows,
+                                       hipStream_t stream);
 // Picks the kernel by type and shape; force_generic: the vector kernel.
 bool gemm(int dtype, int trans_a, int trans_b, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
           const Epilogue& ep, bool force_generic, hipStream_t stream);

@@ -533,7 +533,9 @@ static int st_gemm(po_stage* st, int ta, int tb, int M, int N, int K, const void
   return span_end(st, q, span);
 }
 
-static int st_gemm_grouped(po_stage* st, int n, const GemmProblem* prob, hipStream_t q) {
+// jobs (may be null): column sums over `rows` rows that the same launch does.
+static int st_gemm_grouped(po_stage* st, int n, const GemmProblem* prob, const ReduceJob* jobs, int n_jobs, int rows,
+                           hipStream_t q) {
   bool prof = sample_launch(st, st->gemm_launch_counter);
   size_t span = (size_t)-1;
   if (prof) {
@@ -541,7 +543,8 @@ static int st_gemm_grouped(po_stage* st, int n, const GemmProblem* prob, hipStre
     if (rc) return rc;
     for (int i = 0; i < n; ++i) st->spans[span].flops += 2.0 * prob[i].M * prob[i].N * prob[i].K;
   }
-  PO_K(gemm_grouped_accumulate(st->cfg.dtype, n, prob, q));
+  if (jobs) PO_K(gemm_grouped_accumulate_with_sums(st->cfg.dtype, n, prob, jobs, n_jobs, rows, q));
+  else PO_K(gemm_grouped_accumulate(st->cfg.dtype, n, prob, q));
   return span_end(st, q, span);
 }
 
@@ -723,25 +726,23 @@ static int layer_backward_weight(po_stage* st, int layer, const char* slab, cons
   const void* dz2 = drop ? (const void*)b.dz2 : dy;  // what the input-gradient half fed the MLP output projection
   const void* dz1 = drop ? (const void*)b.dz1 : (const void*)b.dx1;
   const int wq = qkv_width_of(c);
-  // All six column reductions of the layer (four bias gradients, two LayerNorm gain / shift pairs) in two
-  // launches; their inputs are complete once the input-gradient half has run.
-  {
-    const size_t plane = column_reductions_workspace(s, 1) / sizeof(float);  // floats per column
-    float* ws = colws;
-    ReduceJob jobs[6];
-    auto sum_job = [&](const void* a, float* out, int n) {
-      ReduceJob j{a, nullptr, nullptr, out, nullptr, ws, n};
-      ws += plane * n;
-      return j;
-    };
-    jobs[0] = sum_job(dz2, st->G(layer, pl.b_fc2), h);
-    jobs[1] = sum_job(b.du, st->G(layer, pl.b_fc1), f);
-    jobs[2] = sum_job(dz1, st->G(layer, pl.b_o), h);
-    jobs[3] = sum_job(b.dqkv, st->G(layer, pl.b_qkv), wq);
-    jobs[4] = ReduceJob{b.dn2, x1, b.lnws2, st->G(layer, pl.ln2_g), st->G(layer, pl.ln2_b), b.lnws2 + (size_t)s * 2, h};
-    jobs[5] = ReduceJob{b.dn1, x, b.lnws1, st->G(layer, pl.ln1_g), st->G(layer, pl.ln1_b), b.lnws1 + (size_t)s * 2, h};
-    PO_K(column_reductions(dt, jobs, 6, s, q));
-  }
+  // All six column reductions of the layer (four bias gradients, two LayerNorm gain / shift pairs); their inputs are complete
+  // once the input-gradient half has run.
+  const size_t plane = column_reductions_workspace(s, 1) / sizeof(float);  // floats per column
+  float* ws = colws;
+  auto sum_job = [&](const void* a, float* out, int n) {
+    ReduceJob j{a, nullptr, nullptr, out, nullptr, ws, n};
+    ws += plane * n;
+    return j;
+  };
+  const ReduceJob jobs[6] = {
+      sum_job(dz2, st->G(layer, pl.b_fc2), h),
+      sum_job(b.du, st->G(layer, pl.b_fc1), f),
+      sum_job(dz1, st->G(layer, pl.b_o), h),
+      sum_job(b.dqkv, st->G(layer, pl.b_qkv), wq),
+      ReduceJob{b.dn2, x1, b.lnws2, st->G(layer, pl.ln2_g), st->G(layer, pl.ln2_b), b.lnws2 + (size_t)s * 2, h},
+      ReduceJob{b.dn1, x, b.lnws1, st->G(layer, pl.ln1_g), st->G(layer, pl.ln1_b), b.lnws1 + (size_t)s * 2, h},
+  };
   // The four products dW = operand^T gradient.  They do not depend on each other, so they go out as one grouped launch
   // (both LayerNorm outputs recomputed first, into two buffers) and the chip works through the tiles of all four
   // without a launch boundary in between; one launch each where a tensor is not aligned as those kernels need it.
@@ -753,12 +754,15 @@ static int layer_backward_weight(po_stage* st, int layer, const char* slab, cons
       {h, h, s, o, h, dz1, h, st->G(layer, pl.w_o), h},
       {h, wq, s, n1, h, b.dqkv, wq, st->G(layer, pl.w_qkv), wq},
   };
-  if (gemm_grouped_supported(dt, 4, prob)) {
+  const bool grouped = gemm_grouped_supported(dt, 4, prob);
+  const bool with_sums = grouped && gemm_grouped_takes_sums(dt, 4, prob, jobs, 6, s);
+  if (!with_sums) PO_K(column_reductions(dt, jobs, 6, s, q));  // one launch or two
+  if (grouped) {
     if (!n_ready) {
       PO_K(layernorm_forward(dt, x1, st->P(layer, pl.ln2_g), st->P(layer, pl.ln2_b), n2, s, h, c.ln_eps, q));
       PO_K(layernorm_forward(dt, x, st->P(layer, pl.ln1_g), st->P(layer, pl.ln1_b), n1, s, h, c.ln_eps, q));
     }
-    return st_gemm_grouped(st, 4, prob, q);
+    return st_gemm_grouped(st, 4, prob, with_sums ? jobs : nullptr, 6, s, q);
   }
   for (int i = 0; i < 4; ++i) {
     if (i == 1 && !n_ready)

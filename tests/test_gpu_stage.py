@@ -109,6 +109,21 @@ def test_grouped_weight_gradients_of_any_shape(gpu_device, shape):
         _compare(shape, r.results(), _oracle(shape, r, 2), 1e-4 if shape.dtype == "f32" else 2e-2)
 
 
+# Bias, gain and shift gradients as blocks of the launch of a layer's weight-gradient products, in front of 32 x 32 tiles, of 64 x 64
+# tiles of four waves and of one, and of fp32 tiles: rows that leave lanes and rounds without work, columns that end inside a block,
+# and one row more than is taken there.
+@pytest.mark.parametrize("dtype,h,f,s", [("bf16", 64, 192, 1), ("bf16", 64, 192, 33), ("bf16", 64, 192, 1536),
+                                         ("bf16", 64, 192, 1537), ("bf16", 256, 1024, 520), ("bf16", 512, 2048, 130),
+                                         ("f32", 64, 192, 1), ("f32", 64, 192, 97), ("f32", 64, 192, 1025), ("f32", 512, 1024, 385)])
+def test_column_sums_beside_the_weight_gradients(gpu_device, dtype, h, f, s):
+    # one key/value head of size 16: the query-key-value bias has h + 32 columns
+    shape = syn.StageShape(1, 1, h, h // 16, f, s, dtype=dtype, pipeline_degree=1, n_microbatches=2, n_kv_heads=1)
+    with StageRunner(shape) as r:
+        r.make_inputs()
+        r.run(po.PO_SCHED_1F1B, 0.0)
+        _compare(shape, r.results(), _oracle(shape, r, 2), 1e-4 if dtype == "f32" else 2e-2)
+
+
 @pytest.mark.parametrize("shape", [SMALL_BF16, syn.StageShape(2, 1, 128, 2, 512, 96, vocab=50, dtype="f32",
                                                              pipeline_degree=4, n_microbatches=6)],
                          ids=["bf16", "f32-embed"])
