@@ -173,8 +173,8 @@ __device__ __forceinline__ void f32_tile(const SmallProblem& p, int tile, char* 
 }
 
 // The tile of a block of a grid of gemm_f32_grid; of a second dimension the last blocks have none.
-__device__ __forceinline__ int tile_of_f32_block(int before = 0) {
-  return gridDim.y == 1 ? tile_of_block(before) : (int)(blockIdx.y * gridDim.x + blockIdx.x);
+__device__ __forceinline__ int tile_of_f32_block() {
+  return gridDim.y == 1 ? tile_of_block() : (int)(blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 template <typename Form, bool TA, bool TB>
@@ -184,24 +184,28 @@ __global__ __launch_bounds__(Form::THREADS) void gemm_f32_kernel(SmallProblem p)
   if (tile < (p.M + Form::BM - 1) / Form::BM * p.tiles_n) f32_tile<Form, TA, TB>(p, tile, smem);
 }
 
-template <typename Form, typename... Sums>
-__global__ __launch_bounds__(Form::THREADS) void gemm_f32_grouped_kernel(SmallGroup g, Sums... sums) {
-  extern __shared__ __align__(16) char smem[];
-  int before = 0;
-  if constexpr (sizeof...(Sums) > 0) {  // column sums in the first blocks (of a grid of one dimension)
-    before = (sums.blocks, ...);
-    if ((int)blockIdx.x < before) {
-      (column_sums_block<float, Form::THREADS, 64, 4>(sums.batch, blockIdx.x, sums.rows, reinterpret_cast<float*>(smem)), ...);
-      return;
-    }
-  }
-  const int lin = tile_of_f32_block(before);
+template <typename Form>
+__device__ __forceinline__ void f32_group_tile(const SmallGroup& g, int lin, char* smem) {
   if (lin >= g.tiles) return;
   SmallProblem p = g.p[0];  // constant indices only: a run-time index would send the arguments through memory
 #pragma unroll
   for (int i = 1; i < kMaxSmallGroup; ++i)
     if (i < g.n && lin >= g.p[i].first_tile) p = g.p[i];
   f32_tile<Form, true, true>(p, lin - p.first_tile, smem);
+}
+template <typename Form>
+__global__ __launch_bounds__(Form::THREADS) void gemm_f32_grouped_kernel(SmallGroup g) {
+  extern __shared__ __align__(16) char smem[];
+  f32_group_tile<Form>(g, tile_of_f32_block(), smem);
+}
+// And its column sums, in blocks of their own before the others, which hide them (a grid of one dimension).
+template <typename Form>
+__global__ __launch_bounds__(Form::THREADS) void gemm_f32_with_sums_kernel(SmallGroup g, GroupSums sums) {
+  extern __shared__ __align__(16) char smem[];
+  if ((int)blockIdx.x < sums.blocks)
+    column_sums_block<float, Form::THREADS, 64, 4>(sums.batch, blockIdx.x, sums.rows, reinterpret_cast<float*>(smem));
+  else
+    f32_group_tile<Form>(g, tile_of_block(sums.blocks), smem);
 }
 
 // A dimension of a grid ends at 2^32 threads.
@@ -226,11 +230,8 @@ static bool launch_trans(int ta, int tb, SmallProblem& p, hipStream_t stream) {
   if (ta && !tb) return launch_one<Form, true, true>(p, stream);
   return launch_one<Form, true, false>(p, stream);
 }
-template <typename Form, typename... Sums>
-static bool launch_group(SmallGroup& g, hipStream_t stream, const Sums&... sums) {
-  auto kern = gemm_f32_grouped_kernel<Form, Sums...>;
-  static LdsLimit lds;
-  if (!lds.allow(kern, Form::SMEM)) return false;
+template <typename Form>
+static bool launch_group(SmallGroup& g, const GroupSums* sums, hipStream_t stream) {
   int total = 0;
   for (int i = 0; i < g.n; ++i) {
     g.p[i].tiles_n = ceil_div(g.p[i].N, Form::BN);
@@ -238,7 +239,17 @@ static bool launch_group(SmallGroup& g, hipStream_t stream, const Sums&... sums)
     total += ceil_div(g.p[i].M, Form::BM) * g.p[i].tiles_n;
   }
   g.tiles = total;
-  kern<<<gemm_f32_grid(total + (0 + ... + sums.blocks), Form::THREADS), Form::THREADS, Form::SMEM, stream>>>(g, sums...);
+  if (sums) {
+    auto kern = gemm_f32_with_sums_kernel<Form>;
+    static LdsLimit lds;
+    if (!lds.allow(kern, Form::SMEM)) return false;
+    kern<<<total + sums->blocks, Form::THREADS, Form::SMEM, stream>>>(g, *sums);
+  } else {
+    auto kern = gemm_f32_grouped_kernel<Form>;
+    static LdsLimit lds;
+    if (!lds.allow(kern, Form::SMEM)) return false;
+    kern<<<gemm_f32_grid(total, Form::THREADS), Form::THREADS, Form::SMEM, stream>>>(g);
+  }
   return launch_ok("gemm_f32_grouped_kernel");
 }
 
@@ -284,15 +295,6 @@ bool gemm_f32(int ta, int tb, SmallProblem& p, hipStream_t stream) {
   }
 }
 
-template <typename... Sums>
-static bool group_form(int form, SmallGroup& g, hipStream_t stream, const Sums&... sums) {
-  switch (form) {
-    case 0: return launch_group<Form32x64>(g, stream, sums...);
-    case 1: return launch_group<Form64x64>(g, stream, sums...);
-    default: return launch_group<Form128x64>(g, stream, sums...);
-  }
-}
-
 bool gemm_f32_grouped(SmallGroup& g, const GroupSums* sums, hipStream_t stream) {
   int M[kMaxSmallGroup], N[kMaxSmallGroup], K = g.p[0].K;
   for (int i = 0; i < g.n; ++i) {
@@ -300,8 +302,11 @@ bool gemm_f32_grouped(SmallGroup& g, const GroupSums* sums, hipStream_t stream) 
     N[i] = g.p[i].N;
     K = min(K, g.p[i].K);
   }
-  const int form = gemm_f32_form(g.n, M, N, K);
-  return sums ? group_form(form, g, stream, *sums) : group_form(form, g, stream);
+  switch (gemm_f32_form(g.n, M, N, K)) {
+    case 0: return launch_group<Form32x64>(g, sums, stream);
+    case 1: return launch_group<Form64x64>(g, sums, stream);
+    default: return launch_group<Form128x64>(g, sums, stream);
+  }
 }
 
 }  // namespace po

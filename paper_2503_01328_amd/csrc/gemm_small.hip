@@ -136,24 +136,27 @@ template <int KG>
 constexpr int kSumColumns = KG <= 2 ? 32 : 64;
 
 // The four weight-gradient products of a layer in one launch: the tiles of all of them one product after the other.
-// SUMS: and its column sums, in blocks of their own before the others, which hide them.
-template <typename T, int TM, int TN, int KG, typename... Sums>
-__global__ __launch_bounds__(64 * KG) void gemm_small_grouped_kernel(SmallGroup g, Sums... sums) {
-  extern __shared__ __align__(16) char smem[];
-  int before = 0;
-  if constexpr (sizeof...(Sums) > 0) {
-    before = (sums.blocks, ...);
-    if ((int)blockIdx.x < before) {
-      (column_sums_block<T, 64 * KG, kSumColumns<KG>, 4>(sums.batch, blockIdx.x, sums.rows, reinterpret_cast<float*>(smem)), ...);
-      return;
-    }
-  }
-  const int lin = tile_of_block(before);
+template <typename T, int TM, int TN, int KG>
+__device__ __forceinline__ void small_group_tile(const SmallGroup& g, int lin, char* smem) {
   SmallProblem p = g.p[0];  // constant indices only: a run-time index would send the arguments through memory
 #pragma unroll
   for (int i = 1; i < kMaxSmallGroup; ++i)
     if (i < g.n && lin >= g.p[i].first_tile) p = g.p[i];
   small_tile<T, TM, TN, KG, true, true>(p, lin - p.first_tile, smem);
+}
+template <typename T, int TM, int TN, int KG>
+__global__ __launch_bounds__(64 * KG) void gemm_small_grouped_kernel(SmallGroup g) {
+  extern __shared__ __align__(16) char smem[];
+  small_group_tile<T, TM, TN, KG>(g, tile_of_block(), smem);
+}
+// And its column sums, in blocks of their own before the others, which hide them.
+template <typename T, int TM, int TN, int KG>
+__global__ __launch_bounds__(64 * KG) void gemm_small_with_sums_kernel(SmallGroup g, GroupSums sums) {
+  extern __shared__ __align__(16) char smem[];
+  if ((int)blockIdx.x < sums.blocks)
+    column_sums_block<T, 64 * KG, kSumColumns<KG>, 4>(sums.batch, blockIdx.x, sums.rows, reinterpret_cast<float*>(smem));
+  else
+    small_group_tile<T, TM, TN, KG>(g, tile_of_block(sums.blocks), smem);
 }
 
 // ---- host side -------------------------------------------------------------------------------------------------
@@ -244,31 +247,37 @@ bool gemm_small(int dtype, int ta, int tb, int M, int N, int K, const void* A, i
   return launch_form(dtype, f, ta, tb, p, stream);
 }
 
-template <typename T, int TM, int TN, int KG, typename... Sums>
-static bool launch_group(SmallGroup& g, hipStream_t stream, Sums... sums) {
+template <typename T, int TM, int TN, int KG>
+static bool launch_group(SmallGroup& g, GroupSums* sums, hipStream_t stream) {
   constexpr int smem = KG * 2 * 32 * (TM + TN) * 128;
-  auto kern = gemm_small_grouped_kernel<T, TM, TN, KG, Sums...>;
-  static LdsLimit lds;
-  if (!lds.allow(kern, smem)) return false;
   int total = 0;
   for (int i = 0; i < g.n; ++i) {
     g.p[i].tiles_n = ceil_div(g.p[i].N, 32 * TN);
     g.p[i].first_tile = total;
     total += ceil_div(g.p[i].M, 32 * TM) * g.p[i].tiles_n;
   }
-  ((sums.blocks *= 64 / kSumColumns<KG>), ...);
-  kern<<<total + (0 + ... + sums.blocks), 64 * KG, smem, stream>>>(g, sums...);
+  if (sums) {
+    auto kern = gemm_small_with_sums_kernel<T, TM, TN, KG>;
+    static LdsLimit lds;
+    if (!lds.allow(kern, smem)) return false;
+    sums->blocks *= 64 / kSumColumns<KG>;
+    kern<<<total + sums->blocks, 64 * KG, smem, stream>>>(g, *sums);
+  } else {
+    auto kern = gemm_small_grouped_kernel<T, TM, TN, KG>;
+    static LdsLimit lds;
+    if (!lds.allow(kern, smem)) return false;
+    kern<<<total, 64 * KG, smem, stream>>>(g);
+  }
   return launch_ok("gemm_small_grouped_kernel");
 }
 
-template <typename... Sums>
-static bool group_form(int dtype, SmallForm f, SmallGroup& g, hipStream_t stream, const Sums&... sums) {
+static bool group_form(int dtype, SmallForm f, SmallGroup& g, GroupSums* sums, hipStream_t stream) {
   if (dtype == kF32)
-    return f.waves == 8 ? launch_group<float, 1, 1, 8>(g, stream, sums...) : launch_group<float, 1, 1, 4>(g, stream, sums...);
-  if (f.edge == 32) return launch_group<bf16, 1, 1, 4>(g, stream, sums...);
-  if (f.waves == 4) return launch_group<bf16, 2, 2, 4>(g, stream, sums...);
-  if (f.waves == 2) return launch_group<bf16, 2, 2, 2>(g, stream, sums...);
-  return launch_group<bf16, 2, 2, 1>(g, stream, sums...);
+    return f.waves == 8 ? launch_group<float, 1, 1, 8>(g, sums, stream) : launch_group<float, 1, 1, 4>(g, sums, stream);
+  if (f.edge == 32) return launch_group<bf16, 1, 1, 4>(g, sums, stream);
+  if (f.waves == 4) return launch_group<bf16, 2, 2, 4>(g, sums, stream);
+  if (f.waves == 2) return launch_group<bf16, 2, 2, 2>(g, sums, stream);
+  return launch_group<bf16, 2, 2, 1>(g, sums, stream);
 }
 
 bool gemm_small_grouped_supported(int dtype, int n, const GemmProblem* prob) {
@@ -315,7 +324,7 @@ bool gemm_small_grouped_accumulate(int dtype, int n, const GemmProblem* prob, hi
   // a group of bf16 products does best with one wave per tile from 512 on:
   // width 512, 100 / 512 / 4000 rows 9.0 / 12.4 / 44.8 us against 10.7 / 14.5 / 49.9 with two
   if (dtype == kBF16 && tiles64 >= 512) f.waves = 1;
-  return n_jobs > 0 ? group_form(dtype, f, g, stream, sums) : group_form(dtype, f, g, stream);
+  return group_form(dtype, f, g, n_jobs > 0 ? &sums : nullptr, stream);
 }
 
 }  // namespace po
