@@ -130,6 +130,81 @@ __global__ __launch_bounds__(64 * KG) void gemm_small_kernel(SmallProblem p) {
   small_tile<T, TM, TN, KG, TA, TB>(p, tile_of_block(), smem);
 }
 
+// fp32 results of so few tiles that a CU's four SIMDs would be a chain of MFMAs each: tiles of 16 x 16 with eight waves, four
+// times the blocks, a quarter of the MFMAs per wave.  Four stages a wave: up to K 1024 all of its chunks are on their way at
+// once.  Otherwise as above; every sum in eight chains.
+template <bool TA, bool TB>
+__global__ __launch_bounds__(512) void gemm_tiny_f32_kernel(SmallProblem p) {
+  constexpr int KG = 8, NS = 4, KU = MfmaOf<float>::KU, LD = 16 + 4;
+  using OpA = Operand<float, 16, TA>;
+  using OpB = Operand<float, 16, TB>;
+  constexpr int STAGE = OpA::BYTES + OpB::BYTES, LOADS = OpA::LOADS + OpB::LOADS;
+  static_assert(16 * LD * 4 <= NS * STAGE, "a partial tile fits the wave's ring");
+  extern __shared__ __align__(16) char smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int m0, n0;
+  place_of_tile(tile_of_block(), (p.M + 15) / 16, p.tiles_n, m0, n0);
+  m0 *= 16;
+  n0 *= 16;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  const int chunks = (p.K + KU - 1) / KU, mine = chunks > wave ? (chunks - wave + KG - 1) / KG : 0;
+  OpA a;
+  OpB b;
+  a.init(static_cast<const float*>(p.A), p.lda, m0, p.M, p.K, wave, KG, lane);
+  b.init(static_cast<const float*>(p.B), p.ldb, n0, p.N, p.K, wave, KG, lane);
+  char* ring = smem + wave * (NS * STAGE);
+  const unsigned ring_lds = __builtin_amdgcn_readfirstlane((int)lds_byte(ring));
+  auto issue = [&](int t) {
+    const int k_left = p.K - (wave + t * KG) * KU;
+    const unsigned dst = ring_lds + t % NS * STAGE;
+    a.issue(dst, k_left, lane);
+    b.issue(dst + OpA::BYTES, k_left, lane);
+  };
+#pragma unroll
+  for (int t = 0; t < NS; ++t)
+    if (t < mine) issue(t);
+  for (int t = 0; t < mine; ++t) {
+    const int behind = mine - 1 - t;  // chunks that may still be on their way, up to NS - 1
+    if (behind >= 3) wait_loads<3 * LOADS>();
+    else if (behind == 2) wait_loads<2 * LOADS>();
+    else if (behind == 1) wait_loads<LOADS>();
+    else wait_loads<0>();
+    const char* sa = ring + t % NS * STAGE;
+    f32x4 fa[2], fb[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      fa[kk] = fragment16<TA>(sa, kk, lane);
+      fb[kk] = fragment16<TB>(sa + OpA::BYTES, kk, lane);
+    }
+    wait_lds_reads();
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + NS < mine) issue(t + NS);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[kk][j], fa[kk][j], acc, 0, 0, 0);
+  }
+  // lane: row lane % 16, columns 4 (lane / 16) .. + 3
+  *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(ring) + (lane & 15) * LD + 4 * (lane >> 4)) = acc;
+  __syncthreads();
+  const int r = threadIdx.x >> 2, c = (threadIdx.x & 3) * 4;
+  if (r >= 16 || m0 + r >= p.M || n0 + c >= p.N) return;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int g = 0; g < KG; ++g) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(smem + g * (NS * STAGE)) + r * LD + c);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] += x[k];
+  }
+  if (p.vec && n0 + c + 4 <= p.N) {
+    epilogue_vector<float>(p.ep, m0 + r, n0 + c, v);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (n0 + c + i < p.N) epilogue_store<float>(p.ep, m0 + r, n0 + c + i, v[i]);
+  }
+}
+
 // Columns of a column-sum block: half of the 64 where a block has few waves, each of whose rounds over the rows is a chain of
 // memory round trips.
 template <int KG>
@@ -166,7 +241,7 @@ __global__ __launch_bounds__(64 * KG) void gemm_small_with_sums_kernel(SmallGrou
 //   bf16  512 x  512, K 2048:  7.5  6.1   9.0  12.8  21.8        bf16 1024 x 1024, K 1024: 13.4  9.6  6.7  8.3 13.3
 //   bf16  100 x 2048, K 8192: 19.0 19.4  25.3  39.9  73.7        bf16  100 x 8192, K 2048: 22.2 17.7 10.7 13.3 22.0
 //   bf16 2048 x 2048, K  100: 30.0 16.3  14.6  11.2   9.8        bf16 1733 x 6144, K 2048:  207  140   86   76   72
-//   fp32  128 x  256, K 1024:  8.0  8.3  21.0  37.8  72.2
+//   fp32  128 x  256, K 1024:  8.0  8.3  21.0  37.8  72.2 (16 x 16: 5.1)
 // A 32 x 32 tile halves what an operand byte is used for but makes four times as many blocks: it wins while 64 x 64
 // tiles leave half of the CUs without one.  From there on more waves per tile shorten its chain of chunks, as long as
 // every wave has a few chunks and the chip is not full anyway: bf16 has as many as keep four waves on every CU.  fp32 has
@@ -186,6 +261,13 @@ static SmallForm small_form(int dtype, int64_t tiles64, int K) {
 //   300 x 512, K 512 5.4 / 8.2 (160); 356 x 652, K 1844 15.1 / 20.3 (252); 1272 x 216, K 228 5.4 / 6.3 (280);
 //   636 x 496, K 316 6.8 / 6.8 (320); 516 x 712, K 772 13.4 / 11.3 (391); 680 x 572, K 68 3.9 / 5.2 (396)
 static bool f32_few_tiles(int64_t tiles32, int K) { return tiles32 <= 288 || (tiles32 < 448 && K < 128); }
+
+// fp32 results for which 16 x 16 tiles beat 32 x 32 ones: as many as one round of the CUs.  A 32 x 32 x 32 chunk is 1024 cycles of
+// MFMAs on its SIMD, and few tiles leave most of the chip idle.  32 x 32 / 16 x 16, us, 16 x 16 tiles in brackets:
+//   128 x 256, K 256 4.0 / 3.4 (128); 64 x 128, K 512 5.2 / 3.9 (32); 128 x 256, K 1024 7.9 / 5.1 (128); 256 x 256, K 1024 7.9 / 5.4 (256);
+//   128 x 512, K 2048 12.5 / 7.7 (256); 128 x 256, K 4096 21.4 / 10.9 (128); 200 x 320, K 1280 9.0 / 9.6 (260); 128 x 768, K 256
+//   4.0 / 5.3 (384).  Against 64 bits the same, at K 256 1.18e-7 instead of 1.50e-7 (eight chains instead of four).
+static bool f32_tiny(int M, int N) { return (int64_t)ceil_div(M, 16) * ceil_div(N, 16) <= 256; }
 
 static bool vector_epilogue(int dtype, const Epilogue& ep) {
   const int v = dtype == kF32 ? 4 : 8;
@@ -224,6 +306,22 @@ static bool launch_trans(int ta, int tb, SmallProblem& p, hipStream_t stream) {
   return launch_small<T, TM, TN, KG, true, false>(p, stream);
 }
 
+template <bool TA, bool TB>
+static bool launch_tiny(SmallProblem& p, hipStream_t stream) {
+  constexpr int smem = 8 * 4 * 2 * 16 * 128;
+  static LdsLimit lds;  // per instantiation
+  if (!lds.allow(gemm_tiny_f32_kernel<TA, TB>, smem)) return false;
+  p.tiles_n = ceil_div(p.N, 16);
+  gemm_tiny_f32_kernel<TA, TB><<<ceil_div(p.M, 16) * p.tiles_n, 512, smem, stream>>>(p);
+  return launch_ok("gemm_tiny_f32_kernel");
+}
+static bool launch_tiny_trans(int ta, int tb, SmallProblem& p, hipStream_t stream) {
+  if (!ta && !tb) return launch_tiny<false, true>(p, stream);
+  if (!ta && tb) return launch_tiny<false, false>(p, stream);
+  if (ta && !tb) return launch_tiny<true, true>(p, stream);
+  return launch_tiny<true, false>(p, stream);
+}
+
 static bool launch_form(int dtype, SmallForm f, int ta, int tb, SmallProblem& p, hipStream_t stream) {
   if (dtype == kF32)
     return f.waves == 8 ? launch_trans<float, 1, 1, 8>(ta, tb, p, stream) : launch_trans<float, 1, 1, 4>(ta, tb, p, stream);
@@ -242,6 +340,7 @@ bool gemm_small(int dtype, int ta, int tb, int M, int N, int K, const void* A, i
     return false;
   }
   SmallProblem p{A, B, ep, M, N, K, lda, ldb, 0, 0, vector_epilogue(dtype, ep)};
+  if (dtype == kF32 && f32_tiny(M, N)) return launch_tiny_trans(ta, tb, p, stream);
   if (dtype == kF32 && !f32_few_tiles((int64_t)ceil_div(M, 32) * ceil_div(N, 32), K)) return gemm_f32(ta, tb, p, stream);
   SmallForm f = small_form(dtype, (int64_t)ceil_div(M, 64) * ceil_div(N, 64), K);
   return launch_form(dtype, f, ta, tb, p, stream);

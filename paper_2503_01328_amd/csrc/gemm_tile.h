@@ -19,7 +19,8 @@ template <> struct MfmaOf<bf16> {
 // KMAJOR == false: [R rows][128 bytes], 16-byte piece c of row r at c ^ (r & 7).
 // KMAJOR == true: [KU k][R elements].  bf16: 32-byte unit u of row k at u ^ (k & mask), as the transposing reads like
 // it; fp32: 16-byte piece c at c ^ 8 for odd groups of four k, so that the two half-waves (k and k + 4) hit different
-// banks.
+// banks; with 16 elements a row k moves within its group of four instead, by the group's number, so that a wave's four k
+// (4 g + j) do.
 template <typename T, int R, bool KMAJOR>
 struct Operand {
   static constexpr int E = sizeof(T), KU = MfmaOf<T>::KU;
@@ -39,6 +40,9 @@ struct Operand {
     return R >= 64 ? pos16 ^ (((k >> 2) & 1) << 3) : pos16;
   }
 
+  static constexpr bool TURNED = KMAJOR && E == 4 && R == 16;
+  __device__ __forceinline__ static int slot_of(int k) { return TURNED ? (k & ~3) | ((k + (k >> 2)) & 3) : k; }
+
   // p: the operand; ld in elements; row0: first row of the tile (of `rows`); chunk: this wave's first chunk of K.
   __device__ __forceinline__ void init(const T* p, int ld, int row0, int rows, int K, int chunk, int chunk_step, int lane) {
 #pragma unroll
@@ -48,7 +52,8 @@ struct Operand {
         int row = byte >> 7, c = ((byte >> 4) & 7) ^ (row & 7);
         voff[u] = (unsigned)row * (unsigned)ld * E + c * 16;
       } else {
-        int k = byte / ROW_BYTES, c = piece_of((byte % ROW_BYTES) >> 4, k);
+        const int slot = byte / ROW_BYTES, k = TURNED ? (slot & ~3) | ((slot - (slot >> 2)) & 3) : slot;
+        const int c = piece_of((byte % ROW_BYTES) >> 4, k);
         voff[u] = (unsigned)k * (unsigned)ld * E + c * 16;
       }
     }
@@ -114,6 +119,17 @@ __device__ __forceinline__ f32x4 fragment(const float*, const char* lds, int row
   f32x4 v;
 #pragma unroll
   for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float*>(lds + (k + j) * (4 * R) + at);
+  return v;
+}
+// Fragment of 16 rows for kk: k = 16 kk + 4 (lane / 16) + 0..3 of row lane % 16, four MFMAs of 16 x 16 x 4.
+template <bool KMAJOR>
+__device__ __forceinline__ f32x4 fragment16(const char* lds, int kk, int lane) {
+  const int row = lane & 15, g = lane >> 4;
+  if (!KMAJOR) return *reinterpret_cast<const f32x4*>(lds + row * 128 + (((4 * kk + g) ^ (row & 7)) << 4));
+  f32x4 v;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    v[j] = *reinterpret_cast<const float*>(lds + Operand<float, 16, true>::slot_of(16 * kk + 4 * g + j) * 64 + row * 4);
   return v;
 }
 // C^T-wise product: the B fragment goes into the first slot, so a lane holds four consecutive n of one row m.

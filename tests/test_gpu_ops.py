@@ -193,6 +193,30 @@ def test_gemm_small_edges(gpu_device, dtype, ta, tb, M, N, K):
     assert rel(acc, ref + 1.0) < sums + 2.0 ** -23
 
 
+# fp32 results of up to 256 tiles of 16 x 16 and one more row of tiles: less than a tile, fewer chunks of 32 k than waves, more than
+# the waves have stages, K that ends inside a chunk.
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(4, 4, 4), (16, 20, 36), (100, 72, 252), (36, 48, 1024), (20, 32, 1060), (40, 36, 4108),
+                                   (256, 256, 260), (260, 256, 1156)])
+def test_gemm_f32_tiles_of_16(gpu_device, ta, tb, M, N, K):
+    """Against fp64 as above: 2^-24 sqrt(K) for the sums, 2^-23 for the epilogue's additions."""
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(M + N + K + 2 * ta + tb)
+    def rand(rows, cols):  # followed by NaNs
+        t = torch.full((rows * cols + 5000,), float("nan"), device=gpu_device)
+        t[:rows * cols] = torch.randn(rows * cols, generator=g, device=gpu_device)
+        return t[:rows * cols].view(rows, cols)
+    A, B, bias = rand(*((K, M) if ta else (M, K))), rand(*((N, K) if tb else (K, N))), rand(1, N)[0]
+    ref = (A.t() if ta else A).double().contiguous() @ (B.t() if tb else B).double().contiguous()
+    tol = 2.0 ** -24 * K ** 0.5 + 2.0 ** -23
+    out, acc = torch.full((M + 4, N), 7.0, device=gpu_device), torch.ones(M, N, device=gpu_device)
+    po.po_op_gemm(po.PO_F32, ta, tb, M, N, K, A, A.shape[1], B, B.shape[1], out=out, bias=bias)
+    po.po_op_gemm(po.PO_F32, ta, tb, M, N, K, A, A.shape[1], B, B.shape[1], acc_f32=acc)
+    assert (out[M:] == 7).all()
+    for got, want in ((out[:M], ref + bias.double()), (acc, ref + 1.0)):
+        assert (got.double() - want).norm() < tol * want.norm()
+
+
 # Equal rows of A give equal rows of the result, whichever tile they lie in and whichever XCD works on it: whole tiles of 128, 256
 # and 256 x 192, tiles that end inside, and both sizes of small tiles, forward, input-gradient and weight-gradient layouts.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
