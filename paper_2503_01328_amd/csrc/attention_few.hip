@@ -2,7 +2,7 @@
 // (attention_mfma.hip) would leave most CUs without one, where a launch is the chain of its longest block and little else.
 //
 // A block owns only 32 rows (query rows in forward and dQ, keys in dK/dV) and its waves split the tiles of 32 keys (query rows)
-// those meet, tile t to wave t % W; every wave has a ring of two stages of its own, HBM -> LDS directly, and no barrier until the
+// those meet, tile t to wave t % W; every wave has a stage or two of its own, HBM -> LDS directly, and no barrier until the
 // partial results are added in wave order through LDS (deterministic, no atomics).  Against a 128-row block of eight waves that is
 // a quarter of the tiles per wave, at four times the tile loads per row.  Heaviest blocks of the causal triangle first; the
 // backward is one launch, dK/dV blocks and then dQ blocks.  8 heads of 64 at 512 rows: forward 8.9 -> 5.8 us, backward with delta
@@ -25,11 +25,13 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kRows = 32;  // of a tile and of a block
 
-// Waves of a block, bytes of a tile and of a stage (two tiles), and where in LDS what follows the stages begins.  Heads of 128
-// need more than 256 registers in the backward: one wave per SIMD.
-template <int DH>
+// Waves of a block, their stages, bytes of a tile and of a stage (two tiles), and where in LDS what follows the stages begins.  Heads
+// of 128 need more than 256 registers in the backward: one wave per SIMD.  In the forward they have eight waves too, for which LDS has
+// room for one stage each: the next K is requested once the scores are formed, the next V behind the product (four waves of two
+// stages / this, us: 100 rows, 16 heads 6.1 / 5.6, 512 rows, 8 heads 9.0 / 8.6, 777 rows, 10 heads 15.2 / 12.0, 4096 rows, 2 heads 40.6 / 28.7).
+template <int DH, bool FORWARD = false>
 struct Few {
-  static constexpr int W = DH == 64 ? 8 : 4, NS = 2, TILE = kRows * DH * 2, STAGE = 2 * TILE, LOADS = TILE / 1024;
+  static constexpr int W = DH == 64 || FORWARD ? 8 : 4, NS = DH == 64 || !FORWARD ? 2 : 1, TILE = kRows * DH * 2, STAGE = 2 * TILE, LOADS = TILE / 1024;
   static constexpr int AFTER = W * NS * STAGE;
 };
 
@@ -118,10 +120,10 @@ __device__ __forceinline__ void store4(bf16* p, const f32x4& v) {
 }  // namespace
 
 template <int DH, bool EDGE>
-__global__ __launch_bounds__(64 * Few<DH>::W) void attn_few_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ o,
+__global__ __launch_bounds__((64 * Few<DH, true>::W)) void attn_few_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ o,
                                                                        float* __restrict__ lse, int s, int h, int hkv,
                                                                        int group, float scale) {
-  using F = Few<DH>;
+  using F = Few<DH, true>;
   constexpr int DT = DH / 32, W = F::W, PART = F::NS * F::STAGE / 4;
   extern __shared__ __align__(16) char smem[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
@@ -147,10 +149,16 @@ __global__ __launch_bounds__(64 * Few<DH>::W) void attn_few_fwd_kernel(const bf1
   for (int d = 0; d < DT; ++d) acc[d] = zero16();
   float m_run = -INFINITY, l_run = 0.f;
   for (int t = wave, i = 0; t < n_tiles; t += W, ++i) {
-    if (t + W < n_tiles) wait_loads<2 * F::LOADS>();
+    const bool more = t + W < n_tiles;
+    if (F::NS == 1) wait_loads<F::LOADS>();  // K is there, V may be on its way
+    else if (more) wait_loads<2 * F::LOADS>();
     else wait_loads<0>();
     const char* ktile = stages + i % F::NS * F::STAGE;
     f32x16 p = dot_tile<DH>(ktile, qf, zero16(), lane);
+    if (F::NS == 1 && more) {
+      wait_lds_reads();
+      loads.request(stages_lds, kbase, ld, kRows * (t + W), s);
+    }
     if (t == n_tiles - 1) {  // the tile of the diagonal; keys past s lie beyond it for every row there is
 #pragma unroll
       for (int e = 0; e < 16; ++e)
@@ -174,9 +182,18 @@ __global__ __launch_bounds__(64 * Few<DH>::W) void attn_few_fwd_kernel(const bf1
     for (int d = 0; d < DT; ++d)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[d][e] *= alpha;
+    if (F::NS == 1) {
+      if (more) wait_loads<F::LOADS>();
+      else wait_loads<0>();
+    }
     accumulate_tile<DH, EDGE>(acc, ktile + F::TILE, p, lane);
-    wait_lds_reads();
-    if (t + F::NS * W < n_tiles) request(i, t + F::NS * W);
+    if (F::NS == 1 && more) {
+      wait_lds_reads();
+      loads.request(stages_lds + F::TILE, vbase, ld, kRows * (t + W), s);
+    } else if (t + F::NS * W < n_tiles) {
+      wait_lds_reads();
+      request(i, t + F::NS * W);
+    }
   }
   float* part = reinterpret_cast<float*>(smem);
   put_partial<DT>(part + wave * PART, acc, lane);
@@ -417,9 +434,9 @@ __global__ __launch_bounds__(64 * Few<DH>::W) void attn_few_bwd_kernel(const bf1
 // their chains, a quarter as long, win, and the longer the sequence the more rounds that outweighs; beyond, the 128-row blocks' use
 // of a tile for four times the rows does.  Lines drawn over 700 shapes (1 to 64 heads, groups of 1 to 16, 1 to 15000 rows) so that no call
 // of these took over 3 % longer.  128-row / 32-row blocks, us, forward and backward:
-//   8 heads of 64, 512 rows        8.9 /   5.8   17.0 /   9.9      16 heads of 128, 100 rows           9.8 /   6.0   18.0 /  10.9
-//   8 heads of 64, 1024 rows      12.5 /   7.9   25.4 /  16.2      4 heads of 128, 2048 rows          27.4 /  23.2   64.6 /  38.6
-//   10 heads of 64 over 2, 777    15.6 /   8.3    137 /  35.9      16 heads of 128, 1024 rows (not)  18.0 /  18.0   41.9 /  45.9
+//   8 heads of 64, 512 rows        8.9 /   5.8   17.0 /   9.9      16 heads of 128, 100 rows           9.8 /   5.6   18.0 /  10.9
+//   8 heads of 64, 1024 rows      12.5 /   7.9   25.4 /  16.2      4 heads of 128, 2048 rows          27.4 /  18.3   64.6 /  38.6
+//   10 heads of 64 over 2, 777    15.6 /   8.3    137 /  35.9      16 heads of 128, 1024 rows (not)   18.0 /     -   41.9 /  45.9
 //   32 heads of 64, 512 (not)      9.1 /   8.5   17.8 /  22.7      16 heads of 128, 2048 rows (not)   30.2 /  50.8   83.2 /   130
 static bool offsets_fit(int h, int n_heads, int n_kv_heads) {  // a lane's offset in a tile of 32 rows
   return ((int64_t)h + 2 * (int64_t)n_kv_heads * (h / n_heads)) * (2 * kRows) < (int64_t)1 << 32;
@@ -428,7 +445,7 @@ bool attention_few_forward_is_faster(int s, int h, int n_heads, int n_kv_heads) 
   const int64_t tiles = ceil_div(s, kRows), blocks = n_heads * tiles;
   const bool whole = s % 128 == 0;
   const int64_t line = h / n_heads == 64 ? (whole ? std::min<int64_t>(768, 416 + 4 * tiles) : std::min<int64_t>(1024, 416 + 8 * tiles))
-                                         : (whole ? std::min<int64_t>(512, 224 + 6 * tiles) : std::min<int64_t>(704, 320 + 5 * tiles));
+                                         : (whole ? std::min<int64_t>(768, 352 + 2 * tiles) : std::min<int64_t>(1024, 416 + 6 * tiles));
   return blocks <= line && offsets_fit(h, n_heads, n_kv_heads);
 }
 // A dK/dV block's chain grows with the query heads it walks: without partial results 8 heads of 128 over 1 at 1000 rows 118 /
@@ -444,10 +461,11 @@ bool attention_few_backward_is_faster(int s, int h, int n_heads, int n_kv_heads,
 
 template <int DH, bool EDGE>
 static bool few_forward(const bf16* qkv, bf16* o, float* lse, int s, int h, int n_heads, int n_kv_heads, hipStream_t stream) {
-  constexpr int smem = Few<DH>::AFTER + 2 * Few<DH>::W * 256 + Few<DH>::W * 4;
+  using F = Few<DH, true>;
+  constexpr int smem = F::AFTER + 2 * F::W * 256 + F::W * 4;
   static LdsLimit lds;
   if (!lds.allow(attn_few_fwd_kernel<DH, EDGE>, smem)) return false;
-  attn_few_fwd_kernel<DH, EDGE><<<n_heads * ceil_div(s, kRows), 64 * Few<DH>::W, smem, stream>>>(
+  attn_few_fwd_kernel<DH, EDGE><<<n_heads * ceil_div(s, kRows), 64 * F::W, smem, stream>>>(
       qkv, o, lse, s, h, n_kv_heads * DH, n_heads / n_kv_heads, 1.0f / sqrtf((float)DH));
   return launch_ok("attn_few_fwd_kernel");
 }

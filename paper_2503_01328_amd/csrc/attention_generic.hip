@@ -206,8 +206,8 @@ static bool vectors_or_refused(int s, uintptr_t addresses) { return s % 128 == 0
 
 bool attention_forward(int dtype, const void* qkv, void* o, float* lse, int s, int h, int n_heads, int n_kv_heads,
                        bool force_generic, hipStream_t stream) {
-  // Vector / matrix cores in us, 16 heads: of 64 at 16, 43 and 51 rows 6.6 / 4.0, 11.3 / 4.1 and 12.6 / 4.1, of 128 at 16, 51 and
-  // 64 rows 9.1 / 5.2, 18.4 / 5.4 and 21.7 / 5.3.  The line was drawn when the matrix-core kernel took 10.6 and 17.5 us at any
+  // Vector / matrix cores in us, 16 heads: of 64 at 16, 43 and 51 rows 6.6 / 4.0, 11.3 / 4.1 and 12.6 / 4.1, of 128 at 64
+  // rows 21.7 / 5.0.  The line was drawn when the matrix-core kernel took 10.6 and 17.5 us at any
   // of these and has not been moved since.  The backward has none (8 rows: 15.5 / 7.1 and 24.6 / 9.5).
   const int few = h == 64 * (int64_t)n_heads ? 43 : 51;
   if (dtype == kBF16 && !force_generic && s > few && attention_mfma_supported(s, h, n_heads, n_kv_heads) &&

@@ -36,7 +36,7 @@
 // MFMAs of a tile with one, two and three terms: forward 2 : 3 : 4, backward 7 : 10 : 13.  Vector kernels -> two terms -> this
 // form, us: s 1733, 16 heads of 128: forward 2235 -> 73 -> 74, backward 20450 -> 100 -> 112; s 3000, 32 heads of 64 over 8: 5406 -> 115 -> 125 and
 // 72760 -> 278 -> 307; s 100, 16 heads of 128: 35 -> 18 and 147 -> 18.  Since then (one buffer descriptor per tile, heads of 64 with
-// both products of a half tile open at once) 46 and 120, 92 and 278, 10.3 and 18.7; s 100 goes to attention_few.hip, 6.0 and 10.9.
+// both products of a half tile open at once) 46 and 120, 92 and 278, 10.3 and 18.7; s 100 goes to attention_few.hip, 5.6 and 10.9.
 #include "attention_rows.h"
 #include "attention_tile.h"
 

@@ -1,5 +1,5 @@
-// Column sums of several tensors (bias gradients, LayerNorm gain and shift gradients) by blocks of 64 columns over all rows:
-// a launch of their own (elementwise.hip) or the first blocks of a launch of weight-gradient products.
+// Column sums of several tensors (bias gradients, LayerNorm gain and shift gradients): the batch that the launches of
+// elementwise.hip and the first blocks of a launch of weight-gradient products work through, and what such a block does.
 #pragma once
 
 #include "kernels.h"
@@ -21,7 +21,8 @@ bool column_sums_vectors(int dtype, const ReduceJob* jobs, int n_jobs);
 
 // Column sums of block `block` (as first64 numbers them, COLS = 32: twice as many halves of those), added to the job's results.  A
 // lane takes one 16-byte vector of every SLOTS-th row; AT_ONCE rows are in flight per lane and added as a tree before they join the column's sum, so that the order
-// is fixed and no chain of additions is long.  red: 2 COLS floats of LDS per wave.  Needs column_sums_vectors.
+// is fixed and no chain of additions is long.  (As a launch of its own, reduce_batch_direct_kernel's plain
+// order is the faster one: fp32 rows of 100 to 500, three calls 41.0 and 41.6 us.)  red: 2 COLS floats of LDS per wave.  Needs column_sums_vectors.
 template <typename T, int THREADS, int COLS, int AT_ONCE>
 __device__ __forceinline__ void column_sums_block(const ReduceBatch& b, int block, int rows, float* red) {
   constexpr int V = Vec16<T>::N, LPR = COLS / V, SLOTS = THREADS / LPR, WAVES = THREADS / kWave;

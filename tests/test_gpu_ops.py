@@ -577,11 +577,12 @@ def _attention_64(qkv, d_o, o, lse, dh, a, akv):
 
 
 # Blocks of 32 rows: one tile and less, ends around a tile, more tiles than a block's waves have stages (8 x 2 with heads of 64,
-# 4 x 2 with heads of 128), groups, and both sides of the line to the 128-row blocks.  Against 64 bits: P, dS and the results
+# 4 x 2 or 8 with heads of 128), groups, and both sides of the lines to the 128-row blocks.  Against 64 bits: P, dS and the results
 # are rounded to bf16 (2^-9 each); what lies behind the results stays.
 @pytest.mark.parametrize("s,dh,a,akv", [(128, 64, 2, 2), (640, 64, 4, 1), (512, 64, 30, 30), (512, 64, 31, 31), (20, 64, 3, 3),
                                         (44, 64, 2, 1), (97, 64, 8, 1), (545, 64, 4, 2), (777, 64, 25, 25), (128, 128, 2, 2),
-                                        (512, 128, 4, 2), (384, 128, 24, 24), (384, 128, 25, 25), (31, 128, 2, 1),
+                                        (512, 128, 4, 2), (384, 128, 23, 23), (384, 128, 24, 24), (384, 128, 31, 31),
+                                        (384, 128, 32, 32), (31, 128, 2, 1),
                                         (65, 128, 3, 3), (300, 128, 4, 1), (129, 128, 70, 70)])
 def test_attention_blocks_of_32_rows(gpu_device, s, dh, a, akv):
     h, hkv = a * dh, akv * dh
