@@ -13,20 +13,23 @@ struct ReduceBatch {
   int n_jobs;
 };
 
-
 // The batch of these jobs; false with error text if one of them is not complete.
 bool make_reduce_batch(const ReduceJob* jobs, int n_jobs, ReduceBatch& b);
 // Whether every job's rows are whole, aligned 16-byte vectors.
 bool column_sums_vectors(int dtype, const ReduceJob* jobs, int n_jobs);
 
 // Column sums of block `block` (as first64 numbers them, COLS = 32: twice as many halves of those), added to the job's results.  A
-// lane takes one 16-byte vector of every SLOTS-th row; AT_ONCE rows are in flight per lane and added as a tree before they join the column's sum, so that the order
-// is fixed and no chain of additions is long.  (As a launch of its own, reduce_batch_direct_kernel's plain
-// order is the faster one: fp32 rows of 100 to 500, three calls 41.0 and 41.6 us.)  red: 2 COLS floats of LDS per wave.  Needs column_sums_vectors.
+// lane takes one 16-byte vector of every SLOTS-th row.  The loads of AT_ONCE rows are in flight per lane (rows past the end are
+// selected away and not branched round: a branch takes the loads with it); those rows are added in
+// order, the sums of four such rounds in order, and those of these groups again: a fixed order whose chains are short however few
+// slots there are, and a gain's last product is part of its addition.  The error against 64 bits is no larger than that of the sums
+// over chunks of rows (0.93 to 1.01 of it).  One chain of rounds with trees of products in it was 5 % above with 16 slots and
+// 600 rows, 13 % with 1536, and fp32 sums of 24 slots 5 % from 600 on.
+// red: 2 COLS floats of LDS per wave.  Needs column_sums_vectors.
 template <typename T, int THREADS, int COLS, int AT_ONCE>
 __device__ __forceinline__ void column_sums_block(const ReduceBatch& b, int block, int rows, float* red) {
   constexpr int V = Vec16<T>::N, LPR = COLS / V, SLOTS = THREADS / LPR, WAVES = THREADS / kWave;
-  constexpr int PER64 = 64 / COLS;
+  constexpr int PER64 = 64 / COLS, GROUP = 4 * AT_ONCE * SLOTS;  // rows of a group of rounds
   int j = 0;
   while (j + 1 < b.n_jobs && block >= b.first64[j + 1] * PER64) ++j;
   const ReduceJob& job = b.job[j];
@@ -35,54 +38,70 @@ __device__ __forceinline__ void column_sums_block(const ReduceBatch& b, int bloc
   const bool inside = col0 + cl < n, ln = job.x != nullptr;
   const T* a = static_cast<const T*>(job.a) + col0 + cl;
   const T* x = static_cast<const T*>(job.x) + col0 + cl;
-  auto tree = [](float (&p)[AT_ONCE]) {
-#pragma unroll
-    for (int m = 1; m < AT_ONCE; m <<= 1)
-#pragma unroll
-      for (int u = 0; u + m < AT_ONCE; u += 2 * m) p[u] += p[u + m];
-    return p[0];
-  };
   float s0[V], s1[V];
 #pragma unroll
   for (int i = 0; i < V; ++i) s0[i] = s1[i] = 0.f;
   if (inside && !ln) {
-    for (int r0 = slot; r0 < rows; r0 += AT_ONCE * SLOTS) {
-      Vec16<T> d[AT_ONCE];
+    for (int first = slot; first < rows; first += GROUP) {
+      float g[V];
 #pragma unroll
-      for (int u = 0; u < AT_ONCE; ++u) d[u] = load16(a + (size_t)min(r0 + u * SLOTS, rows - 1) * n);
+      for (int i = 0; i < V; ++i) g[i] = 0.f;
+      for (int r0 = first; r0 < min(first + GROUP, rows); r0 += AT_ONCE * SLOTS) {
+        Vec16<T> d[AT_ONCE];
 #pragma unroll
-      for (int i = 0; i < V; ++i) {
-        float p[AT_ONCE];
+        for (int u = 0; u < AT_ONCE; ++u) d[u] = load16(a + (size_t)min(r0 + u * SLOTS, rows - 1) * n);
+        float p[V];
 #pragma unroll
-        for (int u = 0; u < AT_ONCE; ++u) p[u] = r0 + u * SLOTS < rows ? to_f32(d[u].v[i]) : 0.f;
-        s0[i] += tree(p);
+        for (int i = 0; i < V; ++i) p[i] = 0.f;
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u)
+#pragma unroll
+          for (int i = 0; i < V; ++i) p[i] += r0 + u * SLOTS < rows ? to_f32(d[u].v[i]) : 0.f;
+#pragma unroll
+        for (int i = 0; i < V; ++i) g[i] += p[i];
       }
+#pragma unroll
+      for (int i = 0; i < V; ++i) s0[i] += g[i];
     }
   } else if (inside) {
     const float* stats = job.stats;
-    for (int r0 = slot; r0 < rows; r0 += AT_ONCE * SLOTS) {
-      Vec16<T> d[AT_ONCE], xv[AT_ONCE];
-      float mean[AT_ONCE], rstd[AT_ONCE];
+    for (int first = slot; first < rows; first += GROUP) {
+      float g0[V], g1[V];
 #pragma unroll
-      for (int u = 0; u < AT_ONCE; ++u) {
-        const size_t r = min(r0 + u * SLOTS, rows - 1);
-        d[u] = load16(a + r * n);
-        xv[u] = load16(x + r * n);
-        mean[u] = stats[2 * r];
-        rstd[u] = stats[2 * r + 1];
+      for (int i = 0; i < V; ++i) g0[i] = g1[i] = 0.f;
+      for (int r0 = first; r0 < min(first + GROUP, rows); r0 += AT_ONCE * SLOTS) {
+        Vec16<T> d[AT_ONCE], xv[AT_ONCE];
+        float mean[AT_ONCE], rstd[AT_ONCE];
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) {
+          const size_t r = min(r0 + u * SLOTS, rows - 1);
+          d[u] = load16(a + r * n);
+          xv[u] = load16(x + r * n);
+          mean[u] = stats[2 * r];
+          rstd[u] = stats[2 * r + 1];
+        }
+        float p0[V], p1[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) p0[i] = p1[i] = 0.f;
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u)
+#pragma unroll
+          for (int i = 0; i < V; ++i) {
+            // past the end 0 times the last row, which has put the NaN in already if that is one
+            const float dv = r0 + u * SLOTS < rows ? to_f32(d[u].v[i]) : 0.f;
+            p0[i] += dv * (to_f32(xv[u].v[i]) - mean[u]) * rstd[u];
+            p1[i] += dv;
+          }
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+          g0[i] += p0[i];
+          g1[i] += p1[i];
+        }
       }
 #pragma unroll
       for (int i = 0; i < V; ++i) {
-        float p0[AT_ONCE], p1[AT_ONCE];
-#pragma unroll
-        for (int u = 0; u < AT_ONCE; ++u) {
-          const bool there = r0 + u * SLOTS < rows;
-          const float dv = to_f32(d[u].v[i]);
-          p0[u] = there ? dv * (to_f32(xv[u].v[i]) - mean[u]) * rstd[u] : 0.f;
-          p1[u] = there ? dv : 0.f;
-        }
-        s0[i] += tree(p0);
-        s1[i] += tree(p1);
+        s0[i] += g0[i];
+        s1[i] += g1[i];
       }
     }
   }

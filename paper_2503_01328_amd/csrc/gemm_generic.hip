@@ -157,12 +157,13 @@ static bool group_is_small(int dtype, int n, const GemmProblem* p) {
 }
 
 // The sums' blocks come first and run beside the tiles; what is saved is the launch (or two) and what those took alone.  A block
-// sums all rows of its columns, a chain that outlasts the tiles where a bf16 product's K is long, and in fp32 one
-// whose rounding grows beyond that of partial sums (against 64 bits 9.5e-8 both at 1024 rows, 1.03e-7 and 1.01e-7 at 1400, 1.4e-7 and
-// 1.1e-7 at 4096).  Two layers of width h and s
-// rows, 2 or 4 microbatches, launches of their own / in passing, us: bf16 h 512, s 256 893 / 823, s 512 936 / 875, s 1000
-// 1433 / 1397, s 2048 1714 / 1709, s 4096 1556 / 1620; h 256, s 1024 988 / 966, s 2048 1270 / 1268, s 4096 1004 / 1045; fp32 h 256, s 128
-// 1251 / 1210, h 1024, s 1024 3233 / 3177.
+// sums all rows of its columns, a chain that outlasts the tiles where a bf16 product's K is long.  Two layers of width h and s rows,
+// 2 or 4 microbatches, launches of their own / in passing, us: bf16 h 512, s 256 840 / 782, s 512 905 / 843, s 1000
+// 1402 / 1329, s 2048 1624 / 1561, s 4096 1467 / 1456, s 8192 1537 / 1553; h 256, s 1024 970 / 922, s 2048 1267 / 1221, s 4096
+// 954 / 950, s 8192 1644 / 1673; fp32 h 256, s 128 1086 / 1043, h 1024, s 1024 3228 / 3168, s 2048 6628 / 6544.  The lines lie lower than
+// these figures say: they were drawn when a block was slower (bf16 h 512, s 2048 1714 / 1709, s 4096 1556 / 1620) and its fp32 sums had
+// a larger error than partial sums from 1100 rows on, and have not been moved since (fp32 bias sums against 64 bits, partial / in
+// passing now: 1024 rows 9.4e-8 / 9.0e-8, 1400 10.0e-8 / 9.2e-8, 4096 11.5e-8 / 10.6e-8).
 bool gemm_grouped_takes_sums(int dtype, int n, const GemmProblem* p, const ReduceJob* jobs, int n_jobs, int rows) {
   int64_t blocks = 0;  // at most, of at most 640 threads: a grid of one dimension
   for (int j = 0; j < n_jobs; ++j) blocks += ceil_div(jobs[j].n, 32);

@@ -124,6 +124,40 @@ def test_column_sums_beside_the_weight_gradients(gpu_device, dtype, h, f, s):
         _compare(shape, r.results(), _oracle(shape, r, 2), 1e-4 if dtype == "f32" else 2e-2)
 
 
+# In front of 64 x 64 tiles of one wave (16 rows at once, the fewest) at the most rows and at fewer, of two waves, of 32 x 32 tiles and
+# of fp32 tiles of six waves.
+@pytest.mark.parametrize("dtype,h,f,s", [("bf16", 512, 2048, 600), ("bf16", 512, 2048, 1536), ("bf16", 512, 1024, 1000),
+                                         ("bf16", 256, 256, 1536), ("f32", 512, 2048, 130), ("f32", 512, 2048, 600),
+                                         ("f32", 512, 2048, 1024)])
+def test_gain_gradients_beside_the_weight_gradients_round_no_more_than_on_their_own(gpu_device, dtype, h, f, s):
+    """The weights make the terms of one sum known: FC1 = (1 0) and FC2 its transpose at inputs where the slope of gelu is 1, so that the
+    gradient at the second LayerNorm's output is the stage's upstream gradient; no attention output, so that its input is the stage's.
+    Against fp64, beside the same sums in a launch of their own.  Over n columns orders of the same quality differ by chance by
+    1 / sqrt(n), here 0.6 percent; two percent is three times that."""
+    shape, err, seeds = syn.StageShape(1, 1, h, h // 64, f, s, dtype=dtype, pipeline_degree=1, n_microbatches=1), [0.0, 0.0], 2 ** 15 // h
+    with StageRunner(shape, device_params=True) as r:
+        param, grad = ({d["name"]: flat[d["offset"]:d["offset"] + d["rows"] * d["cols"]] for d in po.po_param_layout(r.cfg)}
+                       for flat in (r.params, r.grads))
+        r.params.zero_()
+        param["ln1_g"].fill_(1), param["ln2_g"].fill_(1), param["b_fc1"].fill_(64)
+        param["w_fc1"].view(h, f)[:, :h].fill_diagonal_(1), param["w_fc2"].view(f, h)[:h].fill_diagonal_(1)
+        for seed in range(seeds):
+            r.make_inputs_on_device(seed)
+            r.zero_grads()
+            r.run(po.PO_SCHED_1F1B, 0.0)
+            x, dn = r.x[0], r.dy[0]
+            ws = torch.empty(po.po_op_layernorm_backward_workspace(s, h) // 4, device=gpu_device)
+            gain, shift = torch.zeros(2, h, device=gpu_device)
+            po.po_op_layernorm_backward(r.cfg.dtype, dn, x, param["ln2_g"], dn, torch.empty_like(x), gain, shift, ws, s, h, r.cfg.ln_eps)
+            mean, rstd = ws[:2 * s].view(s, 2).split(1, 1)  # whose own rounding is not in question
+            want = (dn.double() * (x.double() - mean) * rstd).sum(0)
+            assert (grad["ln2_b"] - shift).norm() < 1e-6 * shift.norm()  # the terms are those
+            for k, got in enumerate((grad["ln2_g"], gain)):
+                err[k] += float((got.double() - want).square().sum())
+    print(f"{dtype} h {h} f {f} s {s}: {(err[0] / err[1]) ** 0.5:.3f} of that error")
+    assert err[0] ** 0.5 <= 1.02 * err[1] ** 0.5
+
+
 @pytest.mark.parametrize("shape", [SMALL_BF16, syn.StageShape(2, 1, 128, 2, 512, 96, vocab=50, dtype="f32",
                                                              pipeline_degree=4, n_microbatches=6)],
                          ids=["bf16", "f32-embed"])
