@@ -450,21 +450,48 @@ def test_attention_f32_delta_is_a_tree_of_additions(gpu_device, dh):
     assert (delta.double() - want).norm() < 0.5 * 2.0 ** -24 * (1 + np.log2(dh)) ** 0.5 * want.norm()
 
 
-# shapes the matrix-core kernels take: head size 64 / 128, s a multiple of 128; the last two
+# bf16 shapes (rows, head size, heads, key/value heads) past the lines to the blocks of 32 rows and not so many that the forward
+# takes 256 rows a block, or the backward four waves: forward blocks of 128 rows whose two groups of waves split the keys, eight-wave
+# backward blocks.  Whole tiles; sequences that end inside one; and backward passes alone, over groups.
+TWO_GROUPS = dict(whole=[(128, 64, 120, 120), (256, 128, 48, 48), (384, 64, 40, 40), (640, 64, 27, 27)],
+                  ragged=[(63, 64, 220, 110), (65, 128, 150, 150), (127, 64, 120, 60), (129, 128, 96, 96), (191, 64, 80, 80),
+                          (193, 128, 68, 17), (255, 64, 64, 64), (700, 128, 28, 7)],
+                  precision=[(200, 64, 100, 100), (200, 128, 100, 100), (300, 64, 60, 60)],
+                  infinite=[(300, 64, 100, 100), (300, 128, 100, 100)],
+                  nonfinite=[(200, 64, 100, 100), (200, 128, 100, 50)])
+EIGHT_WAVES = dict(ragged=[(200, 64, 64, 16), (130, 128, 72, 12), (257, 64, 45, 5), (65, 128, 112, 14), (300, 128, 45, 5),
+                           (200, 64, 52, 26), (131, 128, 72, 24), (70, 64, 110, 22)],
+                   whole=[(256, 64, 40, 10), (256, 128, 40, 20)])
+
+
+def test_attention_shapes_reach_the_128_row_blocks():
+    """Host logic: which of the two kinds of blocks a shape goes to, with and without partial results of its groups."""
+    forward, backward = (po.lib[n] for n in ("_ZN2po31attention_few_forward_is_fasterEiiii",
+                                             "_ZN2po32attention_few_backward_is_fasterEiiiii"))
+    forward.restype = backward.restype = ctypes.c_bool
+    for s, dh, a, akv in sum(TWO_GROUPS.values(), []):
+        assert s > 51 and not forward(s, a * dh, a, akv) and a * -(-s // 256) < 256, (s, dh, a, akv)
+    for s, dh, a, akv in sum([*TWO_GROUPS.values(), *EIGHT_WAVES.values()], []):
+        assert a * -(-s // 128) <= (768 if s % 128 else 256), (s, dh, a, akv)
+        for heads_a_block in range(1, a // akv + 1):
+            assert not backward(s, a * dh, a, akv, heads_a_block), (s, dh, a, akv)
+
+
+# shapes the matrix-core kernels take: head size 64 / 128, s a multiple of 128; the last two of the first six
 # are large enough in (s / 256) * heads to select the forward kernel's 256-row blocks (both head sizes)
 @pytest.mark.parametrize("s,h,a", [(128, 128, 2), (256, 256, 2), (384, 128, 1), (640, 192, 3), (512, 16384, 256),
-                                   (512, 32768, 256)])
+                                   (512, 32768, 256), *[(s, dh * a, a) for s, dh, a, _ in TWO_GROUPS["whole"]]])
 def test_attention_mfma(gpu_device, s, h, a):
     _attention_case(gpu_device, "bf16", s, h, a, 0)
 
 
 # bf16 sequences that end inside a tile, both head sizes: one row, ends around 64 and 128 rows, a last key block with one
-# query tile, 256-row forward blocks with four-wave backward blocks, key/value heads shared by groups with one and with
-# two launches.  What lies behind the tensors is NaN and must not be read, what lies behind the results must stay.
+# query tile, 256-row forward blocks, key/value heads shared by groups; in blocks of 32 rows and in those of 128.  What lies behind the tensors is NaN and must not be read, what lies behind the results must stay.
 # 2^-8 for o: half of it is the rounding of o, P enters with 16 bits.
 @pytest.mark.parametrize("s,h,a,akv", [(1, 128, 1, 1), (1, 64, 1, 1), (63, 128, 2, 1), (65, 256, 2, 2), (127, 256, 4, 2),
                                        (129, 128, 1, 1), (191, 64, 1, 1), (193, 512, 4, 1), (255, 256, 4, 4),
-                                       (300, 16384, 128, 128), (300, 8192, 128, 2), (700, 1024, 8, 2)])
+                                       (300, 16384, 128, 128), (300, 8192, 128, 2), (700, 1024, 8, 2),
+                                       *[(s, dh * a, a, akv) for s, dh, a, akv in TWO_GROUPS["ragged"]]])
 def test_attention_ragged_bf16(gpu_device, s, h, a, akv):
     rng = np.random.default_rng(s + h + a)
     dh, hkv, group = h // a, h // a * akv, a // akv
@@ -501,9 +528,10 @@ def test_attention_ragged_bf16(gpu_device, s, h, a, akv):
 # P and dS enter the products with all 24 bits.  Rows of q come in pairs (2 i, 2 i + 1) and keys in pairs (2 j, 2 j + 1) whose
 # scores differ by 2^-11 / sqrt(dh) in the odd rows only, and everything P or dS is multiplied with has alternating
 # signs: results are differences of probabilities that agree in 14 bits.  With 16 bits they are 1.5 to 16 % off, with 24
-# below 0.1 %; the rounding of a result to bf16 is 2^-9, lse and score sums add less than that again.
+# below 0.1 %; the rounding of a result to bf16 is 2^-9, lse and score sums add less than that again.  2, 100 and 400 heads: blocks of
+# 32 rows, of 128 rows and eight waves, of 256 rows and four.
 @pytest.mark.parametrize("generic", [0, 1])
-@pytest.mark.parametrize("a", [2, 400])
+@pytest.mark.parametrize("a", [2, 100, 400])
 @pytest.mark.parametrize("dh", [64, 128])
 def test_attention_ragged_bf16_keeps_probabilities_in_fp32(gpu_device, dh, a, generic):
     s, h = 200, a * dh
@@ -538,7 +566,8 @@ def test_attention_ragged_bf16_keeps_probabilities_in_fp32(gpu_device, dh, a, ge
 # share of the tiles, adds nothing.  (Row i of a query of ones against keys of -inf; rows that see no other key are NaN.)
 @pytest.mark.parametrize("first,last", [(0, 40), (0, 64), (32, 64), (64, 128), (96, 160)])
 @pytest.mark.parametrize("dtype,s,dh,a", [("f32", 200, 64, 2), ("f32", 200, 128, 1), ("bf16", 300, 64, 2),
-                                          ("bf16", 300, 128, 400)])
+                                          ("bf16", 300, 128, 400),
+                                          *[("bf16", s, dh, a) for s, dh, a, _ in TWO_GROUPS["infinite"]]])
 def test_attention_keys_of_minus_infinity_add_nothing(gpu_device, dtype, s, dh, a, first, last):
     code, tdt, _ = DT[dtype]
     h = a * dh
@@ -629,12 +658,14 @@ def test_attention_of_few_rows_runs_on_the_vector_kernels(gpu_device, dtype, dh,
 
 
 # The workspace of a ragged grouped backward: fp32 partials of two query heads, or of the group's next divisor, inside [s, 2h]
-# bf16.  Groups of 4, 6, 8 (two heads each), 9 (three), and of 2, 3, 5, which have no such divisor; both head sizes;
-# eight-wave blocks, and in the last case (800 of them) the four-wave ones.  Nothing behind the workspace is written, an
+# bf16.  Groups of 4, 6, 8 (two heads each), 9 (three), and of 2, 3, 5, which have no such divisor; both head sizes; first blocks of
+# 32 rows, then 800 blocks of four waves, then blocks of eight.  Nothing behind the workspace is written, an
 # unaligned one is not used.  2^-8: the rounding of the results to bf16.
 @pytest.mark.parametrize("s,dh,a,akv,parts", [(200, 64, 8, 2, 2), (130, 128, 6, 1, 3), (257, 64, 9, 1, 3), (65, 128, 16, 2, 4),
                                               (300, 128, 9, 1, 3), (200, 64, 4, 2, 0), (131, 128, 6, 2, 0), (70, 64, 5, 1, 0),
-                                              (130, 64, 800, 200, 2)])
+                                              (130, 64, 800, 200, 2),
+                                              *[(*shape, parts) for shape, parts in
+                                                zip(EIGHT_WAVES["ragged"], (2, 3, 3, 4, 3, 0, 0, 0), strict=True)]])
 def test_attention_ragged_bf16_group_partials(gpu_device, s, dh, a, akv, parts):
     h, hkv = a * dh, akv * dh
     g = torch.Generator(device=gpu_device)
@@ -658,7 +689,8 @@ def test_attention_ragged_bf16_group_partials(gpu_device, s, dh, a, akv, parts):
 # the backward from the same o and lse.  A twentieth is what such an error differs by between two draws of the inputs.
 @pytest.mark.parametrize("dtype,s,dh,a,akv", [("f32", 100, 64, 64, 64), ("f32", 333, 32, 64, 64), ("f32", 333, 96, 32, 32),
                                               ("f32", 777, 128, 24, 8), ("bf16", 1733, 128, 16, 16),
-                                              ("bf16", 300, 128, 40, 40), ("bf16", 300, 64, 32, 8)])
+                                              ("bf16", 300, 128, 40, 40), ("bf16", 300, 64, 32, 8),
+                                              *[("bf16", *shape) for shape in TWO_GROUPS["precision"]]])
 def test_attention_errors_are_no_larger_than_the_vector_kernels(gpu_device, dtype, s, dh, a, akv):
     code, tdt, _ = DT[dtype]
     h, hkv = a * dh, akv * dh
@@ -694,10 +726,11 @@ def _nonfinite_inputs(gpu_device, dtype, s, dh, a, akv, where, value, row):
 
 # A non-finite row among the keys, the values, a whole token or the upstream gradient: what lies behind a row may not
 # reach it.  Compared with the vector kernels, which never read a key behind the row; row: the first, inside the first
-# tile, around tile ends, the last of the sequence.  400 heads: the 256-row and four-wave forms of the bf16 kernels.
+# tile, around tile ends, the last of the sequence.  2 and 4, 100 and 400 heads: blocks of 32 rows, of 128 rows and eight waves, of 256
+# rows and four waves in the bf16 kernels.
 NONFINITE = [("f32", 200, 32, 2, 2), ("f32", 97, 64, 2, 1), ("f32", 128, 96, 1, 1), ("f32", 200, 128, 2, 2),
              ("f32", 512, 64, 4, 4), ("bf16", 200, 64, 2, 2), ("bf16", 200, 128, 4, 2), ("bf16", 300, 64, 400, 400),
-             ("bf16", 300, 128, 400, 400)]
+             ("bf16", 300, 128, 400, 400), *[("bf16", *shape) for shape in TWO_GROUPS["nonfinite"]]]
 
 
 @pytest.mark.parametrize("where", ["k", "v", "qkv", "d_o"])
@@ -768,6 +801,7 @@ def _attention_case(gpu_device, dtype, s, h, a, force_generic, akv=0, with_parti
     ("f32", 37, 128, 4, 2, 1), ("f32", 70, 192, 6, 1, 1), ("bf16", 130, 256, 4, 2, 1),
     ("bf16", 128, 256, 4, 2, 0), ("bf16", 384, 512, 4, 1, 0), ("bf16", 256, 512, 8, 2, 0),
     ("bf16", 640, 768, 6, 3, 0), ("bf16", 512, 1024, 16, 4, 0), ("bf16", 256, 256, 4, 4, 0),
+    *[("bf16", s, dh * a, a, akv, 0) for s, dh, a, akv in EIGHT_WAVES["whole"]],
     # 17 row blocks x 16 heads: more dQ blocks than CUs but fewer dK/dV blocks, so without the workspace the two
     # backward kernels have different block forms and go out as two launches; with it, as one launch of four-wave blocks
     ("bf16", 2176, 1024, 16, 2, 0)])
