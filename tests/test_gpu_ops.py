@@ -148,13 +148,14 @@ def test_gemm_mfma_epilogues(gpu_device, epilogue, shape):
 
 # the kernel for fp32 and for bf16 results of any size: one row, tiles that end inside, K with a remainder, and result
 # sizes on both sides of the lines between its forms (32 x 32 and 64 x 64 tiles, 8, 4, 2 and 1 waves); a multiple of 8
-# in N, and in whichever of M and K is contiguous, is what its 16-byte loads need.  The last three are, in bf16, results
-# whose large tiles (128 x 128, 256 x 192, 256 x 256) end inside.
+# in N, and in whichever of M and K is contiguous, is what its 16-byte loads need.  (1100, 1032, 320) and the last two are, in bf16, results
+# whose large tiles (128 x 128, 256 x 192, 256 x 256) end inside; the three between are, in fp32, results of more tiles of
+# 16 x 16 than one round and few enough of 32 x 32, of eight and four waves.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K", [(8, 8, 8), (40, 24, 520), (1, 64, 72), (33, 200, 1096), (1000, 520, 264),
                                    (1000, 520, 1160), (1032, 2008, 72), (2056, 2008, 328), (1100, 1032, 320),
-                                   (1733, 6152, 128), (1733, 8200, 128)])
+                                   (200, 520, 264), (200, 520, 520), (680, 576, 72), (1733, 6152, 128), (1733, 8200, 128)])
 def test_gemm_small_edges(gpu_device, dtype, ta, tb, M, N, K):
     """Against the product in fp64.  K sums of fp32 products each round by at most 2^-24 of a partial sum, independent of
     each other: 2^-24 sqrt(K) relative (2-norm) is generous; a bf16 result (8 significant bits) adds its own rounding,

@@ -3,6 +3,7 @@
 Gradients, outputs and input gradients of the HIP path are compared per tensor
 with max |got - ref| / max |ref| and with the relative L2 norm (both printed): 1e-4 in fp32, 2e-2 in bf16.  With offload the
 HIP path must reproduce its own no-offload results bit for bit (offload is a copy)."""
+import ctypes
 import threading
 
 import numpy as np
@@ -93,16 +94,33 @@ def test_bf16_stage_against_oracle(gpu_device, shape):
         _compare(shape, r.results(), _oracle(shape, r, shape.n_microbatches), 2e-2)
 
 
+# width and inner width of fp32 stages of 1028 rows whose weight gradients take 32 x 64, 64 x 64 and 128 x 64 tiles
+F32_WITHOUT_SUMS = [(192, 512), (192, 1024), (448, 1024)]
+
+
+def test_f32_stages_without_sums_take_every_tile():
+    form = po.lib["_ZN2po13gemm_f32_formEiPKiS1_i"]
+    form.restype, form.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int), ctypes.c_int]
+    four = lambda *v: (ctypes.c_int * 4)(*v)
+    assert [form(4, four(h, h, h, f), four(3 * h, h, f, h), 1028) for h, f in F32_WITHOUT_SUMS] == [0, 1, 2]
+
+
 @pytest.mark.parametrize("shape", [
     syn.StageShape(1, 1, 448, 7, 1024, 200, dtype="bf16", pipeline_degree=2, n_microbatches=2),
     syn.StageShape(1, 1, 512, 8, 1536, 37, dtype="f32", pipeline_degree=2, n_microbatches=2),
     syn.StageShape(1, 1, 1024, 8, 2048, 300, dtype="f32", pipeline_degree=2, n_microbatches=2),
     syn.StageShape(1, 1, 192, 3, 768, 200, dtype="f32", pipeline_degree=2, n_microbatches=2),
     syn.StageShape(1, 1, 384, 6, 1536, 100, dtype="f32", pipeline_degree=2, n_microbatches=2),
-    syn.StageShape(1, 1, 1088, 17, 4096, 905, dtype="bf16", pipeline_degree=2, n_microbatches=2)],
-    ids=["bf16-64-tiles", "f32-64-tiles-short", "f32-64-tiles-long", "f32-32x64-tiles", "f32-128x64-tiles", "bf16-256-tiles-that-end-inside"])
+    syn.StageShape(1, 1, 1088, 17, 4096, 905, dtype="bf16", pipeline_degree=2, n_microbatches=2),
+    syn.StageShape(1, 1, 448, 7, 1024, 1544, dtype="bf16", pipeline_degree=2, n_microbatches=2),
+    syn.StageShape(1, 1, 512, 8, 2048, 1540, dtype="bf16", pipeline_degree=2, n_microbatches=2),
+    *[syn.StageShape(1, 1, h, h // 64, f, 1028, dtype="f32", pipeline_degree=2, n_microbatches=2) for h, f in F32_WITHOUT_SUMS]],
+    ids=["bf16-64-tiles", "f32-64-tiles-short", "f32-64-tiles-long", "f32-32x64-tiles", "f32-128x64-tiles", "bf16-256-tiles-that-end-inside",
+         "bf16-64-tiles-without-sums", "bf16-64-tiles-of-one-wave-without-sums", "f32-32x64-tiles-without-sums",
+         "f32-64-tiles-without-sums", "f32-128x64-tiles-without-sums"])
 def test_grouped_weight_gradients_of_any_shape(gpu_device, shape):
-    """The one launch of a layer's four weight-gradient products where the shapes are no whole 256 x 256 tiles."""
+    """The one launch of a layer's four weight-gradient products where the shapes are no whole 256 x 256 tiles, with the layer's
+    column sums in front of the small and the fp32 tiles and, of more rows, without."""
     with StageRunner(shape) as r:
         r.make_inputs()
         r.run(po.PO_SCHED_1F1B, 0.0)
