@@ -345,21 +345,31 @@ def test_hot_kernels_keep_their_accumulators_in_registers():
     assert len(gemm) == 48 and len(attn) >= 16
     # results of any size: three tiles x (two forward and two input-gradient epilogues, weight gradients) and the grouped
     # launch; the small tiles, bf16 32 x 32 with four waves and 64 x 64 with four, two and one, fp32 32 x 32 with four and eight, x
-    # four layouts and the grouped launch; larger fp32 results: three tiles x the same; fp32 attention: forward, backward and
-    # delta, four head sizes
+    # four layouts and the grouped launch, without and with column sums in front; larger fp32 results: three tiles x the same;
+    # fp32 16 x 16 tiles: four layouts; fp32 attention: forward, backward and delta, four head sizes; bf16 attention in blocks of
+    # 32 rows: forward and backward, two head sizes, sequences of whole 128 rows and others
     edge = {k: v for k, v in usage.items() if "gemm_edge_kernel" in k or "gemm_edge_grouped_kernel" in k}
     small = {k: v for k, v in usage.items() if "gemm_small_kernel" in k or "gemm_small_grouped_kernel" in k}
     gemm_f32 = {k: v for k, v in usage.items() if "gemm_f32_kernel" in k or "gemm_f32_grouped_kernel" in k}
     f32 = {k: v for k, v in usage.items() if "attn_f32_" in k}
+    small_sums = {k: v for k, v in usage.items() if "gemm_small_with_sums_kernel" in k}
+    f32_sums = {k: v for k, v in usage.items() if "gemm_f32_with_sums_kernel" in k}
+    tiny = {k: v for k, v in usage.items() if "gemm_tiny_f32_kernel" in k}
+    few = {k: v for k, v in usage.items() if "attn_few_" in k}
     assert len(edge) == 16 and len(small) == 6 * 5 and len(gemm_f32) == 3 * 5 and len(f32) == 12
-    for name, v in {**gemm, **grouped, **attn, **edge, **small, **gemm_f32, **f32}.items():
+    assert len(small_sums) == 6 and len(f32_sums) == 3 and len(tiny) == 4 and len(few) == 8
+    for name, v in {**gemm, **grouped, **attn, **edge, **small, **small_sums, **gemm_f32, **f32_sums, **tiny, **f32, **few}.items():
         assert v["ScratchSize"] == 0, (name, v)
     for name, v in attn.items():
         assert v["Occupancy"] >= 2, (name, v)
     for name, v in {**gemm, **edge}.items():
         assert v["VGPRs"] + v["AGPRs"] <= 512
-    for name, v in gemm_f32.items():  # two waves of each of three blocks on a SIMD
+    for name, v in {**gemm_f32, **f32_sums}.items():  # two waves of each of three blocks on a SIMD
         assert v["Occupancy"] >= 6, (name, v)
+    for name, v in few.items():  # eight waves a block, four in the backward of heads of 128
+        assert v["Occupancy"] >= (1 if "attn_few_bwd_kernelILi128" in name else 2), (name, v)
+    for name, v in tiny.items():  # eight waves a block
+        assert v["Occupancy"] >= 2, (name, v)
 
 
 def test_trace_viewer_reads_the_span_file(tmp_path):
