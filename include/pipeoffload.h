@@ -127,7 +127,8 @@ typedef struct po_stats {
   double pack_busy_s;       /* sum of pack + unpack kernel durations (staged copies only) */
   double compute_span_s;    /* first compute pass start to last compute pass end */
   double gemm_busy_s;       /* profile_kernels: sum of the timed GEMM launches' durations on the compute stream */
-  double gemm_flops;        /* profile_kernels: 2 M N K summed over those launches */
+  double gemm_flops;        /* profile_kernels: 2 M N K summed over those launches; those of a layer's weight gradients do its column
+                               sums too where that is faster (small and fp32 tiles, few rows), in gemm_busy_s but not here */
   double attn_busy_s;       /* profile_kernels: sum of the timed attention forward/backward launches' durations */
   double attn_flops;        /* profile_kernels: causal model flops of those, 2 s^2 h forward, 4 s^2 h backward */
   double copy_hidden_s;     /* part of d2h_busy_s + h2d_busy_s during which a compute pass was running as well */

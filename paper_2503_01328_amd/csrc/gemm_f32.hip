@@ -244,12 +244,12 @@ static bool launch_group(SmallGroup& g, const GroupSums* sums, hipStream_t strea
     static LdsLimit lds;
     if (!lds.allow(kern, Form::SMEM)) return false;
     kern<<<total + sums->blocks, Form::THREADS, Form::SMEM, stream>>>(g, *sums);
-  } else {
-    auto kern = gemm_f32_grouped_kernel<Form>;
-    static LdsLimit lds;
-    if (!lds.allow(kern, Form::SMEM)) return false;
-    kern<<<gemm_f32_grid(total, Form::THREADS), Form::THREADS, Form::SMEM, stream>>>(g);
+    return launch_ok("gemm_f32_with_sums_kernel");
   }
+  auto kern = gemm_f32_grouped_kernel<Form>;
+  static LdsLimit lds;
+  if (!lds.allow(kern, Form::SMEM)) return false;
+  kern<<<gemm_f32_grid(total, Form::THREADS), Form::THREADS, Form::SMEM, stream>>>(g);
   return launch_ok("gemm_f32_grouped_kernel");
 }
 

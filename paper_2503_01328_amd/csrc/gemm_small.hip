@@ -361,12 +361,12 @@ static bool launch_group(SmallGroup& g, GroupSums* sums, hipStream_t stream) {
     if (!lds.allow(kern, smem)) return false;
     sums->blocks *= 64 / kSumColumns<KG>;
     kern<<<total + sums->blocks, 64 * KG, smem, stream>>>(g, *sums);
-  } else {
-    auto kern = gemm_small_grouped_kernel<T, TM, TN, KG>;
-    static LdsLimit lds;
-    if (!lds.allow(kern, smem)) return false;
-    kern<<<total, 64 * KG, smem, stream>>>(g);
+    return launch_ok("gemm_small_with_sums_kernel");
   }
+  auto kern = gemm_small_grouped_kernel<T, TM, TN, KG>;
+  static LdsLimit lds;
+  if (!lds.allow(kern, smem)) return false;
+  kern<<<total, 64 * KG, smem, stream>>>(g);
   return launch_ok("gemm_small_grouped_kernel");
 }
 
