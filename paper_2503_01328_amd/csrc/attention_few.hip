@@ -432,30 +432,49 @@ __global__ __launch_bounds__(64 * Few<DH>::W) void attn_few_bwd_kernel(const bf1
 // ---- host side -------------------------------------------------------------------------------------------------
 // Which of two launches is the faster hangs on their blocks: as long as the blocks of 32 rows find a place within a round or two,
 // their chains, a quarter as long, win, and the longer the sequence the more rounds that outweighs; beyond, the 128-row blocks' use
-// of a tile for four times the rows does.  Lines drawn over 700 shapes (1 to 64 heads, groups of 1 to 16, 1 to 15000 rows) so that no call
-// of these took over 3 % longer.  128-row / 32-row blocks, us, forward and backward:
-//   8 heads of 64, 512 rows        8.9 /   5.8   17.0 /   9.9      16 heads of 128, 100 rows           9.8 /   5.6   18.0 /  10.9
+// of a tile for four times the rows does.  Lines drawn over 4800 calls of 4000 shapes (1 to 300 heads, groups of 1, 2 and 4, 1 to 15000
+// rows, at 0.25 to 1.15 times the line), both kinds of blocks in turn: none of these took over 3 % longer.  128-row / 32-row blocks, us,
+// forward and backward:
+//   8 heads of 64, 512 rows        8.9 /   5.7   16.9 /   9.9      16 heads of 128, 100 rows           9.8 /   5.6   18.0 /  10.9
 //   8 heads of 64, 1024 rows      12.5 /   7.9   25.4 /  16.2      4 heads of 128, 2048 rows          27.4 /  18.3   64.6 /  38.6
-//   10 heads of 64 over 2, 777    15.6 /   8.3    137 /  35.9      16 heads of 128, 1024 rows (not)   18.0 /     -   41.9 /  45.9
-//   32 heads of 64, 512 (not)      9.1 /   8.5   17.8 /  22.7      16 heads of 128, 2048 rows (not)   30.2 /  50.8   83.2 /   130
+//   10 heads of 64 over 2, 777    15.6 /   8.3    137 /  35.9      16 heads of 128, 1024 rows (not)   17.7 /  16.5   41.2 /  46.1
+//   32 heads of 64, 512 (not)      9.2 /   8.5   17.8 /  22.7      16 heads of 128, 2048 rows (not)   30.1 /  42.2   83.2 /   130
 static bool offsets_fit(int h, int n_heads, int n_kv_heads) {  // a lane's offset in a tile of 32 rows
   return ((int64_t)h + 2 * (int64_t)n_kv_heads * (h / n_heads)) * (2 * kRows) < (int64_t)1 << 32;
 }
+constexpr int kFewHeads = 150;  // tiles from which on the caps leave a handful of heads, whose chains decide
 bool attention_few_forward_is_faster(int s, int h, int n_heads, int n_kv_heads) {
   const int64_t tiles = ceil_div(s, kRows), blocks = n_heads * tiles;
   const bool whole = s % 128 == 0;
-  const int64_t line = h / n_heads == 64 ? (whole ? std::min<int64_t>(768, 416 + 4 * tiles) : std::min<int64_t>(1024, 416 + 8 * tiles))
-                                         : (whole ? std::min<int64_t>(768, 352 + 2 * tiles) : std::min<int64_t>(1024, 416 + 6 * tiles));
+  // 32 x 544 / 14 x 518 / 72 x 936 / 93 x 1023 blocks (tiles x blocks) of heads of 64 took 5 / 6 / 4 / 3 % longer, 112 x 1008 of 128 4 %
+  const bool few_heads = tiles > kFewHeads;
+  const int64_t line = h / n_heads == 64
+                           ? (whole ? std::min<int64_t>(768, 412 + 4 * tiles) : std::min<int64_t>(few_heads ? 1024 : 928, 408 + 7 * tiles))
+                           : (whole ? std::min<int64_t>(768, 352 + 2 * tiles) : std::min<int64_t>(few_heads ? 1024 : 864, 416 + 6 * tiles));
   return blocks <= line && offsets_fit(h, n_heads, n_kv_heads);
 }
 // A dK/dV block's chain grows with the query heads it walks: without partial results 8 heads of 128 over 1 at 1000 rows 118 /
-// 146 us, 16 heads of 64 over 2 at 847 rows 65 / 56, 16 heads of 128 over 1 at 30 rows 25 / 18.
+// 146 us, 16 heads of 64 over 2 at 847 rows 65 / 56, 16 heads of 128 over 1 at 30 rows 25 / 18.  But so does a 128-row block's, and groups
+// win by a fifth and more up to their lines.  Without groups the lines are lower: one round of 256 blocks where 128-row blocks
+// waste few rows (96 heads of 64 at 66 rows 11.2 / 13.3, 36 at 256 rows 13.2 / 14.4, 25 at 384 rows 15.6 / 16.6), and caps (10 heads of 64
+// at 3250 rows 115 / 128, 9 at 2048 rows 44.1 / 46.6, 11 heads of 128 at 2565 rows 168 / 186, 9 at 1792 rows 63.9 / 68.6).
 bool attention_few_backward_is_faster(int s, int h, int n_heads, int n_kv_heads, int hpb) {
   const int64_t tiles = ceil_div(s, kRows), blocks = n_heads * tiles;
   const bool whole = s % 128 == 0;
   const int waves = h / n_heads == 64 ? Few<64>::W : Few<128>::W;
-  const int64_t line = h / n_heads == 64 ? (whole ? std::min<int64_t>(640, 256 + 5 * tiles) : std::min<int64_t>(1024, 288 + 8 * tiles))
-                                         : (whole ? std::min<int64_t>(512, 224 + 5 * tiles) : std::min<int64_t>(896, 288 + 8 * tiles));
+  int64_t line = h / n_heads == 64 ? (whole ? std::min<int64_t>(640, 256 + 5 * tiles) : std::min<int64_t>(1024, 288 + 8 * tiles))
+                                   : (whole ? std::min<int64_t>(512, 224 + 5 * tiles) : std::min<int64_t>(896, 288 + 8 * tiles));
+  if (hpb == 1) {
+    const bool few_heads = tiles > kFewHeads;
+    if (!whole) {
+      const int64_t cap = h / n_heads == 64 ? (few_heads ? 1024 : 768) : (few_heads ? 896 : 720);
+      line = tiles == 3 || tiles == 4 ? 256 : std::min(line, cap);
+    } else if (h / n_heads == 64) {
+      line = std::min(line, std::min<int64_t>(few_heads ? 640 : 560, std::max<int64_t>(256, 160 + 8 * tiles)));
+    } else {
+      line = std::min<int64_t>(few_heads ? 512 : 448, 224 + 4 * tiles);
+    }
+  }
   return blocks <= line && (hpb <= (whole ? waves / 2 : waves) || hpb * tiles <= 24) && offsets_fit(h, n_heads, n_kv_heads);
 }
 

@@ -613,7 +613,8 @@ def _attention_64(qkv, d_o, o, lse, dh, a, akv):
                                         (44, 64, 2, 1), (97, 64, 8, 1), (545, 64, 4, 2), (777, 64, 25, 25), (128, 128, 2, 2),
                                         (512, 128, 4, 2), (384, 128, 23, 23), (384, 128, 24, 24), (384, 128, 31, 31),
                                         (384, 128, 32, 32), (31, 128, 2, 1),
-                                        (65, 128, 3, 3), (300, 128, 4, 1), (129, 128, 70, 70)])
+                                        (65, 128, 3, 3), (300, 128, 4, 1), (129, 128, 70, 70), (512, 64, 18, 18),
+                                        (512, 64, 29, 29), (384, 128, 22, 22)])
 def test_attention_blocks_of_32_rows(gpu_device, s, dh, a, akv):
     h, hkv = a * dh, akv * dh
     g = torch.Generator(device=gpu_device)
