@@ -834,9 +834,9 @@ def test_colsum_accumulate(gpu_device, dtype, rows, n):
 
 
 # one launch over all rows (up to 512; bf16 up to 256 blocks of 64 columns) and the two of more: rows that leave lanes, waves and
-# a lane's four rows without work, a last block of few columns, rows that are no whole vectors
+# a lane's one, two or four rows without work, a last block of few columns, rows that are no whole vectors
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("rows,h", [(1, 8), (63, 72), (129, 200), (511, 64), (512, 136), (513, 136), (30, 16384), (30, 16392)])
+@pytest.mark.parametrize("rows,h", [(1, 8), (63, 72), (65, 72), (129, 200), (511, 64), (512, 136), (513, 136), (30, 16384), (30, 16392)])
 def test_column_reductions_of_few_rows(gpu_device, dtype, rows, h):
     """Against fp64.  Each sum has `rows` terms, which no order of additions rounds by more than rows * 2^-24 of their
     magnitudes' sum; a LayerNorm gain's terms are off by the statistics' rounding too, 2^-20 of theirs."""
