@@ -313,7 +313,7 @@ def test_attention_keeps_to_the_faster_of_its_two_kinds_of_blocks():
     forward, backward = (po.lib[n] for n in ("_ZN2po31attention_few_forward_is_fasterEiiii",
                                              "_ZN2po32attention_few_backward_is_fasterEiiiii"))
     forward.restype = backward.restype = ctypes.c_bool
-    slow = dict(forward=[(410, 64, 40), (421, 64, 37), (512, 64, 34), (2290, 64, 13), (2951, 64, 11), (2560, 128, 11), (3560, 128, 9)],
+    slow = dict(forward=[(410, 64, 40), (421, 64, 37), (1024, 64, 17), (2951, 64, 11), (2550, 128, 11), (2655, 128, 11)],
                 backward=[(66, 64, 96), (101, 64, 80), (128, 64, 65), (256, 64, 36), (384, 64, 25), (512, 64, 21), (2048, 64, 9),
                           (2276, 64, 12), (3250, 64, 10), (4090, 64, 8), (74, 128, 96), (99, 128, 80), (896, 128, 13), (1152, 128, 11),
                           (1792, 128, 9), (2304, 128, 7), (2159, 128, 11), (2565, 128, 11), (3572, 128, 8)])
