@@ -66,6 +66,14 @@ __device__ __forceinline__ void float_to_lds(unsigned lds, const float* p) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(p) : "memory");
 }
 
+// A maximum in units of the exponent, rounded once: what a sum is scaled by cancels exactly where it is scaled again, between tiles, in
+// the merge and in lse, which a product fused into those differences would not (scores of deviation 6, 2048 rows: lse 6.7e-8 off,
+// as the 128-row blocks' is 5.5e-8).
+__device__ __forceinline__ float exponent_of(float m, float c) {
+#pragma clang fp contract(off)
+  return m * c;
+}
+
 // c += rows of the tile times b over the head dimension.
 template <int DH>
 __device__ __forceinline__ f32x16 dot_tile(const char* tile, const bf16x8 (&b)[DH / 16], f32x16 c, int lane) {
@@ -147,7 +155,7 @@ __global__ __launch_bounds__((64 * Few<DH, true>::W)) void attn_few_fwd_kernel(c
   f32x16 acc[DT];
 #pragma unroll
   for (int d = 0; d < DT; ++d) acc[d] = zero16();
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = -INFINITY, mc_run = -INFINITY, l_run = 0.f;
   for (int t = wave, i = 0; t < n_tiles; t += W, ++i) {
     const bool more = t + W < n_tiles;
     if (F::NS == 1) wait_loads<F::LOADS>();  // K is there, V may be on its way
@@ -168,8 +176,8 @@ __global__ __launch_bounds__((64 * Few<DH, true>::W)) void attn_few_fwd_kernel(c
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, p[e]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mc = (mx == -INFINITY ? 0.f : mx) * c;  // scores that are all -inf add nothing, instead of inf - inf
-    const float alpha = fast_exp2(fmaf(m_run, c, -mc));
+    const float mc_new = exponent_of(mx, c), mc = mx == -INFINITY ? 0.f : mc_new;  // scores that are all -inf add nothing, instead of inf - inf
+    const float alpha = fast_exp2(mc_run - mc);
     float sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -177,6 +185,7 @@ __global__ __launch_bounds__((64 * Few<DH, true>::W)) void attn_few_fwd_kernel(c
       sum += p[e];
     }
     m_run = mx;
+    mc_run = mc_new;
     l_run = l_run * alpha + sum;
 #pragma unroll
     for (int d = 0; d < DT; ++d)
@@ -210,9 +219,10 @@ __global__ __launch_bounds__((64 * Few<DH, true>::W)) void attn_few_fwd_kernel(c
   float m = stat[lane], f[W], l = 0.f;
 #pragma unroll
   for (int w = 1; w < W; ++w) m = fmaxf(m, stat[w * 64 + lane]);  // wave 0 has seen key 0: finite
+  const float mc = exponent_of(m, c);
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    f[w] = fast_exp2((stat[w * 64 + lane] - m) * c);
+    f[w] = fast_exp2(exponent_of(stat[w * 64 + lane], c) - mc);
     l += stat[(W + w) * 64 + lane] * f[w];
   }
   if constexpr (EDGE) {
@@ -233,7 +243,11 @@ __global__ __launch_bounds__((64 * Few<DH, true>::W)) void attn_few_fwd_kernel(c
     }
     store4(o + (size_t)q * h + head * DH + 8 * g + 4 * half, v);
   }
-  if (wave == 0 && half == 0) lse[(size_t)head * s + q] = fmaf(m * c, 0.6931471805599453f, __logf(l));
+  if (wave == 0 && half == 0) {
+    // by whichever constant is the more exact: 1 / 8, or c ln 2, whose two roundings all but cancel
+    const float log_l = __logf(l), ln2 = 0.6931471805599453f;
+    lse[(size_t)head * s + q] = DH == 64 ? m * scale + fmaf(fmaf(-m, c, mc), ln2, log_l) : fmaf(mc, ln2, log_l);
+  }
 }
 
 // Block `at` of heads * tiles, heaviest first: 32 query rows of a head.

@@ -633,6 +633,24 @@ def test_attention_blocks_of_32_rows(gpu_device, s, dh, a, akv):
         assert err(dqkv[:s, part], want["dqkv"][:, part]) < 2.0 ** -7, part
 
 
+# Row sums of many tiles, scaled again between tiles and in the merge of the waves, at scores of deviation 6 where the maximum moves:
+# lse is an fp32 number near that maximum, and its own rounding is the largest part of its error (2^-25 at most, root mean square; the
+# other parts, the maximum in units of the exponent, the constants, log l, are each below that).
+@pytest.mark.parametrize("s,dh,a", [(2048, 128, 2), (1500, 128, 3), (4096, 128, 1), (1024, 64, 8), (777, 64, 10)])
+def test_attention_blocks_of_32_rows_lse_is_exact_to_a_rounding(gpu_device, s, dh, a):
+    h, err = a * dh, [0.0, 0.0]
+    for seed in range(3):
+        g = torch.Generator(device=gpu_device)
+        g.manual_seed(s + a + seed)
+        qkv = (2.5 * torch.randn(s, 3 * h, generator=g, device=gpu_device)).bfloat16()
+        o, lse = torch.empty(s, h, dtype=torch.bfloat16, device=gpu_device), torch.empty(a, s, device=gpu_device)
+        po.po_op_attention_forward(po.PO_BF16, qkv, o, lse, s, h, a)
+        want = _attention_64(qkv, torch.zeros_like(o), o, lse, dh, a, a)["lse"]
+        err[0] += float((lse.double() - want).square().sum())
+        err[1] += float(want.square().sum())
+    assert err[0] ** 0.5 < 2.0 ** -24 * err[1] ** 0.5
+
+
 # Short sequences stay with the vector kernels, bit for bit; one row more and a call goes to the matrix cores (the bf16
 # backward always does).
 @pytest.mark.parametrize("dtype,dh,forward,backward", [("f32", 32, 4, 6), ("f32", 64, 9, 12), ("f32", 96, 13, 18),
